@@ -159,13 +159,13 @@ def prepare(case, seed):
     layers = [_layer_weights(case, seed, l) for l in range(s.L)]
     for name in skd.PER_LAYER:
         weights[name] = [w[name] for w in layers]
-    stream = torch.cuda.Stream()
     cfg = skd.make_config(s, B, P, P + T, case["n_min"], case["n_max"], case["warmup"], dtype=skd.BF16, io_on_device=int(device))
-    torch.cuda.synchronize()  # the weights come from another stream
-    dec = skd.Decoder(cfg, weights, location=skd.DEVICE, elem=skd.W_BF16, stream=stream.cuda_stream)
+    # the default stream, as in a program with one generation at a time: passes follow each other, and do not overlap
+    # those of another state
+    dec = skd.Decoder(cfg, weights, location=skd.DEVICE, elem=skd.W_BF16)
     tokens, start, uniforms = _tokens(case, seed), _start(case, seed), _uniforms(case, seed)
     mask = (np.arange(P)[None, :] >= start[:, None]).astype(np.uint8) if case["shortest"] else None
-    st = {"kind": case["kind"], "head": case["head"], "dec": dec, "stream": stream, "P": P, "mask": mask}
+    st = {"kind": case["kind"], "head": case["head"], "dec": dec, "P": P, "mask": mask}
     if device:
         st["prompt"] = torch.from_numpy(tokens[:P].copy()).cuda()
         st["tape"] = list(torch.from_numpy(tokens[P:].copy()).cuda().unbind(0))
