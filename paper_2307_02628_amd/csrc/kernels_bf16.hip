@@ -368,7 +368,7 @@ static void launch_gemm_epi(hipStream_t s, const GemmArgs &a, int epi, dim3 grid
     case EPI_QKV: SKD_LAUNCH((k_gemm<MB, R, EPI_QKV, U, WAVES>), grid, blk, lds, s, a); break;
     case EPI_RELU: SKD_LAUNCH((k_gemm<MB, R, EPI_RELU, U, WAVES>), grid, blk, lds, s, a); break;
     case EPI_QKV_ROWS:
-      if constexpr (MB == 8) SKD_LAUNCH((k_gemm<MB, R, EPI_QKV_ROWS, U, WAVES>), grid, blk, lds, s, a);
+      SKD_LAUNCH((k_gemm<MB, R, EPI_QKV_ROWS, U, WAVES>), grid, blk, lds, s, a);
       break;
     case EPI_RESID:
       if constexpr (MB == 8) SKD_LAUNCH((k_gemm<MB, R, EPI_RESID, U, WAVES>), grid, blk, lds, s, a);
@@ -418,7 +418,8 @@ static bool gemm_shape(const GemmArgs &a, int epi, int R, int &U, int waves, dim
   if (U < 1) return false;
   groups = bf16_gemm_groups(a.N, R);
   const bool by_rows = epi == EPI_QKV_ROWS || epi == EPI_RESID || (epi == EPI_RELU && a.rows > 0);
-  if ((epi == EPI_QKV_ROWS || epi == EPI_RESID) && (MB != 8 || a.rows <= 0)) return false;
+  if (epi == EPI_RESID && MB != 8) return false;
+  if ((epi == EPI_QKV_ROWS || epi == EPI_RESID) && a.rows <= 0) return false;
   if (by_rows && (a.rows % a.B_pad || split != 1)) return false;
   grid = dim3(groups, split, by_rows ? a.rows / a.B_pad : 1);
   return true;
@@ -721,24 +722,141 @@ __device__ inline void wait_vmcnt_le(int n) {
   }
 }
 
+// Epilogue of the tiled prompt GEMMs: a wave's RT x MT output tiles, weight tiles nt0 .. nt0 + RT - 1 and activation-row
+// tiles mt0 .. mt0 + MT - 1.  acc[r][m]: lane l holds output rows (weight rows) n0 .. n0 + 3 of activation row
+// row0(m) + (l & 15), n0 = 16 * (weight tile) + 4 * (l >> 4).
+template <int EPI, int RT, int MT>
+__device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT][MT], int nt0, int mt0, int sp, int lane) {
+  const int grp = lane >> 4, j = lane & 15;
+  auto n0_of = [&](int r) { return ((nt0 + r) << 4) + 4 * grp; };
+  auto row0_of = [&](int m) { return (mt0 + m) << 4; };
+  if constexpr (EPI == EPI_PARTIAL) {  // partial sums of K part sp
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        *(floatx4 *)&a.partial[((long)sp * a.B_pad + row0_of(m) + j) * a.N + n0_of(r)] = acc[r][m];
+  } else if constexpr (EPI == EPI_RELU) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int n0 = n0_of(r);
+      EpiPre pre;
+      pre.bias = *(const floatx4 *)&a.bias[n0];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) gemm_epilogue<EPI>(a, row0_of(m) + j, n0, acc[r][m], pre);
+    }
+  } else if constexpr (EPI == EPI_RESID) {
+    // the residual values of the next weight tile are requested before the current one is stored: one exposed
+    // round trip per workgroup instead of four
+    floatx4 xv[2][MT];
+    auto fetch = [&](int r, floatx4(&x)[MT]) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) x[m] = *(const floatx4 *)&a.x[(long)(row0_of(m) + j) * a.N + n0_of(r)];
+    };
+    auto store = [&](int r, const floatx4(&x)[MT]) {
+      const floatx4 bias = *(const floatx4 *)&a.bias[n0_of(r)];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) *(floatx4 *)&a.x[(long)(row0_of(m) + j) * a.N + n0_of(r)] = x[m] + (acc[r][m] + bias);
+    };
+    fetch(0, xv[0]);
+    if constexpr (RT > 1) fetch(1, xv[1]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      store(r, xv[r & 1]);
+      if (r + 2 < RT) fetch(r + 2, xv[r & 1]);
+    }
+  } else {  // EPI_QKV_ROWS
+    // The output rows of a wave lie inside one of q | k | v (d is a multiple of 64, a head), and the
+    // 16 activation rows of a tile belong to one sequence and one page: what the stores need to know about a tile
+    // is wave-uniform and is looked up once, with scalar loads, not once per weight tile and lane.
+    const int which = nt0 * 16 / a.d;
+    int t_page[MT], t_slot0[MT], t_len[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      t_page[m] = -1;
+      t_slot0[m] = 0;
+      t_len[m] = 0;
+      const int row0 = row0_of(m);
+      if (which != 0 && row0 < a.rows) {
+        const int b = a.rm.seq[row0];
+        if (b >= 0) {
+          t_slot0[m] = row0 - a.rm.first_row[b];  // = real position of the tile's first row
+          t_len[m] = a.rm.P - a.rm.start[b];      // positions of the sequence; the rest of its last tile is padding
+          if (t_slot0[m] < t_len[m]) t_page[m] = a.bt_layer[(long)b * a.kv.max_pages + t_slot0[m] / a.kv.page_tokens];
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int n0 = n0_of(r), within = n0 - which * a.d;
+      const floatx4 bias = *(const floatx4 *)&a.bias[n0];
+      const int h = within / a.kv.dh, e = within - h * a.kv.dh;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        floatx4 v = acc[r][m] + bias;
+        if (which == 0) {
+          if (row0_of(m) < a.rows)
+            *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, within, a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+          continue;
+        }
+        if (t_page[m] < 0) continue;
+        bf16_t *pg = a.kv_pool + (long)t_page[m] * a.kv.page_elems;
+        const int tt = (t_slot0[m] + j) % a.kv.page_tokens;
+        if (which == 1) {
+          if (t_slot0[m] + j < t_len[m])
+            *(uint2 *)&pg[kv_k_off(h, tt, e, a.kv)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+          continue;
+        }
+        // v: a page holds, for one element e, four consecutive positions side by side.  The four lanes of a quad
+        // hold positions 4q .. 4q + 3 for elements e .. e + 3 each: transposed inside the quad (two exchanges,
+        // with the lane 1 and the lane 2 away), lane t ends up with element e + t of all four positions and
+        // stores them as one 8-byte word.
+        const int t = j & 3;
+        {
+          const float s0 = (t & 1) ? v[0] : v[1], s1 = (t & 1) ? v[2] : v[3];
+          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0xB1, 0xF, 0xF, true));
+          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0xB1, 0xF, 0xF, true));
+          if (t & 1) { v[0] = r0; v[2] = r1; } else { v[1] = r0; v[3] = r1; }
+        }
+        {
+          const float s0 = (t & 2) ? v[0] : v[2], s1 = (t & 2) ? v[1] : v[3];
+          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0x4E, 0xF, 0xF, true));
+          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0x4E, 0xF, 0xF, true));
+          if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
+        }
+        // now v[s] = element e + t of position 4 * (j / 4) + s
+        const int pos0 = t_slot0[m] + (j & ~3), nvalid = t_len[m] - pos0;
+        bf16_t *dst = &pg[kv_v_off(h, pos0 % a.kv.page_tokens, e + t, a.kv)];
+        if (nvalid >= 4) {
+          *(uint2 *)dst = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        } else {
+          for (int s_ = 0; s_ < 4; ++s_)
+            if (s_ < nvalid) dst[s_] = (bf16_t)f2bf(v[s_]);
+        }
+        (void)tt;
+      }
+    }
+  }
+}
+
 template <int EPI>
 __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   extern __shared__ bf16x8 tile_lds[];  // [TILE_NS stages][TILE_FR][64 lanes]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wr = wave >> 1, wc = wave & 1;  // sub-tile: weight tiles 4wr .. 4wr+3, activation tiles 8wc .. 8wc+7
-  const int Kf = a.K >> 5;
-
   // workgroup -> output tile.  Workgroups are dealt to the 8 XCDs round-robin; the ones that share an XCD (and
   // its L2) at any moment should share operands, so each XCD walks its own contiguous range of tiles in bands
   // of 4 activation tiles x all weight tiles, weight tile fastest in groups of 4 rows (the last band has the
   // gy % 4 activation tiles that are left; XCD x owns the workgroups with id % 8 == x, one more than the others
   // when x < total % 8).
-  int tn, tm;
+  int tn, tm, sp;
   {
-    const int gx = gridDim.x, gy = gridDim.y, total = gx * gy;
-    const int id = blockIdx.x + gx * blockIdx.y;
+    const int gx = a.N >> 8, gy = (a.rows + 255) >> 8, tiles = gx * gy, total = tiles * a.split;
+    const int id = blockIdx.x;
     const int xcd = id & 7, per = total >> 3, rem = total & 7;
-    const int logical = xcd * per + min(xcd, rem) + (id >> 3);
+    int logical = xcd * per + min(xcd, rem) + (id >> 3);
+    sp = logical / tiles;  // K part
+    logical -= sp * tiles;
     const int full = gy >> 2, tail0 = full * 4 * gx;
     if (logical < tail0) {
       const int band = logical / (4 * gx), within = logical - band * 4 * gx;
@@ -751,6 +869,8 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
     }
   }
 
+  const int k0 = (int)((long)(a.K >> 5) * sp / a.split), Kf = (int)((long)(a.K >> 5) * (sp + 1) / a.split) - k0;
+
   // this wave's share of a stage: 4 fragments; waves 0..3 fetch the weight tiles, waves 4..7 the activation tiles.
   // Fragment bases are wave-uniform (scalar registers); the only per-lane part of an address is the lane's place
   // in the fragment, one 32-bit register.
@@ -762,13 +882,13 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int T = tn * 16 + ld_t0 + i;
-      src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * Kf) * a.G + T % a.G) * 64;
+      src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * (a.K >> 5) + k0) * a.G + T % a.G) * 64;
     }
     sstride = (long)a.G * 64;
     vlane = lane;
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) src[i] = (const bf16x8 *)a.A + ((long)(tm * 16 + ld_t0 + i) * Kf) * 64;
+    for (int i = 0; i < 4; ++i) src[i] = (const bf16x8 *)a.A + ((long)(tm * 16 + ld_t0 + i) * (a.K >> 5) + k0) * 64;
     sstride = 64;
     vlane = act_lane(lane);  // fetched in MFMA lane order, so that LDS holds ready-made fragments
   }
@@ -870,125 +990,20 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
     }
   }
 
-  // ---- epilogue.  acc[r][m]: lane l holds output rows (weight rows) n0 .. n0 + 3 of activation row
-  // row0(m) + (l & 15), n0 = 16 * (weight tile) + 4 * (l >> 4).
-  const int grp = lane >> 4, j = lane & 15;
-  auto n0_of = [&](int r) { return ((tn * 16 + wr * 4 + r) << 4) + 4 * grp; };
-  auto row0_of = [&](int m) { return (tm * 16 + wc * 8 + m) << 4; };
-  if constexpr (EPI == EPI_RELU) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int n0 = n0_of(r);
-      EpiPre pre;
-      pre.bias = *(const floatx4 *)&a.bias[n0];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) gemm_epilogue<EPI>(a, row0_of(m) + j, n0, acc[r][m], pre);
-    }
-  } else if constexpr (EPI == EPI_RESID) {
-    // the residual values of the next weight tile are requested before the current one is stored: one exposed
-    // round trip per workgroup instead of four
-    floatx4 xv[2][8];
-    auto fetch = [&](int r, floatx4(&x)[8]) {
-#pragma unroll
-      for (int m = 0; m < 8; ++m) x[m] = *(const floatx4 *)&a.x[(long)(row0_of(m) + j) * a.N + n0_of(r)];
-    };
-    auto store = [&](int r, const floatx4(&x)[8]) {
-      const floatx4 bias = *(const floatx4 *)&a.bias[n0_of(r)];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) *(floatx4 *)&a.x[(long)(row0_of(m) + j) * a.N + n0_of(r)] = x[m] + (acc[r][m] + bias);
-    };
-    fetch(0, xv[0]);
-    fetch(1, xv[1]);
-    store(0, xv[0]);
-    fetch(2, xv[0]);
-    store(1, xv[1]);
-    fetch(3, xv[1]);
-    store(2, xv[0]);
-    store(3, xv[1]);
-  } else {  // EPI_QKV_ROWS
-    // The 256 output rows of a workgroup lie inside one of q | k | v (d is a multiple of 256 when 3 d is), and the
-    // 16 activation rows of a tile belong to one sequence and one page: what the stores need to know about a tile
-    // is wave-uniform and is looked up once, with scalar loads, not once per weight tile and lane.
-    const int which = (tn * 256) / a.d;
-    int t_page[8], t_slot0[8], t_len[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      t_page[m] = -1;
-      t_slot0[m] = 0;
-      t_len[m] = 0;
-      const int row0 = row0_of(m);
-      if (which != 0 && row0 < a.rows) {
-        const int b = a.rm.seq[row0];
-        if (b >= 0) {
-          t_slot0[m] = row0 - a.rm.first_row[b];  // = real position of the tile's first row
-          t_len[m] = a.rm.P - a.rm.start[b];      // positions of the sequence; the rest of its last tile is padding
-          if (t_slot0[m] < t_len[m]) t_page[m] = a.bt_layer[(long)b * a.kv.max_pages + t_slot0[m] / a.kv.page_tokens];
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int n0 = n0_of(r), within = n0 - which * a.d;
-      const floatx4 bias = *(const floatx4 *)&a.bias[n0];
-      const int h = within / a.kv.dh, e = within - h * a.kv.dh;
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        floatx4 v = acc[r][m] + bias;
-        if (which == 0) {
-          if (row0_of(m) < a.rows)
-            *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, within, a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-          continue;
-        }
-        if (t_page[m] < 0) continue;
-        bf16_t *pg = a.kv_pool + (long)t_page[m] * a.kv.page_elems;
-        const int tt = (t_slot0[m] + j) % a.kv.page_tokens;
-        if (which == 1) {
-          if (t_slot0[m] + j < t_len[m])
-            *(uint2 *)&pg[kv_k_off(h, tt, e, a.kv)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-          continue;
-        }
-        // v: a page holds, for one element e, four consecutive positions side by side.  The four lanes of a quad
-        // hold positions 4q .. 4q + 3 for elements e .. e + 3 each: transposed inside the quad (two exchanges,
-        // with the lane 1 and the lane 2 away), lane t ends up with element e + t of all four positions and
-        // stores them as one 8-byte word.
-        const int t = j & 3;
-        {
-          const float s0 = (t & 1) ? v[0] : v[1], s1 = (t & 1) ? v[2] : v[3];
-          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0xB1, 0xF, 0xF, true));
-          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0xB1, 0xF, 0xF, true));
-          if (t & 1) { v[0] = r0; v[2] = r1; } else { v[1] = r0; v[3] = r1; }
-        }
-        {
-          const float s0 = (t & 2) ? v[0] : v[2], s1 = (t & 2) ? v[1] : v[3];
-          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0x4E, 0xF, 0xF, true));
-          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0x4E, 0xF, 0xF, true));
-          if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
-        }
-        // now v[s] = element e + t of position 4 * (j / 4) + s
-        const int pos0 = t_slot0[m] + (j & ~3), nvalid = t_len[m] - pos0;
-        bf16_t *dst = &pg[kv_v_off(h, pos0 % a.kv.page_tokens, e + t, a.kv)];
-        if (nvalid >= 4) {
-          *(uint2 *)dst = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-        } else {
-          for (int s_ = 0; s_ < 4; ++s_)
-            if (s_ < nvalid) dst[s_] = (bf16_t)f2bf(v[s_]);
-        }
-        (void)tt;
-      }
-    }
-  }
+  tile_epilogue<EPI, 4, 8>(a, acc, tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
 }
 
-// Batched-prompt projections on 256 x 256 tiles.  Returns 0, or -1 when the shape does not tile (the caller then
-// uses bf16_gemm on row chunks).
+// Batched-prompt projections on 256 x 256 tiles.  Returns 0, or -1 when the shape does not tile.
 int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
-  if (a.rows <= 0 || a.rows % 256 || a.N % 256 || a.K % 32 || a.G < 1 || a.G > 4) return -1;
-  const dim3 grid(a.N / 256, a.rows / 256), blk(512);
+  if (a.rows <= 0 || a.N % 256 || a.K % 32 || a.G < 1 || a.G > 4 || a.split < 1 || a.split > a.K / 32) return -1;
+  if (a.split != 1 && epi != EPI_PARTIAL) return -1;
+  const dim3 grid((a.N / 256) * ((a.rows + 255) / 256) * a.split), blk(512);
   const size_t lds = (size_t)TILE_NS * TILE_FR * 64 * sizeof(bf16x8);  // 128 KiB of the CU's 160
   static bool configured = false;
   if (!configured) {
     if (hipFuncSetAttribute((const void *)k_gemm_tile<EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_gemm_tile<EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_tile<EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_gemm_tile<EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return -1;
     configured = true;
@@ -996,10 +1011,191 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
   switch (epi) {
     case EPI_QKV_ROWS: SKD_LAUNCH(k_gemm_tile<EPI_QKV_ROWS>, grid, blk, lds, s, a); break;
     case EPI_RESID: SKD_LAUNCH(k_gemm_tile<EPI_RESID>, grid, blk, lds, s, a); break;
+    case EPI_PARTIAL: SKD_LAUNCH(k_gemm_tile<EPI_PARTIAL>, grid, blk, lds, s, a); break;
     case EPI_RELU: SKD_LAUNCH(k_gemm_tile<EPI_RELU>, grid, blk, lds, s, a); break;
     default: return -1;
   }
   return 0;
+}
+
+// ------------------------------------------------------------------ tiled GEMM for prompts of a few hundred rows
+// On 256 x 256 tiles a prompt of a few hundred rows gives a handful of workgroups (912 rows at d = 2048: 32 for the
+// N = d projections, on 256 CUs).  The same ring and fragment order with 4 waves (2 x 2, RT x MT MFMA tiles each) own
+// 32 RT weight rows x 32 MT activation rows; two workgroups share a CU (5 stages of (RT + MT) * 2 KiB each), so one
+// multiplies while the other waits at its barrier, and the K range can be split over `a.split` workgroups whose fp32
+// partial sums the row reducer adds.  The price is operand traffic: a 128 x 128 tile moves twice the bytes per MFMA
+// of a 256 x 256 one, which is why prompts that fill the chip with the larger tile stay there.
+// us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
+// FFN1 80 -> 44, FFN2 296 -> 47 (split 4); 1024 rows of the 1.3B shape QKV 45 -> 37, output 52 -> 15 (split 2), FFN1
+// 46 -> 41, FFN2 154 -> 42 (split 2).
+constexpr int MID_NS = 5;  // ring stages
+
+template <int N>
+__device__ inline void wait_vmcnt() {  // at most N vector-memory operations of this wave outstanding (vmcnt: bits 15:14, 3:0)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+template <int RT, int MT, int EPI>
+__global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
+  constexpr int FR = 2 * (RT + MT), LPW = FR / 4;  // fragments per stage, loads per wave and stage
+  extern __shared__ bf16x8 mid_lds[];              // [MID_NS][FR][64 lanes]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wr = wave >> 1, wc = wave & 1;
+  const int Kf = a.K >> 5;
+  // workgroup -> (K part, output tile), XCD-aware as in k_gemm_tile: every XCD walks a contiguous range, bands of 4
+  // activation tiles x all weight tiles
+  int tn, tm, sp;
+  {
+    const int gx = a.N / (32 * RT), gy = (a.rows + 32 * MT - 1) / (32 * MT), tiles = gx * gy, total = tiles * a.split;
+    const int id = blockIdx.x, xcd = id & 7;
+    int logical = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+    sp = logical / tiles;
+    logical -= sp * tiles;
+    const int band = logical / (4 * gx), hb = min(4, gy - 4 * band), within = logical - band * 4 * gx;
+    tn = within / hb;
+    tm = band * 4 + within % hb;
+  }
+  const int k0 = (int)((long)Kf * sp / a.split), n = (int)((long)Kf * (sp + 1) / a.split) - k0;
+
+  // this wave's fragments of a stage: LPW consecutive ones of [2 RT weight tiles, 2 MT activation-row tiles]
+  const bf16x8 *src[LPW];
+  long stride[LPW];
+  unsigned vl[LPW];
+#pragma unroll
+  for (int i = 0; i < LPW; ++i) {
+    const int fr = wave * LPW + i;
+    if (fr < 2 * RT) {
+      const int T = tn * 2 * RT + fr;
+      src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * Kf + k0) * a.G + T % a.G) * 64;
+      stride[i] = (long)a.G * 64;
+      vl[i] = lane;
+    } else {
+      src[i] = (const bf16x8 *)a.A + ((long)(tm * 2 * MT + fr - 2 * RT) * Kf + k0) * 64;
+      stride[i] = 64;
+      vl[i] = act_lane(lane);  // fetched in MFMA lane order
+    }
+  }
+  floatx4 acc[RT][MT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[r][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  auto issue = [&](int st) {
+    bf16x8 *dst = mid_lds + ((st % MID_NS) * FR + wave * LPW) * 64;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)&(src[i] + (long)st * stride[i])[vl[i]],
+                                       (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
+  };
+  auto read = [&](int st, bf16x8(&wf)[RT], bf16x8(&xf)[MT]) {
+    const bf16x8 *base = mid_lds + (st % MID_NS) * (FR * 64) + lane;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) wf[r] = base[(wr * RT + r) * 64];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xf[m] = base[(2 * RT + wc * MT + m) * 64];
+  };
+  auto mma = [&](const bf16x8(&wf)[RT], const bf16x8(&xf)[MT]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[r][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[r], xf[m], acc[r][m], 0, 0, 0);
+  };
+  auto bar = [&]() {  // this wave's LDS reads are done; bare barrier: __syncthreads() would wait for the loads in flight
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // stage st becomes readable, the slot of stage st - 1 is refilled (see k_gemm_tile)
+  auto open_stage = [&](int st) {
+    const int later = min(n - 1 - st, MID_NS - 2);
+    if (later == 0) wait_vmcnt<0>();
+    else if (later == 1) wait_vmcnt<LPW>();
+    else if (later == 2) wait_vmcnt<2 * LPW>();
+    else wait_vmcnt<3 * LPW>();
+    bar();
+    if (st + MID_NS - 1 < n) issue(st + MID_NS - 1);
+  };
+#pragma unroll
+  for (int i = 0; i < MID_NS - 1; ++i)
+    if (i < n) issue(i);
+  bf16x8 wfA[RT], xfA[MT], wfB[RT], xfB[MT];
+  open_stage(0);
+  read(0, wfA, xfA);
+  // steady state: the LDS reads of the next stage are dealt out among the MFMAs of the current one
+  auto steady = [&](int nx, bf16x8(&wn)[RT], bf16x8(&xn)[MT], const bf16x8(&wc_)[RT], const bf16x8(&xc)[MT]) {
+    wait_vmcnt<(MID_NS - 2) * LPW>();
+    bar();
+    issue(nx + MID_NS - 1);
+    read(nx, wn, xn);
+    mma(wc_, xc);
+    __builtin_amdgcn_sched_group_barrier(0x020, LPW, 0);
+#pragma unroll
+    for (int i = 0; i < RT + MT; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, RT * MT - (RT + MT), 0);
+  };
+  int st = 0;
+  for (; st + MID_NS + 1 < n; st += 2) {
+    steady(st + 1, wfB, xfB, wfA, xfA);
+    steady(st + 2, wfA, xfA, wfB, xfB);
+  }
+  for (; st < n; st += 2) {  // the last stages
+    if (st + 1 < n) {
+      open_stage(st + 1);
+      read(st + 1, wfB, xfB);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mma(wfA, xfA);
+    if (st + 1 < n) {
+      if (st + 2 < n) {
+        open_stage(st + 2);
+        read(st + 2, wfA, xfA);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma(wfB, xfB);
+    }
+  }
+  tile_epilogue<EPI, RT, MT>(a, acc, tn * 2 * RT + wr * RT, tm * 2 * MT + wc * MT, sp, lane);
+}
+
+template <int RT, int MT>
+static int launch_gemm_mid(hipStream_t s, const GemmArgs &a, int epi) {
+  constexpr size_t lds = (size_t)MID_NS * 2 * (RT + MT) * 64 * sizeof(bf16x8);
+  if (a.N % (32 * RT)) return -1;
+  static bool configured = false;
+  if (!configured) {
+    if (hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return -1;
+    configured = true;
+  }
+  const dim3 grid((a.N / (32 * RT)) * ((a.rows + 32 * MT - 1) / (32 * MT)) * a.split), blk(256);
+  switch (epi) {
+    case EPI_QKV_ROWS: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_QKV_ROWS>), grid, blk, lds, s, a); break;
+    case EPI_RESID: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_RESID>), grid, blk, lds, s, a); break;
+    case EPI_PARTIAL: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_PARTIAL>), grid, blk, lds, s, a); break;
+    case EPI_RELU: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_RELU>), grid, blk, lds, s, a); break;
+    default: return -1;
+  }
+  return 0;
+}
+// weight_rows x act_rows per workgroup: 128 x 128, 64 x 128, 128 x 64 or 64 x 64.  Returns 0, or -1 when the shape does
+// not tile (nothing launched).
+int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epi, int weight_rows, int act_rows) {
+  const int Kf = a.K >> 5;
+  if (a.rows <= 0 || a.N < 1 || a.K < 32 || a.K % 32 || a.G < 1 || a.G > 4 || a.split < 1 || a.split > Kf) return -1;
+  if (a.split != 1 && epi != EPI_PARTIAL) return -1;
+  if (weight_rows == 128 && act_rows == 128) return launch_gemm_mid<4, 4>(s, a, epi);
+  if (weight_rows == 64 && act_rows == 128) return launch_gemm_mid<2, 4>(s, a, epi);
+  if (weight_rows == 128 && act_rows == 64) return launch_gemm_mid<4, 2>(s, a, epi);
+  if (weight_rows == 64 && act_rows == 64) return launch_gemm_mid<2, 2>(s, a, epi);
+  return -1;
 }
 
 // ------------------------------------------------------------------ row kernels: embedding / split-K reduce, + LayerNorm
@@ -1508,15 +1704,44 @@ void bf16_attention_rows(hipStream_t s, const AttnRowsArgs &a) {
 }
 
 // ------------------------------------------------------------------ row kernels of the batched prompt
+// The row map of a prompt from by-value kernel arguments (at most 128 sequences): workgroup b fills the rows of
+// sequence b, the last one the rows past the last sequence.  Replaces four pageable copies and two host waits.
+__global__ __launch_bounds__(256) void k_prompt_map(PromptMap pm, int B, int rows, int rows_pad, int P, int32_t *start,
+                                                    int32_t *order, int32_t *first, int32_t *seq) {
+  const int b = blockIdx.x;
+  int lo = rows, n = rows_pad - rows, val = -1;
+  if (b < B) {
+    lo = pm.first[b];
+    n = ((P - pm.start[b]) + 15) / 16 * 16;
+    val = b;
+    if (threadIdx.x == 0) {
+      start[b] = pm.start[b];
+      order[b] = pm.order[b];
+      first[b] = lo;
+    }
+  }
+  for (int i = threadIdx.x; i < n; i += 256) seq[lo + i] = val;
+}
+void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, int32_t *start,
+                     int32_t *order, int32_t *first, int32_t *seq) {
+  SKD_LAUNCH(k_prompt_map, dim3(B + 1), dim3(256), 0, s, pm, B, rows, rows_pad, P, start, order, first, seq);
+}
+
 __global__ __launch_bounds__(1024) void k_embed_ln_rows(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb,
                                                         const bf16_t *pos_emb, const float *g, const float *bt, float *x,
                                                         bf16_t *a_out, int B, int d, int V) {
   __shared__ float sh[32];
   const int row = blockIdx.x, d4 = d >> 2;
   const int b = rm.seq[row];
-  if (b < 0) return;  // rows past the last sequence stay zero
+  if (b < 0) return;
   const int pos = row - rm.first_row[b];  // real position = position id
-  if (pos >= rm.P - rm.start[b]) return;  // padding of the sequence's last 16-row tile: stays zero
+  if (pos >= rm.P - rm.start[b]) {  // padding of the sequence's last 16-row tile: zero (no other row ever depends on it)
+    for (int c = threadIdx.x; c < d4; c += 1024) {
+      ((floatx4 *)x)[(long)row * d4 + c] = floatx4{0.f, 0.f, 0.f, 0.f};
+      *(uint2 *)&a_out[d_act_index(row, 4 * c, d)] = make_uint2(0, 0);
+    }
+    return;
+  }
   int tok = tokens[(long)(rm.start[b] + pos) * B + b];
   tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
   const uint2 *te = (const uint2 *)(tok_emb + (long)tok * d), *pe = (const uint2 *)(pos_emb + (long)pos * d);
@@ -1592,10 +1817,31 @@ __global__ __launch_bounds__(1024) void k_ln_rows16(const float *x, const float 
     }
 }
 
-__global__ void k_gather_rows(const float *x_rows, float *x_out, RowMap rm, int d) {
-  const int b = blockIdx.x;
-  const long src = ((long)rm.first_row[b] + (rm.P - rm.start[b]) - 1) * d;  // the sequence's last prompt position
-  for (int k = threadIdx.x; k < d; k += blockDim.x) x_out[(long)blockIdx.x * d + k] = x_rows[src + k];
+// Hidden state of each sequence's last prompt position: x_out[b] = its row of x_rows (+ bias + the partial sums of the
+// last projection when split > 0), and its LayerNorm.
+__global__ __launch_bounds__(1024) void k_last_rows_ln(const float *x_rows, RowMap rm, const float *partial, int split,
+                                                       int stride, const float *bias, const float *g, const float *bt,
+                                                       float *x_out, bf16_t *a_out, int d) {
+  __shared__ float sh[32];
+  const int b = blockIdx.x, d4 = d >> 2;
+  const long row = (long)rm.first_row[b] + (rm.P - rm.start[b]) - 1;
+  floatx4 v[LN_NC], gv[LN_NC], bv[LN_NC];
+#pragma unroll
+  for (int i = 0; i < LN_NC; ++i) {
+    const int c = (int)(threadIdx.x + blockDim.x * i);
+    if (c < d4) {
+      v[i] = ((const floatx4 *)x_rows)[row * d4 + c];
+      gv[i] = ((const floatx4 *)g)[c];
+      bv[i] = ((const floatx4 *)bt)[c];
+      if (split) {
+        floatx4 acc = ((const floatx4 *)partial)[row * d4 + c];
+        for (int sp = 1; sp < split; ++sp) acc += ((const floatx4 *)partial)[((long)sp * stride + row) * d4 + c];
+        v[i] += acc + ((const floatx4 *)bias)[c];
+      }
+      ((floatx4 *)x_out)[(long)b * d4 + c] = v[i];
+    }
+  }
+  ln_finish_row(v, gv, bv, d, b, a_out, sh);
 }
 
 void bf16_embed_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb,
@@ -1610,8 +1856,9 @@ void bf16_ln_rows(hipStream_t s, const float *x, const float *g, const float *b,
   }
   SKD_LAUNCH(k_ln_rows, dim3(rows), dim3(1024), 0, s, x, g, b, a_out, d);
 }
-void bf16_gather_rows(hipStream_t s, const float *x_rows, float *x_out, RowMap rm, int B, int d) {
-  SKD_LAUNCH(k_gather_rows, dim3(B), dim3(256), 0, s, x_rows, x_out, rm, d);
+void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
+                       const float *bias, const float *g, const float *b, float *x_out, bf16_t *a_out, int B, int d) {
+  SKD_LAUNCH(k_last_rows_ln, dim3(B), dim3(row_threads(d)), 0, s, x_rows, rm, partial, split, stride, bias, g, b, x_out, a_out, d);
 }
 
 // ------------------------------------------------------------------ argmax over workgroup partials

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -105,7 +106,7 @@ struct skd_state {
   int32_t *order_dev = nullptr;    // [B] rows by descending real length (attention dispatch order)
   bool ragged = false;             // rows differ in length: use order_dev
   int32_t *start_dev = nullptr;    // [B] first real column
-  std::vector<int32_t> start_host;
+  std::vector<int32_t> start_host, order_host;
   int32_t *argmax_dev = nullptr;   // [B]
   float *u_dev = nullptr;          // [B] uniform numbers of the sampling head
   float *x = nullptr;              // residual stream fp32 [B_pad][d]
@@ -124,10 +125,12 @@ struct skd_state {
   int max_split = 1, attn_splits = 1, attn_waves = 4;
   // batched prompt workspace (allocated by the first batched skd_prefill)
   float *pf_x = nullptr;
+  float *pf_partial = nullptr;     // K parts of the prompt projections
   bf16_t *pf_a = nullptr, *pf_q = nullptr, *pf_o = nullptr, *pf_u = nullptr;
   int32_t *pf_seq = nullptr, *pf_first = nullptr;  // row map of the prompt pass (sequence of each row, first row of each sequence)
   int prefill_mode = 1;            // 1 = whole prompt per layer (bf16 path), 0 = column by column
-  int prefill_tiles = 1;           // 1 = prompt projections on 256 x 256 tiles where the shape allows
+  int prefill_tiles = 1;           // 1 = prompt projections as plan_rows says, 0 = 128-row chunks on the skinny kernel
+  int prefill_wr = 0, prefill_ar = 0, prefill_split = 1;  // forced tile of the prompt projections (0 = plan_rows decides)
   int device = 0;                  // HIP device the state lives on
   // sequencing
   bool prefilled = false, have_hidden = false, have_argmax = false;
@@ -619,6 +622,16 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
   if (st->bf16) {
     st->prefill_mode = env_int("SKD_PREFILL_BATCHED", 1) != 0 ? 1 : 0;
     st->prefill_tiles = env_int("SKD_PREFILL_TILES", 1) != 0 ? 1 : 0;
+    {  // "<weight rows>x<activation rows>x<split>": one tile for every prompt projection that it divides
+      int wr = 0, ar = 0, sp = 1;
+      const char *e = getenv("SKD_PREFILL_TILE");
+      if (e && sscanf(e, "%dx%dx%d", &wr, &ar, &sp) == 3 && sp >= 1 && sp <= 16 &&
+          ((wr == 256 && ar == 256) || ((wr == 128 || wr == 64) && (ar == 128 || ar == 64)))) {
+        st->prefill_wr = wr;
+        st->prefill_ar = ar;
+        st->prefill_split = sp;
+      }
+    }
     st->max_split = std::max(st->p_out.split, st->p_ffn2.split);
     // split the key range of one head over several workgroups only when rows*heads alone cannot fill the chip
     // decode attention wants 16 waves on every CU: few (row, head) pairs get wider workgroups first (merged in
@@ -683,22 +696,84 @@ extern "C" void skd_destroy(skd_state *st) {
 }
 
 // per-row padding offsets and the dispatch order of the attention workgroups (longest rows first)
-static int upload_start(skd_state *st, const std::vector<int32_t> &start) {
+static void set_start(skd_state *st, const std::vector<int32_t> &start) {
   const int B = st->cfg.batch;
-  std::vector<int32_t> order(B);
-  for (int b = 0; b < B; ++b) order[b] = b;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return start[x] < start[y]; });
+  st->order_host.resize(B);
+  for (int b = 0; b < B; ++b) st->order_host[b] = b;
+  std::stable_sort(st->order_host.begin(), st->order_host.end(), [&](int x, int y) { return start[x] < start[y]; });
   st->ragged = *std::max_element(start.begin(), start.end()) != *std::min_element(start.begin(), start.end());
   st->start_host = start;
-  HIPCHECK(hipMemcpyAsync(st->start_dev, start.data(), B * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
-  HIPCHECK(hipMemcpyAsync(st->order_dev, order.data(), B * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
+}
+static int upload_start(skd_state *st) {
+  const int B = st->cfg.batch;
+  HIPCHECK(hipMemcpyAsync(st->start_dev, st->start_host.data(), B * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
+  HIPCHECK(hipMemcpyAsync(st->order_dev, st->order_host.data(), B * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
   HIPCHECK(hipStreamSynchronize(st->stream));
   return SKD_OK;
 }
 
+// Kernel and launch shape of a prompt projection (N outputs, `rows` activation rows in whole 16-row tiles).
+struct RowsGemm {
+  enum Kind { SKINNY, MID, TILE, CHUNKS } kind = CHUNKS;
+  int B_pad = 128;      // SKINNY: padded rows, R and split as in a decode projection of that batch
+  int R = 4, split = 1; // split > 1, or SKINNY with split_ok: partial sums, added by the row reducer
+  int wr = 128, ar = 128;  // MID: tile
+  bool partial = false;
+};
+constexpr long kRowsPartialMax = 32L << 20;  // fp32 partial sums of one projection (128 MiB)
+
+// Up to 64 rows a projection is a weight stream, as in decode: 6.7B shape, 64 rows, us on the 256 x 256 tiles / on
+// the decode kernel: QKV 80 / 23, output 87 / 9.9, FFN1 80 / 26, FFN2 292 / 27.
+// Beyond, the tile and the K split with the least estimated time.  The estimate is (k-steps of a workgroup) x (time of
+// a k-step with the number of workgroups a CU then holds), summed over the rounds of workgroups, plus the traffic of
+// the partial sums.  Step times measured at the 6.7B and 1.3B shapes, 64 to 4096 rows (us): 256 x 256 0.57 (few
+// workgroups) to 0.75 (all CUs: the clock drops); 128 x 128 0.32 alone on a CU, 0.52 for two; 64 x 128 0.255 / 0.44;
+// 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
+// at 1024 rows of the 6.7B shape FFN1 takes 100 us on 256 x 256 and 138 on 128 x 128, at 256 rows 80 and 44.
+RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
+  RowsGemm best;
+  const int Kf = K / 32;
+  if (rows <= 64) {
+    best.kind = RowsGemm::SKINNY;
+    best.B_pad = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
+    const GemmPlan p = split_ok ? plan_split(N, K, best.B_pad) : plan_direct(N, best.B_pad);
+    best.R = p.R;
+    best.split = p.split;
+    best.partial = split_ok;
+    return best;
+  }
+  static const struct { int wr, ar, cap; double step[4]; } cfg[] = {
+      {256, 256, 1, {0.57}}, {128, 128, 2, {0.32, 0.52}}, {64, 128, 2, {0.255, 0.44}}, {128, 64, 2, {0.255, 0.44}},
+      {64, 64, 4, {0.19, 0.33, 0.44, 0.55}}};
+  static const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16};
+  double best_t = 1e30;
+  for (const auto &c : cfg) {
+    if (N % c.wr) continue;
+    const long tiles = (long)(N / c.wr) * ((rows + c.ar - 1) / c.ar);
+    for (int sp : splits) {
+      if (sp > 1 && (!split_ok || Kf / sp < 8 || (long)sp * (rows + 255) * N > kRowsPartialMax)) break;
+      const long wgs = tiles * sp, slots = 256L * c.cap, full = wgs / slots, rem = wgs % slots;
+      const double clock = c.wr == 256 ? 0.18 * std::min(1.0, wgs / 256.0) : 0.0;
+      double step = full * (c.step[c.cap - 1] + clock);
+      if (rem) step += c.step[(rem + 255) / 256 - 1] + clock;
+      const double t = 3.0 + (double)((Kf + sp - 1) / sp) * step + (sp > 1 ? (sp - 1) * 8.0 * rows * N / 4.5e6 : 0.0);
+      if (t < best_t) {
+        best_t = t;
+        best.kind = c.wr == 256 ? RowsGemm::TILE : RowsGemm::MID;
+        best.wr = c.wr;
+        best.ar = c.ar;
+        best.split = sp;
+        best.partial = sp > 1;
+      }
+    }
+  }
+  return best;  // CHUNKS when no tile divides N
+}
+
 // Whole prompt at once, layer by layer (Section 2.3: the prompt needs no generation, so it can be batched over
-// positions): activation rows are the real (sequence, position) pairs (left padding gets no rows), the projections
-// run on 256 x 256 tiles, attention is causal over the pages the QKV projection has just filled.
+// positions): activation rows are the real (sequence, position) pairs (left padding gets no rows), attention is
+// causal over the pages the QKV projection has just filled.  A row depends on rows of its own sequence before it
+// only, so what padding rows hold never matters.
 static int prefill_batched(skd_state *st, const int32_t *cols) {
   const skd_config &c = st->cfg;
   const int B = c.batch, P = c.prompt_size, d = c.d_model, f = c.ffn, L = c.L;
@@ -706,64 +781,93 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
   const long cap = ((long)B * P_pad + 255) / 256 * 256;  // workspace rows: every position of every sequence
   hipStream_t s = st->stream;
   if (!st->pf_x) {
-    SKDCHECK(dev_alloc(st, &st->pf_x, (size_t)cap * d));
-    SKDCHECK(dev_alloc(st, &st->pf_a, (size_t)cap * d));
-    SKDCHECK(dev_alloc(st, &st->pf_q, (size_t)cap * d));
-    SKDCHECK(dev_alloc(st, &st->pf_o, (size_t)cap * d));
-    SKDCHECK(dev_alloc(st, &st->pf_u, (size_t)cap * f));
+    auto rows_alloc = [&](auto **p, size_t n) -> int {
+      SKDCHECK(dev_alloc(st, p, n));
+      HIPCHECK(hipMemsetAsync(*p, 0, n * sizeof(**p), s));  // once: padding rows are read by the projections
+      return SKD_OK;
+    };
+    SKDCHECK(rows_alloc(&st->pf_a, (size_t)cap * d));
+    SKDCHECK(rows_alloc(&st->pf_q, (size_t)cap * d));
+    SKDCHECK(rows_alloc(&st->pf_o, (size_t)cap * d));
+    SKDCHECK(rows_alloc(&st->pf_u, (size_t)cap * f));
+    SKDCHECK(dev_alloc(st, &st->pf_partial, (size_t)std::min(kRowsPartialMax, 16 * cap * d)));
     SKDCHECK(dev_alloc(st, &st->pf_seq, (size_t)cap));
     SKDCHECK(dev_alloc(st, &st->pf_first, (size_t)B));
+    SKDCHECK(rows_alloc(&st->pf_x, (size_t)cap * d));
   }
   // only real tokens get rows: sequence b owns its P - start[b] positions, padded to whole 16-row tiles
-  std::vector<int32_t> first(B), seq((size_t)cap, -1);
-  long rows = 0;
+  PromptMap pm{};
+  int rows = 0;
   for (int b = 0; b < B; ++b) {
-    const int len = P - st->start_host[b], lp = (len + 15) / 16 * 16;
-    first[b] = (int32_t)rows;
-    std::fill(seq.begin() + rows, seq.begin() + rows + lp, b);
-    rows += lp;
+    pm.start[b] = st->start_host[b];
+    pm.first[b] = rows;
+    pm.order[b] = (uint8_t)st->order_host[b];
+    rows += (P - st->start_host[b] + 15) / 16 * 16;
   }
-  const long rows_pad = (rows + 255) / 256 * 256;
-  HIPCHECK(hipMemcpyAsync(st->pf_seq, seq.data(), (size_t)rows_pad * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIPCHECK(hipMemcpyAsync(st->pf_first, first.data(), (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIPCHECK(hipStreamSynchronize(s));  // the host vectors go out of scope
+  const int rows_pad = (rows + 255) / 256 * 256;
+  bf16_prompt_map(s, pm, B, rows, rows_pad, P, st->start_dev, st->order_dev, st->pf_first, st->pf_seq);
   RowMap rm{st->pf_seq, st->pf_first, st->start_dev, P};
-  // padding rows are read by the projections: keep them finite
-  HIPCHECK(hipMemsetAsync(st->pf_x, 0, (size_t)rows_pad * d * sizeof(float), s));
-  HIPCHECK(hipMemsetAsync(st->pf_a, 0, (size_t)rows_pad * d * sizeof(bf16_t), s));
-  HIPCHECK(hipMemsetAsync(st->pf_q, 0, (size_t)rows_pad * d * sizeof(bf16_t), s));
-  HIPCHECK(hipMemsetAsync(st->pf_o, 0, (size_t)rows_pad * d * sizeof(bf16_t), s));
-  bf16_embed_ln_rows(s, cols, rm, (int)rows, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, st->lw[0].ln1_g,
+  bf16_embed_ln_rows(s, cols, rm, rows, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, st->lw[0].ln1_g,
                      st->lw[0].ln1_b, st->pf_x, st->pf_a, B, d, c.vocab);
-  // 256 x 256 tiles where the shape allows, else 128-row chunks through the skinny kernel
-  auto proj = [&](const GemmArgs &g, int epi) {
-    if (st->prefill_tiles && bf16_gemm_tile(s, g, epi) == 0) return 0;
+  auto plan = [&](int N, int K, bool split_ok) {
+    RowsGemm p;
+    if (st->prefill_tiles && !st->prefill_wr) return plan_rows(N, K, rows, split_ok);
+    if (st->prefill_tiles && N % st->prefill_wr == 0) {  // forced tile
+      p.kind = st->prefill_wr == 256 ? RowsGemm::TILE : RowsGemm::MID;
+      p.wr = st->prefill_wr;
+      p.ar = st->prefill_ar;
+      p.split = split_ok ? std::min(st->prefill_split, K / 32) : 1;
+      if ((long)p.split * rows_pad * N > kRowsPartialMax) p.split = 1;
+      p.partial = p.split > 1;
+    }
+    return p;
+  };
+  const RowsGemm r_qkv = plan(3 * d, d, false), r_out = plan(d, d, true), r_ffn1 = plan(f, d, false), r_ffn2 = plan(d, f, true);
+  auto stride = [&](const RowsGemm &p) { return p.kind == RowsGemm::SKINNY ? p.B_pad : rows_pad; };  // of the partial sums
+  auto proj = [&](GemmArgs g, int epi, const RowsGemm &p) {
+    if (p.partial) epi = EPI_PARTIAL;
+    g.split = p.split;
+    g.B_pad = stride(p);
+    g.rows = rows;
+    if (p.kind == RowsGemm::TILE) return bf16_gemm_tile(s, g, epi);
+    if (p.kind == RowsGemm::MID) return bf16_gemm_mid(s, g, epi, p.wr, p.ar);
+    if (p.kind == RowsGemm::SKINNY) {
+      g.rows = p.B_pad;
+      return bf16_gemm(s, g, epi, p.R, 1, 8);
+    }
+    g.B_pad = 128;  // 128-row chunks through the skinny kernel
+    g.rows = (rows + 127) / 128 * 128;
     return bf16_gemm(s, g, epi, g.N % 64 ? 1 : 4, 1, 4);
   };
   for (int l = 0; l < L; ++l) {
     const LayerW &w = st->lw[l];
     GemmArgs ga{};
-    ga.B = B; ga.B_pad = 128; ga.rows = (int)rows_pad; ga.rm = rm; ga.kv = st->geom; ga.d = d; ga.split = 1;
+    ga.B = B; ga.rm = rm; ga.kv = st->geom; ga.d = d; ga.partial = st->pf_partial; ga.x = st->pf_x;
     ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = st->pf_a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d;
     ga.q_out = st->pf_q; ga.kv_pool = (bf16_t *)st->pool; ga.bt_layer = bt_layer(st, l);
-    if (proj(ga, EPI_QKV_ROWS) < 0) return SKD_ERR_SHAPE;
+    if (proj(ga, EPI_QKV_ROWS, r_qkv) < 0) return SKD_ERR_SHAPE;
     AttnRowsArgs aa{};
     aa.q = st->pf_q; aa.pool = (const bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.rm = rm;
-    aa.rows = (int)rows; aa.kv = st->geom; aa.o = st->pf_o;
+    aa.rows = rows; aa.kv = st->geom; aa.o = st->pf_o;
     bf16_attention_rows(s, aa);
-    ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = st->pf_o; ga.bias = w.bo; ga.N = d; ga.K = d; ga.x = st->pf_x;
-    if (proj(ga, EPI_RESID) < 0) return SKD_ERR_SHAPE;
-    bf16_ln_rows(s, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, (int)rows, d);
+    ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = st->pf_o; ga.bias = w.bo; ga.N = d; ga.K = d;
+    if (proj(ga, EPI_RESID, r_out) < 0) return SKD_ERR_SHAPE;
+    if (r_out.partial) bf16_reduce_ln(s, st->pf_partial, r_out.split, stride(r_out), w.bo, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, rows, d);
+    else bf16_ln_rows(s, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, rows, d);
     ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = st->pf_a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.act_out = st->pf_u;
-    if (proj(ga, EPI_RELU) < 0) return SKD_ERR_SHAPE;
-    ga.W = (const bf16_t *)w.w2; ga.G = st->p_ffn2.R; ga.A = st->pf_u; ga.bias = w.b2; ga.N = d; ga.K = f; ga.x = st->pf_x;
-    if (proj(ga, EPI_RESID) < 0) return SKD_ERR_SHAPE;
-    if (l + 1 < L) bf16_ln_rows(s, st->pf_x, st->lw[l + 1].ln1_g, st->lw[l + 1].ln1_b, st->pf_a, (int)rows, d);
+    if (proj(ga, EPI_RELU, r_ffn1) < 0) return SKD_ERR_SHAPE;
+    ga.W = (const bf16_t *)w.w2; ga.G = st->p_ffn2.R; ga.A = st->pf_u; ga.bias = w.b2; ga.N = d; ga.K = f;
+    if (proj(ga, EPI_RESID, r_ffn2) < 0) return SKD_ERR_SHAPE;
+    if (l + 1 < L) {
+      const LayerW &nw = st->lw[l + 1];
+      if (r_ffn2.partial) bf16_reduce_ln(s, st->pf_partial, r_ffn2.split, stride(r_ffn2), w.b2, st->pf_x, nw.ln1_g, nw.ln1_b, st->pf_a, rows, d);
+      else bf16_ln_rows(s, st->pf_x, nw.ln1_g, nw.ln1_b, st->pf_a, rows, d);
+    }
     st->kv_len[l] = P;
   }
   // hidden state of the last prompt column, and its final LayerNorm, where the heads expect them
-  bf16_gather_rows(s, st->pf_x, st->x, rm, B, d);
-  bf16_ln_rows(s, st->x, st->lnf_g, st->lnf_b, (bf16_t *)st->a, B, d);
+  bf16_last_rows_ln(s, st->pf_x, rm, st->pf_partial, r_ffn2.partial ? r_ffn2.split : 0, stride(r_ffn2), st->lw[L - 1].b2,
+                    st->lnf_g, st->lnf_b, st->x, (bf16_t *)st->a, B, d);
   HIPCHECK(hipGetLastError());
   st->have_hidden = true;
   st->have_argmax = false;
@@ -800,7 +904,7 @@ extern "C" int skd_prefill(skd_state *st, const int32_t *tokens, const uint8_t *
     HIPCHECK(hipStreamSynchronize(st->stream));
     cols = st->prompt_dev;
   }
-  SKDCHECK(upload_start(st, start));
+  set_start(st, start);
   std::fill(st->kv_len.begin(), st->kv_len.end(), 0);
   st->prefilled = false;
   st->steps_done = 0;
@@ -810,6 +914,7 @@ extern "C" int skd_prefill(skd_state *st, const int32_t *tokens, const uint8_t *
   if (st->bf16 && st->prefill_mode == 1 && full_depth_prompt) {
     SKDCHECK(prefill_batched(st, cols));
   } else {
+    SKDCHECK(upload_start(st));
     for (int i = 0; i < P; ++i) {  // column by column
       const int n = state_active_layers(st, i, st->layers_tmp.data());
       if (n < 0) return n;
@@ -1024,7 +1129,8 @@ extern "C" int skd_debug_kv_load(skd_state *st, int32_t cols, const float *const
   {
     std::vector<int32_t> start(B, 0);
     if (start_in) start.assign(start_in, start_in + B);
-    SKDCHECK(upload_start(st, start));  // the bf16 pages are addressed by real position
+    set_start(st, start);
+    SKDCHECK(upload_start(st));  // the bf16 pages are addressed by real position
   }
   const size_t n = (size_t)B * cols * d;
   float *kd = nullptr, *vd = nullptr;

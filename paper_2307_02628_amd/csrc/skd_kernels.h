@@ -82,6 +82,14 @@ struct RowMap {
   int P;                     // prompt columns
 };
 
+struct PromptMap {  // by-value kernel argument
+  int32_t start[128], first[128];
+  uint8_t order[128];
+};
+// start, order, first [B] and seq [rows_pad] from pm; rows = rows of all sequences (each padded to 16)
+void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, int32_t *start,
+                     int32_t *order, int32_t *first, int32_t *seq);
+
 enum GemmEpilogue {
   EPI_PARTIAL = 0,  // fp32 partial sums [split][B_pad][N], no bias
   EPI_QKV = 1,      // + bias; q -> row-major bf16, k/v -> row-major staging rows (filed into the page by bf16_attention)
@@ -100,8 +108,8 @@ struct GemmArgs {
   int split;           // workgroups along K (grid.y)
   int ws_rot;          // bf16_gemm_ws: workgroups start their K range at different stages
   // batched prompt processing: activation rows are the real (sequence, position) pairs of `rm`, handled in
-  // 256 x 256 tiles or in chunks of B_pad rows along grid.z.  rows = 0: one chunk whose rows are the batch (decode).
-  int rows;            // rows of the prompt pass, padded to 256
+  // output tiles or in chunks of B_pad rows along grid.z.  rows = 0: one chunk whose rows are the batch (decode).
+  int rows;            // rows of the prompt pass (whole 16-row tiles)
   RowMap rm;           // EPI_QKV_ROWS
   float *x;            // EPI_RESID: [rows][N] fp32
   // outputs (by epilogue)
@@ -129,9 +137,14 @@ int bf16_gemm_groups(int N, int R);
 // shapes it does not handle; bf16_gemm_ws_check answers the same without launching.
 int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epilogue, int R);
 int bf16_gemm_ws_check(const GemmArgs &a, int epilogue, int R);
-// Batched prompt only (a.rows > 0; EPI_QKV_ROWS, EPI_RESID or EPI_RELU): 256 x 256 output tiles with LDS-staged
-// operands.  Needs rows % 256 == 0 and N % 256 == 0 (K % 32 == 0 as everywhere); returns -1 otherwise (nothing launched).
+// Batched prompt only (a.rows > 0; EPI_QKV_ROWS, EPI_RESID, EPI_RELU or EPI_PARTIAL; a.split > 1 with EPI_PARTIAL
+// only): output tiles with LDS-staged operands.  Buffers are padded to whole tiles of 256 rows: the rows past a.rows of
+// the last tile are read and written.  EPI_PARTIAL: fp32 sums [split][B_pad][N], B_pad = rows of that buffer.
+// Both return -1 for shapes that do not tile (nothing launched).
+// 256 x 256 tiles: N % 256 == 0.
 int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epilogue);
+// weight_rows x act_rows = 128 x 128, 64 x 128, 128 x 64 or 64 x 64 tiles: N % weight_rows == 0.
+int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epilogue, int weight_rows, int act_rows);
 
 void bf16_embed_ln(hipStream_t s, const int32_t *tokens, const int32_t *start, int t, const bf16_t *tok_emb,
                    const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
@@ -172,8 +185,10 @@ void bf16_embed_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int row
                         const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
                         int V);
 void bf16_ln_rows(hipStream_t s, const float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d);
-// x_out[b][:] = row of sequence b's last prompt position
-void bf16_gather_rows(hipStream_t s, const float *x_rows, float *x_out, RowMap rm, int B, int d);
+// x_out[b][:] = row of sequence b's last prompt position (+ bias + sum of `split` partial sums [split][stride][d] when
+// split > 0); a_out = its LayerNorm
+void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
+                       const float *bias, const float *g, const float *b, float *x_out, bf16_t *a_out, int B, int d);
 void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens,
                        int B);
 
