@@ -1020,33 +1020,33 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
 
 // ------------------------------------------------------------------ tiled GEMM for prompts of a few hundred rows
 // On 256 x 256 tiles a prompt of a few hundred rows gives a handful of workgroups (912 rows at d = 2048: 32 for the
-// N = d projections, on 256 CUs).  The same ring and fragment order with 4 waves (2 x 2, RT x MT MFMA tiles each) own
-// 32 RT weight rows x 32 MT activation rows; two workgroups share a CU (5 stages of (RT + MT) * 2 KiB each), so one
-// multiplies while the other waits at its barrier, and the K range can be split over `a.split` workgroups whose fp32
-// partial sums the row reducer adds.  The price is operand traffic: a 128 x 128 tile moves twice the bytes per MFMA
-// of a 256 x 256 one, which is why prompts that fill the chip with the larger tile stay there.
+// N = d projections, on 256 CUs).  The same ring and fragment order with WN x WM waves of RT x MT MFMA tiles each: the
+// workgroup owns 16 RT WN weight rows x 16 MT WM activation rows, the ring has NS stages, and the K range can be split
+// over `a.split` workgroups whose fp32 partial sums the row reducer adds.  With 4 waves two workgroups share a CU, so
+// one multiplies while the other waits at its barrier.  What bounds it is how many bytes a CU takes in per MFMA: the
+// memory path delivers about 60 GB/s to a CU at the latency of these loads whatever the ring depth (64 x 128 tiles: 5
+// and 6 stages alike, 64 x 64: 5 and 9), so the largest tile that still fills the chip wins.
 // us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
-// FFN1 80 -> 44, FFN2 296 -> 47 (split 4); 1024 rows of the 1.3B shape QKV 45 -> 37, output 52 -> 15 (split 2), FFN1
-// 46 -> 41, FFN2 154 -> 42 (split 2).
-constexpr int MID_NS = 5;  // ring stages
-
+// FFN1 80 -> 44, FFN2 296 -> 46 (split 4), all 128 x 128; 1024 rows of the 1.3B shape QKV 44 -> 32 and FFN1 45 -> 35
+// (128 x 256; 128 x 128: 37 and 41), output 51 -> 15 (128 x 128, split 2), FFN2 153 -> 37 (128 x 256, split 4).
 template <int N>
 __device__ inline void wait_vmcnt() {  // at most N vector-memory operations of this wave outstanding (vmcnt: bits 15:14, 3:0)
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-template <int RT, int MT, int EPI>
-__global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
-  constexpr int FR = 2 * (RT + MT), LPW = FR / 4;  // fragments per stage, loads per wave and stage
-  extern __shared__ bf16x8 mid_lds[];              // [MID_NS][FR][64 lanes]
+template <int RT, int MT, int WN, int WM, int NS, int EPI>
+__global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
+  constexpr int FW = WN * RT, FA = WM * MT, FR = FW + FA;  // weight and activation fragments per stage
+  constexpr int LPW = FR / (WN * WM);                      // loads per wave and stage
+  extern __shared__ bf16x8 mid_lds[];                      // [NS][FR][64 lanes]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wr = wave >> 1, wc = wave & 1;
+  const int wr = wave / WM, wc = wave % WM;
   const int Kf = a.K >> 5;
   // workgroup -> (K part, output tile), XCD-aware as in k_gemm_tile: every XCD walks a contiguous range, bands of 4
   // activation tiles x all weight tiles
   int tn, tm, sp;
   {
-    const int gx = a.N / (32 * RT), gy = (a.rows + 32 * MT - 1) / (32 * MT), tiles = gx * gy, total = tiles * a.split;
+    const int gx = a.N / (16 * FW), gy = (a.rows + 16 * FA - 1) / (16 * FA), tiles = gx * gy, total = tiles * a.split;
     const int id = blockIdx.x, xcd = id & 7;
     int logical = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
     sp = logical / tiles;
@@ -1057,20 +1057,20 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
   }
   const int k0 = (int)((long)Kf * sp / a.split), n = (int)((long)Kf * (sp + 1) / a.split) - k0;
 
-  // this wave's fragments of a stage: LPW consecutive ones of [2 RT weight tiles, 2 MT activation-row tiles]
+  // this wave's fragments of a stage: LPW consecutive ones of [FW weight tiles, FA activation-row tiles]
   const bf16x8 *src[LPW];
   long stride[LPW];
   unsigned vl[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
     const int fr = wave * LPW + i;
-    if (fr < 2 * RT) {
-      const int T = tn * 2 * RT + fr;
+    if (fr < FW) {
+      const int T = tn * FW + fr;
       src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * Kf + k0) * a.G + T % a.G) * 64;
       stride[i] = (long)a.G * 64;
       vl[i] = lane;
     } else {
-      src[i] = (const bf16x8 *)a.A + ((long)(tm * 2 * MT + fr - 2 * RT) * Kf + k0) * 64;
+      src[i] = (const bf16x8 *)a.A + ((long)(tm * FA + fr - FW) * Kf + k0) * 64;
       stride[i] = 64;
       vl[i] = act_lane(lane);  // fetched in MFMA lane order
     }
@@ -1082,18 +1082,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
     for (int m = 0; m < MT; ++m) acc[r][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   auto issue = [&](int st) {
-    bf16x8 *dst = mid_lds + ((st % MID_NS) * FR + wave * LPW) * 64;
+    bf16x8 *dst = mid_lds + ((st % NS) * FR + wave * LPW) * 64;
 #pragma unroll
     for (int i = 0; i < LPW; ++i)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)&(src[i] + (long)st * stride[i])[vl[i]],
                                        (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
   };
   auto read = [&](int st, bf16x8(&wf)[RT], bf16x8(&xf)[MT]) {
-    const bf16x8 *base = mid_lds + (st % MID_NS) * (FR * 64) + lane;
+    const bf16x8 *base = mid_lds + (st % NS) * (FR * 64) + lane;
 #pragma unroll
     for (int r = 0; r < RT; ++r) wf[r] = base[(wr * RT + r) * 64];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xf[m] = base[(2 * RT + wc * MT + m) * 64];
+    for (int m = 0; m < MT; ++m) xf[m] = base[(FW + wc * MT + m) * 64];
   };
   auto mma = [&](const bf16x8(&wf)[RT], const bf16x8(&xf)[MT]) {
 #pragma unroll
@@ -1109,25 +1109,26 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
   };
   // stage st becomes readable, the slot of stage st - 1 is refilled (see k_gemm_tile)
   auto open_stage = [&](int st) {
-    const int later = min(n - 1 - st, MID_NS - 2);
+    const int later = min(n - 1 - st, NS - 2);
     if (later == 0) wait_vmcnt<0>();
     else if (later == 1) wait_vmcnt<LPW>();
     else if (later == 2) wait_vmcnt<2 * LPW>();
-    else wait_vmcnt<3 * LPW>();
+    else if (later == 3) wait_vmcnt<3 * LPW>();
+    else wait_vmcnt<(NS - 2) * LPW>();
     bar();
-    if (st + MID_NS - 1 < n) issue(st + MID_NS - 1);
+    if (st + NS - 1 < n) issue(st + NS - 1);
   };
 #pragma unroll
-  for (int i = 0; i < MID_NS - 1; ++i)
+  for (int i = 0; i < NS - 1; ++i)
     if (i < n) issue(i);
   bf16x8 wfA[RT], xfA[MT], wfB[RT], xfB[MT];
   open_stage(0);
   read(0, wfA, xfA);
   // steady state: the LDS reads of the next stage are dealt out among the MFMAs of the current one
   auto steady = [&](int nx, bf16x8(&wn)[RT], bf16x8(&xn)[MT], const bf16x8(&wc_)[RT], const bf16x8(&xc)[MT]) {
-    wait_vmcnt<(MID_NS - 2) * LPW>();
+    wait_vmcnt<(NS - 2) * LPW>();
     bar();
-    issue(nx + MID_NS - 1);
+    issue(nx + NS - 1);
     read(nx, wn, xn);
     mma(wc_, xc);
     __builtin_amdgcn_sched_group_barrier(0x020, LPW, 0);
@@ -1139,7 +1140,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
     __builtin_amdgcn_sched_group_barrier(0x008, RT * MT - (RT + MT), 0);
   };
   int st = 0;
-  for (; st + MID_NS + 1 < n; st += 2) {
+  for (; st + NS + 1 < n; st += 2) {
     steady(st + 1, wfB, xfB, wfA, xfA);
     steady(st + 2, wfA, xfA, wfB, xfB);
   }
@@ -1159,42 +1160,45 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mid(GemmArgs a) {
       mma(wfB, xfB);
     }
   }
-  tile_epilogue<EPI, RT, MT>(a, acc, tn * 2 * RT + wr * RT, tm * 2 * MT + wc * MT, sp, lane);
+  tile_epilogue<EPI, RT, MT>(a, acc, tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);
 }
 
-template <int RT, int MT>
+template <int RT, int MT, int WN, int WM, int NS>
 static int launch_gemm_mid(hipStream_t s, const GemmArgs &a, int epi) {
-  constexpr size_t lds = (size_t)MID_NS * 2 * (RT + MT) * 64 * sizeof(bf16x8);
-  if (a.N % (32 * RT)) return -1;
+  constexpr int BN = 16 * RT * WN, BM = 16 * MT * WM;
+  constexpr size_t lds = (size_t)NS * (BN + BM) * 4 * sizeof(bf16x8);
+  if (a.N % BN) return -1;
   static bool configured = false;
   if (!configured) {
-    if (hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return -1;
     configured = true;
   }
-  const dim3 grid((a.N / (32 * RT)) * ((a.rows + 32 * MT - 1) / (32 * MT)) * a.split), blk(256);
+  const dim3 grid((a.N / BN) * ((a.rows + BM - 1) / BM) * a.split), blk(WN * WM * 64);
   switch (epi) {
-    case EPI_QKV_ROWS: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_QKV_ROWS>), grid, blk, lds, s, a); break;
-    case EPI_RESID: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_RESID>), grid, blk, lds, s, a); break;
-    case EPI_PARTIAL: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_PARTIAL>), grid, blk, lds, s, a); break;
-    case EPI_RELU: SKD_LAUNCH((k_gemm_mid<RT, MT, EPI_RELU>), grid, blk, lds, s, a); break;
+    case EPI_QKV_ROWS: SKD_LAUNCH((k_gemm_mid<RT, MT, WN, WM, NS, EPI_QKV_ROWS>), grid, blk, lds, s, a); break;
+    case EPI_RESID: SKD_LAUNCH((k_gemm_mid<RT, MT, WN, WM, NS, EPI_RESID>), grid, blk, lds, s, a); break;
+    case EPI_PARTIAL: SKD_LAUNCH((k_gemm_mid<RT, MT, WN, WM, NS, EPI_PARTIAL>), grid, blk, lds, s, a); break;
+    case EPI_RELU: SKD_LAUNCH((k_gemm_mid<RT, MT, WN, WM, NS, EPI_RELU>), grid, blk, lds, s, a); break;
     default: return -1;
   }
   return 0;
 }
-// weight_rows x act_rows per workgroup: 128 x 128, 64 x 128, 128 x 64 or 64 x 64.  Returns 0, or -1 when the shape does
+// weight_rows x act_rows per workgroup: 256 x 128, 128 x 256, 128 x 128, 64 x 128, 128 x 64 or 64 x 64.  Returns 0, or -1 when the shape does
 // not tile (nothing launched).
 int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epi, int weight_rows, int act_rows) {
   const int Kf = a.K >> 5;
   if (a.rows <= 0 || a.N < 1 || a.K < 32 || a.K % 32 || a.G < 1 || a.G > 4 || a.split < 1 || a.split > Kf) return -1;
   if (a.split != 1 && epi != EPI_PARTIAL) return -1;
-  if (weight_rows == 128 && act_rows == 128) return launch_gemm_mid<4, 4>(s, a, epi);
-  if (weight_rows == 64 && act_rows == 128) return launch_gemm_mid<2, 4>(s, a, epi);
-  if (weight_rows == 128 && act_rows == 64) return launch_gemm_mid<4, 2>(s, a, epi);
-  if (weight_rows == 64 && act_rows == 64) return launch_gemm_mid<2, 2>(s, a, epi);
+  if (weight_rows == 256 && act_rows == 128) return launch_gemm_mid<4, 4, 4, 2, 6>(s, a, epi);
+  if (weight_rows == 128 && act_rows == 256) return launch_gemm_mid<4, 4, 2, 4, 6>(s, a, epi);
+  if (weight_rows == 128 && act_rows == 128) return launch_gemm_mid<4, 4, 2, 2, 5>(s, a, epi);
+  if (weight_rows == 64 && act_rows == 128) return launch_gemm_mid<2, 4, 2, 2, 5>(s, a, epi);
+  if (weight_rows == 128 && act_rows == 64) return launch_gemm_mid<4, 2, 2, 2, 5>(s, a, epi);
+  if (weight_rows == 64 && act_rows == 64) return launch_gemm_mid<2, 2, 2, 2, 5>(s, a, epi);
   return -1;
 }
 

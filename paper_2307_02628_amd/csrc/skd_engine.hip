@@ -626,7 +626,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
       int wr = 0, ar = 0, sp = 1;
       const char *e = getenv("SKD_PREFILL_TILE");
       if (e && sscanf(e, "%dx%dx%d", &wr, &ar, &sp) == 3 && sp >= 1 && sp <= 16 &&
-          ((wr == 256 && ar == 256) || ((wr == 128 || wr == 64) && (ar == 128 || ar == 64)))) {
+          (wr == 256 || wr == 128 || wr == 64) && (ar == 256 || ar == 128 || ar == 64) && wr * ar != 256 * 64) {
         st->prefill_wr = wr;
         st->prefill_ar = ar;
         st->prefill_split = sp;
@@ -727,8 +727,8 @@ constexpr long kRowsPartialMax = 32L << 20;  // fp32 partial sums of one project
 // Beyond, the tile and the K split with the least estimated time.  The estimate is (k-steps of a workgroup) x (time of
 // a k-step with the number of workgroups a CU then holds), summed over the rounds of workgroups, plus the traffic of
 // the partial sums.  Step times measured at the 6.7B and 1.3B shapes, 64 to 4096 rows (us): 256 x 256 0.57 (few
-// workgroups) to 0.75 (all CUs: the clock drops); 128 x 128 0.32 alone on a CU, 0.52 for two; 64 x 128 0.255 / 0.44;
-// 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
+// workgroups) to 0.75 (all CUs: the clock drops); 256 x 128 and 128 x 256 0.45 to 0.51; 128 x 128 0.32 alone on a CU,
+// 0.52 for two; 64 x 128 0.255 / 0.44; 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
 // at 1024 rows of the 6.7B shape FFN1 takes 100 us on 256 x 256 and 138 on 128 x 128, at 256 rows 80 and 44.
 RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   RowsGemm best;
@@ -742,9 +742,10 @@ RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
     best.partial = split_ok;
     return best;
   }
-  static const struct { int wr, ar, cap; double step[4]; } cfg[] = {
-      {256, 256, 1, {0.57}}, {128, 128, 2, {0.32, 0.52}}, {64, 128, 2, {0.255, 0.44}}, {128, 64, 2, {0.255, 0.44}},
-      {64, 64, 4, {0.19, 0.33, 0.44, 0.55}}};
+  // tile, workgroups a CU holds, step time by workgroups on the CU, what a full chip adds
+  static const struct { int wr, ar, cap; double step[4], full; } cfg[] = {
+      {256, 256, 1, {0.57}, 0.18}, {256, 128, 1, {0.455}, 0.06}, {128, 256, 1, {0.45}, 0.05}, {128, 128, 2, {0.32, 0.52}, 0.0},
+      {64, 128, 2, {0.255, 0.44}, 0.0}, {128, 64, 2, {0.255, 0.44}, 0.0}, {64, 64, 4, {0.19, 0.33, 0.44, 0.55}, 0.0}};
   static const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16};
   double best_t = 1e30;
   for (const auto &c : cfg) {
@@ -753,13 +754,13 @@ RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
     for (int sp : splits) {
       if (sp > 1 && (!split_ok || Kf / sp < 8 || (long)sp * (rows + 255) * N > kRowsPartialMax)) break;
       const long wgs = tiles * sp, slots = 256L * c.cap, full = wgs / slots, rem = wgs % slots;
-      const double clock = c.wr == 256 ? 0.18 * std::min(1.0, wgs / 256.0) : 0.0;
+      const double clock = c.full * std::min(1.0, wgs / 256.0);
       double step = full * (c.step[c.cap - 1] + clock);
       if (rem) step += c.step[(rem + 255) / 256 - 1] + clock;
       const double t = 3.0 + (double)((Kf + sp - 1) / sp) * step + (sp > 1 ? (sp - 1) * 8.0 * rows * N / 4.5e6 : 0.0);
       if (t < best_t) {
         best_t = t;
-        best.kind = c.wr == 256 ? RowsGemm::TILE : RowsGemm::MID;
+        best.kind = c.wr == 256 && c.ar == 256 ? RowsGemm::TILE : RowsGemm::MID;
         best.wr = c.wr;
         best.ar = c.ar;
         best.split = sp;
@@ -813,7 +814,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     RowsGemm p;
     if (st->prefill_tiles && !st->prefill_wr) return plan_rows(N, K, rows, split_ok);
     if (st->prefill_tiles && N % st->prefill_wr == 0) {  // forced tile
-      p.kind = st->prefill_wr == 256 ? RowsGemm::TILE : RowsGemm::MID;
+      p.kind = st->prefill_wr == 256 && st->prefill_ar == 256 ? RowsGemm::TILE : RowsGemm::MID;
       p.wr = st->prefill_wr;
       p.ar = st->prefill_ar;
       p.split = split_ok ? std::min(st->prefill_split, K / 32) : 1;

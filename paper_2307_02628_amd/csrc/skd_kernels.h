@@ -143,7 +143,7 @@ int bf16_gemm_ws_check(const GemmArgs &a, int epilogue, int R);
 // Both return -1 for shapes that do not tile (nothing launched).
 // 256 x 256 tiles: N % 256 == 0.
 int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epilogue);
-// weight_rows x act_rows = 128 x 128, 64 x 128, 128 x 64 or 64 x 64 tiles: N % weight_rows == 0.
+// weight_rows x act_rows = 256 x 128, 128 x 256, 128 x 128, 64 x 128, 128 x 64 or 64 x 64 tiles: N % weight_rows == 0.
 int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epilogue, int weight_rows, int act_rows);
 
 void bf16_embed_ln(hipStream_t s, const int32_t *tokens, const int32_t *start, int t, const bf16_t *tok_emb,

@@ -44,7 +44,7 @@ def check(shape, B, P, shortest, env, seed):
 
 
 @pytest.mark.parametrize("shape", [WIDE, NARROW])
-@pytest.mark.parametrize("tile", ["256x256x1", "256x256x3", "128x128x1", "128x128x4", "64x128x2", "128x64x3", "64x64x1", "64x64x5"])
+@pytest.mark.parametrize("tile", ["256x256x1", "256x256x3", "256x128x3", "128x256x1", "128x128x1", "128x128x4", "64x128x2", "128x64x3", "64x64x1", "64x64x5"])
 def test_forced_tiles(shape, tile):
     check(shape, 7, 83, 9, {"SKD_PREFILL_TILE": tile}, 40)      # rows: no multiple of 64; K parts of unequal length
 
