@@ -1548,134 +1548,164 @@ void bf16_attention(hipStream_t s, const AttnArgs &a) {
 }
 
 // ------------------------------------------------------------------ causal attention over a whole prompt
-// Same block arithmetic as k_attention, but the 16 MFMA columns now carry 16
-// different queries (consecutive positions of one sequence) instead of one
-// replicated query.  A wave owns NT = 2 consecutive 16-position tiles of one
-// sequence and one head when both exist (every K and V fragment it loads then
-// serves 32 queries: the kernel is bound by what the vector memory path delivers
-// to registers, 64 bytes per clock and CU, so bytes per query are what counts),
-// else one tile; it walks all key blocks of its tiles itself (no merge; softmax
-// state per column), loading the keys of block i + 1 while it works on block i.  A workgroup
-// is 4 waves on 128 consecutive rows: they read almost the same keys at almost
-// the same time, so all but the first of those loads are cache hits (L2 at
-// worst).  Keys of a query: real positions 0 .. own.
-template <int DH, int NT>
-__device__ inline void attention_rows_tiles(const AttnRowsArgs &a, int h, long row0, int b) {
-  constexpr int QC = DH / 32, VM = DH / 16;
-  const int lane = threadIdx.x & 63, grp = lane >> 4, col = lane & 15;
+// Same fragments as k_attention, but the 16 MFMA columns carry 16 different queries (consecutive positions of one
+// sequence).  A workgroup is 4 waves on 128 consecutive positions of one sequence and one head, a wave two 16-query
+// tiles.  The waves share the K and V blocks: a ring of ATT_NS stages (32 keys, K and V, one contiguous piece of a page)
+// is filled by LDS-direct loads ahead of their use, one bare barrier per stage; each wave loading its own fragments
+// asked four times as much of the CU's memory path (64 bytes per clock).
+// Positions of a wave start at a multiple of 32, so exactly one block, its last, needs the causal mask.
+// The softmax works in units of log2 and against a reference m that is raised only when a score exceeds it by more than
+// 8 (weights up to 2^8: bf16 and fp32 keep their relative precision), so that most blocks need no cross-lane maximum
+// and no rescaling of the 64 accumulators; the denominator comes from the matrix cores (a row of ones), summed over the
+// rounded weights as the numerator is.
+constexpr int ATT_NS = 3;
+
+template <int DH>
+__global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
+  constexpr int QC = DH / 32, VM = DH / 16, NT = 2;
+  constexpr int FR = 2 * QC + VM, LPW = FR / 4;  // fragments per stage, loads per wave and stage
+  extern __shared__ bf16x8 ring[];               // [ATT_NS][FR][64 lanes]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int grp = lane >> 4, col = lane & 15;
+  const int h = blockIdx.x, b = blockIdx.y % a.B;
+  const int g0 = (int)(gridDim.y / a.B - 1 - blockIdx.y / a.B) * 128;  // longest key ranges are dispatched first
+  const int len = a.rm.P - a.rm.start[b];                               // real positions of this sequence
+  if (g0 >= len) return;
   const int d = a.kv.H * DH;
-  const int p0 = (int)(row0 - a.rm.first_row[b]);        // real position of the first query
-  const int len = a.rm.P - a.rm.start[b];                // real positions of this sequence
-  const int last = min(p0 + 16 * NT - 1, len - 1);       // last real position of the tiles
-  const int nblk = (last >> 5) + 1;
+  const int nblk = (min(g0 + 127, len - 1) >> 5) + 1;  // blocks the workgroup walks
+  const int p0 = g0 + 32 * wave;                       // first position of this wave
+  const int mine = p0 < len ? p0 >> 5 : -1;            // this wave's last block
+  const long row0 = (long)a.rm.first_row[b] + p0;
   const int bpp = a.kv.page_tokens >> 5;
   const int32_t *bt_row = a.bt_layer + (long)b * a.kv.max_pages;
-  const float scale = 1.0f / sqrtf((float)DH);
+  const float c = 1.4426950408889634f / sqrtf((float)DH);  // scores -> log2 of the weights
 
+  floatx4 O[NT][VM], L[NT];
+  float m_ref[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    m_ref[t] = -1.0e30f;
+    L[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < VM; ++m) O[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  bf16x8 ones;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+
+  // blocks are issued in order: block ib of page ip comes next.  Lane l holds page 64 w + l of the row for the window w
+  // of 64 pages that ip is in; a window is waited for where it is loaded (waited for at its use, in the loop, the
+  // compiler would wait for the ring's loads as well).
+  int ip = 0, ib = 0, pages = 0;
+  auto issue = [&](int blk) {
+    if (ib == 0 && (ip & 63) == 0) {
+      pages = ip + lane < a.kv.max_pages ? bt_row[ip + lane] : 0;
+      asm volatile("" : "+v"(pages));
+    }
+    const int page = __builtin_amdgcn_readlane(pages, ip & 63);
+    const bf16x8 *src = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * (a.kv.page_tokens * DH * 2) +
+                                         (long)ib * (64 * DH)) + wave * LPW * 64;
+    bf16x8 *dst = ring + ((blk % ATT_NS) * FR + wave * LPW) * 64;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)&(src + i * 64)[lane],
+                                       (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
+    if (++ib == bpp) { ib = 0; ++ip; }
+  };
+#pragma unroll
+  for (int i = 0; i < ATT_NS - 1; ++i)
+    if (i < nblk) issue(i);
   bf16x8 qf[NT][QC];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int c = 0; c < QC; ++c)
-      qf[t][c] = ((const bf16x8 *)a.q)[(((row0 >> 4) + t) * (d >> 5) + ((h * DH) >> 5) + c) * 64 + act_lane(lane)];
-
-  floatx4 O[NT][VM];
-  float m_run[NT], l_run[NT];
+    for (int k = 0; k < QC; ++k) {
+      qf[t][k] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      if (p0 + 16 * t < len)  // the tile exists
+        qf[t][k] = ((const bf16x8 *)a.q)[(((row0 >> 4) + t) * (d >> 5) + ((h * DH) >> 5) + k) * 64 + act_lane(lane)];
+    }
+  // the queries arrive before the loop: waited for inside it, they would make the compiler wait for every load in flight
+  wait_vmcnt<0>();
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    m_run[t] = -1.0e30f;
-    l_run[t] = 0.f;
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int m = 0; m < VM; ++m) O[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  auto blk_ptr = [&](int blk) {
-    const int page = bt_row[blk / bpp];
-    return (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * (a.kv.page_tokens * DH * 2) +
-                            (long)(blk % bpp) * (64 * DH)) + lane;
-  };
-  auto load_k = [&](int blk, bf16x8(&kf)[2][QC]) {
-    const bf16x8 *kp = blk_ptr(blk);
+    for (int k = 0; k < QC; ++k) asm volatile("" : "+v"(qf[t][k]));
+  auto use = [&](int blk, bool diagonal) {
+    const bf16x8 *kv = ring + (blk % ATT_NS) * (FR * 64) + lane;
+    floatx4 S[NT][2];
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl)
+    for (int tl = 0; tl < 2; ++tl) {
+      bf16x8 kf[QC];
 #pragma unroll
-      for (int c = 0; c < QC; ++c) kf[tl][c] = kp[(tl * QC + c) * 64];
-  };
-  auto load_v = [&](int blk, bf16x8(&vf)[VM]) {
-    const bf16x8 *kp = blk_ptr(blk);
+      for (int k = 0; k < QC; ++k) kf[k] = kv[(tl * QC + k) * 64];
 #pragma unroll
-    for (int m = 0; m < VM; ++m) vf[m] = kp[4 * DH + m * 64];
-  };
-  auto use_blk = [&](int blk, const bf16x8(&kf)[2][QC], const bf16x8(&vf)[VM]) {
+      for (int t = 0; t < NT; ++t) {
+        S[t][tl] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < QC; ++k) S[t][tl] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[k], qf[t][k], S[t][tl], 0, 0, 0);
+      }
+    }
+    // S[t][tl][i] = query 16 t + col of this wave . key 32 blk + 16 tl + 4 grp + i
+    bf16x8 pv[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int my_len = p0 + 16 * t + col + 1;  // keys of this column's query: real positions 0 .. own
-      if (NT > 1 && t == 0 && blk * 32 > p0 + 15) continue;  // (uniform) the block lies past the first tile's keys
-      floatx4 S[2];
+      if (diagonal) {
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        S[tl] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int tl = 0; tl < 2; ++tl)
 #pragma unroll
-        for (int c = 0; c < QC; ++c) S[tl] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tl][c], qf[t][c], S[tl], 0, 0, 0);
+          for (int i = 0; i < 4; ++i)
+            if (16 * tl + 4 * grp + i > 16 * t + col) S[t][tl][i] = -1.0e30f;
       }
-      float sv[8];
-      bool ok[8];
-      float bm = -1.0e30f;
+      float bm = fmaxf(fmaxf(fmaxf(S[t][0][0], S[t][0][1]), fmaxf(S[t][0][2], S[t][0][3])),
+                       fmaxf(fmaxf(S[t][1][0], S[t][1][1]), fmaxf(S[t][1][2], S[t][1][3]))) * c;
+      if (__any(bm > m_ref[t] + 8.0f)) {
+        bm = fmaxf(bm, __shfl_xor(bm, 16));  // lanes 16 and 32 apart hold the same query
+        bm = fmaxf(bm, __shfl_xor(bm, 32));
+        const float m_new = fmaxf(m_ref[t], bm);
+        const float alpha = __builtin_amdgcn_exp2f(m_ref[t] - m_new);
+        m_ref[t] = m_new;
+        L[t] *= alpha;
+#pragma unroll
+        for (int m = 0; m < VM; ++m) O[t][m] *= alpha;
+      }
+      uint32_t pk[4];
 #pragma unroll
       for (int tl = 0; tl < 2; ++tl)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int key = blk * 32 + 16 * tl + 4 * grp + i;
-          ok[tl * 4 + i] = key < my_len;
-          sv[tl * 4 + i] = S[tl][i] * scale;
-          if (ok[tl * 4 + i]) bm = fmaxf(bm, sv[tl * 4 + i]);
-        }
-      bm = fmaxf(bm, __shfl_xor(bm, 16));  // lanes 16 and 32 apart hold the same query column
-      bm = fmaxf(bm, __shfl_xor(bm, 32));
-      const float m_new = fmaxf(m_run[t], bm);
-      const float alpha = __expf(m_run[t] - m_new);
-      float ps = 0.f;
-      uint32_t pk[4];
+        for (int i = 0; i < 4; i += 2)
+          pk[tl * 2 + i / 2] = pack2(__builtin_amdgcn_exp2f(__builtin_fmaf(S[t][tl][i], c, -m_ref[t])),
+                                     __builtin_amdgcn_exp2f(__builtin_fmaf(S[t][tl][i + 1], c, -m_ref[t])));
+      pv[t] = __builtin_bit_cast(bf16x8, (uint32x4{pk[0], pk[1], pk[2], pk[3]}));
+      L[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pv[t], L[t], 0, 0, 0);
+    }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float p_lo = ok[2 * j] ? __expf(sv[2 * j] - m_new) : 0.f;
-        const float p_hi = ok[2 * j + 1] ? __expf(sv[2 * j + 1] - m_new) : 0.f;
-        pk[j] = pack2(p_lo, p_hi);
-        ps += bf2f(pk[j] & 0xffffu) + bf2f(pk[j] >> 16);
-      }
-      l_run[t] = l_run[t] * alpha + ps;
-      m_run[t] = m_new;
-      const uint32x4 pku = uint32x4{pk[0], pk[1], pk[2], pk[3]};
-      const bf16x8 pv = __builtin_bit_cast(bf16x8, pku);
+    for (int m = 0; m < VM; ++m) {
+      const bf16x8 vf = kv[(2 * QC + m) * 64];
 #pragma unroll
-      for (int m = 0; m < VM; ++m) {
-        O[t][m] *= alpha;
-        O[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[m], pv, O[t][m], 0, 0, 0);
-      }
+      for (int t = 0; t < NT; ++t) O[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pv[t], O[t][m], 0, 0, 0);
     }
   };
-
-  // keys one block ahead (two register sets), values requested at the top of their block: they are not needed
-  // before the scores and the softmax of the first tile are done
-  bf16x8 kA[2][QC], kB[2][QC], vf[VM];
-  load_k(0, kA);
-  for (int blk = 0; blk < nblk; blk += 2) {
-    load_v(blk, vf);
-    if (blk + 1 < nblk) load_k(blk + 1, kB);
-    use_blk(blk, kA, vf);
-    if (blk + 1 < nblk) {
-      load_v(blk + 1, vf);
-      if (blk + 2 < nblk) load_k(blk + 2, kA);
-      use_blk(blk + 1, kB, vf);
-    }
+  auto open = [&](int blk) {
+    // this wave's loads of stage blk have landed once only those of the later stages in flight are outstanding
+    if (blk + 1 < nblk) wait_vmcnt<(ATT_NS - 2) * LPW>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of stage blk - 1
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (blk + ATT_NS - 1 < nblk) issue(blk + ATT_NS - 1);  // into the slot of stage blk - 1
+  };
+  int blk = 0;
+  for (; blk <= mine; ++blk) {
+    open(blk);
+    use(blk, blk == mine);
   }
+  for (; blk < nblk; ++blk) open(blk);  // blocks that only the other waves need
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float l = l_run[t];
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    // O[t][m][i] = numerator of query `col` of tile t, head-dim element 16m + 4grp + i
-    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    if (p0 + 16 * t >= len) continue;
+    // O[t][m][i] = numerator of query `col` of tile t, head-dim element 16m + 4grp + i; L[t]: its denominator
+    const float inv = L[t][0] > 0.f ? 1.0f / L[t][0] : 0.f;
 #pragma unroll
     for (int m = 0; m < VM; ++m) {
       const uint2 pk = make_uint2(pack2(O[t][m][0] * inv, O[t][m][1] * inv), pack2(O[t][m][2] * inv, O[t][m][3] * inv));
@@ -1684,27 +1714,11 @@ __device__ inline void attention_rows_tiles(const AttnRowsArgs &a, int h, long r
   }
 }
 
-template <int DH>
-__global__ __launch_bounds__(256, 2) void k_attention_rows(AttnRowsArgs a) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int h = blockIdx.x;
-  const long row0 = ((long)blockIdx.y * 4 + wave) * 32;  // first row of this wave's pair of tiles (no barriers below)
-  // rows past the last sequence carry -1; a sequence's rows are whole 16-row tiles, so the second tile of a pair may
-  // belong to the next sequence
-  const int b0 = row0 < a.rows ? a.rm.seq[row0] : -1;
-  const int b1 = row0 + 16 < a.rows ? a.rm.seq[row0 + 16] : -1;
-  if (b0 >= 0 && b1 == b0) {
-    attention_rows_tiles<DH, 2>(a, h, row0, b0);
-    return;
-  }
-  if (b0 >= 0) attention_rows_tiles<DH, 1>(a, h, row0, b0);
-  if (b1 >= 0) attention_rows_tiles<DH, 1>(a, h, row0 + 16, b1);
-}
-
 void bf16_attention_rows(hipStream_t s, const AttnRowsArgs &a) {
-  const dim3 grid(a.kv.H, (a.rows + 127) / 128);
-  if (a.kv.dh == 64) SKD_LAUNCH(k_attention_rows<64>, grid, dim3(256), 0, s, a);
-  else SKD_LAUNCH(k_attention_rows<128>, grid, dim3(256), 0, s, a);
+  const dim3 grid(a.kv.H, a.B * ((a.max_len + 127) / 128));
+  const size_t lds = (size_t)ATT_NS * 32 * a.kv.dh * 2 * sizeof(bf16_t);  // 32 or 64 KiB
+  if (a.kv.dh == 64) SKD_LAUNCH(k_attention_rows<64>, grid, dim3(256), lds, s, a);
+  else SKD_LAUNCH(k_attention_rows<128>, grid, dim3(256), lds, s, a);
 }
 
 // ------------------------------------------------------------------ row kernels of the batched prompt

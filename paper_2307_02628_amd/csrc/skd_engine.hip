@@ -798,8 +798,9 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
   }
   // only real tokens get rows: sequence b owns its P - start[b] positions, padded to whole 16-row tiles
   PromptMap pm{};
-  int rows = 0;
+  int rows = 0, max_len = 0;
   for (int b = 0; b < B; ++b) {
+    max_len = std::max(max_len, P - st->start_host[b]);
     pm.start[b] = st->start_host[b];
     pm.first[b] = rows;
     pm.order[b] = (uint8_t)st->order_host[b];
@@ -849,7 +850,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     if (proj(ga, EPI_QKV_ROWS, r_qkv) < 0) return SKD_ERR_SHAPE;
     AttnRowsArgs aa{};
     aa.q = st->pf_q; aa.pool = (const bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.rm = rm;
-    aa.rows = rows; aa.kv = st->geom; aa.o = st->pf_o;
+    aa.B = B; aa.max_len = max_len; aa.kv = st->geom; aa.o = st->pf_o;
     bf16_attention_rows(s, aa);
     ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = st->pf_o; ga.bias = w.bo; ga.N = d; ga.K = d;
     if (proj(ga, EPI_RESID, r_out) < 0) return SKD_ERR_SHAPE;

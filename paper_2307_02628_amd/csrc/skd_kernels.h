@@ -169,13 +169,13 @@ struct AttnArgs {
   float *part;              // splits > 1: [splits][B*H][dh + 2]
 };
 void bf16_attention(hipStream_t s, const AttnArgs &a);
-// Causal attention of a whole prompt: query rows (b, pos), 64 positions per workgroup, keys of columns start[b] .. pos.
+// Causal attention of a whole prompt: query rows (b, pos), 128 positions per workgroup, keys of columns start[b] .. pos.
 struct AttnRowsArgs {
   const bf16_t *q;          // activation tiles [rows][d]
   const bf16_t *pool;
   const int32_t *bt_layer;  // [B][max_pages]
   RowMap rm;
-  int rows;                 // multiple of 16
+  int B, max_len;           // sequences, positions of the longest one
   KvGeom kv;
   bf16_t *o;                // activation tiles [rows][d]
 };
