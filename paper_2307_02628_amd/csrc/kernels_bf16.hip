@@ -1754,7 +1754,7 @@ __global__ __launch_bounds__(1024) void k_embed_ln_rows(const int32_t *tokens, R
   if (b < 0) return;
   const int pos = row - rm.first_row[b];  // real position = position id
   if (pos >= rm.P - rm.start[b]) {  // padding of the sequence's last 16-row tile: zero (no other row ever depends on it)
-    for (int c = threadIdx.x; c < d4; c += 1024) {
+    for (int c = threadIdx.x; c < d4; c += blockDim.x) {
       ((floatx4 *)x)[(long)row * d4 + c] = floatx4{0.f, 0.f, 0.f, 0.f};
       *(uint2 *)&a_out[d_act_index(row, 4 * c, d)] = make_uint2(0, 0);
     }
@@ -1766,7 +1766,7 @@ __global__ __launch_bounds__(1024) void k_embed_ln_rows(const int32_t *tokens, R
   floatx4 v[LN_NC], gv[LN_NC], bv[LN_NC];
 #pragma unroll
   for (int i = 0; i < LN_NC; ++i) {
-    const int c = (int)threadIdx.x + 1024 * i;
+    const int c = (int)(threadIdx.x + blockDim.x * i);
     if (c < d4) {
       const uint2 aa = te[c], p = pe[c];
       gv[i] = ((const floatx4 *)g)[c];
@@ -1785,7 +1785,7 @@ __global__ __launch_bounds__(1024) void k_ln_rows(const float *x, const float *g
   floatx4 v[LN_NC], gv[LN_NC], bv[LN_NC];
 #pragma unroll
   for (int i = 0; i < LN_NC; ++i) {
-    const int c = (int)threadIdx.x + 1024 * i;
+    const int c = (int)(threadIdx.x + blockDim.x * i);
     if (c < d4) {
       v[i] = ((const floatx4 *)x)[(long)row * d4 + c];
       gv[i] = ((const floatx4 *)g)[c];
@@ -1795,44 +1795,87 @@ __global__ __launch_bounds__(1024) void k_ln_rows(const float *x, const float *g
   ln_finish_row(v, gv, bv, d, row, a_out, sh);
 }
 
-// LayerNorm of 16 consecutive rows (one activation row tile) per workgroup: wave w keeps row 16 * tile + w in
-// registers (rows up to 4096 wide) and needs no barrier for its statistics; the normalised values go through an
-// 8 KiB LDS buffer per 256 columns so that the tile leaves the workgroup as whole, contiguous 8 KiB runs.
-constexpr int LNW_NC = 16;
-__global__ __launch_bounds__(1024) void k_ln_rows16(const float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
-  __shared__ uint2 stage[2][1024];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const long row = (long)blockIdx.x * 16 + wave;
+// LayerNorm of the prompt rows, one wave per row and four rows per workgroup: the row stays in registers (NC chunks of
+// 256 columns), the statistics need no barrier, and four to eight workgroups per CU keep the loads of one row running
+// under the arithmetic and stores of others.  A row's 64-byte pieces of the 16 x 32 tiles are stored directly: two
+// neighbouring rows share a 128-byte line and leave their workgroup at about the same time.  EMBED: the row is the sum
+// of its token and position embeddings (zero in the padding of a sequence's last tile) and is stored to x.
+// Memory-bound: 16384 rows of 4096, 402 MB: 80 us, 5.0 TB/s (113 with 16 rows per 1024-thread workgroup, one such
+// workgroup per CU and a barrier per 256 columns); with the embedding 235 us (one row per workgroup) -> 105.
+template <int NC, bool EMBED>
+__global__ __launch_bounds__(256) void k_ln_rows4(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb, const bf16_t *pos_emb,
+                                                  float *x, const float *g, const float *bt, bf16_t *a_out, int B, int d, int V) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const long row = (long)blockIdx.x * 4 + wave;
   const int nc = d >> 8;  // 256-column chunks
-  const floatx4 *xr = (const floatx4 *)x + row * (d >> 2);
-  floatx4 v[LNW_NC];
+  floatx4 *xr = (floatx4 *)x + row * (d >> 2) + lane;
+  uint2 *out = (uint2 *)(a_out + (row >> 4) * 16 * d) + (lane >> 3) * 128 + (row & 15) * 8 + (lane & 7);
+  floatx4 v[NC];
+  if constexpr (EMBED) {
+    const int b = rm.seq[row];
+    if (b < 0) return;
+    const int pos = (int)row - rm.first_row[b];  // real position = position id
+    if (pos >= rm.P - rm.start[b]) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+        if (i < nc) {
+          xr[64 * i] = floatx4{0.f, 0.f, 0.f, 0.f};
+          out[(long)i * 1024] = make_uint2(0, 0);
+        }
+      return;
+    }
+    int tok = tokens[(long)(rm.start[b] + pos) * B + b];
+    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+    const uint2 *te = (const uint2 *)(tok_emb + (long)tok * d) + lane, *pe = (const uint2 *)(pos_emb + (long)pos * d) + lane;
+    uint2 tv[NC], pv[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (i < nc) {
+        tv[i] = te[64 * i];
+        pv[i] = pe[64 * i];
+      }
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (i < nc) {
+        v[i] = floatx4{bf2f(tv[i].x & 0xffffu) + bf2f(pv[i].x & 0xffffu), bf2f(tv[i].x >> 16) + bf2f(pv[i].x >> 16),
+                       bf2f(tv[i].y & 0xffffu) + bf2f(pv[i].y & 0xffffu), bf2f(tv[i].y >> 16) + bf2f(pv[i].y >> 16)};
+        xr[64 * i] = v[i];
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (i < nc) v[i] = xr[64 * i];
+  }
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < LNW_NC; ++i)
-    if (i < nc) {
-      v[i] = xr[lane + 64 * i];
-      s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-    }
+  for (int i = 0; i < NC; ++i)
+    if (i < nc) s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
   const float mean = wave_sum_f(s) / d;
   float q = 0.f;
 #pragma unroll
-  for (int i = 0; i < LNW_NC; ++i)
+  for (int i = 0; i < NC; ++i)
     if (i < nc) {
       const floatx4 t = v[i] - mean;
       q += (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]);
     }
   const float rstd = 1.0f / sqrtf(wave_sum_f(q) / d + 1e-5f);
-  uint2 *out = (uint2 *)(a_out + (long)blockIdx.x * 16 * d);  // the row tile: d / 32 tiles of 1 KiB, back to back
 #pragma unroll
-  for (int i = 0; i < LNW_NC; ++i)
+  for (int i = 0; i < NC; ++i)
     if (i < nc) {
       const floatx4 gv = ((const floatx4 *)g)[lane + 64 * i], bv = ((const floatx4 *)bt)[lane + 64 * i];
       const floatx4 y = (v[i] - mean) * rstd * gv + bv;
-      // columns 256 i + 4 lane .. + 3 of row `wave`: tile lane / 8 of this chunk, byte wave * 64 + (lane % 8) * 8
-      stage[i & 1][(lane >> 3) * 128 + wave * 8 + (lane & 7)] = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
-      __syncthreads();
-      out[(long)i * 1024 + threadIdx.x] = stage[i & 1][threadIdx.x];
+      out[(long)i * 1024] = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
     }
+}
+template <bool EMBED>
+static bool launch_ln_rows4(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb, const bf16_t *pos_emb,
+                            float *x, const float *g, const float *b, bf16_t *a_out, int B, int d, int V) {
+  if (rows % 4 || d % 256 || d > 4096) return false;  // other widths: one workgroup per row
+  const dim3 grid(rows / 4), blk(256);
+  if (d <= 1024) SKD_LAUNCH((k_ln_rows4<4, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
+  else if (d <= 2048) SKD_LAUNCH((k_ln_rows4<8, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
+  else SKD_LAUNCH((k_ln_rows4<16, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
+  return true;
 }
 
 // Hidden state of each sequence's last prompt position: x_out[b] = its row of x_rows (+ bias + the partial sums of the
@@ -1865,14 +1908,12 @@ __global__ __launch_bounds__(1024) void k_last_rows_ln(const float *x_rows, RowM
 void bf16_embed_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb,
                         const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
                         int V) {
-  SKD_LAUNCH(k_embed_ln_rows, dim3(rows), dim3(1024), 0, s, tokens, rm, tok_emb, pos_emb, g, b, x, a_out, B, d, V);
+  if (launch_ln_rows4<true>(s, tokens, rm, rows, tok_emb, pos_emb, x, g, b, a_out, B, d, V)) return;
+  SKD_LAUNCH(k_embed_ln_rows, dim3(rows), dim3(row_threads(d)), 0, s, tokens, rm, tok_emb, pos_emb, g, b, x, a_out, B, d, V);
 }
-void bf16_ln_rows(hipStream_t s, const float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d) {
-  if (rows % 16 == 0 && d % 256 == 0 && d <= 256 * LNW_NC) {
-    SKD_LAUNCH(k_ln_rows16, dim3(rows / 16), dim3(1024), 0, s, x, g, b, a_out, d);
-    return;
-  }
-  SKD_LAUNCH(k_ln_rows, dim3(rows), dim3(1024), 0, s, x, g, b, a_out, d);
+void bf16_ln_rows(hipStream_t s, float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d) {
+  if (launch_ln_rows4<false>(s, nullptr, RowMap{}, rows, nullptr, nullptr, x, g, b, a_out, 0, d, 0)) return;
+  SKD_LAUNCH(k_ln_rows, dim3(rows), dim3(row_threads(d)), 0, s, x, g, b, a_out, d);
 }
 void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
                        const float *bias, const float *g, const float *b, float *x_out, bf16_t *a_out, int B, int d) {

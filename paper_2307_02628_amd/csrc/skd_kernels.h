@@ -184,7 +184,7 @@ void bf16_attention_rows(hipStream_t s, const AttnRowsArgs &a);
 void bf16_embed_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb,
                         const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
                         int V);
-void bf16_ln_rows(hipStream_t s, const float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d);
+void bf16_ln_rows(hipStream_t s, float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d);
 // x_out[b][:] = row of sequence b's last prompt position (+ bias + sum of `split` partial sums [split][stride][d] when
 // split > 0); a_out = its LayerNorm
 void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
