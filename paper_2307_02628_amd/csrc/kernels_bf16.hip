@@ -33,9 +33,18 @@ __device__ inline uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
+// Sum over the wave, the same value in every lane: rotations inside the rows of 16 lanes (DPP, no LDS round trip as in
+// __shfl_xor), then the four row sums as scalars.
 __device__ inline float wave_sum_f(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  const int i = __builtin_bit_cast(int, v);
+  auto row = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, l)); };
+  return (row(0) + row(16)) + (row(32) + row(48));
 }
 // one barrier: `sh` (16 floats) must not have been read since the last barrier of the block
 __device__ inline float block_sum_once(float v, float *sh) {
@@ -1210,6 +1219,7 @@ int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epi, int weight_rows, in
 constexpr int LN_NC = 4;
 
 // v[i] = elements 4c .. 4c+3 of row b.  LayerNorm (mean, biased variance, eps 1e-5) -> bf16 row of the activation tiles.
+template <int LN_NC>
 __device__ inline void ln_finish_row(const floatx4 (&v)[LN_NC], const floatx4 (&gv)[LN_NC], const floatx4 (&bv)[LN_NC],
                                      int d, int b, bf16_t *a_out, float *sh) {
   const int d4 = d >> 2;
@@ -1271,34 +1281,54 @@ void bf16_embed_ln(hipStream_t s, const int32_t *tokens, const int32_t *start, i
   SKD_LAUNCH(k_embed_ln, dim3(B), dim3(row_threads(d)), 0, s, tokens, start, t, tok_emb, pos_emb, g, b, x, a_out, d, V);
 }
 
-// x[b][:] += bias + sum_s partial[s][b][:] (fixed order), then LayerNorm
+// x[b][:] += bias + sum_s partial[s][b][:] (fixed order), then LayerNorm.  A latency chain: S is the number of partial
+// sums (0 = any, `split` of them), so that all loads are in flight together; as a loop of unknown length the loads
+// of the second and later sums waited for one another.
+template <int S, int NC>
 __global__ __launch_bounds__(1024) void k_reduce_ln(const float *partial, int split, int B_pad, const float *bias,
                                                     float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
   __shared__ float sh[32];
   const int b = blockIdx.x, d4 = d >> 2;
   const floatx4 *p4 = (const floatx4 *)partial;
   floatx4 *x4 = (floatx4 *)x + (long)b * d4;
-  floatx4 v[LN_NC], gv[LN_NC], bv[LN_NC];
+  floatx4 v[NC], gv[NC], bv[NC];
 #pragma unroll
-  for (int i = 0; i < LN_NC; ++i) {
+  for (int i = 0; i < NC; ++i) {
     const int c = (int)(threadIdx.x + blockDim.x * i);
     if (c < d4) {
       const floatx4 xv = x4[c], bias4 = ((const floatx4 *)bias)[c];
       gv[i] = ((const floatx4 *)g)[c];
       bv[i] = ((const floatx4 *)bt)[c];
       floatx4 acc = p4[(long)b * d4 + c];
-#pragma unroll 8
-      for (int sp = 1; sp < split; ++sp) acc += p4[((long)sp * B_pad + b) * d4 + c];
+      if constexpr (S > 0) {
+        floatx4 p[S];
+#pragma unroll
+        for (int sp = 1; sp < S; ++sp) p[sp] = p4[((long)sp * B_pad + b) * d4 + c];
+#pragma unroll
+        for (int sp = 1; sp < S; ++sp) acc += p[sp];
+      } else {
+        for (int sp = 1; sp < split; ++sp) acc += p4[((long)sp * B_pad + b) * d4 + c];
+      }
       v[i] = xv + (acc + bias4);
       x4[c] = v[i];
     }
   }
-  ln_finish_row(v, gv, bv, d, b, a_out, sh);
+  ln_finish_row<NC>(v, gv, bv, d, b, a_out, sh);
 }
 
 void bf16_reduce_ln(hipStream_t s, const float *partial, int split, int B_pad, const float *bias, float *x,
                     const float *g, const float *b, bf16_t *a_out, int B, int d) {
-  SKD_LAUNCH(k_reduce_ln, dim3(B), dim3(row_threads(d)), 0, s, partial, split, B_pad, bias, x, g, b, a_out, d);
+  const dim3 grid(B), blk(row_threads(d));
+#define SKD_RED(S, NC) SKD_LAUNCH((k_reduce_ln<S, NC>), grid, blk, 0, s, partial, split, B_pad, bias, x, g, b, a_out, d)
+  if (d > 4096) SKD_RED(0, LN_NC);
+  else if (split == 1) SKD_RED(1, 1);
+  else if (split == 2) SKD_RED(2, 1);
+  else if (split == 3) SKD_RED(3, 1);
+  else if (split == 4) SKD_RED(4, 1);
+  else if (split == 6) SKD_RED(6, 1);
+  else if (split == 8) SKD_RED(8, 1);
+  else SKD_RED(0, 1);
+#undef SKD_RED
 }
 
 // ------------------------------------------------------------------ decode attention over the paged KV cache
@@ -1512,18 +1542,31 @@ __global__ __launch_bounds__(NW * 64, 4) void k_attention(AttnArgs a) {  // 4 wa
   }
 }
 
+// merges the splits of a (row, head); at most 16, all of them requested together
 template <int DH>
-__global__ void k_attn_merge(AttnArgs a) {
+__global__ __launch_bounds__(DH) void k_attn_merge(AttnArgs a) {
   const int H = a.kv.H, b = blockIdx.x / H, h = blockIdx.x % H, d = H * DH, e = threadIdx.x;
+  float m[16], n[16], l[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    if (s < a.splits) {
+      const float *pp = a.part + ((long)s * gridDim.x + blockIdx.x) * (DH + 2);
+      m[s] = pp[DH];
+      l[s] = pp[DH + 1];
+      n[s] = pp[e];
+    }
   float M = -1.0e30f;
-  for (int s = 0; s < a.splits; ++s) M = fmaxf(M, a.part[((long)s * gridDim.x + blockIdx.x) * (DH + 2) + DH]);
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    if (s < a.splits) M = fmaxf(M, m[s]);
   float num = 0.f, den = 0.f;
-  for (int s = 0; s < a.splits; ++s) {
-    const float *pp = a.part + ((long)s * gridDim.x + blockIdx.x) * (DH + 2);
-    const float f = __expf(pp[DH] - M);
-    num += f * pp[e];
-    den += f * pp[DH + 1];
-  }
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    if (s < a.splits) {
+      const float f = __expf(m[s] - M);
+      num += f * n[s];
+      den += f * l[s];
+    }
   a.o[d_act_index(b, h * DH + e, d)] = (bf16_t)f2bf(den > 0.f ? num / den : 0.f);
 }
 

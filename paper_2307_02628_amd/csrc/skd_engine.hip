@@ -123,6 +123,8 @@ struct skd_state {
   // plans (bf16)
   GemmPlan p_qkv, p_out, p_ffn1, p_ffn2, p_head;
   int max_split = 1, attn_splits = 1, attn_waves = 4;
+  bool attn_fixed = false;         // by override: the same shape at every position
+  int start_min = 0;               // first real column of the longest row
   // batched prompt workspace (allocated by the first batched skd_prefill)
   float *pf_x = nullptr;
   float *pf_partial = nullptr;     // K parts of the prompt projections
@@ -426,6 +428,20 @@ bool decode_shapes_ok(const skd_state *st) {
          ok(d, f, st->p_ffn2, EPI_PARTIAL) && ok(c.vocab, d, st->p_head, EPI_LOGITS);
 }
 
+// Waves per workgroup and workgroups per (row, head) of decode attention at position t: no more waves than there are
+// 32-key blocks, and up to 16 blocks in one workgroup (a split needs a second kernel: at 16 to 32 keys of two rows of 4
+// heads, one block, attention + merge of 8 splits took 9.9 us, without a split 3.9).  Where fewer (row, head) pairs than
+// CUs share long rows, the workgroups are spread over the CUs first and get the waves that are left (one row of 32
+// heads at 2000 keys, 63 blocks: 8 workgroups of 8 waves instead of 8 of 16, half of them idle).
+void attn_shape(const skd_state *st, int t, int &waves, int &splits) {
+  waves = st->attn_waves;
+  splits = st->attn_splits;
+  if (st->attn_fixed) return;
+  const int nblk = (t - st->start_min + 31) / 32;
+  if (nblk <= 16) splits = 1;
+  while (waves > 2 && waves / 2 * splits >= nblk) waves /= 2;
+}
+
 // One column (all B rows at position t) through the given ascending layer list.  Everything that can refuse
 // the column (layer list, cache lengths, launch shapes) is checked before the first launch, so an error leaves
 // the caches as they were.
@@ -472,7 +488,7 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
       if (grc < 0) return SKD_ERR_SHAPE;
       AttnArgs aa{};
       aa.q = q; aa.kv_new = st->kv_new; aa.pool = (bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.start = st->start_dev; aa.order = st->ragged ? st->order_dev : nullptr;
-      aa.t = t; aa.B = B; aa.splits = st->attn_splits; aa.waves = st->attn_waves; aa.kv = st->geom; aa.o = o; aa.part = st->attn_part;
+      aa.t = t; aa.B = B; attn_shape(st, t, aa.waves, aa.splits); aa.kv = st->geom; aa.o = o; aa.part = st->attn_part;
       { ProfScope ps_(st, SKD_PROF_ATTENTION); bf16_attention(s, aa); }
       // output projection -> partials; bias + residual + LayerNorm 2 in the reducer
       ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = o; ga.N = d; ga.K = d; ga.split = st->p_out.split; ga.partial = st->partial;
@@ -645,6 +661,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     ov("SKD_ATTN_SPLITS", splits, 1, 16);
     st->attn_waves = waves;
     st->attn_splits = splits;
+    st->attn_fixed = env_int("SKD_ATTN_WAVES", 0) > 0 || env_int("SKD_ATTN_SPLITS", 0) > 0;
     bf16_t *t16 = nullptr;
     A(&t16, (size_t)Bp * d); st->a = t16; if (rc == SKD_OK) rc = hipMemsetAsync(st->a, 0, (size_t)Bp * d * 2, st->stream) == hipSuccess ? SKD_OK : SKD_ERR_HIP;
     A(&t16, (size_t)Bp * d); st->q = t16;
@@ -701,7 +718,8 @@ static void set_start(skd_state *st, const std::vector<int32_t> &start) {
   st->order_host.resize(B);
   for (int b = 0; b < B; ++b) st->order_host[b] = b;
   std::stable_sort(st->order_host.begin(), st->order_host.end(), [&](int x, int y) { return start[x] < start[y]; });
-  st->ragged = *std::max_element(start.begin(), start.end()) != *std::min_element(start.begin(), start.end());
+  st->start_min = *std::min_element(start.begin(), start.end());
+  st->ragged = *std::max_element(start.begin(), start.end()) != st->start_min;
   st->start_host = start;
 }
 static int upload_start(skd_state *st) {
