@@ -1964,33 +1964,35 @@ void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const floa
 }
 
 // ------------------------------------------------------------------ argmax over workgroup partials
-__global__ void k_argmax_final(const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens) {
-  __shared__ float sv[256];
-  __shared__ int si[256];
+// One workgroup per row; the token goes to both destinations (tokens2 may be null).  A wave reduces without barriers, the
+// four results meet in LDS once.
+__global__ __launch_bounds__(256) void k_argmax_final(const float *pmax, const int32_t *pidx, int groups, int B_pad,
+                                                      int32_t *tokens, int32_t *tokens2) {
+  __shared__ float sv[4];
+  __shared__ int si[4];
   const int b = blockIdx.x;
   float best = -3.0e38f;
   int bi = 0x7fffffff;
-  for (int g = threadIdx.x; g < groups; g += 256) {
-    const float v = pmax[(long)g * B_pad + b];
-    const int i = pidx[(long)g * B_pad + b];
+  auto take = [&](float v, int i) {  // larger value, lower index on ties
     if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+  };
+#pragma unroll 4
+  for (int g = threadIdx.x; g < groups; g += 256) take(pmax[(long)g * B_pad + b], pidx[(long)g * B_pad + b]);
+  for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o), __shfl_xor(bi, o));
+  if ((threadIdx.x & 63) == 0) {
+    sv[threadIdx.x >> 6] = best;
+    si[threadIdx.x >> 6] = bi;
   }
-  sv[threadIdx.x] = best;
-  si[threadIdx.x] = bi;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      const float ov = sv[threadIdx.x + s];
-      const int oi = si[threadIdx.x + s];
-      if (ov > sv[threadIdx.x] || (ov == sv[threadIdx.x] && oi < si[threadIdx.x])) { sv[threadIdx.x] = ov; si[threadIdx.x] = oi; }
-    }
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) take(sv[w], si[w]);
+    tokens[b] = bi;
+    if (tokens2) tokens2[b] = bi;
   }
-  if (threadIdx.x == 0) tokens[b] = si[0];
 }
 void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens,
-                       int B) {
-  SKD_LAUNCH(k_argmax_final, dim3(B), dim3(256), 0, s, pmax, pidx, groups, B_pad, tokens);
+                       int32_t *tokens2, int B) {
+  SKD_LAUNCH(k_argmax_final, dim3(B), dim3(256), 0, s, pmax, pidx, groups, B_pad, tokens, tokens2);
 }
 
 // ------------------------------------------------------------------ weight preparation

@@ -149,7 +149,7 @@ constexpr int SAMPLE_CAND = 1024;  // candidates one wave finishes alone (16 per
 // RC: rows compiled in (>= R); 52 rows cover vocabularies up to 53248 without register spills
 template <int RC>
 __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int V, float inv_temp, float top_p,
-                                                       const float *u, int32_t *tokens) {
+                                                       const float *u, int32_t *tokens, int32_t *tokens2) {
   __shared__ float sh[16], wmass[16];
   __shared__ int wcount[16];
   __shared__ float cand_p[SAMPLE_CAND];  // candidates of the short cut, ascending token index
@@ -277,7 +277,11 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
           for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
           k = last;
         }
-        if (lane == 0) tokens[b] = k >= 0 ? cand_i[k] : 0;
+        if (lane == 0) {
+          const int tok = k >= 0 ? cand_i[k] : 0;
+          tokens[b] = tok;
+          if (tokens2) tokens2[b] = tok;
+        }
       }
       return;
     }
@@ -340,18 +344,22 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
     if (lane == 0) hit_tok = tok;
   }
   __syncthreads();
-  if (tid == 0) tokens[b] = hit_tok >= 0 ? hit_tok : last_in;  // rounding at the very end: last member
+  if (tid == 0) {
+    const int tok = hit_tok >= 0 ? hit_tok : last_in;  // rounding at the very end: last member
+    tokens[b] = tok;
+    if (tokens2) tokens2[b] = tok;
+  }
 }
 
 int sample_top_p(hipStream_t s, const float *logits, int B, int V, float temperature, float top_p, const float *u,
-                 int32_t *tokens) {
+                 int32_t *tokens, int32_t *tokens2) {
   if (V > 1024 * SAMPLE_C) return -1;
   const int R = (V + 1023) / 1024;
   const float it = 1.0f / temperature;
-  if (R <= 16) SKD_LAUNCH(k_sample_top_p<16>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens);
-  else if (R <= 32) SKD_LAUNCH(k_sample_top_p<32>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens);
-  else if (R <= 52) SKD_LAUNCH(k_sample_top_p<52>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens);
-  else SKD_LAUNCH(k_sample_top_p<SAMPLE_C>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens);
+  if (R <= 16) SKD_LAUNCH(k_sample_top_p<16>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
+  else if (R <= 32) SKD_LAUNCH(k_sample_top_p<32>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
+  else if (R <= 52) SKD_LAUNCH(k_sample_top_p<52>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
+  else SKD_LAUNCH(k_sample_top_p<SAMPLE_C>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
   return 0;
 }
 

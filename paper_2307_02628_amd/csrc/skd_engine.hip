@@ -975,7 +975,8 @@ extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_i
 
 // Final LayerNorm + LM head (+ greedy argmax into argmax_dev).  logits_target: device buffer [B][V] or null.
 // final LayerNorm output -> logits (optional) and, unless the caller picks the token itself, the greedy token
-static int head_logits(skd_state *st, float *logits_target, bool want_argmax = true) {
+// tokens_target: second destination of the greedy token (device memory), or null
+static int head_logits(skd_state *st, float *logits_target, bool want_argmax, int32_t *tokens_target) {
   const skd_config &c = st->cfg;
   const int B = c.batch, d = c.d_model, V = c.vocab;
   hipStream_t s = st->stream;
@@ -991,7 +992,7 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax = t
     int groups = 0;
     { ProfScope ps_(st, SKD_PROF_LM_HEAD); groups = launch_gemm(s, ga, EPI_LOGITS, st->p_head); }
     if (groups < 0) return SKD_ERR_SHAPE;
-    if (want_argmax) { ProfScope ps_(st, SKD_PROF_ARGMAX); bf16_argmax_final(s, st->pmax, st->pidx, groups, st->B_pad, st->argmax_dev, B); }
+    if (want_argmax) { ProfScope ps_(st, SKD_PROF_ARGMAX); bf16_argmax_final(s, st->pmax, st->pidx, groups, st->B_pad, st->argmax_dev, tokens_target, B); }
   }
   HIPCHECK(hipGetLastError());
   return SKD_OK;
@@ -1005,10 +1006,10 @@ extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logi
   hipStream_t s = st->stream;
   float *logits_target = nullptr;  // where the kernels write logits, if anywhere
   if (logits_out) logits_target = c.io_on_device ? logits_out : st->logits_dev;
-  SKDCHECK(head_logits(st, logits_target));
+  SKDCHECK(head_logits(st, logits_target, true, c.io_on_device ? tokens_out : nullptr));
   st->have_argmax = true;
   if (c.io_on_device) {
-    if (tokens_out)
+    if (tokens_out && !st->bf16)  // the bf16 path has written it
       HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     return SKD_OK;
   }
@@ -1040,11 +1041,9 @@ extern "C" int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, flo
   if (check_gemm(ga, EPI_LOGITS, st->p_head) != groups) return SKD_ERR_SHAPE;
   // every partial the final reduction reads is written by the projection of this same call: nothing to clear
   (void)launch_gemm(s, ga, EPI_LOGITS, st->p_head);
-  bf16_argmax_final(s, pmax, pidx, groups, st->B_pad, st->argmax_dev, c.batch);
+  bf16_argmax_final(s, pmax, pidx, groups, st->B_pad, st->argmax_dev, tokens_out, c.batch);
   HIPCHECK(hipGetLastError());
   st->have_argmax = true;
-  if (tokens_out)
-    HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, c.batch * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
   return SKD_OK;
 }
 
@@ -1066,15 +1065,11 @@ extern "C" int skd_logits_sample(skd_state *st, const float *u, float temperatur
     u_dev = st->u_dev;
   }
   float *lg = (logits_out && c.io_on_device) ? logits_out : st->logits_dev;
-  SKDCHECK(head_logits(st, lg, false));
-  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev) < 0) return SKD_ERR_SHAPE; }
+  SKDCHECK(head_logits(st, lg, false, nullptr));
+  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev, c.io_on_device ? tokens_out : nullptr) < 0) return SKD_ERR_SHAPE; }
   HIPCHECK(hipGetLastError());
   st->have_argmax = true;  // skd_decode_step(.., NULL) continues from the sampled tokens
-  if (c.io_on_device) {
-    if (tokens_out)
-      HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    return SKD_OK;
-  }
+  if (c.io_on_device) return SKD_OK;  // the sampler has written tokens_out
   if (tokens_out) HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   if (logits_out)
     HIPCHECK(hipMemcpyAsync(logits_out, st->logits_dev, (size_t)B * V * sizeof(float), hipMemcpyDeviceToHost, s));

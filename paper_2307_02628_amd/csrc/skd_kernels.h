@@ -56,9 +56,10 @@ void f32_kv_write(hipStream_t s, const float *qkv, float *pool, const int32_t *b
 void f32_attention(hipStream_t s, const float *qkv, const float *pool, const int32_t *bt_layer, const int32_t *start,
                    int t, float *o, float *scores, int score_stride, int B, KvGeom g);
 void f32_argmax(hipStream_t s, const float *logits, int32_t *tokens, int B, int V);
-// temperature + top-p sampling from fp32 logits [B][V] with one uniform number per row; -1 if V > 65536
+// temperature + top-p sampling from fp32 logits [B][V] with one uniform number per row; -1 if V > 65536.
+// tokens2: second destination, or null
 int sample_top_p(hipStream_t s, const float *logits, int B, int V, float temperature, float top_p, const float *u,
-                 int32_t *tokens);
+                 int32_t *tokens, int32_t *tokens2);
 
 // ---------------------------------------------------------------- bf16 production path
 // Weights [N][K] are "fragment-major": 16-row x 32-column fragments stored as
@@ -189,8 +190,9 @@ void bf16_ln_rows(hipStream_t s, float *x, const float *g, const float *b, bf16_
 // split > 0); a_out = its LayerNorm
 void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
                        const float *bias, const float *g, const float *b, float *x_out, bf16_t *a_out, int B, int d);
+// tokens2: second destination, or null
 void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens,
-                       int B);
+                       int32_t *tokens2, int B);
 
 // weight preparation (source fp32 or bf16 row-major, on device)
 void prep_matrix_frag(hipStream_t s, const void *src, int src_is_bf16, bf16_t *dst, long N, long K, long N_pad,
