@@ -33,19 +33,6 @@ __device__ inline uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
-// Sum over the wave, the same value in every lane: rotations inside the rows of 16 lanes (DPP, no LDS round trip as in
-// __shfl_xor), then the four row sums as scalars.
-__device__ inline float wave_sum_f(float v) {
-#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
-  SKD_ROR(8);
-  SKD_ROR(4);
-  SKD_ROR(2);
-  SKD_ROR(1);
-#undef SKD_ROR
-  const int i = __builtin_bit_cast(int, v);
-  auto row = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, l)); };
-  return (row(0) + row(16)) + (row(32) + row(48));
-}
 // one barrier: `sh` (16 floats) must not have been read since the last barrier of the block
 __device__ inline float block_sum_once(float v, float *sh) {
   v = wave_sum_f(v);

@@ -5,17 +5,13 @@
 
 namespace skd {
 
-__device__ inline float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 __device__ inline float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   return v;
 }
 // sum over a 256-thread workgroup; `sh` holds >= 4 floats; result to all threads
 __device__ inline float block_sum(float v, float *sh) {
-  v = wave_sum(v);
+  v = wave_sum_f(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -55,7 +51,7 @@ __global__ void k_f32_linear(const float *W, const float *bias, const float *in,
   const float *w = W + (long)n * K, *a = in + (long)b * K;
   float acc = 0;
   for (int k = threadIdx.x & 63; k < K; k += 64) acc += w[k] * a[k];
-  acc = wave_sum(acc);
+  acc = wave_sum_f(acc);
   if ((threadIdx.x & 63) == 0) {
     float v = acc + (bias ? bias[n] : 0.f);
     if (relu) v = fmaxf(v, 0.f);
@@ -104,7 +100,7 @@ __global__ void k_f32_attention(const float *qkv, const float *pool, const int32
     sc[j] = p;
     den += p;
   }
-  den = wave_sum(den);
+  den = wave_sum_f(den);
   __syncthreads();  // scores written by other lanes are read below
   for (int e = lane; e < g.dh; e += 64) {
     float acc = 0;
@@ -140,20 +136,115 @@ __global__ void k_f32_argmax(const float *logits, int32_t *tokens, int V) {
 // Wave w keeps the contiguous index range [w*R*64, (w+1)*R*64) in registers, R = ceil(V / 1024) <= 64 rows of 64
 // tokens, lane l holding token w*R*64 + 64 i + l of row i (coalesced 256-byte loads).
 //   p_i = exp((z_i - max z) / T);  nucleus = {p_i >= tau}, tau = the largest value whose upper set has mass
-//   >= top_p * sum p  (found bit by bit on the float bit pattern, 31 block sums; tokens tied with tau are in);
+//   >= top_p * sum p  (found bit by bit on the float bit pattern; tokens tied with tau are in);
 //   token = first index of the nucleus whose running mass (ascending index) exceeds u * mass(nucleus).
 // Every sum is taken in a fixed order, so a given (logits, u) always yields the same token.
 constexpr int SAMPLE_C = 64;
-constexpr int SAMPLE_CAND = 1024;  // candidates one wave finishes alone (16 per lane; 32 per lane spills registers)
+constexpr int SAMPLE_CAND = 4096;  // candidates that four waves finish, 16 per lane
+
+struct SampleExchange {  // LDS of the finishing waves
+  float sums[2][4];      // one set per round in turn
+  int pick[4], tail[4];
+};
+// The rest of a row on its C <= 64 PER NW candidates (ascending index), by the first NW (1 or 4) waves of the workgroup:
+// threshold bit by bit, then the draw.
+template <int PER, int NW>
+__device__ inline void sample_finish(const float *cand_p, const int *cand_i, int C, unsigned lower, unsigned upper,
+                                     float target, float u, int32_t *token, int32_t *token2, SampleExchange &ex) {
+  const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = (w * 64 + lane) * PER;  // this lane's candidates c0 .. c0 + PER - 1 (index order)
+  float v[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = c0 + j < C ? cand_p[c0 + j] : 0.f;
+  int set = 0;
+  unsigned T = 0;
+  for (int bit = 29; bit >= 0; --bit) {
+    const unsigned cand = T | (1u << bit);
+    if (cand >= upper) continue;
+    if (cand <= lower) { T = cand; continue; }
+    float m = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) m += (__float_as_uint(v[j]) >= cand) ? v[j] : 0.f;
+    m = wave_sum_f(m);
+    if constexpr (NW > 1) {
+      set ^= 1;
+      if (lane == 0) ex.sums[set][w] = m;
+      __syncthreads();  // the set is written again two rounds later, after the next round's barrier
+      m = (ex.sums[set][0] + ex.sums[set][1]) + (ex.sums[set][2] + ex.sums[set][3]);
+    }
+    if (m >= target) T = cand;
+  }
+  float lm = 0;
+  int last = -1;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (__float_as_uint(v[j]) < T) v[j] = 0.f;
+    lm += v[j];
+    if (v[j] > 0.f) last = c0 + j;
+  }
+  float inc = lm;  // inclusive prefix of the lanes' masses = prefix in index order
+  for (int off = 1; off < 64; off <<= 1) {
+    const float t = __shfl_up(inc, off);
+    if (lane >= off) inc += t;
+  }
+  float before = 0, mass = __shfl(inc, 63);
+  if constexpr (NW > 1) {
+    if (lane == 0) ex.sums[set ^ 1][w] = mass;  // last read before the barrier of the last round
+    __syncthreads();
+    float run = 0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      if (k == w) before = run;
+      run += ex.sums[set ^ 1][k];
+    }
+    mass = run;
+  }
+  const float goal = u * mass;
+  const unsigned long long over = __ballot(before + inc > goal);
+  int k = -1;
+  if (over) {
+    const int L = (int)__builtin_ctzll(over);
+    if (lane == L) {
+      float run = before + (inc - lm);
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        run += v[j];
+        if (k < 0 && v[j] > 0.f && run > goal) k = c0 + j;
+      }
+      if (k < 0) k = last;  // rounding between the lane's two summation orders: its last member
+    }
+    k = __shfl(k, L);
+  }
+  for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
+  if constexpr (NW > 1) {  // the first wave that found it
+    if (lane == 0) {
+      ex.pick[w] = k;
+      ex.tail[w] = last;
+    }
+    __syncthreads();
+    if (w) return;
+    for (int i = 1; i < NW; ++i) {
+      if (k < 0) k = ex.pick[i];
+      last = max(last, ex.tail[i]);
+    }
+  }
+  if (k < 0) k = last;  // rounding at the very end: the last member of the nucleus
+  if (lane == 0) {
+    const int tok = k >= 0 ? cand_i[k] : 0;
+    *token = tok;
+    if (token2) *token2 = tok;
+  }
+}
 
 // RC: rows compiled in (>= R); 52 rows cover vocabularies up to 53248 without register spills
 template <int RC>
 __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int V, float inv_temp, float top_p,
                                                        const float *u, int32_t *tokens, int32_t *tokens2) {
-  __shared__ float sh[16], wmass[16];
+  __shared__ float sh[16], wmass[16], mass_at[3][16];
   __shared__ int wcount[16];
   __shared__ float cand_p[SAMPLE_CAND];  // candidates of the short cut, ascending token index
   __shared__ int cand_i[SAMPLE_CAND];
+  __shared__ SampleExchange ex;
   __shared__ float rows[RC * 64];  // the rows of the one wave that walks its range
   __shared__ int last_in, hit_tok;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -172,39 +263,51 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   __syncthreads();
   mx = sh[0];
   for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sh[w]);
-  float loc = 0;
+  // Masses of all tokens and of those at or above 2^-5 and 2^-10 of the most likely one, in one pass.
+  constexpr int NQ = 3;
+  float q[NQ] = {};
 #pragma unroll
   for (int i = 0; i < RC; ++i) {
     p[i] = p[i] > -1.0e38f ? expf(p[i] - mx) : 0.f;
-    loc += p[i];
-  }
-  const float total = block_sum(loc, sh);
-  const float target = top_p * total;
-
-  // The threshold is found bit by bit on the float bit pattern, from the top.  The first 8 rounds (sign excluded:
-  // the exponent bits) are taken by the whole workgroup; they fix the threshold to within a factor of two, and every
-  // token below that lower bound is out of the nucleus whatever the remaining bits turn out to be.  If the tokens at
-  // or above it are few (<= SAMPLE_CAND: nearly always at the paper's temperature 0.3, where the nucleus is a few
-  // hundred tokens), they are compacted in index order into LDS and one wave finishes the row alone with wave-level
-  // sums: no workgroup barrier in the remaining 23 rounds.  For every trial threshold at or above the lower bound
-  // the sums run over the same tokens as in the whole-workgroup search, so the threshold is the same up to the
-  // order of the fp32 additions.
-  unsigned T = 0;
-  for (int bit = 30; bit >= 23; --bit) {
-    const unsigned cand = T | (1u << bit);
-    float m = 0;
+    q[0] += p[i];
 #pragma unroll
-    for (int i = 0; i < RC; ++i) m += (__float_as_uint(p[i]) >= cand) ? p[i] : 0.f;  // absent tokens hold zeros
-    if (block_sum(m, sh) >= target) T = cand;  // uniform decision: every thread sees the same sum
+    for (int j = 1; j < NQ; ++j) q[j] += p[i] >= __uint_as_float((127u - 5u * j) << 23) ? p[i] : 0.f;
   }
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    q[j] = wave_sum_f(q[j]);
+    if (lane == 0) mass_at[j][wave] = q[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    q[j] = mass_at[j][0];
+    for (int w = 1; w < 16; ++w) q[j] += mass_at[j][w];
+  }
+  const float total = q[0], target = top_p * total;
+
+  // Short cut.  The threshold lies at or above the larger of the two bounds whose upper set already has the target
+  // mass; failing that, at or above (1 - top_p) total / (2 V): all tokens below it together hold less than half of the
+  // mass that may be left out (the other half covers rounding, except where top_p is so close to 1 that the bound keeps
+  // everything anyway).  The tokens at or above the bound are compacted in index order; if they are at most 4096 (at the
+  // paper's temperature 0.3 a few dozen to a few hundred of 50272), one wave (up to 1024) or four finish the row: no
+  // more passes over the vocabulary, and sums that need no workgroup barrier, or one of four waves.
+  // 50272 tokens, 32 rows: 46 us with eight rounds over the whole row before the compaction, 36 us now.
+  unsigned lower = max(__float_as_uint((1.0f - top_p) * total / (2.0f * (float)V)), 1u);  // 0 = absent or underflowed
+  unsigned upper = 1u << 30;  // 2: p <= 1.  Rounds of the search whose trial lies outside [lower, upper) need no sum
+#pragma unroll
+  for (int j = NQ - 1; j > 0; --j) {
+    if (q[j] >= target) lower = (127u - 5u * j) << 23;
+  }
+#pragma unroll
+  for (int j = 1; j < NQ; ++j)
+    if (q[j] < target) upper = (127u - 5u * j) << 23;
   {
-    const unsigned lower = max(T, 1u);  // bit pattern 0 = an absent token or an underflowed probability: never a candidate
     int cnt = 0;  // per lane first (a ballot per row here would be kept for the compaction below: 2 SGPRs per row)
     const unsigned below = lower - 1u;  // lower >= 1
 #pragma unroll
     for (int i = 0; i < RC; ++i) cnt += (__float_as_uint(p[i]) > below) ? 1 : 0;  // non-negative floats order like their bits
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-    __syncthreads();  // sh (read by block_sum above) is free
     if (lane == 0) wcount[wave] = cnt;
     __syncthreads();
     int C = 0, wbase = 0;
@@ -224,77 +327,41 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
         // here instead of keeping one lane mask per row from there)
         const bool c = __float_as_uint(p[i]) >= lower;
         const unsigned long long m = __ballot(c);
-        if (c) {
-          const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
-          cand_p[k] = p[i];
-          cand_i[k] = base + 64 * i;
+        if (m) {  // most rows have none
+          if (c) {
+            const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
+            cand_p[k] = p[i];
+            cand_i[k] = base + 64 * i;
+          }
+          pos += __popcll(m);
         }
-        pos += __popcll(m);
         __builtin_amdgcn_sched_barrier(0);  // row by row: hoisted, the rows' lane masks would need 2 SGPRs each
       }
       __syncthreads();
-      if (__builtin_amdgcn_readfirstlane(wave) == 0) {
-        constexpr int PER = SAMPLE_CAND / 64;  // lane l owns candidates l * PER .. l * PER + PER - 1 (index order)
-        float v[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) v[j] = lane * PER + j < C ? cand_p[lane * PER + j] : 0.f;
-        for (int bit = 22; bit >= 0; --bit) {
-          const unsigned cand = T | (1u << bit);
-          float m = 0;
-#pragma unroll
-          for (int j = 0; j < PER; ++j) m += (__float_as_uint(v[j]) >= cand) ? v[j] : 0.f;
-          if (wave_sum(m) >= target) T = cand;
-        }
-        float lm = 0;
-        int last = -1;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          if (__float_as_uint(v[j]) < T) v[j] = 0.f;
-          lm += v[j];
-          if (v[j] > 0.f) last = lane * PER + j;
-        }
-        float inc = lm;  // inclusive prefix of the lanes' masses = prefix in index order
-        for (int off = 1; off < 64; off <<= 1) {
-          const float t = __shfl_up(inc, off);
-          if (lane >= off) inc += t;
-        }
-        const float goal = u[b] * __shfl(inc, 63);
-        const unsigned long long over = __ballot(inc > goal);
-        int k = -1;
-        if (over) {
-          const int L = (int)__builtin_ctzll(over);
-          if (lane == L) {
-            float run = inc - lm;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-              run += v[j];
-              if (k < 0 && v[j] > 0.f && run > goal) k = lane * PER + j;
-            }
-            if (k < 0) k = last;  // rounding between the lane's two summation orders: its last member
-          }
-          k = __shfl(k, L);
-        } else {  // rounding at the very end: the last member of the nucleus
-          for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
-          k = last;
-        }
-        if (lane == 0) {
-          const int tok = k >= 0 ? cand_i[k] : 0;
-          tokens[b] = tok;
-          if (tokens2) tokens2[b] = tok;
-        }
+      const int w = __builtin_amdgcn_readfirstlane(wave);
+      if (C <= 256) {
+        if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+      } else if (C <= 1024) {
+        if (w == 0) sample_finish<16, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+      } else if (w < 4) {  // the barriers in there are those of the waves that remain
+        sample_finish<16, 4>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
       }
       return;
     }
   }
-  for (int bit = 22; bit >= 0; --bit) {
+  // Flat distributions: the whole workgroup searches over all tokens.
+  unsigned T = 0;
+  for (int bit = 30; bit >= 0; --bit) {
     const unsigned cand = T | (1u << bit);
+    if (cand >= upper) continue;
+    if (cand <= lower) { T = cand; continue; }
     float m = 0;
 #pragma unroll
     for (int i = 0; i < RC; ++i) m += (__float_as_uint(p[i]) >= cand) ? p[i] : 0.f;  // absent tokens hold zeros
     if (block_sum(m, sh) >= target) T = cand;  // uniform decision: every thread sees the same sum
   }
   // nucleus: zero everything else; mass per wave (each wave owns a contiguous index range)
-  loc = 0;
+  float loc = 0;
   int last = -1;
 #pragma unroll
   for (int i = 0; i < RC; ++i) {
@@ -302,7 +369,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
     loc += p[i];
     if (p[i] > 0.f) last = base + 64 * i;
   }
-  loc = wave_sum(loc);
+  loc = wave_sum_f(loc);
   __syncthreads();  // sh is free again
   if (lane == 0) wmass[wave] = loc;
   if (last >= 0) atomicMax(&last_in, last);

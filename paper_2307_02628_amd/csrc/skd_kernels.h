@@ -32,6 +32,20 @@ extern thread_local LaunchTimer *g_launch_timer;
     }                                                                                          \
   } while (0)
 
+// Sum over the wave, the same value in every lane: rotations inside the rows of 16 lanes (DPP, no LDS round trip as in
+// __shfl_xor), then the four row sums as scalars.
+__device__ inline float wave_sum_f(float v) {
+#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  const int i = __builtin_bit_cast(int, v);
+  auto row = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, l)); };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 // Geometry of the paged KV cache.  A page holds `page_tokens` consecutive
 // positions of ONE batch row in ONE layer, all heads.  On the bf16 path a row's
 // keys are stored by real position (column j of a row that starts at column
