@@ -877,7 +877,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   if (!ld_is_a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int T = tn * 16 + ld_t0 + i;
+      const int T = a.t0 + tn * 16 + ld_t0 + i;
       src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * (a.K >> 5) + k0) * a.G + T % a.G) * 64;
     }
     sstride = (long)a.G * 64;
@@ -986,7 +986,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
     }
   }
 
-  tile_epilogue<EPI, 4, 8>(a, acc, tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
+  tile_epilogue<EPI, 4, 8>(a, acc, a.t0 + tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
 }
 
 // Batched-prompt projections on 256 x 256 tiles.  Returns 0, or -1 when the shape does not tile.
@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
   for (int i = 0; i < LPW; ++i) {
     const int fr = wave * LPW + i;
     if (fr < FW) {
-      const int T = tn * FW + fr;
+      const int T = a.t0 + tn * FW + fr;
       src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * Kf + k0) * a.G + T % a.G) * 64;
       stride[i] = (long)a.G * 64;
       vl[i] = lane;
@@ -1156,7 +1156,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
       mma(wfB, xfB);
     }
   }
-  tile_epilogue<EPI, RT, MT>(a, acc, tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);
+  tile_epilogue<EPI, RT, MT>(a, acc, a.t0 + tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);
 }
 
 template <int RT, int MT, int WN, int WM, int NS>

@@ -442,6 +442,42 @@ void attn_shape(const skd_state *st, int t, int &waves, int &splits) {
   while (waves > 2 && waves / 2 * splits >= nblk) waves /= 2;
 }
 
+// One layer of the column at position t on the bf16 path.  st->a holds LayerNorm 1 of its input, st->x the residual
+// stream; next_g, next_b: the LayerNorm that follows (LayerNorm 1 of the next active layer, or the final one), which the
+// reducer of the last sub-block applies.
+int run_layer(skd_state *st, int l, int t, const float *next_g, const float *next_b) {
+  const skd_config &c = st->cfg;
+  const int B = c.batch, d = c.d_model, f = c.ffn;
+  hipStream_t s = st->stream;
+  bf16_t *a = (bf16_t *)st->a, *q = (bf16_t *)st->q, *o = (bf16_t *)st->o, *u = (bf16_t *)st->u;
+  const LayerW &w = st->lw[l];
+  int grc = 0;
+  GemmArgs ga{};
+  ga.B = B; ga.B_pad = st->B_pad; ga.kv = st->geom; ga.d = d;
+  // q, k, v projection; the attention kernel files k and v into this layer's page slot for column t
+  ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d; ga.split = 1;
+  ga.q_out = q; ga.kv_new = st->kv_new;
+  { ProfScope ps_(st, SKD_PROF_GEMM_QKV); grc = launch_gemm(s, ga, EPI_QKV, st->p_qkv); }
+  if (grc < 0) return SKD_ERR_SHAPE;
+  AttnArgs aa{};
+  aa.q = q; aa.kv_new = st->kv_new; aa.pool = (bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.start = st->start_dev; aa.order = st->ragged ? st->order_dev : nullptr;
+  aa.t = t; aa.B = B; attn_shape(st, t, aa.waves, aa.splits); aa.kv = st->geom; aa.o = o; aa.part = st->attn_part;
+  { ProfScope ps_(st, SKD_PROF_ATTENTION); bf16_attention(s, aa); }
+  // output projection -> partials; bias + residual + LayerNorm 2 in the reducer
+  ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = o; ga.N = d; ga.K = d; ga.split = st->p_out.split; ga.partial = st->partial;
+  { ProfScope ps_(st, SKD_PROF_GEMM_OUT); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_out); }
+  if (grc < 0) return SKD_ERR_SHAPE;
+  { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_out.split, st->B_pad, w.bo, st->x, w.ln2_g, w.ln2_b, a, B, d); }
+  ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.split = 1; ga.act_out = u;
+  { ProfScope ps_(st, SKD_PROF_GEMM_FFN1); grc = launch_gemm(s, ga, EPI_RELU, st->p_ffn1); }
+  if (grc < 0) return SKD_ERR_SHAPE;
+  ga.W = (const bf16_t *)w.w2; ga.G = st->p_ffn2.R; ga.A = u; ga.N = d; ga.K = f; ga.split = st->p_ffn2.split;
+  { ProfScope ps_(st, SKD_PROF_GEMM_FFN2); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_ffn2); }
+  if (grc < 0) return SKD_ERR_SHAPE;
+  { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_ffn2.split, st->B_pad, w.b2, st->x, next_g, next_b, a, B, d); }
+  return SKD_OK;
+}
+
 // One column (all B rows at position t) through the given ascending layer list.  Everything that can refuse
 // the column (layer list, cache lengths, launch shapes) is checked before the first launch, so an error leaves
 // the caches as they were.
@@ -472,41 +508,12 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
       st->kv_len[layers[i]] = t + 1;
     }
   } else {
-    bf16_t *a = (bf16_t *)st->a, *q = (bf16_t *)st->q, *o = (bf16_t *)st->o, *u = (bf16_t *)st->u;
     const LayerW &w0 = st->lw[layers[0]];
-    { ProfScope ps_(st, SKD_PROF_EMBED_LN); bf16_embed_ln(s, tokens_dev, st->start_dev, t, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, w0.ln1_g, w0.ln1_b, st->x, a, B, d, c.vocab); }
-    int grc = 0;
+    { ProfScope ps_(st, SKD_PROF_EMBED_LN); bf16_embed_ln(s, tokens_dev, st->start_dev, t, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, w0.ln1_g, w0.ln1_b, st->x, (bf16_t *)st->a, B, d, c.vocab); }
     for (int i = 0; i < n; ++i) {
-      const int l = layers[i];
-      const LayerW &w = st->lw[l];
-      GemmArgs ga{};
-      ga.B = B; ga.B_pad = st->B_pad; ga.kv = st->geom; ga.d = d;
-      // q, k, v projection; the attention kernel files k and v into this layer's page slot for column t
-      ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d; ga.split = 1;
-      ga.q_out = q; ga.kv_new = st->kv_new;
-      { ProfScope ps_(st, SKD_PROF_GEMM_QKV); grc = launch_gemm(s, ga, EPI_QKV, st->p_qkv); }
-      if (grc < 0) return SKD_ERR_SHAPE;
-      AttnArgs aa{};
-      aa.q = q; aa.kv_new = st->kv_new; aa.pool = (bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.start = st->start_dev; aa.order = st->ragged ? st->order_dev : nullptr;
-      aa.t = t; aa.B = B; attn_shape(st, t, aa.waves, aa.splits); aa.kv = st->geom; aa.o = o; aa.part = st->attn_part;
-      { ProfScope ps_(st, SKD_PROF_ATTENTION); bf16_attention(s, aa); }
-      // output projection -> partials; bias + residual + LayerNorm 2 in the reducer
-      ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = o; ga.N = d; ga.K = d; ga.split = st->p_out.split; ga.partial = st->partial;
-      { ProfScope ps_(st, SKD_PROF_GEMM_OUT); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_out); }
-      if (grc < 0) return SKD_ERR_SHAPE;
-      { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_out.split, st->B_pad, w.bo, st->x, w.ln2_g, w.ln2_b, a, B, d); }
-      ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.split = 1; ga.act_out = u;
-      { ProfScope ps_(st, SKD_PROF_GEMM_FFN1); grc = launch_gemm(s, ga, EPI_RELU, st->p_ffn1); }
-      if (grc < 0) return SKD_ERR_SHAPE;
-      ga.W = (const bf16_t *)w.w2; ga.G = st->p_ffn2.R; ga.A = u; ga.N = d; ga.K = f; ga.split = st->p_ffn2.split;
-      { ProfScope ps_(st, SKD_PROF_GEMM_FFN2); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_ffn2); }
-      if (grc < 0) return SKD_ERR_SHAPE;
-      // the reducer of the last sub-block already applies the next LayerNorm:
-      // LayerNorm 1 of the next ACTIVE layer, or the final LayerNorm
-      const float *ng = (i + 1 < n) ? st->lw[layers[i + 1]].ln1_g : st->lnf_g;
-      const float *nb = (i + 1 < n) ? st->lw[layers[i + 1]].ln1_b : st->lnf_b;
-      { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_ffn2.split, st->B_pad, w.b2, st->x, ng, nb, a, B, d); }
-      st->kv_len[l] = t + 1;
+      const LayerW *nw = i + 1 < n ? &st->lw[layers[i + 1]] : nullptr;
+      SKDCHECK(run_layer(st, layers[i], t, nw ? nw->ln1_g : st->lnf_g, nw ? nw->ln1_b : st->lnf_b));
+      st->kv_len[layers[i]] = t + 1;
     }
   }
   HIPCHECK(hipGetLastError());
@@ -859,12 +866,33 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     g.rows = (rows + 127) / 128 * 128;
     return bf16_gemm(s, g, epi, g.N % 64 ? 1 : 4, 1, 4);
   };
+  // What leaves the prompt pass is the cache of every layer and the hidden state of each sequence's last position, so
+  // of the top layer's rows only the last positions are needed beyond their keys and values: its q | k | v projection
+  // computes k | v for all rows, and the last positions go through that layer as a decode column at position P - 1.
+  // From 512 rows on (below, a layer of all rows costs little more than streaming its weights, which the column streams
+  // too: 256 rows of the 6.7B shape, 165 us against 130; at 912 rows of the 1.3B shape 165 against 70, at 16384 of
+  // the 6.7B shape 5200 against 950).
+  const RowsGemm r_kv = plan(2 * d, d, false);
+  const bool last_as_column = rows >= 512 && (r_kv.kind == RowsGemm::TILE || r_kv.kind == RowsGemm::MID);
   for (int l = 0; l < L; ++l) {
     const LayerW &w = st->lw[l];
     GemmArgs ga{};
     ga.B = B; ga.rm = rm; ga.kv = st->geom; ga.d = d; ga.partial = st->pf_partial; ga.x = st->pf_x;
     ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = st->pf_a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d;
     ga.q_out = st->pf_q; ga.kv_pool = (bf16_t *)st->pool; ga.bt_layer = bt_layer(st, l);
+    if (l == L - 1 && last_as_column) {
+      ga.t0 = d / 16;
+      ga.N = 2 * d;
+      if (proj(ga, EPI_QKV_ROWS, r_kv) < 0) return SKD_ERR_SHAPE;
+      bf16_last_rows_ln(s, st->pf_x, rm, nullptr, 0, 0, nullptr, w.ln1_g, w.ln1_b, st->x, (bf16_t *)st->a, B, d);
+      const int profiling = st->profiling;
+      st->profiling = 0;  // the timed classes are those of decode steps
+      const int rc = run_layer(st, l, P - 1, st->lnf_g, st->lnf_b);
+      st->profiling = profiling;
+      SKDCHECK(rc);
+      st->kv_len[l] = P;
+      break;
+    }
     if (proj(ga, EPI_QKV_ROWS, r_qkv) < 0) return SKD_ERR_SHAPE;
     AttnRowsArgs aa{};
     aa.q = st->pf_q; aa.pool = (const bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.rm = rm;
@@ -886,8 +914,9 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     st->kv_len[l] = P;
   }
   // hidden state of the last prompt column, and its final LayerNorm, where the heads expect them
-  bf16_last_rows_ln(s, st->pf_x, rm, st->pf_partial, r_ffn2.partial ? r_ffn2.split : 0, stride(r_ffn2), st->lw[L - 1].b2,
-                    st->lnf_g, st->lnf_b, st->x, (bf16_t *)st->a, B, d);
+  if (!last_as_column)
+    bf16_last_rows_ln(s, st->pf_x, rm, st->pf_partial, r_ffn2.partial ? r_ffn2.split : 0, stride(r_ffn2), st->lw[L - 1].b2,
+                      st->lnf_g, st->lnf_b, st->x, (bf16_t *)st->a, B, d);
   HIPCHECK(hipGetLastError());
   st->have_hidden = true;
   st->have_argmax = false;

@@ -120,6 +120,7 @@ struct GemmArgs {
   const bf16_t *A;     // activation tiles [B_pad][K]
   const float *bias;   // [N] or null
   int N, K, B, B_pad;
+  int t0;              // bf16_gemm_tile, bf16_gemm_mid: first weight tile (N outputs from row 16 t0 on; EPI_QKV_ROWS only)
   int split;           // workgroups along K (grid.y)
   int ws_rot;          // bf16_gemm_ws: workgroups start their K range at different stages
   // batched prompt processing: activation rows are the real (sequence, position) pairs of `rm`, handled in

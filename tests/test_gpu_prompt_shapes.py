@@ -51,6 +51,7 @@ def test_forced_tiles(shape, tile):
 
 @pytest.mark.parametrize("shape,B,P,shortest", [
     (WIDE, 1, 1, 0), (NARROW, 1, 16, 0), (WIDE, 2, 16, 0), (NARROW, 1, 33, 0),     # 16, 16, 32, 48 rows: decode kernels
-    (WIDE, 4, 13, 1), (WIDE, 1, 65, 0), (NARROW, 5, 47, 20), (WIDE, 3, 301, 0)])   # 64 rows; 80, ragged, 912: tiles
+    (WIDE, 4, 13, 1), (WIDE, 1, 65, 0), (NARROW, 5, 47, 20), (WIDE, 3, 301, 0),     # 64 rows; 80, ragged, 912: tiles
+    (WIDE, 13, 97, 20), (NARROW, 40, 31, 1)])                                      # ragged, more than 512 rows: top layer as a column
 def test_planned_shapes(shape, B, P, shortest):
     check(shape, B, P, shortest, {}, 50)
