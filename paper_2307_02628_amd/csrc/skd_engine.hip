@@ -81,8 +81,19 @@ struct StateTimer final : LaunchTimer {
   void next(hipEvent_t *start, hipEvent_t *stop) override;
 };
 
+// Pinned host memory of a bf16 state with host buffers: the kernels read tokens and uniform numbers from it and write
+// tokens to it, and small logits are copied into it, so that a call needs one wait instead of one per copy.  Every call
+// waits for its work before it returns, so the next one finds the buffers free.
+constexpr size_t kPinnedLogits = 1 << 20;  // bytes; larger logits are copied to the caller's memory directly
+struct Pinned {
+  int32_t tok_in[128], tok_out[128];
+  float u_in[128];
+  float logits[kPinnedLogits / sizeof(float)];
+};
+
 struct skd_state {
   skd_config cfg{};
+  Pinned *pin = nullptr;           // null: device I/O, fp32 path
   hipStream_t stream = nullptr;
   int B_pad = 0, dh = 0;
   bool bf16 = true;
@@ -690,6 +701,10 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     A(&st->logits_dev, (size_t)B * V);
   }
   if (rc != SKD_OK) return fail(rc);
+  if (st->bf16 && !c.io_on_device) {
+    const hipError_t e = hipHostMalloc((void **)&st->pin, sizeof(Pinned), hipHostMallocDefault);
+    if (e != hipSuccess) { g_last_hip = (int)e; st->pin = nullptr; return fail(SKD_ERR_NOMEM); }
+  }
   if (hipStreamSynchronize(st->stream) != hipSuccess) return fail(SKD_ERR_HIP);
   *out = st;
   return SKD_OK;
@@ -716,6 +731,7 @@ extern "C" void skd_destroy(skd_state *st) {
   for (auto &r : st->prof_pending) { if (r.a) (void)hipEventDestroy(r.a); if (r.b) (void)hipEventDestroy(r.b); }
   for (hipEvent_t e : st->prof_free) (void)hipEventDestroy(e);
   for (void *p : st->allocs) (void)hipFree(p);
+  if (st->pin) (void)hipHostFree(st->pin);
   delete st;
 }
 
@@ -990,9 +1006,14 @@ extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_i
   } else {
     for (int b = 0; b < c.batch; ++b)
       if (tokens_in[b] < 0 || tokens_in[b] >= c.vocab) return SKD_ERR_RANGE;
-    HIPCHECK(hipMemcpyAsync(st->tok_dev, tokens_in, c.batch * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
-    HIPCHECK(hipStreamSynchronize(st->stream));
-    tok = st->tok_dev;
+    if (st->pin) {
+      std::copy(tokens_in, tokens_in + c.batch, st->pin->tok_in);
+      tok = st->pin->tok_in;
+    } else {
+      HIPCHECK(hipMemcpyAsync(st->tok_dev, tokens_in, c.batch * sizeof(int32_t), hipMemcpyHostToDevice, st->stream));
+      HIPCHECK(hipStreamSynchronize(st->stream));
+      tok = st->tok_dev;
+    }
   }
   const int n = state_active_layers(st, t, st->layers_tmp.data());
   if (n < 0) return n;
@@ -1027,26 +1048,38 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
   return SKD_OK;
 }
 
+// Host buffers: waits for the head and hands its results over.
+static int head_results(skd_state *st, int32_t *tokens_out, float *logits_out) {
+  const skd_config &c = st->cfg;
+  const size_t n = (size_t)c.batch * c.vocab;
+  hipStream_t s = st->stream;
+  const bool pin_logits = st->pin && n * sizeof(float) <= kPinnedLogits;
+  if (tokens_out && !st->pin)
+    HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, c.batch * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if (logits_out)
+    HIPCHECK(hipMemcpyAsync(pin_logits ? st->pin->logits : logits_out, st->logits_dev, n * sizeof(float), hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipStreamSynchronize(s));
+  if (tokens_out && st->pin) std::copy(st->pin->tok_out, st->pin->tok_out + c.batch, tokens_out);
+  if (logits_out && pin_logits) std::copy(st->pin->logits, st->pin->logits + n, logits_out);
+  return SKD_OK;
+}
+
 extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logits_out) {
   if (!st) return SKD_ERR_NULL;
   if (!st->have_hidden) return SKD_ERR_ORDER;
   const skd_config &c = st->cfg;
-  const int B = c.batch, V = c.vocab;
+  const int B = c.batch;
   hipStream_t s = st->stream;
   float *logits_target = nullptr;  // where the kernels write logits, if anywhere
   if (logits_out) logits_target = c.io_on_device ? logits_out : st->logits_dev;
-  SKDCHECK(head_logits(st, logits_target, true, c.io_on_device ? tokens_out : nullptr));
+  SKDCHECK(head_logits(st, logits_target, true, c.io_on_device ? tokens_out : st->pin ? st->pin->tok_out : nullptr));
   st->have_argmax = true;
   if (c.io_on_device) {
     if (tokens_out && !st->bf16)  // the bf16 path has written it
       HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     return SKD_OK;
   }
-  if (tokens_out) HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  if (logits_out)
-    HIPCHECK(hipMemcpyAsync(logits_out, st->logits_dev, (size_t)B * V * sizeof(float), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  return SKD_OK;
+  return head_results(st, tokens_out, logits_out);
 }
 
 // skd_logits_argmax for callers that cannot allocate: same kernels, with the LM head's per-workgroup partials in
@@ -1089,21 +1122,22 @@ extern "C" int skd_logits_sample(skd_state *st, const float *u, float temperatur
   if (!c.io_on_device) {
     for (int b = 0; b < B; ++b)
       if (!(u[b] >= 0.f) || u[b] >= 1.f) return SKD_ERR_RANGE;
-    HIPCHECK(hipMemcpyAsync(st->u_dev, u, B * sizeof(float), hipMemcpyHostToDevice, s));
-    HIPCHECK(hipStreamSynchronize(s));
-    u_dev = st->u_dev;
+    if (st->pin) {
+      std::copy(u, u + B, st->pin->u_in);
+      u_dev = st->pin->u_in;
+    } else {
+      HIPCHECK(hipMemcpyAsync(st->u_dev, u, B * sizeof(float), hipMemcpyHostToDevice, s));
+      HIPCHECK(hipStreamSynchronize(s));
+      u_dev = st->u_dev;
+    }
   }
   float *lg = (logits_out && c.io_on_device) ? logits_out : st->logits_dev;
   SKDCHECK(head_logits(st, lg, false, nullptr));
-  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev, c.io_on_device ? tokens_out : nullptr) < 0) return SKD_ERR_SHAPE; }
+  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev, c.io_on_device ? tokens_out : st->pin ? st->pin->tok_out : nullptr) < 0) return SKD_ERR_SHAPE; }
   HIPCHECK(hipGetLastError());
   st->have_argmax = true;  // skd_decode_step(.., NULL) continues from the sampled tokens
   if (c.io_on_device) return SKD_OK;  // the sampler has written tokens_out
-  if (tokens_out) HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  if (logits_out)
-    HIPCHECK(hipMemcpyAsync(logits_out, st->logits_dev, (size_t)B * V * sizeof(float), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  return SKD_OK;
+  return head_results(st, tokens_out, logits_out);
 }
 
 extern "C" int skd_rewind(skd_state *st, int32_t t) {
