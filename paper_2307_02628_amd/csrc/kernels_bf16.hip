@@ -179,7 +179,109 @@ __device__ inline void gemm_epilogue<EPI_RESID>(const GemmArgs &a, int row, int 
   *(floatx4 *)&a.x[(long)row * a.N + n0] = pre.x + (v + pre.bias);
 }
 
-template <int MB, int R, int EPI, int U, int WAVES>
+// With NB > 0 (decode, at most NB <= 4 rows, 8 waves) the activations are not read: the workgroup makes them itself, in
+// LDS, from the residual rows and the partial sums of the projection before: x + bias + sums, then LayerNorm.  Every
+// workgroup repeats that, workgroup 0 also stores the new residual rows (to another buffer: the others still read the
+// old ones).  The first weights are requested before it, so they arrive under it.  For few rows this costs less than
+// the reducer's launch (one row of 4096: about 64 KiB from L2 per workgroup).
+constexpr int ln_chunks(int NB) { return NB > 2 ? 1 : 2; }  // float4 chunks per thread: rows of 2048 NC at most
+constexpr int ln_row_stride(int K) { return K + 32; }  // bf16 units: rows start 16 banks apart
+template <int NB, typename F>
+__device__ inline void ln_prologue(const GemmArgs &a, bf16_t *act, float *sh, int wave, int lane, F request_weights) {
+  constexpr int NC = ln_chunks(NB);
+  const int d4 = a.K >> 2, tid = threadIdx.x;
+  auto bar = [&]() {  // bare: __syncthreads() would wait for the weights in flight
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // all loads of the rows, then the first weights, then the sums: what is waited for first is requested first
+  floatx4 v[NB][NC], p[NB][NC][4], bias[NC], gv[NC], bv[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = tid + 512 * i;
+    if (c < d4) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const long at = (long)min(b, a.B - 1) * d4 + c;  // rows past the batch repeat the last one
+        v[b][i] = ((const floatx4 *)a.ln_x)[at];
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp)
+          if (sp < a.ln_split) p[b][i][sp] = ((const floatx4 *)a.ln_partial)[(long)sp * a.B_pad * d4 + at];
+      }
+      bias[i] = ((const floatx4 *)a.ln_bias)[c];
+      gv[i] = ((const floatx4 *)a.ln_g)[c];
+      bv[i] = ((const floatx4 *)a.ln_b)[c];
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  request_weights();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = tid + 512 * i;
+    if (c < d4) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const long at = (long)min(b, a.B - 1) * d4 + c;
+        floatx4 acc = p[b][i][0];
+#pragma unroll
+        for (int sp = 1; sp < 4; ++sp)
+          if (sp < a.ln_split) acc += p[b][i][sp];
+        for (int sp = 4; sp < a.ln_split; ++sp) acc += ((const floatx4 *)a.ln_partial)[(long)sp * a.B_pad * d4 + at];
+        v[b][i] += acc + bias[i];
+        if (blockIdx.x == 0 && b < a.B) ((floatx4 *)a.ln_x_out)[at] = v[b][i];
+      }
+    }
+  }
+  float mean[NB], rstd[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (tid + 512 * i < d4) s += (v[b][i][0] + v[b][i][1]) + (v[b][i][2] + v[b][i][3]);
+    s = wave_sum_f(s);
+    if (lane == 0) sh[b * 8 + wave] = s;
+  }
+  bar();
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) s += sh[b * 8 + w];
+    mean[b] = s / a.K;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (tid + 512 * i < d4) {
+        const floatx4 t = v[b][i] - mean[b];
+        q += (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]);
+      }
+    q = wave_sum_f(q);
+    if (lane == 0) sh[32 + b * 8 + wave] = q;
+  }
+  bar();
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    float q = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) q += sh[32 + b * 8 + w];
+    rstd[b] = 1.0f / sqrtf(q / a.K + 1e-5f);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int c = tid + 512 * i;
+      if (c < d4) {
+        const floatx4 y = (v[b][i] - mean[b]) * rstd[b] * gv[i] + bv[i];
+        *(uint2 *)&act[b * ln_row_stride(a.K) + 4 * c] = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+      }
+    }
+  }
+  bar();
+}
+
+template <int MB, int R, int EPI, int U, int WAVES, int NB = 0>
 __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
   constexpr int RM = R * MB;
   extern __shared__ floatx4 red[];  // [WAVES][RM][64 lanes]
@@ -217,11 +319,23 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int r = 0; r < R; ++r) w[u][r] = __builtin_nontemporal_load(&Wl[woff[r] + (long)(j * U + u) * kstride]);
+      if constexpr (NB == 0) {
 #pragma unroll
-      for (int m = 0; m < MB; ++m) x[u][m] = Ab[((long)m * Kf + j * U + u) * 64];
+        for (int m = 0; m < MB; ++m) x[u][m] = Ab[((long)m * Kf + j * U + u) * 64];
+      }
     }
   };
-  auto fma = [&](bf16x8(&w)[U][R], bf16x8(&x)[U][MB]) {
+  // NB > 0: rows of the activations in LDS behind the reduction buffer; lanes of rows that do not exist hold zeros
+  bf16_t *act = (bf16_t *)(red + WAVES * gemm_stage_rows(WAVES, R, MB) * MB * 64);
+  auto fma = [&](int j, bf16x8(&w)[U][R], bf16x8(&x)[U][MB]) {
+    if constexpr (NB > 0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x[u][0] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        if ((lane & 15) < NB)
+          x[u][0] = *(const bf16x8 *)&act[(lane & 15) * ln_row_stride(a.K) + (kw0 + j * U + u) * 32 + 8 * (lane >> 4)];
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -253,7 +367,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
   // makes the compiler keep two copies of the accumulators and move all of them between the copies every iteration.
   const bool idle = wave >= nbuf;
   int j = idle ? 0 : wave;
-  load(j, w0, x0);
+  if constexpr (NB > 0) ln_prologue<NB>(a, act, (float *)red, wave, lane, [&]() { load(j, w0, x0); });
+  else load(j, w0, x0);
   if (idle) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -267,10 +382,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
   while (true) {
     const int j1 = j + WAVES, j2 = j + 2 * WAVES;
     if (j1 < nbuf) load(j1, w1, x1);
-    fma(w0, x0);
+    fma(j, w0, x0);
     if (j1 >= nbuf) break;
     if (j2 < nbuf) load(j2, w0, x0);
-    fma(w1, x1);
+    fma(j1, w1, x1);
     if (j2 >= nbuf) break;
     j = j2;
   }
@@ -398,6 +513,41 @@ static void launch_gemm_r(hipStream_t s, const GemmArgs &a, int epi, int R, int 
   else if (R == 2) launch_gemm_u<MB, 2>(s, a, epi, U, waves, grid);
   else if (R == 3) launch_gemm_u<MB, 3>(s, a, epi, U, waves, grid);
   else launch_gemm_u<MB, 4>(s, a, epi, U, waves, grid);
+}
+
+// Decode projections of at most 4 rows with the reducer's work in their prologue (a.ln_*; see k_gemm).
+template <int R, int EPI>
+static int launch_gemm_ln(hipStream_t s, const GemmArgs &a, dim3 grid) {
+  const int NB = a.B <= 1 ? 1 : a.B <= 2 ? 2 : 4;
+  const size_t lds = (size_t)8 * R * 64 * sizeof(floatx4) + (size_t)NB * ln_row_stride(a.K) * sizeof(bf16_t);
+  static bool configured = false;
+  if (!configured) {
+    const int most = 8 * R * 64 * (int)sizeof(floatx4) + 4 * ln_row_stride(2048) * (int)sizeof(bf16_t);  // more than 2 rows of 4096
+    if (hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess)
+      return -1;
+    configured = true;
+  }
+  if (NB == 1) SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 1>), grid, dim3(512), lds, s, a);
+  else if (NB == 2) SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 2>), grid, dim3(512), lds, s, a);
+  else SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 4>), grid, dim3(512), lds, s, a);
+  return 0;
+}
+int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epi, int R) {
+  if (a.B < 1 || a.B > 4 || a.B_pad != 16 || a.K % 32 || a.K < 32 || a.K > 2048 * ln_chunks(a.B) || a.split != 1 || a.rows != 0)
+    return -1;
+  if (R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.N < 1 || a.ln_split < 1 || (epi != EPI_QKV && epi != EPI_RELU)) return -1;
+  const int groups = bf16_gemm_groups(a.N, R);
+  const dim3 grid(groups);
+  int rc;
+#define SKD_LN(R) (epi == EPI_QKV ? launch_gemm_ln<R, EPI_QKV>(s, a, grid) : launch_gemm_ln<R, EPI_RELU>(s, a, grid))
+  if (R == 1) rc = SKD_LN(1);
+  else if (R == 2) rc = SKD_LN(2);
+  else if (R == 3) rc = SKD_LN(3);
+  else rc = SKD_LN(4);
+#undef SKD_LN
+  return rc < 0 ? -1 : groups;
 }
 
 // Batch tiles of 16 rows are compiled for B_pad in {16, 32, 64, 128}.
@@ -1268,22 +1418,23 @@ void bf16_embed_ln(hipStream_t s, const int32_t *tokens, const int32_t *start, i
   SKD_LAUNCH(k_embed_ln, dim3(B), dim3(row_threads(d)), 0, s, tokens, start, t, tok_emb, pos_emb, g, b, x, a_out, d, V);
 }
 
-// x[b][:] += bias + sum_s partial[s][b][:] (fixed order), then LayerNorm.  A latency chain: S is the number of partial
+// x[b][:] = x_in[b][:] + bias + sum_s partial[s][b][:] (fixed order), then LayerNorm; x_in may be x.  A latency chain: S is the number of partial
 // sums (0 = any, `split` of them), so that all loads are in flight together; as a loop of unknown length the loads
 // of the second and later sums waited for one another.
 template <int S, int NC>
 __global__ __launch_bounds__(1024) void k_reduce_ln(const float *partial, int split, int B_pad, const float *bias,
-                                                    float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
+                                                    const float *x_in, float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
   __shared__ float sh[32];
   const int b = blockIdx.x, d4 = d >> 2;
   const floatx4 *p4 = (const floatx4 *)partial;
   floatx4 *x4 = (floatx4 *)x + (long)b * d4;
+  const floatx4 *xi4 = (const floatx4 *)x_in + (long)b * d4;
   floatx4 v[NC], gv[NC], bv[NC];
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     const int c = (int)(threadIdx.x + blockDim.x * i);
     if (c < d4) {
-      const floatx4 xv = x4[c], bias4 = ((const floatx4 *)bias)[c];
+      const floatx4 xv = xi4[c], bias4 = ((const floatx4 *)bias)[c];
       gv[i] = ((const floatx4 *)g)[c];
       bv[i] = ((const floatx4 *)bt)[c];
       floatx4 acc = p4[(long)b * d4 + c];
@@ -1303,10 +1454,10 @@ __global__ __launch_bounds__(1024) void k_reduce_ln(const float *partial, int sp
   ln_finish_row<NC>(v, gv, bv, d, b, a_out, sh);
 }
 
-void bf16_reduce_ln(hipStream_t s, const float *partial, int split, int B_pad, const float *bias, float *x,
-                    const float *g, const float *b, bf16_t *a_out, int B, int d) {
+void bf16_reduce_ln(hipStream_t s, const float *partial, int split, int B_pad, const float *bias, const float *x_in,
+                    float *x, const float *g, const float *b, bf16_t *a_out, int B, int d) {
   const dim3 grid(B), blk(row_threads(d));
-#define SKD_RED(S, NC) SKD_LAUNCH((k_reduce_ln<S, NC>), grid, blk, 0, s, partial, split, B_pad, bias, x, g, b, a_out, d)
+#define SKD_RED(S, NC) SKD_LAUNCH((k_reduce_ln<S, NC>), grid, blk, 0, s, partial, split, B_pad, bias, x_in, x, g, b, a_out, d)
   if (d > 4096) SKD_RED(0, LN_NC);
   else if (split == 1) SKD_RED(1, 1);
   else if (split == 2) SKD_RED(2, 1);

@@ -121,6 +121,8 @@ struct skd_state {
   int32_t *argmax_dev = nullptr;   // [B]
   float *u_dev = nullptr;          // [B] uniform numbers of the sampling head
   float *x = nullptr;              // residual stream fp32 [B_pad][d]
+  float *x2 = nullptr;             // its second buffer (fuse_ln)
+  bool fuse_ln = false;            // few rows: the row reducers are prologues of the projections behind them
   void *a = nullptr;               // LayerNorm output
   void *q = nullptr;               // bf16: q [B_pad][d]; fp32: qkv [B][3d]
   void *o = nullptr;               // attention output
@@ -454,9 +456,12 @@ void attn_shape(const skd_state *st, int t, int &waves, int &splits) {
 }
 
 // One layer of the column at position t on the bf16 path.  st->a holds LayerNorm 1 of its input, st->x the residual
-// stream; next_g, next_b: the LayerNorm that follows (LayerNorm 1 of the next active layer, or the final one), which the
-// reducer of the last sub-block applies.
-int run_layer(skd_state *st, int l, int t, const float *next_g, const float *next_b) {
+// stream; next: the active layer that follows (null: none), whose LayerNorm 1, or the final one, the reducer of the last
+// sub-block applies.
+// With few rows (st->fuse_ln) the reducers between the projections of a layer, and between layers, are the prologues of
+// the projections that follow: prev (null: the first layer of the column) is the layer whose FFN2 partial sums are
+// still to be added to st->x, and the residual stream alternates between st->x and st->x2.
+int run_layer(skd_state *st, int l, int t, const LayerW *prev, const LayerW *next) {
   const skd_config &c = st->cfg;
   const int B = c.batch, d = c.d_model, f = c.ffn;
   hipStream_t s = st->stream;
@@ -468,7 +473,14 @@ int run_layer(skd_state *st, int l, int t, const float *next_g, const float *nex
   // q, k, v projection; the attention kernel files k and v into this layer's page slot for column t
   ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d; ga.split = 1;
   ga.q_out = q; ga.kv_new = st->kv_new;
-  { ProfScope ps_(st, SKD_PROF_GEMM_QKV); grc = launch_gemm(s, ga, EPI_QKV, st->p_qkv); }
+  ga.ln_partial = st->partial;
+  if (st->fuse_ln && prev) {
+    ga.ln_x = st->x2; ga.ln_x_out = st->x; ga.ln_split = st->p_ffn2.split; ga.ln_bias = prev->b2; ga.ln_g = w.ln1_g; ga.ln_b = w.ln1_b;
+    { ProfScope ps_(st, SKD_PROF_GEMM_QKV); grc = bf16_gemm_ln(s, ga, EPI_QKV, st->p_qkv.R); }
+  } else {
+    ProfScope ps_(st, SKD_PROF_GEMM_QKV);
+    grc = launch_gemm(s, ga, EPI_QKV, st->p_qkv);
+  }
   if (grc < 0) return SKD_ERR_SHAPE;
   AttnArgs aa{};
   aa.q = q; aa.kv_new = st->kv_new; aa.pool = (bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.start = st->start_dev; aa.order = st->ragged ? st->order_dev : nullptr;
@@ -478,14 +490,22 @@ int run_layer(skd_state *st, int l, int t, const float *next_g, const float *nex
   ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = o; ga.N = d; ga.K = d; ga.split = st->p_out.split; ga.partial = st->partial;
   { ProfScope ps_(st, SKD_PROF_GEMM_OUT); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_out); }
   if (grc < 0) return SKD_ERR_SHAPE;
-  { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_out.split, st->B_pad, w.bo, st->x, w.ln2_g, w.ln2_b, a, B, d); }
+  if (!st->fuse_ln) { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_out.split, st->B_pad, w.bo, st->x, st->x, w.ln2_g, w.ln2_b, a, B, d); }
   ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.split = 1; ga.act_out = u;
-  { ProfScope ps_(st, SKD_PROF_GEMM_FFN1); grc = launch_gemm(s, ga, EPI_RELU, st->p_ffn1); }
+  if (st->fuse_ln) {
+    ga.ln_x = st->x; ga.ln_x_out = st->x2; ga.ln_split = st->p_out.split; ga.ln_bias = w.bo; ga.ln_g = w.ln2_g; ga.ln_b = w.ln2_b;
+    { ProfScope ps_(st, SKD_PROF_GEMM_FFN1); grc = bf16_gemm_ln(s, ga, EPI_RELU, st->p_ffn1.R); }
+  } else {
+    ProfScope ps_(st, SKD_PROF_GEMM_FFN1);
+    grc = launch_gemm(s, ga, EPI_RELU, st->p_ffn1);
+  }
   if (grc < 0) return SKD_ERR_SHAPE;
   ga.W = (const bf16_t *)w.w2; ga.G = st->p_ffn2.R; ga.A = u; ga.N = d; ga.K = f; ga.split = st->p_ffn2.split;
   { ProfScope ps_(st, SKD_PROF_GEMM_FFN2); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_ffn2); }
   if (grc < 0) return SKD_ERR_SHAPE;
-  { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_ffn2.split, st->B_pad, w.b2, st->x, next_g, next_b, a, B, d); }
+  if (st->fuse_ln && next) return SKD_OK;  // the next layer adds the partial sums
+  const float *next_g = next ? next->ln1_g : st->lnf_g, *next_b = next ? next->ln1_b : st->lnf_b;
+  { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_ffn2.split, st->B_pad, w.b2, st->fuse_ln ? st->x2 : st->x, st->x, next_g, next_b, a, B, d); }
   return SKD_OK;
 }
 
@@ -522,8 +542,7 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
     const LayerW &w0 = st->lw[layers[0]];
     { ProfScope ps_(st, SKD_PROF_EMBED_LN); bf16_embed_ln(s, tokens_dev, st->start_dev, t, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, w0.ln1_g, w0.ln1_b, st->x, (bf16_t *)st->a, B, d, c.vocab); }
     for (int i = 0; i < n; ++i) {
-      const LayerW *nw = i + 1 < n ? &st->lw[layers[i + 1]] : nullptr;
-      SKDCHECK(run_layer(st, layers[i], t, nw ? nw->ln1_g : st->lnf_g, nw ? nw->ln1_b : st->lnf_b));
+      SKDCHECK(run_layer(st, layers[i], t, i ? &st->lw[layers[i - 1]] : nullptr, i + 1 < n ? &st->lw[layers[i + 1]] : nullptr));
       st->kv_len[layers[i]] = t + 1;
     }
   }
@@ -588,6 +607,23 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     ov("SKD_W_OUT", st->p_out.waves, 4, 8); ov("SKD_W_FFN2", st->p_ffn2.waves, 4, 8);
   }
 
+  if (st->bf16) {
+    st->max_split = std::max(st->p_out.split, st->p_ffn2.split);
+    // The prologue reads x and the partial sums of every row in every workgroup: up to 128 KiB (two rows of 4096 with a
+    // split of 2, three of 2048 with 4) that takes less than the reducer's launch.  It is paid per workgroup, and the
+    // activations come from LDS, so the projections behind it take the row groups of a wider batch: one workgroup per CU
+    // instead of two for FFN1 at 4096 x 16384.  One row of 4096, 4 steps of 2 to 4 layers at 2000 keys: 1355 us with
+    // separate reducers, 1300 with two workgroups per CU, 1287 with one; two rows of 256: 1910 -> 1740 us for 16 steps.
+    st->fuse_ln = B <= 4 && d <= (B <= 2 ? 4096 : 2048) && (long)B * d * 4 * (1 + st->max_split) <= (128L << 10) &&
+                  env_int("SKD_FUSE_LN", 1) != 0;
+    if (st->fuse_ln) {
+      st->p_qkv = plan_direct(3 * d, 32);
+      st->p_ffn1 = plan_direct(f, 32);
+      ov("SKD_R_QKV", st->p_qkv.R, 1, 4); ov("SKD_R_FFN1", st->p_ffn1.R, 1, 4);
+      ov("SKD_U_QKV", st->p_qkv.U, 1, 4); ov("SKD_U_FFN1", st->p_ffn1.U, 1, 4);
+      ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8);
+    }
+  }
   if (st->bf16 && st->B_pad == 128 && env_int("SKD_GEMM_WS", 1) != 0) {
     // 128 batch rows: every projection whose K range divides into stages of 4 k-steps per workgroup
     GemmArgs ga{};
@@ -666,7 +702,6 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
         st->prefill_split = sp;
       }
     }
-    st->max_split = std::max(st->p_out.split, st->p_ffn2.split);
     // split the key range of one head over several workgroups only when rows*heads alone cannot fill the chip
     // decode attention wants 16 waves on every CU: few (row, head) pairs get wider workgroups first (merged in
     // LDS), then splits of the key range (merged by a second kernel)
@@ -680,6 +715,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     st->attn_waves = waves;
     st->attn_splits = splits;
     st->attn_fixed = env_int("SKD_ATTN_WAVES", 0) > 0 || env_int("SKD_ATTN_SPLITS", 0) > 0;
+    if (st->fuse_ln) A(&st->x2, (size_t)Bp * d);
     bf16_t *t16 = nullptr;
     A(&t16, (size_t)Bp * d); st->a = t16; if (rc == SKD_OK) rc = hipMemsetAsync(st->a, 0, (size_t)Bp * d * 2, st->stream) == hipSuccess ? SKD_OK : SKD_ERR_HIP;
     A(&t16, (size_t)Bp * d); st->q = t16;
@@ -903,7 +939,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
       bf16_last_rows_ln(s, st->pf_x, rm, nullptr, 0, 0, nullptr, w.ln1_g, w.ln1_b, st->x, (bf16_t *)st->a, B, d);
       const int profiling = st->profiling;
       st->profiling = 0;  // the timed classes are those of decode steps
-      const int rc = run_layer(st, l, P - 1, st->lnf_g, st->lnf_b);
+      const int rc = run_layer(st, l, P - 1, nullptr, nullptr);
       st->profiling = profiling;
       SKDCHECK(rc);
       st->kv_len[l] = P;
@@ -916,7 +952,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     bf16_attention_rows(s, aa);
     ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = st->pf_o; ga.bias = w.bo; ga.N = d; ga.K = d;
     if (proj(ga, EPI_RESID, r_out) < 0) return SKD_ERR_SHAPE;
-    if (r_out.partial) bf16_reduce_ln(s, st->pf_partial, r_out.split, stride(r_out), w.bo, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, rows, d);
+    if (r_out.partial) bf16_reduce_ln(s, st->pf_partial, r_out.split, stride(r_out), w.bo, st->pf_x, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, rows, d);
     else bf16_ln_rows(s, st->pf_x, w.ln2_g, w.ln2_b, st->pf_a, rows, d);
     ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = st->pf_a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.act_out = st->pf_u;
     if (proj(ga, EPI_RELU, r_ffn1) < 0) return SKD_ERR_SHAPE;
@@ -924,7 +960,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     if (proj(ga, EPI_RESID, r_ffn2) < 0) return SKD_ERR_SHAPE;
     if (l + 1 < L) {
       const LayerW &nw = st->lw[l + 1];
-      if (r_ffn2.partial) bf16_reduce_ln(s, st->pf_partial, r_ffn2.split, stride(r_ffn2), w.b2, st->pf_x, nw.ln1_g, nw.ln1_b, st->pf_a, rows, d);
+      if (r_ffn2.partial) bf16_reduce_ln(s, st->pf_partial, r_ffn2.split, stride(r_ffn2), w.b2, st->pf_x, st->pf_x, nw.ln1_g, nw.ln1_b, st->pf_a, rows, d);
       else bf16_ln_rows(s, st->pf_x, nw.ln1_g, nw.ln1_b, st->pf_a, rows, d);
     }
     st->kv_len[l] = P;

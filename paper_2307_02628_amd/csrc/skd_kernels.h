@@ -137,6 +137,11 @@ struct GemmArgs {
   int d;               // EPI_QKV, EPI_QKV_ROWS: d_model (N = 3d)
   KvGeom kv;           // EPI_QKV_ROWS
   bf16_t *act_out;     // EPI_RELU
+  // bf16_gemm_ln: A = LayerNorm(ln_x + ln_bias + sum of ln_split partial sums [ln_split][B_pad][K]; ln_g, ln_b), made by
+  // every workgroup; ln_x_out (another buffer than ln_x) receives the sum
+  const float *ln_x, *ln_partial, *ln_bias, *ln_g, *ln_b;
+  float *ln_x_out;
+  int ln_split;
   float *logits;       // EPI_LOGITS (nullable)
   float *pmax;         // EPI_LOGITS: [groups][B_pad]
   int32_t *pidx;       // EPI_LOGITS
@@ -145,6 +150,8 @@ struct GemmArgs {
 // waves in {4,8}: waves per workgroup.  K/32 must be a multiple of a.split.
 // Returns the number of row groups launched (grid.x), or -1 for an unsupported shape.
 int bf16_gemm(hipStream_t s, const GemmArgs &a, int epilogue, int R, int U, int waves);
+// At most 4 rows, K <= 4096, EPI_QKV or EPI_RELU: with the row reducer in the prologue (ln_*; a.A is not read).
+int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epilogue, int R);
 // The same shape checks without a launch (only N, K, B_pad, G, split and rows of `a` are read): groups or -1.
 int bf16_gemm_check(const GemmArgs &a, int epilogue, int R, int U, int waves);
 int bf16_gemm_groups(int N, int R);
@@ -165,9 +172,9 @@ int bf16_gemm_mid(hipStream_t s, const GemmArgs &a, int epilogue, int weight_row
 void bf16_embed_ln(hipStream_t s, const int32_t *tokens, const int32_t *start, int t, const bf16_t *tok_emb,
                    const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
                    int V);
-// x[b][:] += bias + sum_s partial[s][b][:]; a_out = LayerNorm(x; g, b) as bf16 activation tiles
-void bf16_reduce_ln(hipStream_t s, const float *partial, int split, int B_pad, const float *bias, float *x,
-                    const float *g, const float *b, bf16_t *a_out, int B, int d);
+// x[b][:] = x_in[b][:] + bias + sum_s partial[s][b][:] (x_in may be x); a_out = LayerNorm(x; g, b) as bf16 activation tiles
+void bf16_reduce_ln(hipStream_t s, const float *partial, int split, int B_pad, const float *bias, const float *x_in,
+                    float *x, const float *g, const float *b, bf16_t *a_out, int B, int d);
 // Decode attention at position t.  Keys of columns start[b] .. t-1 (slots 0 .. t-start[b]-1) come from the pages; k and v of position t itself come
 // from kv_new (written by the EPI_QKV projection) and are stored into the page slot of t by this kernel.
 struct AttnArgs {
