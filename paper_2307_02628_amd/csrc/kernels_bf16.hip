@@ -43,6 +43,12 @@ __device__ inline float block_sum_once(float v, float *sh) {
   return r;
 }
 
+template <int N>
+__device__ inline void wait_vmcnt() {  // at most N vector-memory operations of this wave outstanding (vmcnt: bits 15:14, 3:0)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+
 // Activations [rows][K]: 16-row x 32-column tiles in the order [row / 16][col / 32], each tile 16 rows of 64
 // contiguous bytes.  A producer that owns one row writes 64-byte runs (whole 32-byte sectors); a consumer reads a
 // tile as one MFMA B-operand fragment, lane l taking the 16 bytes at row l % 16, columns 8 * (l / 16) .. + 7,
@@ -489,8 +495,8 @@ static void launch_gemm_epi(hipStream_t s, const GemmArgs &a, int epi, dim3 grid
 }
 template <int MB, int R, int U>
 static void launch_gemm_w(hipStream_t s, const GemmArgs &a, int epi, int waves, dim3 grid) {
-  // 8 batch tiles need 4-wave workgroups: with 8 waves (2 per SIMD, 256 registers each) the accumulators spill
-  if constexpr (MB < 8) {
+  // 6 and 8 batch tiles need 4-wave workgroups: with 8 waves (2 per SIMD, 256 registers each) the accumulators spill
+  if constexpr (MB < 6) {
     if (waves >= 8) { launch_gemm_epi<MB, R, U, 8>(s, a, epi, grid); return; }
   }
   launch_gemm_epi<MB, R, U, 4>(s, a, epi, grid);
@@ -550,12 +556,12 @@ int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epi, int R) {
   return rc < 0 ? -1 : groups;
 }
 
-// Batch tiles of 16 rows are compiled for B_pad in {16, 32, 64, 128}.
+// Batch tiles of 16 rows are compiled for B_pad in {16, 32, 48, 64, 96, 128}.
 // Launch shape of a skinny GEMM, or false if the kernel cannot run it: nothing is launched here.
 static bool gemm_shape(const GemmArgs &a, int epi, int R, int &U, int waves, dim3 &grid, int &groups) {
   const int MB = a.B_pad / 16;
   if (R < 1 || R > 4 || a.G < 1 || a.G > 4 || (waves != 4 && waves != 8)) return false;
-  if (a.B_pad % 16 || (MB != 1 && MB != 2 && MB != 4 && MB != 8)) return false;
+  if (a.B_pad % 16 || (MB != 1 && MB != 2 && MB != 3 && MB != 4 && MB != 6 && MB != 8)) return false;
   if (a.K < 32 || a.K % 32 || a.N < 1) return false;
   const int split = epi == EPI_LOGITS ? 1 : a.split;
   const int Kf = a.K / 32;
@@ -584,13 +590,15 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
   switch (a.B_pad / 16) {
     case 1: launch_gemm_r<1>(s, a, epi, R, U, waves, grid); break;
     case 2: launch_gemm_r<2>(s, a, epi, R, U, waves, grid); break;
+    case 3: launch_gemm_r<3>(s, a, epi, R, U, waves, grid); break;
     case 4: launch_gemm_r<4>(s, a, epi, R, U, waves, grid); break;
+    case 6: launch_gemm_r<6>(s, a, epi, R, U, waves, grid); break;
     default: launch_gemm_r<8>(s, a, epi, R, U, waves, grid); break;
   }
   return groups;
 }
 
-// ------------------------------------------------------------------ skinny GEMM for 128 batch rows
+// ------------------------------------------------------------------ skinny GEMM for 96 and 128 batch rows
 // With 8 batch tiles a workgroup pulls two bytes of activations out of L2 for every byte of weights it streams
 // from HBM, and on this part a CU's vector memory path serves the two kinds of request largely one after the
 // other: measured per CU with plain streaming waves, 512 KiB of HBM misses take 19.9 us and every further MiB of
@@ -606,12 +614,12 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
 // it off for the LM head, where identical vocabulary rows are to give identical logits).
 constexpr int WS_NS = 4;  // ring stages
 constexpr int WS_CW = 4;  // MFMA waves = loader waves = k-steps per stage
-constexpr int WS_MB = 8;  // batch tiles
+// MB: batch tiles, 6 or 8
 
-template <int R, int EPI>
+template <int MB, int R, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
-  constexpr int MB = WS_MB, NS = WS_NS;
-  constexpr int STAGE = WS_CW * MB * 64;     // bf16x8 units per stage (32 KiB)
+  constexpr int NS = WS_NS;
+  constexpr int STAGE = WS_CW * MB * 64;     // bf16x8 units per stage (24 or 32 KiB)
   extern __shared__ bf16x8 ws_lds[];         // ring [NS][WS_CW][MB][64 lanes]; later the reduction buffer
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int Kf = a.K >> 5;
@@ -643,12 +651,12 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
     for (int i = 0; i < NS - 1; ++i)
       if (i < nchunk) issue(i);
     for (int ci = 0; ci < nchunk; ++ci) {
-      // this wave's 8 loads of stage ci have landed once only those of the (up to two) later stages in flight
+      // this wave's MB loads of stage ci have landed once only those of the (up to two) later stages in flight
       // are outstanding (vector-memory operations of a wave complete in order)
       const int later = min(nchunk - 1 - ci, NS - 2);
-      if (later == 0) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt = 0
-      else if (later == 1) __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt <= 8
-      else __builtin_amdgcn_s_waitcnt(0x4F70);                  // vmcnt <= 16
+      if (later == 0) wait_vmcnt<0>();
+      else if (later == 1) wait_vmcnt<MB>();
+      else wait_vmcnt<2 * MB>();
       bar();  // stage ci is complete; every wave has finished reading stage ci - 1
       if (ci + NS - 1 < nchunk) issue(ci + NS - 1);  // into the slot of stage ci - 1
     }
@@ -791,10 +799,10 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
   }
 }
 
-// Decode projections at 128 (padded) batch rows on the wave-specialised kernel.  Returns the number of row groups,
+// Decode projections at 96 or 128 (padded) batch rows on the wave-specialised kernel.  Returns the number of row groups,
 // or -1 when the shape is not one it handles (the caller then uses bf16_gemm); nothing is launched in that case.
 static bool gemm_ws_shape(const GemmArgs &a, int epi, int R, dim3 &grid, int &groups) {
-  if (a.B_pad != 128 || a.rows != 0 || R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.K < 32 || a.K % 32 || a.N < 1) return false;
+  if ((a.B_pad != 96 && a.B_pad != 128) || a.rows != 0 || R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.K < 32 || a.K % 32 || a.N < 1) return false;
   if (epi != EPI_PARTIAL && epi != EPI_QKV && epi != EPI_RELU && epi != EPI_LOGITS) return false;
   const int split = epi == EPI_LOGITS ? 1 : a.split;
   const int Kf = a.K / 32;
@@ -808,27 +816,27 @@ int bf16_gemm_ws_check(const GemmArgs &a, int epi, int R) {
   int groups = 0;
   return gemm_ws_shape(a, epi, R, grid, groups) ? groups : -1;
 }
-template <int R>
+template <int MB, int R>
 static int launch_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, dim3 grid) {
-  // the activation ring (4 stages of 32 KiB), reused for the cross-wave reduction (4 waves x R x 8 KiB): 128 KiB
-  constexpr size_t ring = (size_t)WS_NS * WS_CW * WS_MB * 64 * sizeof(bf16x8);
-  constexpr size_t redb = (size_t)WS_CW * R * WS_MB * 64 * sizeof(floatx4);
+  // the activation ring (4 stages of 4 MB KiB), reused for the cross-wave reduction (4 waves x R x MB KiB): 128 KiB at most
+  constexpr size_t ring = (size_t)WS_NS * WS_CW * MB * 64 * sizeof(bf16x8);
+  constexpr size_t redb = (size_t)WS_CW * R * MB * 64 * sizeof(floatx4);
   constexpr size_t lds = ring > redb ? ring : redb;
   static bool configured = false;
   if (!configured) {
-    if (hipFuncSetAttribute((const void *)k_gemm_ws<R, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<R, EPI_QKV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<R, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<R, EPI_LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_QKV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return -1;
     configured = true;
   }
   const dim3 blk(512);
   switch (epi) {
-    case EPI_PARTIAL: SKD_LAUNCH((k_gemm_ws<R, EPI_PARTIAL>), grid, blk, lds, s, a); break;
-    case EPI_QKV: SKD_LAUNCH((k_gemm_ws<R, EPI_QKV>), grid, blk, lds, s, a); break;
-    case EPI_RELU: SKD_LAUNCH((k_gemm_ws<R, EPI_RELU>), grid, blk, lds, s, a); break;
-    default: SKD_LAUNCH((k_gemm_ws<R, EPI_LOGITS>), grid, blk, lds, s, a); break;
+    case EPI_PARTIAL: SKD_LAUNCH((k_gemm_ws<MB, R, EPI_PARTIAL>), grid, blk, lds, s, a); break;
+    case EPI_QKV: SKD_LAUNCH((k_gemm_ws<MB, R, EPI_QKV>), grid, blk, lds, s, a); break;
+    case EPI_RELU: SKD_LAUNCH((k_gemm_ws<MB, R, EPI_RELU>), grid, blk, lds, s, a); break;
+    default: SKD_LAUNCH((k_gemm_ws<MB, R, EPI_LOGITS>), grid, blk, lds, s, a); break;
   }
   return 0;
 }
@@ -837,10 +845,12 @@ int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, int R) {
   int groups = 0;
   if (!gemm_ws_shape(a, epi, R, grid, groups)) return -1;
   int rc;
-  if (R == 1) rc = launch_gemm_ws<1>(s, a, epi, grid);
-  else if (R == 2) rc = launch_gemm_ws<2>(s, a, epi, grid);
-  else if (R == 3) rc = launch_gemm_ws<3>(s, a, epi, grid);
-  else rc = launch_gemm_ws<4>(s, a, epi, grid);
+#define SKD_WS(R) (a.B_pad == 96 ? launch_gemm_ws<6, R>(s, a, epi, grid) : launch_gemm_ws<8, R>(s, a, epi, grid))
+  if (R == 1) rc = SKD_WS(1);
+  else if (R == 2) rc = SKD_WS(2);
+  else if (R == 3) rc = SKD_WS(3);
+  else rc = SKD_WS(4);
+#undef SKD_WS
   return rc < 0 ? -1 : groups;
 }
 
@@ -1175,11 +1185,6 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
 // us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
 // FFN1 80 -> 44, FFN2 296 -> 46 (split 4), all 128 x 128; 1024 rows of the 1.3B shape QKV 44 -> 32 and FFN1 45 -> 35
 // (128 x 256; 128 x 128: 37 and 41), output 51 -> 15 (128 x 128, split 2), FFN2 153 -> 37 (128 x 256, split 4).
-template <int N>
-__device__ inline void wait_vmcnt() {  // at most N vector-memory operations of this wave outstanding (vmcnt: bits 15:14, 3:0)
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
 template <int RT, int MT, int WN, int WM, int NS, int EPI>
 __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
   constexpr int FW = WN * RT, FA = WM * MT, FR = FW + FA;  // weight and activation fragments per stage

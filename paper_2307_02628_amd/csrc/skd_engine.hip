@@ -64,7 +64,7 @@ struct LayerW {
 
 struct GemmPlan {
   int R = 1, split = 1, U = 1, waves = 8;
-  bool ws = false;  // 128 batch rows: the wave-specialised kernel (weight-streaming waves + activation-loading waves)
+  bool ws = false;  // 96 and 128 batch rows: the wave-specialised kernel (weight-streaming waves + activation-loading waves)
   int ws_rot = 0;   // workgroups start their K range at different stages
 };
 
@@ -249,11 +249,11 @@ int upload_mat(skd_state *st, const skd_weights &w, const void *src, long N, lon
 
 // Launch shapes.  Measured on MI355X at the OPT-6.7B widths: up to batch 64, 8
 // waves per workgroup interleaving k-steps with 48-64 weight rows per workgroup
-// and one k-step per register buffer stream best; at batch 128 the 4 x 8 tile
-// accumulators need the whole register file, so workgroups have 4 waves.
+// and one k-step per register buffer stream best; at batch 96 and 128 the 4 x 6 and
+// 4 x 8 tile accumulators need the whole register file, so workgroups have 4 waves.
 // Every CU should get a workgroup; when K is split across workgroups a wave
 // should still see at least 2 k-steps.
-int plan_waves(int B_pad) { return B_pad >= 128 ? 4 : 8; }
+int plan_waves(int B_pad) { return B_pad >= 96 ? 4 : 8; }
 GemmPlan plan_direct(int N, int B_pad) {  // whole K inside the workgroup
   GemmPlan p;
   p.waves = plan_waves(B_pad);
@@ -585,8 +585,9 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
   st->dh = cfg->d_model / cfg->n_heads;
   const skd_config &c = st->cfg;
   const int B = c.batch, d = c.d_model, f = c.ffn, V = c.vocab, L = c.L;
-  st->B_pad = 16;
-  while (st->B_pad < B) st->B_pad *= 2;
+  for (int pad : {16, 32, 48, 64, 96, 128})  // batch tiles the bf16 kernels are compiled for
+    if (st->B_pad < B) st->B_pad = pad;
+  if (st->B_pad < B) st->B_pad = B;  // fp32 path only
   st->layers_tmp.resize(L);
 
   // ---- launch shapes (the weight layout below depends on them)
@@ -624,8 +625,8 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
       ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8);
     }
   }
-  if (st->bf16 && st->B_pad == 128 && env_int("SKD_GEMM_WS", 1) != 0) {
-    // 128 batch rows: every projection whose K range divides into stages of 4 k-steps per workgroup
+  if (st->bf16 && st->B_pad >= 96 && env_int("SKD_GEMM_WS", 1) != 0) {
+    // 96 and 128 batch rows: every projection whose K range divides into stages of 4 k-steps per workgroup
     GemmArgs ga{};
     ga.B = B; ga.B_pad = st->B_pad;
     auto pick = [&](int N, int K, GemmPlan &p, int epi) {
@@ -812,7 +813,7 @@ RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   const int Kf = K / 32;
   if (rows <= 64) {
     best.kind = RowsGemm::SKINNY;
-    best.B_pad = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
+    best.B_pad = rows <= 16 ? 16 : rows <= 32 ? 32 : rows <= 48 ? 48 : 64;
     const GemmPlan p = split_ok ? plan_split(N, K, best.B_pad) : plan_direct(N, best.B_pad);
     best.R = p.R;
     best.split = p.split;
