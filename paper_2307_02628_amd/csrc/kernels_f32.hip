@@ -236,10 +236,84 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
   }
 }
 
+__device__ __forceinline__ void sample_rest(const float *cand_p, const int *cand_i, int C, unsigned lower, unsigned upper, float target,
+                                   const float *u, int b, int32_t *tokens, int32_t *tokens2, SampleExchange &ex) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (C <= 256) {
+    if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+  } else if (C <= 1024) {
+    if (w == 0) sample_finish<16, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+  } else if (w < 4) {  // the barriers in there are those of the waves that remain
+    sample_finish<16, 4>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+  }
+}
+
+// First pass over a large vocabulary, spread over the chip: a workgroup takes SAMPLE_CHUNK tokens of a row, relative to
+// their own maximum (the row's is not known yet): the chunk's maximum and mass, and, in index order, the tokens at or
+// above 2^-10 of its maximum, a superset of those at or above 2^-10 of the row's.  A factor of 0.99 covers the rounding
+// of expf.  One workgroup per row read and exponentiated 200 KB on one of 256 CUs: 50272 tokens, 32 rows, 36 us for
+// everything; 24 us for both kernels.
+constexpr int SAMPLE_CHUNK = 4096;
+
+__global__ __launch_bounds__(256) void k_sample_chunk(const float *logits, int V, float inv_temp, SampleScratch sc) {
+  __shared__ float sh[4];
+  __shared__ int wcount[4];
+  const int b = blockIdx.y, ch = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int base = ch * SAMPLE_CHUNK + wave * (SAMPLE_CHUNK / 4) + lane;
+  const float *zr = logits + (long)b * V;
+  float z[16], mx = -3.0e38f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = base + 64 * i < V ? zr[base + 64 * i] * inv_temp : -3.0e38f;  // sentinel: no such token
+#pragma unroll
+  for (int i = 0; i < 16; ++i) mx = fmaxf(mx, z[i]);
+  mx = wave_max(mx);
+  if (lane == 0) sh[wave] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+  __syncthreads();
+  const float bound = 0.99f * 0x1p-10f;
+  float mass = 0;
+  int cnt = 0;
+  unsigned keep = 0;  // bit i: this lane's token of row i
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float p = z[i] > -1.0e38f ? expf(z[i] - mx) : 0.f;
+    mass += p;
+    keep |= (p >= bound ? 1u : 0u) << i;
+  }
+  cnt = __popc(keep);
+  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+  mass = wave_sum_f(mass);
+  if (lane == 0) {
+    sh[wave] = mass;
+    wcount[wave] = cnt;
+  }
+  __syncthreads();
+  const long part = (long)b * sc.chunks + ch;
+  int pos = 0;
+  for (int w = 0; w < wave; ++w) pos += wcount[w];
+  if (threadIdx.x == 0) {
+    sc.max_mass[2 * part] = mx;
+    sc.max_mass[2 * part + 1] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    sc.count[part] = wcount[0] + wcount[1] + wcount[2] + wcount[3];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const bool c = (keep >> i) & 1;
+    const unsigned long long m = __ballot(c);
+    const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
+    if (c && k < SAMPLE_CHUNK_CAND) {  // more: the count says so, and the second pass takes the whole row
+      sc.z[part * SAMPLE_CHUNK_CAND + k] = z[i];
+      sc.idx[part * SAMPLE_CHUNK_CAND + k] = base + 64 * i;
+    }
+    pos += __popcll(m);
+  }
+}
+
 // RC: rows compiled in (>= R); 52 rows cover vocabularies up to 53248 without register spills
 template <int RC>
 __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int V, float inv_temp, float top_p,
-                                                       const float *u, int32_t *tokens, int32_t *tokens2) {
+                                                       const float *u, int32_t *tokens, int32_t *tokens2, SampleScratch sc) {
   __shared__ float sh[16], wmass[16], mass_at[3][16];
   __shared__ int wcount[16];
   __shared__ float cand_p[SAMPLE_CAND];  // candidates of the short cut, ascending token index
@@ -250,6 +324,89 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int R = (V + 1023) / 1024, base = wave * R * 64 + lane;
   const float *z = logits + (long)b * V;
+  if constexpr (RC <= 52) if (sc.chunks) {  // the first pass's candidates, if they hold the target mass
+    __shared__ float hm[16], hs[16];
+    __shared__ int hoff[17], kw[4][16];
+    if (tid < 16) {
+      const long part = (long)b * sc.chunks + tid;
+      const bool have = tid < sc.chunks;
+      hm[tid] = have ? sc.max_mass[2 * part] : -3.0e38f;
+      hs[tid] = have ? sc.max_mass[2 * part + 1] : 0.f;
+      int n = have ? sc.count[part] : 0;
+      if (n > SAMPLE_CHUNK_CAND) n = SAMPLE_CAND + 1;  // does not fit: none of this
+      for (int off = 1; off < 16; off <<= 1) {
+        const int t = __shfl_up(n, off);
+        if (lane >= off) n += t;
+      }
+      hoff[tid + 1] = n;
+      if (tid == 0) hoff[0] = 0;
+    }
+    __syncthreads();
+    const int N = __builtin_amdgcn_readfirstlane(hoff[16]);
+    if (N <= SAMPLE_CAND) {
+      float M = hm[0], total = 0;
+      for (int c = 1; c < 16; ++c) M = fmaxf(M, hm[c]);
+      for (int c = 0; c < sc.chunks; ++c) total += hs[c] * expf(hm[c] - M);
+      const float target = top_p * total;
+      float pc[4], q5 = 0, q10 = 0;
+      int ic[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = tid + 1024 * k;
+        pc[k] = 0;
+        ic[k] = 0;
+        if (i < N) {
+          int c = 0;
+          while (hoff[c + 1] <= i) ++c;
+          const long at = ((long)b * sc.chunks + c) * SAMPLE_CHUNK_CAND + (i - hoff[c]);
+          pc[k] = expf(sc.z[at] - M);
+          ic[k] = sc.idx[at];
+        }
+        const bool in = pc[k] >= 0x1p-10f;
+        if (!in) pc[k] = 0;
+        q10 += pc[k];
+        q5 += pc[k] >= 0x1p-5f ? pc[k] : 0.f;
+        const unsigned long long m = __ballot(in);
+        if (lane == 0) kw[k][wave] = __popcll(m);
+      }
+      q10 = wave_sum_f(q10);
+      q5 = wave_sum_f(q5);
+      if (lane == 0) {
+        mass_at[1][wave] = q5;
+        mass_at[2][wave] = q10;
+      }
+      __syncthreads();
+      q5 = q10 = 0;
+      for (int w = 0; w < 16; ++w) {
+        q5 += mass_at[1][w];
+        q10 += mass_at[2][w];
+      }
+      if (__builtin_amdgcn_readfirstlane(q10 >= target)) {  // uniform: every thread has the same sums
+        int C = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          int at = C;
+          for (int w = 0; w < 16; ++w) {
+            if (w == wave) at = C;
+            C += kw[k][w];
+          }
+          const bool in = pc[k] > 0.f;
+          const unsigned long long m = __ballot(in);
+          if (in) {
+            const int j = at + __popcll(m & ((1ull << lane) - 1ull));
+            cand_p[j] = pc[k];
+            cand_i[j] = ic[k];
+          }
+        }
+        __syncthreads();
+        C = __builtin_amdgcn_readfirstlane(C);
+        const unsigned lower = q5 >= target ? (127u - 5u) << 23 : (127u - 10u) << 23, upper = q5 >= target ? 1u << 30 : (127u - 5u) << 23;
+        sample_rest(cand_p, cand_i, C, lower, upper, target, u, b, tokens, tokens2, ex);
+        return;
+      }
+    }
+    __syncthreads();  // mass_at is written again below
+  }
   float p[RC];
   float mx = -3.0e38f;
 #pragma unroll
@@ -338,14 +495,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
         __builtin_amdgcn_sched_barrier(0);  // row by row: hoisted, the rows' lane masks would need 2 SGPRs each
       }
       __syncthreads();
-      const int w = __builtin_amdgcn_readfirstlane(wave);
-      if (C <= 256) {
-        if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
-      } else if (C <= 1024) {
-        if (w == 0) sample_finish<16, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
-      } else if (w < 4) {  // the barriers in there are those of the waves that remain
-        sample_finish<16, 4>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
-      }
+      sample_rest(cand_p, cand_i, C, lower, upper, target, u, b, tokens, tokens2, ex);
       return;
     }
   }
@@ -418,15 +568,21 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   }
 }
 
+// Chunks of the first pass, 0 without one: up to 8192 tokens (8 per thread) a second launch costs more than it saves;
+// above 53248 the second pass has no registers left for it.
+int sample_chunks(int V) { return V > 8192 && V <= 53248 ? (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK : 0; }
+
 int sample_top_p(hipStream_t s, const float *logits, int B, int V, float temperature, float top_p, const float *u,
-                 int32_t *tokens, int32_t *tokens2) {
+                 int32_t *tokens, int32_t *tokens2, SampleScratch sc) {
   if (V > 1024 * SAMPLE_C) return -1;
   const int R = (V + 1023) / 1024;
   const float it = 1.0f / temperature;
-  if (R <= 16) SKD_LAUNCH(k_sample_top_p<16>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
-  else if (R <= 32) SKD_LAUNCH(k_sample_top_p<32>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
-  else if (R <= 52) SKD_LAUNCH(k_sample_top_p<52>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
-  else SKD_LAUNCH(k_sample_top_p<SAMPLE_C>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2);
+  sc.chunks = sc.z ? sample_chunks(V) : 0;
+  if (sc.chunks) SKD_LAUNCH(k_sample_chunk, dim3(sc.chunks, B), dim3(256), 0, s, logits, V, it, sc);
+  if (R <= 16) SKD_LAUNCH(k_sample_top_p<16>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
+  else if (R <= 32) SKD_LAUNCH(k_sample_top_p<32>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
+  else if (R <= 52) SKD_LAUNCH(k_sample_top_p<52>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
+  else SKD_LAUNCH(k_sample_top_p<SAMPLE_C>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
   return 0;
 }
 

@@ -120,6 +120,7 @@ struct skd_state {
   std::vector<int32_t> start_host, order_host;
   int32_t *argmax_dev = nullptr;   // [B]
   float *u_dev = nullptr;          // [B] uniform numbers of the sampling head
+  SampleScratch sample{};          // its candidates
   float *x = nullptr;              // residual stream fp32 [B_pad][d]
   float *x2 = nullptr;             // its second buffer (fuse_ln)
   bool fuse_ln = false;            // few rows: the row reducers are prologues of the projections behind them
@@ -689,6 +690,10 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
   const int Bp = st->B_pad;
   auto A = [&](auto **p, size_t n) { if (rc == SKD_OK) rc = dev_alloc(st, p, n); };
   A(&st->tok_dev, B); A(&st->prompt_dev, (size_t)c.prompt_size * B); A(&st->start_dev, B); A(&st->order_dev, B); A(&st->argmax_dev, B); A(&st->u_dev, B);
+  if (const size_t parts = (size_t)B * sample_chunks(V)) {
+    A(&st->sample.z, parts * SAMPLE_CHUNK_CAND); A(&st->sample.idx, parts * SAMPLE_CHUNK_CAND);
+    A(&st->sample.max_mass, parts * 2); A(&st->sample.count, parts);
+  }
   A(&st->x, (size_t)Bp * d);
   if (st->bf16) {
     st->prefill_mode = env_int("SKD_PREFILL_BATCHED", 1) != 0 ? 1 : 0;
@@ -1170,7 +1175,7 @@ extern "C" int skd_logits_sample(skd_state *st, const float *u, float temperatur
   }
   float *lg = (logits_out && c.io_on_device) ? logits_out : st->logits_dev;
   SKDCHECK(head_logits(st, lg, false, nullptr));
-  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev, c.io_on_device ? tokens_out : st->pin ? st->pin->tok_out : nullptr) < 0) return SKD_ERR_SHAPE; }
+  { ProfScope ps_(st, SKD_PROF_ARGMAX); if (sample_top_p(s, lg, B, V, temperature, top_p, u_dev, st->argmax_dev, c.io_on_device ? tokens_out : st->pin ? st->pin->tok_out : nullptr, st->sample) < 0) return SKD_ERR_SHAPE; }
   HIPCHECK(hipGetLastError());
   st->have_argmax = true;  // skd_decode_step(.., NULL) continues from the sampled tokens
   if (c.io_on_device) return SKD_OK;  // the sampler has written tokens_out

@@ -70,10 +70,20 @@ void f32_kv_write(hipStream_t s, const float *qkv, float *pool, const int32_t *b
 void f32_attention(hipStream_t s, const float *qkv, const float *pool, const int32_t *bt_layer, const int32_t *start,
                    int t, float *o, float *scores, int score_stride, int B, KvGeom g);
 void f32_argmax(hipStream_t s, const float *logits, int32_t *tokens, int B, int V);
+// Candidates of the sampling head's first pass, per row and chunk of the vocabulary; z null: single pass.
+constexpr int SAMPLE_CHUNK_CAND = 512;
+struct SampleScratch {
+  float *z;         // [B][chunks][SAMPLE_CHUNK_CAND] logit / temperature
+  int32_t *idx;     // the same, token
+  float *max_mass;  // [B][chunks][2]
+  int32_t *count;   // [B][chunks]
+  int chunks;       // set by sample_top_p
+};
+int sample_chunks(int V);
 // temperature + top-p sampling from fp32 logits [B][V] with one uniform number per row; -1 if V > 65536.
 // tokens2: second destination, or null
 int sample_top_p(hipStream_t s, const float *logits, int B, int V, float temperature, float top_p, const float *u,
-                 int32_t *tokens, int32_t *tokens2);
+                 int32_t *tokens, int32_t *tokens2, SampleScratch sc);
 
 // ---------------------------------------------------------------- bf16 production path
 // Weights [N][K] are "fragment-major": 16-row x 32-column fragments stored as
