@@ -276,6 +276,10 @@ GemmPlan plan_direct(int N, int B_pad) {  // whole K inside the workgroup
 GemmPlan plan_split(int N, int K, int B_pad) {  // partial sums, reduced by the LayerNorm kernel
   GemmPlan p;
   p.waves = plan_waves(B_pad);
+  // A wave of these short K ranges has 2 to 16 k-steps: two per buffer with one batch tile (1.3B model, 16 rows, 8 steps:
+  // 7172 -> 7029 us; 6.7B widths, 8 rows: 921 -> 918); four put too much in flight (7118), and wider batches have no
+  // registers to gain from it
+  if (B_pad <= 16) p.U = 2;
   const int Kf = K / 32;
   // tile rows per workgroup: enough that the activation re-reads (B_pad / (16 R) of the weight bytes) stay at
   // half the weight stream; more rows than that only force a deeper split, whose partials the reducer pays for
