@@ -177,8 +177,10 @@ def run_generation(skd, torch, shape, w, B, P, T, n_min, n_max, mask, steps, war
             t = {k: a.elapsed_time(b) for k, a, b in pairs}
             rep_ms.append(sum(t[k] for k in ks))
             first_ms.append(t[0])
-    # projections of the prompt pass: 2 flops per weight and real prompt token, all L layers (attention not counted)
-    prefill_flop = 2.0 * float(P * B - start.sum()) * shape.L * (4 * shape.d * shape.d + 2 * shape.d * shape.f)
+    # projections of the prompt pass: 2 flops per weight and real prompt token, all L layers, of the top one only k and v
+    # (the rest of it runs for the last positions; attention not counted)
+    prefill_flop = 2.0 * float(P * B - start.sum()) * ((shape.L - 1) * (4 * shape.d * shape.d + 2 * shape.d * shape.f) +
+                                                       2 * shape.d * shape.d)
     out = {"rep_ms": rep_ms, "first_step_ms": first_ms, "prefill_s": prefill_s, "ks": ks,
            "prefill_projection_pflops": prefill_flop / prefill_s / 1e15,
            "layers": [layers[k] for k in ks], "sum_len": [sum_len[k] for k in ks],

@@ -165,7 +165,7 @@ int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epilogue, int R);
 // The same shape checks without a launch (only N, K, B_pad, G, split and rows of `a` are read): groups or -1.
 int bf16_gemm_check(const GemmArgs &a, int epilogue, int R, int U, int waves);
 int bf16_gemm_groups(int N, int R);
-// Decode projections with B_pad = 128 on the wave-specialised kernel (weight-streaming waves + activation-loading
+// Decode projections with B_pad = 96 or 128 on the wave-specialised kernel (weight-streaming waves + activation-loading
 // waves); (K / 32 / split) must be a multiple of 4.  Returns the row groups launched, or -1 (nothing launched) for
 // shapes it does not handle; bf16_gemm_ws_check answers the same without launching.
 int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epilogue, int R);
