@@ -5,9 +5,19 @@
 
 namespace skd {
 
-__device__ inline float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+__device__ inline float row_max_f(float v) {  // over each row of 16 lanes, the same value in every lane of the row
+#define SKD_ROR(n) v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true)))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
   return v;
+}
+__device__ inline float wave_max(float v) {
+  const int i = __builtin_bit_cast(int, row_max_f(v));
+  auto row = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, l)); };
+  return fmaxf(fmaxf(row(0), row(16)), fmaxf(row(32), row(48)));
 }
 // sum over a 256-thread workgroup; `sh` holds >= 4 floats; result to all threads
 __device__ inline float block_sum(float v, float *sh) {
@@ -141,6 +151,7 @@ __global__ void k_f32_argmax(const float *logits, int32_t *tokens, int V) {
 // Every sum is taken in a fixed order, so a given (logits, u) always yields the same token.
 constexpr int SAMPLE_C = 64;
 constexpr int SAMPLE_CAND = 4096;  // candidates that four waves finish, 16 per lane
+constexpr int SAMPLE_MID = 1024;   // tokens between the bounds of the threshold that one wave searches, 16 per lane
 
 struct SampleExchange {  // LDS of the finishing waves
   float sums[2][4];      // one set per round in turn
@@ -250,63 +261,130 @@ __device__ __forceinline__ void sample_rest(const float *cand_p, const int *cand
 
 // First pass over a large vocabulary, spread over the chip: a workgroup takes SAMPLE_CHUNK tokens of a row, relative to
 // their own maximum (the row's is not known yet): the chunk's maximum and mass, and, in index order, the tokens at or
-// above 2^-10 of its maximum, a superset of those at or above 2^-10 of the row's.  A factor of 0.99 covers the rounding
-// of expf.  One workgroup per row read and exponentiated 200 KB on one of 256 CUs: 50272 tokens, 32 rows, 36 us for
-// everything; 24 us for both kernels.
+// above the lowest of four bounds that no more than sc.cap of them reach (with one bound for all, 2^-10, any chunk with
+// more than 512 tokens above it sent its row back to a single workgroup).  A factor of 0.99 covers the rounding of expf.
+// One workgroup per row read and exponentiated 200 KB on one of 256 CUs: 50272 tokens, 32 rows, 46 us for everything;
+// 18 us for both kernels.
 constexpr int SAMPLE_CHUNK = 4096;
+constexpr int SAMPLE_BOUNDS = 4;
+// 2^-first, 2^-(first + 3), .. of the chunk's maximum; first = 4 or, for nuclei that reach deep (top_p above 0.97), 10
+__device__ inline float sample_bound(int first, int j) { return __uint_as_float((127u - (first + 3u * j)) << 23); }
+// Sums over each row of 16 lanes, the same value in every lane of the row (the pairs that are added are the same seen
+// from each lane, so the float result is too).
+__device__ inline int row_sum_i(int v) {
+#define SKD_ROR(n) v += __builtin_amdgcn_mov_dpp(v, 0x120 + n, 0xF, 0xF, true)
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  return v;
+}
+__device__ inline int wave_sum_i(int v) {  // the same value in every lane, as wave_sum_f
+  v = row_sum_i(v);
+  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) + (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+__device__ inline float row_sum_f(float v) {
+#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  return v;
+}
 
-__global__ __launch_bounds__(256) void k_sample_chunk(const float *logits, int V, float inv_temp, SampleScratch sc) {
-  __shared__ float sh[4];
-  __shared__ int wcount[4];
-  const int b = blockIdx.y, ch = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int base = ch * SAMPLE_CHUNK + wave * (SAMPLE_CHUNK / 4) + lane;
+template <int NW>  // waves
+__global__ __launch_bounds__(NW * 64) void k_sample_chunk(const float *logits, int V, float inv_temp, SampleScratch sc) {
+  constexpr int NR = SAMPLE_CHUNK / (64 * NW);  // tokens per lane
+  __shared__ float sh[2][NW];
+  __shared__ int wcount[NW][SAMPLE_BOUNDS];
+  const int b = blockIdx.y, ch = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int base = ch * SAMPLE_CHUNK + wave * (SAMPLE_CHUNK / NW) + lane;
   const float *zr = logits + (long)b * V;
-  float z[16], mx = -3.0e38f;
+  float z[NR], mx = -3.0e38f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = base + 64 * i < V ? zr[base + 64 * i] * inv_temp : -3.0e38f;  // sentinel: no such token
+  for (int i = 0; i < NR; ++i) z[i] = base + 64 * i < V ? zr[base + 64 * i] * inv_temp : -3.0e38f;  // sentinel: no such token
 #pragma unroll
-  for (int i = 0; i < 16; ++i) mx = fmaxf(mx, z[i]);
+  for (int i = 0; i < NR; ++i) mx = fmaxf(mx, z[i]);
   mx = wave_max(mx);
-  if (lane == 0) sh[wave] = mx;
+  if (lane == 0) sh[0][wave] = mx;
   __syncthreads();
-  mx = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
-  __syncthreads();
-  const float bound = 0.99f * 0x1p-10f;
-  float mass = 0;
-  int cnt = 0;
-  unsigned keep = 0;  // bit i: this lane's token of row i
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const float p = z[i] > -1.0e38f ? expf(z[i] - mx) : 0.f;
-    mass += p;
-    keep |= (p >= bound ? 1u : 0u) << i;
+  for (int w = 0; w < NW; ++w) mx = fmaxf(mx, sh[0][w]);
+  float p[NR], mass = 0;
+  int cnt[SAMPLE_BOUNDS] = {};
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    p[i] = z[i] > -1.0e38f ? expf(z[i] - mx) : 0.f;
+    mass += p[i];
+#pragma unroll
+    for (int j = 0; j < SAMPLE_BOUNDS; ++j) cnt[j] += p[i] >= 0.99f * sample_bound(sc.first, j) ? 1 : 0;
   }
-  cnt = __popc(keep);
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
   mass = wave_sum_f(mass);
-  if (lane == 0) {
-    sh[wave] = mass;
-    wcount[wave] = cnt;
+  if (lane == 0) sh[1][wave] = mass;
+#pragma unroll
+  for (int j = 0; j < SAMPLE_BOUNDS; ++j) {
+    const int n = wave_sum_i(cnt[j]);
+    if (lane == 0) wcount[wave][j] = n;
   }
   __syncthreads();
-  const long part = (long)b * sc.chunks + ch;
-  int pos = 0;
-  for (int w = 0; w < wave; ++w) pos += wcount[w];
-  if (threadIdx.x == 0) {
-    sc.max_mass[2 * part] = mx;
-    sc.max_mass[2 * part + 1] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    sc.count[part] = wcount[0] + wcount[1] + wcount[2] + wcount[3];
-  }
+  int total = sc.cap + 1, pos = 0;  // none of the bounds: too many tokens close to the maximum
+  float bound = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const bool c = (keep >> i) & 1;
+  for (int j = 0; j < SAMPLE_BOUNDS; ++j) {
+    int n = 0, before = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int c = wcount[w][j];
+      before += w < wave ? c : 0;
+      n += c;
+    }
+    if (n <= sc.cap) {
+      total = n;
+      pos = before;
+      bound = sample_bound(sc.first, j);
+    }
+  }
+  const long part = (long)b * sc.chunks + ch;
+  if (threadIdx.x == 0) {
+    mass = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mass += sh[1][w];
+    sc.max_mass[3 * part] = mx;
+    sc.max_mass[3 * part + 1] = mass;
+    sc.max_mass[3 * part + 2] = bound;
+    sc.count[part] = total;
+  }
+  if (total > sc.cap) return;
+  float *zc = sc.z + part * sc.cap;
+  int32_t *ic = sc.idx + part * sc.cap;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const bool c = p[i] >= 0.99f * bound;
     const unsigned long long m = __ballot(c);
-    const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
-    if (c && k < SAMPLE_CHUNK_CAND) {  // more: the count says so, and the second pass takes the whole row
-      sc.z[part * SAMPLE_CHUNK_CAND + k] = z[i];
-      sc.idx[part * SAMPLE_CHUNK_CAND + k] = base + 64 * i;
+    if (m == 0) continue;
+    if (c) {
+      const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
+      zc[k] = z[i];
+      ic[k] = base + 64 * i;
     }
     pos += __popcll(m);
+  }
+}
+
+// What is known of the threshold's bit pattern: lower <= threshold < upper, above = mass of the tokens at or above upper.
+struct SampleBounds {
+  unsigned lower, upper;
+  float above;
+};
+// One step of the search: the trial value `cand` of a prefix T, given the mass at or above it.
+__device__ inline void sample_decide(SampleBounds &s, unsigned &T, unsigned cand, float m, float target) {
+  if (__builtin_amdgcn_readfirstlane(m >= target)) {  // uniform: every thread has the same sum
+    T = s.lower = cand;
+  } else {
+    s.upper = cand;
+    s.above = m;
   }
 }
 
@@ -314,201 +392,284 @@ __global__ __launch_bounds__(256) void k_sample_chunk(const float *logits, int V
 template <int RC>
 __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int V, float inv_temp, float top_p,
                                                        const float *u, int32_t *tokens, int32_t *tokens2, SampleScratch sc) {
-  __shared__ float sh[16], wmass[16], mass_at[3][16];
-  __shared__ int wcount[16];
+  __shared__ float sh[16], wmass[16], mass_at[3][16], sums[2][16];
+  __shared__ int wcount[2][16];
   __shared__ float cand_p[SAMPLE_CAND];  // candidates of the short cut, ascending token index
   __shared__ int cand_i[SAMPLE_CAND];
   __shared__ SampleExchange ex;
   __shared__ float rows[RC * 64];  // the rows of the one wave that walks its range
   __shared__ int last_in, hit_tok;
+  __shared__ unsigned threshold;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int R = (V + 1023) / 1024, base = wave * R * 64 + lane;
   const float *z = logits + (long)b * V;
+  SampleBounds s{1u, 1u << 30, 0.f};  // upper 2: p <= 1
+  // (1 - top_p) total / (2 V): all tokens below it together hold less than half of the mass that may be left out (the
+  // other half covers rounding, except where top_p is so close to 1 that the bound keeps everything anyway)
+  auto left_out = [&](float total) { return max(__float_as_uint((1.0f - top_p) * total / (2.0f * (float)V)), 1u); };  // 0 = absent or underflowed
+  float mx = -3.0e38f, target = 0.f;
+  bool known = false;  // (uniform) mx, target and s from the first pass
   if constexpr (RC <= 52) if (sc.chunks) {  // the first pass's candidates, if they hold the target mass
-    __shared__ float hm[16], hs[16];
-    __shared__ int hoff[17], kw[4][16];
-    if (tid < 16) {
-      const long part = (long)b * sc.chunks + tid;
-      const bool have = tid < sc.chunks;
-      hm[tid] = have ? sc.max_mass[2 * part] : -3.0e38f;
-      hs[tid] = have ? sc.max_mass[2 * part + 1] : 0.f;
-      int n = have ? sc.count[part] : 0;
-      if (n > SAMPLE_CHUNK_CAND) n = SAMPLE_CAND + 1;  // does not fit: none of this
-      for (int off = 1; off < 16; off <<= 1) {
-        const int t = __shfl_up(n, off);
-        if (lane >= off) n += t;
-      }
-      hoff[tid + 1] = n;
-      if (tid == 0) hoff[0] = 0;
+    constexpr int NK = (SAMPLE_CHUNK_CAND + 1023) / 1024;
+    __shared__ int kw[NK][16];
+    // lane 16 r + c of every wave holds chunk c: no barrier
+    const int c16 = lane & 15;
+    const bool have = c16 < sc.chunks;
+    const long part = (long)b * sc.chunks + c16;
+    const float cm = have ? sc.max_mass[3 * part] : -3.0e38f, cs = have ? sc.max_mass[3 * part + 1] : 0.f, cb = have ? sc.max_mass[3 * part + 2] : 0.f;
+    int n = have ? sc.count[part] : 0;
+    if (n > sc.cap) n = SAMPLE_CHUNK_CAND + 1;  // not listed: none of this
+    for (int off = 1; off < 16; off <<= 1) {
+      const int t = __shfl_up(n, off, 16);
+      if (c16 >= off) n += t;
     }
-    __syncthreads();
-    const int N = __builtin_amdgcn_readfirstlane(hoff[16]);
-    if (N <= SAMPLE_CAND) {
-      float M = hm[0], total = 0;
-      for (int c = 1; c < 16; ++c) M = fmaxf(M, hm[c]);
-      for (int c = 0; c < sc.chunks; ++c) total += hs[c] * expf(hm[c] - M);
-      const float target = top_p * total;
-      float pc[4], q5 = 0, q10 = 0;
-      int ic[4];
+    const int N = __builtin_amdgcn_readlane(n, 15);
+    const float M = row_max_f(cm), e = expf(cm - M), total = row_sum_f(cs * e);
+    float beta = row_max_f(cb * e);
+    mx = M;
+    target = top_p * total;
+    known = true;
+    s.lower = left_out(total);
+    if (N <= SAMPLE_CHUNK_CAND) {
+      // every token of the row at or above beta (and 1 % for rounding) is among the candidates
+      beta = fmaxf(1.01f * beta, 0x1p-40f);
+      const float bound[3] = {fmaxf(0x1p-5f, beta), fmaxf(0x1p-10f, beta), beta};
+      float pc[NK], q[3] = {};
+      int ic[NK];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < NK; ++k) {
         const int i = tid + 1024 * k;
         pc[k] = 0;
         ic[k] = 0;
         if (i < N) {
-          int c = 0;
-          while (hoff[c + 1] <= i) ++c;
-          const long at = ((long)b * sc.chunks + c) * SAMPLE_CHUNK_CAND + (i - hoff[c]);
+          int c = 0, first = 0;
+#pragma unroll
+          for (int j = 1; j < 16; ++j) {  // the chunk whose candidates start at or before i (the last of equal starts: empty ones)
+            const int start = __builtin_amdgcn_readlane(n, j - 1);
+            if (i >= start) { c = j; first = start; }
+          }
+          const long at = ((long)b * sc.chunks + c) * sc.cap + (i - first);
           pc[k] = expf(sc.z[at] - M);
           ic[k] = sc.idx[at];
         }
-        const bool in = pc[k] >= 0x1p-10f;
-        if (!in) pc[k] = 0;
-        q10 += pc[k];
-        q5 += pc[k] >= 0x1p-5f ? pc[k] : 0.f;
-        const unsigned long long m = __ballot(in);
-        if (lane == 0) kw[k][wave] = __popcll(m);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) q[j] += pc[k] >= bound[j] ? pc[k] : 0.f;
       }
-      q10 = wave_sum_f(q10);
-      q5 = wave_sum_f(q5);
-      if (lane == 0) {
-        mass_at[1][wave] = q5;
-        mass_at[2][wave] = q10;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        q[j] = wave_sum_f(q[j]);
+        if (lane == 0) mass_at[j][wave] = q[j];
       }
       __syncthreads();
-      q5 = q10 = 0;
-      for (int w = 0; w < 16; ++w) {
-        q5 += mass_at[1][w];
-        q10 += mass_at[2][w];
-      }
-      if (__builtin_amdgcn_readfirstlane(q10 >= target)) {  // uniform: every thread has the same sums
-        int C = 0;
+      // the highest bound whose upper set has the target mass, and the next one above it, which has not
+      bool enough = false;
+      s.upper = 1u << 30;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          int at = C;
-          for (int w = 0; w < 16; ++w) {
-            if (w == wave) at = C;
-            C += kw[k][w];
-          }
-          const bool in = pc[k] > 0.f;
-          const unsigned long long m = __ballot(in);
-          if (in) {
-            const int j = at + __popcll(m & ((1ull << lane) - 1ull));
+      for (int j = 0; j < 3; ++j) {
+        const float sum = row_sum_f(mass_at[j][lane & 15]);
+        if (enough) continue;
+        if (sum >= target) {
+          enough = true;
+          s.lower = __float_as_uint(bound[j]);
+        } else {
+          s.upper = __float_as_uint(bound[j]);
+          s.above = sum;
+        }
+      }
+      if (__builtin_amdgcn_readfirstlane(enough)) {  // uniform: every thread has the same sums
+        unsigned long long in[NK];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+          in[k] = __ballot(__float_as_uint(pc[k]) >= s.lower);
+          if (lane == 0) kw[k][wave] = __popcll(in[k]);
+        }
+        __syncthreads();
+        int C = 0, at[NK];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+          const int c = kw[k][lane & 15];
+          at[k] = C + row_sum_i((lane & 15) < wave ? c : 0);
+          C += row_sum_i(c);
+        }
+        C = __builtin_amdgcn_readfirstlane(C);
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+          if (__float_as_uint(pc[k]) >= s.lower) {
+            const int j = at[k] + __popcll(in[k] & ((1ull << lane) - 1ull));
             cand_p[j] = pc[k];
             cand_i[j] = ic[k];
           }
-        }
         __syncthreads();
-        C = __builtin_amdgcn_readfirstlane(C);
-        const unsigned lower = q5 >= target ? (127u - 5u) << 23 : (127u - 10u) << 23, upper = q5 >= target ? 1u << 30 : (127u - 5u) << 23;
-        sample_rest(cand_p, cand_i, C, lower, upper, target, u, b, tokens, tokens2, ex);
+        sample_rest(cand_p, cand_i, C, __builtin_amdgcn_readfirstlane(s.lower), __builtin_amdgcn_readfirstlane(s.upper), target, u, b, tokens, tokens2, ex);
         return;
       }
     }
-    __syncthreads();  // mass_at is written again below
   }
   float p[RC];
-  float mx = -3.0e38f;
 #pragma unroll
-  for (int i = 0; i < RC; ++i) {
-    p[i] = (i < R && base + 64 * i < V) ? z[base + 64 * i] * inv_temp : -3.0e38f;  // sentinel: no such token
-    mx = fmaxf(mx, p[i]);
-  }
-  mx = wave_max(mx);
-  if (lane == 0) sh[wave] = mx;
+  for (int i = 0; i < RC; ++i) p[i] = (i < R && base + 64 * i < V) ? z[base + 64 * i] * inv_temp : -3.0e38f;  // sentinel: no such token
   if (tid == 0) { last_in = -1; hit_tok = -1; }
-  __syncthreads();
-  mx = sh[0];
-  for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sh[w]);
-  // Masses of all tokens and of those at or above 2^-5 and 2^-10 of the most likely one, in one pass.
-  constexpr int NQ = 3;
-  float q[NQ] = {};
+  if (known) {
 #pragma unroll
-  for (int i = 0; i < RC; ++i) {
-    p[i] = p[i] > -1.0e38f ? expf(p[i] - mx) : 0.f;
-    q[0] += p[i];
+    for (int i = 0; i < RC; ++i) p[i] = p[i] > -1.0e38f ? expf(p[i] - mx) : 0.f;
+  } else {
 #pragma unroll
-    for (int j = 1; j < NQ; ++j) q[j] += p[i] >= __uint_as_float((127u - 5u * j) << 23) ? p[i] : 0.f;
+    for (int i = 0; i < RC; ++i) mx = fmaxf(mx, p[i]);
+    mx = wave_max(mx);
+    if (lane == 0) sh[wave] = mx;
+    __syncthreads();
+    mx = sh[0];
+    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sh[w]);
+    // Masses of all tokens and of those at or above 2^-5 and 2^-10 of the most likely one, in one pass.
+    constexpr int NQ = 3;
+    float q[NQ] = {};
+#pragma unroll
+    for (int i = 0; i < RC; ++i) {
+      p[i] = p[i] > -1.0e38f ? expf(p[i] - mx) : 0.f;
+      q[0] += p[i];
+#pragma unroll
+      for (int j = 1; j < NQ; ++j) q[j] += p[i] >= __uint_as_float((127u - 5u * j) << 23) ? p[i] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      q[j] = wave_sum_f(q[j]);
+      if (lane == 0) mass_at[j][wave] = q[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      q[j] = row_sum_f(mass_at[j][lane & 15]);  // added up as the search adds: with top_p 1, target is a sum it can reach
+    }
+    target = top_p * q[0];
+    // the threshold lies at or above the larger of the two bounds whose upper set already has the target mass
+    s.lower = left_out(q[0]);
+#pragma unroll
+    for (int j = NQ - 1; j > 0; --j)
+      if (q[j] >= target) s.lower = (127u - 5u * j) << 23;
+#pragma unroll
+    for (int j = 1; j < NQ; ++j)
+      if (q[j] < target) { s.upper = (127u - 5u * j) << 23; s.above = q[j]; }
   }
-#pragma unroll
-  for (int j = 0; j < NQ; ++j) {
-    q[j] = wave_sum_f(q[j]);
-    if (lane == 0) mass_at[j][wave] = q[j];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < NQ; ++j) {
-    q[j] = mass_at[j][0];
-    for (int w = 1; w < 16; ++w) q[j] += mass_at[j][w];
-  }
-  const float total = q[0], target = top_p * total;
+  s.lower = __builtin_amdgcn_readfirstlane(s.lower);
+  s.upper = __builtin_amdgcn_readfirstlane(s.upper);
 
-  // Short cut.  The threshold lies at or above the larger of the two bounds whose upper set already has the target
-  // mass; failing that, at or above (1 - top_p) total / (2 V): all tokens below it together hold less than half of the
-  // mass that may be left out (the other half covers rounding, except where top_p is so close to 1 that the bound keeps
-  // everything anyway).  The tokens at or above the bound are compacted in index order; if they are at most 4096 (at the
-  // paper's temperature 0.3 a few dozen to a few hundred of 50272), one wave (up to 1024) or four finish the row: no
-  // more passes over the vocabulary, and sums that need no workgroup barrier, or one of four waves.
-  // 50272 tokens, 32 rows: 46 us with eight rounds over the whole row before the compaction, 36 us now.
-  unsigned lower = max(__float_as_uint((1.0f - top_p) * total / (2.0f * (float)V)), 1u);  // 0 = absent or underflowed
-  unsigned upper = 1u << 30;  // 2: p <= 1.  Rounds of the search whose trial lies outside [lower, upper) need no sum
-#pragma unroll
-  for (int j = NQ - 1; j > 0; --j) {
-    if (q[j] >= target) lower = (127u - 5u * j) << 23;
-  }
-#pragma unroll
-  for (int j = 1; j < NQ; ++j)
-    if (q[j] < target) upper = (127u - 5u * j) << 23;
-  {
-    int cnt = 0;  // per lane first (a ballot per row here would be kept for the compaction below: 2 SGPRs per row)
-    const unsigned below = lower - 1u;  // lower >= 1
+  // The threshold is found bit by bit on the float bit pattern, from the top; trials outside [lower, upper) need no sum.
+  // Before the first round, after the exponent and after three and six more bits the tokens that still matter are counted.
+  // If at most 4096 are at or above `lower` they are compacted in index order and one wave (up to 1024) or four finish the
+  // row: no more passes over the vocabulary, and sums that need no workgroup barrier, or one of four waves.  Else, if at
+  // most 1024 lie in [lower, upper), one wave searches those alone (the mass at or above `upper` is known).  With the
+  // first count only, a nucleus of more than the bounds above hold took 30 rounds over the whole row: 50272 tokens, 32
+  // rows, top_p 0.95, us of this kernel: logits of standard deviation 4.8 (a nucleus of some hundreds) 76 -> 14, of 1.6
+  // 78 -> 57; at temperature 0.3, top_p 0.7 (the paper's setting) and a deviation of 1.6 11.8 -> 10.3.
+  unsigned T = 0;
+  int set = 0;
+  auto wg_sum = [&](float m) {  // the same value in every thread, one barrier: a set is written again two sums later
+    m = wave_sum_f(m);
+    set ^= 1;
+    if (lane == 0) sums[set][wave] = m;
+    __syncthreads();
+    return row_sum_f(sums[set][lane & 15]);
+  };
+  int bit = 29, few = -1;  // few: candidates, if they are few enough to be finished by one or four waves
+#pragma unroll 1
+  for (int stage = 0;; ++stage) {
+    int cnt = 0, mid = 0;  // per lane first (a ballot per row here would be kept for the compaction below: 2 SGPRs per row)
+    const unsigned below = s.lower - 1u;  // lower >= 1
 #pragma unroll
     for (int i = 0; i < RC; ++i) cnt += (__float_as_uint(p[i]) > below) ? 1 : 0;  // non-negative floats order like their bits
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-    if (lane == 0) wcount[wave] = cnt;
-    __syncthreads();
-    int C = 0, wbase = 0;
-    for (int w = 0; w < 16; ++w) {
-      if (w < wave) wbase += wcount[w];
-      C += wcount[w];
+    if (stage) {
+#pragma unroll
+      for (int i = 0; i < RC; ++i) mid += (__float_as_uint(p[i]) >= s.upper) ? 1 : 0;
+      mid = cnt - mid;
+      __syncthreads();  // wcount has been read
     }
+    const int lane_mid = mid;
+    cnt = wave_sum_i(cnt);
+    mid = wave_sum_i(mid);
+    if (lane == 0) {
+      wcount[0][wave] = cnt;
+      wcount[1][wave] = mid;
+    }
+    __syncthreads();
     // uniform over the workgroup, and said so: as a divergent branch it would keep the 52-64 probabilities of the
     // other path alive in registers next to this path's candidates
-    C = __builtin_amdgcn_readfirstlane(C);
-    wbase = __builtin_amdgcn_readfirstlane(wbase);
+    const int c0 = wcount[0][lane & 15], c1 = wcount[1][lane & 15];
+    const int C = __builtin_amdgcn_readfirstlane(row_sum_i(c0)), n = __builtin_amdgcn_readfirstlane(row_sum_i(c1));
+    const int wbase = __builtin_amdgcn_readfirstlane(row_sum_i((lane & 15) < wave ? c0 : 0)), nbase = row_sum_i((lane & 15) < wave ? c1 : 0);
     if (C <= SAMPLE_CAND) {
-      int pos = wbase;
+      int pos = wbase, first = base;
+      asm volatile("" : "+v"(first));  // the rows' token indices are made here, not kept in registers from before the loop
 #pragma unroll
       for (int i = 0; i < RC; ++i) {
         // (the counting loop tests "> lower - 1", this one ">= lower": the same test, but the compiler recomputes it
         // here instead of keeping one lane mask per row from there)
-        const bool c = __float_as_uint(p[i]) >= lower;
+        const bool c = __float_as_uint(p[i]) >= s.lower;
         const unsigned long long m = __ballot(c);
         if (m) {  // most rows have none
           if (c) {
             const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
             cand_p[k] = p[i];
-            cand_i[k] = base + 64 * i;
+            cand_i[k] = first + 64 * i;
           }
           pos += __popcll(m);
         }
         __builtin_amdgcn_sched_barrier(0);  // row by row: hoisted, the rows' lane masks would need 2 SGPRs each
       }
-      __syncthreads();
-      sample_rest(cand_p, cand_i, C, lower, upper, target, u, b, tokens, tokens2, ex);
-      return;
+      few = C;
+      break;
     }
-  }
-  // Flat distributions: the whole workgroup searches over all tokens.
-  unsigned T = 0;
-  for (int bit = 30; bit >= 0; --bit) {
-    const unsigned cand = T | (1u << bit);
-    if (cand >= upper) continue;
-    if (cand <= lower) { T = cand; continue; }
-    float m = 0;
+    if (stage && n <= SAMPLE_MID) {
+      const float above = s.above;
+      float *val = cand_p;  // in any order that is the same every time: a lane's values side by side
+      int inc = lane_mid;
+      for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(inc, off);
+        if (lane >= off) inc += t;
+      }
+      int pos = nbase + inc - lane_mid;
 #pragma unroll
-    for (int i = 0; i < RC; ++i) m += (__float_as_uint(p[i]) >= cand) ? p[i] : 0.f;  // absent tokens hold zeros
-    if (block_sum(m, sh) >= target) T = cand;  // uniform decision: every thread sees the same sum
+      for (int i = 0; i < RC; ++i) {
+        const unsigned v = __float_as_uint(p[i]);
+        if (v >= s.lower && v < s.upper) val[pos++] = p[i];
+      }
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(wave) == 0) {
+        float v[SAMPLE_MID / 64];
+#pragma unroll
+        for (int k = 0; k < SAMPLE_MID / 64; ++k) v[k] = lane + 64 * k < n ? val[lane + 64 * k] : 0.f;
+#pragma unroll 1
+        for (; bit >= 0; --bit) {
+          const unsigned cand = T | (1u << bit);
+          if (cand >= s.upper) continue;
+          if (cand <= s.lower) { T = cand; continue; }
+          float m = 0;
+#pragma unroll
+          for (int k = 0; k < SAMPLE_MID / 64; ++k) m += (__float_as_uint(v[k]) >= cand) ? v[k] : 0.f;
+          sample_decide(s, T, cand, above + wave_sum_f(m), target);
+        }
+        if (lane == 0) threshold = T;
+      }
+      __syncthreads();
+      T = threshold;
+      break;
+    }
+    const int stop = stage < 3 ? 23 - 3 * stage : 0;
+#pragma unroll 1
+    for (; bit >= stop; --bit) {
+      const unsigned cand = T | (1u << bit);
+      if (cand >= s.upper) continue;
+      if (cand <= s.lower) { T = cand; continue; }
+      float m = 0;
+#pragma unroll
+      for (int i = 0; i < RC; ++i) m += (__float_as_uint(p[i]) >= cand) ? p[i] : 0.f;  // absent tokens hold zeros
+      sample_decide(s, T, cand, wg_sum(m), target);
+    }
+    if (bit < 0) break;
+  }
+  if (few >= 0) {
+    __syncthreads();
+    sample_rest(cand_p, cand_i, few, s.lower, s.upper, target, u, b, tokens, tokens2, ex);
+    return;
   }
   // nucleus: zero everything else; mass per wave (each wave owns a contiguous index range)
   float loc = 0;
@@ -520,7 +681,6 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
     if (p[i] > 0.f) last = base + 64 * i;
   }
   loc = wave_sum_f(loc);
-  __syncthreads();  // sh is free again
   if (lane == 0) wmass[wave] = loc;
   if (last >= 0) atomicMax(&last_in, last);
   __syncthreads();
@@ -534,24 +694,30 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   const bool mine = before <= goal && before + wmass[wave] > goal;  // at most one wave: the prefix sums are monotone
   if (mine) {
 #pragma unroll
-    for (int i = 0; i < RC; ++i) rows[i * 64 + lane] = p[i];  // own lane's column: no barrier needed
-    float run = before;
-    int tok = -1;
-    for (int i = 0; i < R && tok < 0; ++i) {
-      {
-        const float pi = rows[i * 64 + lane];
-        float inc = pi;  // inclusive prefix over the lanes of this row
-        for (int off = 1; off < 64; off <<= 1) {
-          const float t = __shfl_up(inc, off);
-          if (lane >= off) inc += t;
-        }
-        const float row = __shfl(inc, 63);
-        if (run + row > goal) {
-          const unsigned long long over = __ballot(pi > 0.f && run + inc > goal);
-          if (over) tok = wave * R * 64 + 64 * i + (int)__builtin_ctzll(over);
-        }
-        run += row;
+    for (int i = 0; i < RC; ++i) rows[i * 64 + lane] = p[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // lane i adds row i up, from its own column on (no bank conflicts); the first row that takes the running sum past the
+    // goal, then the first token of that row
+    float row = 0;
+    if (lane < R)
+      for (int k = 0; k < 64; ++k) row += rows[lane * 64 + ((lane + k) & 63)];
+    auto prefix = [&](float v) {  // inclusive, over the lanes
+      for (int off = 1; off < 64; off <<= 1) {
+        const float t = __shfl_up(v, off);
+        if (lane >= off) v += t;
       }
+      return v;
+    };
+    const float run = before + prefix(row);
+    int tok = -1;
+    const unsigned long long past = __ballot(row > 0.f && run > goal);
+    if (past) {
+      const int i = (int)__builtin_ctzll(past);
+      const float start = i ? __shfl(run, i - 1) : before, pi = rows[i * 64 + lane];
+      const float in = start + prefix(pi);
+      const unsigned long long over = __ballot(pi > 0.f && in > goal), have = __ballot(pi > 0.f);
+      // rounding between the two summation orders: the row's last member
+      tok = wave * R * 64 + 64 * i + (over ? (int)__builtin_ctzll(over) : 63 - (int)__builtin_clzll(have));
     }
     if (tok < 0) {  // rounding between the two summation orders: the last member of this wave's range
       int wl = last;
@@ -577,8 +743,14 @@ int sample_top_p(hipStream_t s, const float *logits, int B, int V, float tempera
   if (V > 1024 * SAMPLE_C) return -1;
   const int R = (V + 1023) / 1024;
   const float it = 1.0f / temperature;
-  sc.chunks = sc.z ? sample_chunks(V) : 0;
-  if (sc.chunks) SKD_LAUNCH(k_sample_chunk, dim3(sc.chunks, B), dim3(256), 0, s, logits, V, it, sc);
+  // (top_p 1: the nucleus is all the tokens whose mass does not get lost in rounding, more than the first pass lists)
+  sc.chunks = sc.z && top_p < 1.0f ? sample_chunks(V) : 0;
+  sc.cap = sc.chunks ? SAMPLE_CHUNK_CAND / sc.chunks : 0;
+  sc.first = top_p > 0.97f ? 10 : 4;
+  // 8 waves per chunk while all of them fit the chip at once (32 waves on each of 256 CUs), else 4: 50272 tokens, 8, 32 and
+  // 128 rows, us: 6.6, 7.6, 16.1 with 8 waves, 9.7, 9.7, 15.3 with 4
+  if (sc.chunks && sc.chunks * B <= 1024) SKD_LAUNCH(k_sample_chunk<8>, dim3(sc.chunks, B), dim3(512), 0, s, logits, V, it, sc);
+  else if (sc.chunks) SKD_LAUNCH(k_sample_chunk<4>, dim3(sc.chunks, B), dim3(256), 0, s, logits, V, it, sc);
   if (R <= 16) SKD_LAUNCH(k_sample_top_p<16>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
   else if (R <= 32) SKD_LAUNCH(k_sample_top_p<32>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);
   else if (R <= 52) SKD_LAUNCH(k_sample_top_p<52>, dim3(B), dim3(1024), 0, s, logits, V, it, top_p, u, tokens, tokens2, sc);

@@ -695,8 +695,8 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
   auto A = [&](auto **p, size_t n) { if (rc == SKD_OK) rc = dev_alloc(st, p, n); };
   A(&st->tok_dev, B); A(&st->prompt_dev, (size_t)c.prompt_size * B); A(&st->start_dev, B); A(&st->order_dev, B); A(&st->argmax_dev, B); A(&st->u_dev, B);
   if (const size_t parts = (size_t)B * sample_chunks(V)) {
-    A(&st->sample.z, parts * SAMPLE_CHUNK_CAND); A(&st->sample.idx, parts * SAMPLE_CHUNK_CAND);
-    A(&st->sample.max_mass, parts * 2); A(&st->sample.count, parts);
+    A(&st->sample.z, (size_t)B * SAMPLE_CHUNK_CAND); A(&st->sample.idx, (size_t)B * SAMPLE_CHUNK_CAND);
+    A(&st->sample.max_mass, parts * 3); A(&st->sample.count, parts);
   }
   A(&st->x, (size_t)Bp * d);
   if (st->bf16) {

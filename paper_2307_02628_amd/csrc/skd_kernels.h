@@ -70,14 +70,15 @@ void f32_kv_write(hipStream_t s, const float *qkv, float *pool, const int32_t *b
 void f32_attention(hipStream_t s, const float *qkv, const float *pool, const int32_t *bt_layer, const int32_t *start,
                    int t, float *o, float *scores, int score_stride, int B, KvGeom g);
 void f32_argmax(hipStream_t s, const float *logits, int32_t *tokens, int B, int V);
-// Candidates of the sampling head's first pass, per row and chunk of the vocabulary; z null: single pass.
-constexpr int SAMPLE_CHUNK_CAND = 512;
+// Candidates of the sampling head's first pass, SAMPLE_CHUNK_CAND per row, shared out among the chunks of the vocabulary
+// (the chunks are few: cap >= 315); z null: single pass.
+constexpr int SAMPLE_CHUNK_CAND = 4096;
 struct SampleScratch {
-  float *z;         // [B][chunks][SAMPLE_CHUNK_CAND] logit / temperature
+  float *z;         // [B][chunks][cap] logit / temperature
   int32_t *idx;     // the same, token
-  float *max_mass;  // [B][chunks][2]
-  int32_t *count;   // [B][chunks]
-  int chunks;       // set by sample_top_p
+  float *max_mass;  // [B][chunks][3] maximum, mass, bound of the candidates relative to the maximum
+  int32_t *count;   // [B][chunks], above cap: none listed
+  int chunks, cap, first;  // set by sample_top_p
 };
 int sample_chunks(int V);
 // temperature + top-p sampling from fp32 logits [B][V] with one uniform number per row; -1 if V > 65536.
