@@ -1931,7 +1931,7 @@ void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int ro
   SKD_LAUNCH(k_prompt_map, dim3(B + 1), dim3(256), 0, s, pm, B, rows, rows_pad, P, start, order, first, seq);
 }
 
-__global__ __launch_bounds__(1024) void k_embed_ln_rows(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb,
+__global__ __launch_bounds__(1024) void k_embed_ln_rows_wide(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb,
                                                         const bf16_t *pos_emb, const float *g, const float *bt, float *x,
                                                         bf16_t *a_out, int B, int d, int V) {
   __shared__ float sh[32];
@@ -1965,7 +1965,7 @@ __global__ __launch_bounds__(1024) void k_embed_ln_rows(const int32_t *tokens, R
   ln_finish_row(v, gv, bv, d, row, a_out, sh);
 }
 
-__global__ __launch_bounds__(1024) void k_ln_rows(const float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
+__global__ __launch_bounds__(1024) void k_ln_rows_wide(const float *x, const float *g, const float *bt, bf16_t *a_out, int d) {
   __shared__ float sh[32];
   const int row = blockIdx.x, d4 = d >> 2;
   floatx4 v[LN_NC], gv[LN_NC], bv[LN_NC];
@@ -1981,33 +1981,32 @@ __global__ __launch_bounds__(1024) void k_ln_rows(const float *x, const float *g
   ln_finish_row(v, gv, bv, d, row, a_out, sh);
 }
 
-// LayerNorm of the prompt rows, one wave per row and four rows per workgroup: the row stays in registers (NC chunks of
-// 256 columns), the statistics need no barrier, and four to eight workgroups per CU keep the loads of one row running
-// under the arithmetic and stores of others.  A row's 64-byte pieces of the 16 x 32 tiles are stored directly: two
-// neighbouring rows share a 128-byte line and leave their workgroup at about the same time.  EMBED: the row is the sum
-// of its token and position embeddings (zero in the padding of a sequence's last tile) and is stored to x.
-// Memory-bound: 16384 rows of 4096, 402 MB: 80 us, 5.0 TB/s (113 with 16 rows per 1024-thread workgroup, one such
-// workgroup per CU and a barrier per 256 columns); with the embedding 235 us (one row per workgroup) -> 105.
+// LayerNorm of the prompt rows, one wave per row: the row stays in registers (NC chunks of 256 columns), and so do gain and
+// offset, requested with it; the statistics need no barrier.  A row's 64-byte pieces of the 16 x 32 tiles are stored
+// directly: two neighbouring rows share a 128-byte line and leave their workgroup at about the same time.  EMBED: the row
+// is the sum of its token and position embeddings (zero in the padding of a sequence's last tile) and is stored to x.
+// Memory-bound where the rows fill the chip, else one latency chain per row.  NC is exact: with the next of 4, 8 or 16 and
+// a test per chunk, and gain and offset loaded behind the statistics, 16384 rows of 2048 took 93 us instead of 63 (a
+// workgroup of 16 waves that put whole tiles together in LDS: 75), 64 rows of 4096 with the embedding 15 instead of 8.
 template <int NC, bool EMBED>
-__global__ __launch_bounds__(256) void k_ln_rows4(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb, const bf16_t *pos_emb,
-                                                  float *x, const float *g, const float *bt, bf16_t *a_out, int B, int d, int V) {
+__global__ __launch_bounds__(512) void k_ln_rows(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb, const bf16_t *pos_emb,
+                                                  float *x, const float *g, const float *bt, bf16_t *a_out, int B, int V) {
+  constexpr int d = 256 * NC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const long row = (long)blockIdx.x * 4 + wave;
-  const int nc = d >> 8;  // 256-column chunks
+  const long row = (long)blockIdx.x * (blockDim.x >> 6) + wave;
   floatx4 *xr = (floatx4 *)x + row * (d >> 2) + lane;
   uint2 *out = (uint2 *)(a_out + (row >> 4) * 16 * d) + (lane >> 3) * 128 + (row & 15) * 8 + (lane & 7);
-  floatx4 v[NC];
+  floatx4 v[NC], gv[NC], bv[NC];
   if constexpr (EMBED) {
     const int b = rm.seq[row];
     if (b < 0) return;
     const int pos = (int)row - rm.first_row[b];  // real position = position id
     if (pos >= rm.P - rm.start[b]) {
 #pragma unroll
-      for (int i = 0; i < NC; ++i)
-        if (i < nc) {
-          xr[64 * i] = floatx4{0.f, 0.f, 0.f, 0.f};
-          out[(long)i * 1024] = make_uint2(0, 0);
-        }
+      for (int i = 0; i < NC; ++i) {
+        xr[64 * i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        out[(long)i * 1024] = make_uint2(0, 0);
+      }
       return;
     }
     int tok = tokens[(long)(rm.start[b] + pos) * B + b];
@@ -2015,52 +2014,58 @@ __global__ __launch_bounds__(256) void k_ln_rows4(const int32_t *tokens, RowMap 
     const uint2 *te = (const uint2 *)(tok_emb + (long)tok * d) + lane, *pe = (const uint2 *)(pos_emb + (long)pos * d) + lane;
     uint2 tv[NC], pv[NC];
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (i < nc) {
-        tv[i] = te[64 * i];
-        pv[i] = pe[64 * i];
-      }
+    for (int i = 0; i < NC; ++i) {
+      tv[i] = te[64 * i];
+      pv[i] = pe[64 * i];
+    }
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (i < nc) {
-        v[i] = floatx4{bf2f(tv[i].x & 0xffffu) + bf2f(pv[i].x & 0xffffu), bf2f(tv[i].x >> 16) + bf2f(pv[i].x >> 16),
-                       bf2f(tv[i].y & 0xffffu) + bf2f(pv[i].y & 0xffffu), bf2f(tv[i].y >> 16) + bf2f(pv[i].y >> 16)};
-        xr[64 * i] = v[i];
-      }
+    for (int i = 0; i < NC; ++i) {
+      v[i] = floatx4{bf2f(tv[i].x & 0xffffu) + bf2f(pv[i].x & 0xffffu), bf2f(tv[i].x >> 16) + bf2f(pv[i].x >> 16),
+                     bf2f(tv[i].y & 0xffffu) + bf2f(pv[i].y & 0xffffu), bf2f(tv[i].y >> 16) + bf2f(pv[i].y >> 16)};
+      xr[64 * i] = v[i];
+    }
   } else {
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (i < nc) v[i] = xr[64 * i];
+    for (int i = 0; i < NC; ++i) v[i] = xr[64 * i];
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    gv[i] = ((const floatx4 *)g)[lane + 64 * i];
+    bv[i] = ((const floatx4 *)bt)[lane + 64 * i];
   }
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
-    if (i < nc) s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+  for (int i = 0; i < NC; ++i) s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
   const float mean = wave_sum_f(s) / d;
   float q = 0.f;
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
-    if (i < nc) {
-      const floatx4 t = v[i] - mean;
-      q += (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]);
-    }
+  for (int i = 0; i < NC; ++i) {
+    const floatx4 t = v[i] - mean;
+    q += (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]);
+  }
   const float rstd = 1.0f / sqrtf(wave_sum_f(q) / d + 1e-5f);
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
-    if (i < nc) {
-      const floatx4 gv = ((const floatx4 *)g)[lane + 64 * i], bv = ((const floatx4 *)bt)[lane + 64 * i];
-      const floatx4 y = (v[i] - mean) * rstd * gv + bv;
-      out[(long)i * 1024] = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
-    }
+  for (int i = 0; i < NC; ++i) {
+    const floatx4 y = (v[i] - mean) * rstd * gv[i] + bv[i];
+    out[(long)i * 1024] = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+  }
 }
+// Up to 1024 rows one row per workgroup (every CU gets rows: 64, 512, 1024 rows of 4096 with the embedding 6.6, 9.6, 13.9 us
+// against 8.3, 10.3, 15.3 with four), beyond four, or eight rows of 3072 and more (16384 rows of 4096 with the embedding:
+// 173 us with one, 145 with four, 127 with eight; of 2048: 88, 81, 82).
 template <bool EMBED>
-static bool launch_ln_rows4(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb, const bf16_t *pos_emb,
+static bool launch_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb, const bf16_t *pos_emb,
                             float *x, const float *g, const float *b, bf16_t *a_out, int B, int d, int V) {
-  if (rows % 4 || d % 256 || d > 4096) return false;  // other widths: one workgroup per row
-  const dim3 grid(rows / 4), blk(256);
-  if (d <= 1024) SKD_LAUNCH((k_ln_rows4<4, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
-  else if (d <= 2048) SKD_LAUNCH((k_ln_rows4<8, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
-  else SKD_LAUNCH((k_ln_rows4<16, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, d, V);
+  if (rows % 16 || d % 256 || d < 256 || d > 4096) return false;  // other widths: one workgroup per row
+  const int per = rows <= 1024 ? 1 : d >= 3072 ? 8 : 4;
+  const dim3 grid(rows / per), blk(64 * per);
+  switch (d / 256) {
+#define SKD_NC(NC) \
+  case NC: SKD_LAUNCH((k_ln_rows<NC, EMBED>), grid, blk, 0, s, tokens, rm, tok_emb, pos_emb, x, g, b, a_out, B, V); break;
+    SKD_NC(1) SKD_NC(2) SKD_NC(3) SKD_NC(4) SKD_NC(5) SKD_NC(6) SKD_NC(7) SKD_NC(8)
+    SKD_NC(9) SKD_NC(10) SKD_NC(11) SKD_NC(12) SKD_NC(13) SKD_NC(14) SKD_NC(15) SKD_NC(16)
+#undef SKD_NC
+  }
   return true;
 }
 
@@ -2094,12 +2099,12 @@ __global__ __launch_bounds__(1024) void k_last_rows_ln(const float *x_rows, RowM
 void bf16_embed_ln_rows(hipStream_t s, const int32_t *tokens, RowMap rm, int rows, const bf16_t *tok_emb,
                         const bf16_t *pos_emb, const float *g, const float *b, float *x, bf16_t *a_out, int B, int d,
                         int V) {
-  if (launch_ln_rows4<true>(s, tokens, rm, rows, tok_emb, pos_emb, x, g, b, a_out, B, d, V)) return;
-  SKD_LAUNCH(k_embed_ln_rows, dim3(rows), dim3(row_threads(d)), 0, s, tokens, rm, tok_emb, pos_emb, g, b, x, a_out, B, d, V);
+  if (launch_ln_rows<true>(s, tokens, rm, rows, tok_emb, pos_emb, x, g, b, a_out, B, d, V)) return;
+  SKD_LAUNCH(k_embed_ln_rows_wide, dim3(rows), dim3(row_threads(d)), 0, s, tokens, rm, tok_emb, pos_emb, g, b, x, a_out, B, d, V);
 }
 void bf16_ln_rows(hipStream_t s, float *x, const float *g, const float *b, bf16_t *a_out, int rows, int d) {
-  if (launch_ln_rows4<false>(s, nullptr, RowMap{}, rows, nullptr, nullptr, x, g, b, a_out, 0, d, 0)) return;
-  SKD_LAUNCH(k_ln_rows, dim3(rows), dim3(row_threads(d)), 0, s, x, g, b, a_out, d);
+  if (launch_ln_rows<false>(s, nullptr, RowMap{}, rows, nullptr, nullptr, x, g, b, a_out, 0, d, 0)) return;
+  SKD_LAUNCH(k_ln_rows_wide, dim3(rows), dim3(row_threads(d)), 0, s, x, g, b, a_out, d);
 }
 void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const float *partial, int split, int stride,
                        const float *bias, const float *g, const float *b, float *x_out, bf16_t *a_out, int B, int d) {
