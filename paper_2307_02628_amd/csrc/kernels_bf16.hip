@@ -1735,30 +1735,34 @@ void bf16_attention(hipStream_t s, const AttnArgs &a) {
 
 // ------------------------------------------------------------------ causal attention over a whole prompt
 // Same fragments as k_attention, but the 16 MFMA columns carry 16 different queries (consecutive positions of one
-// sequence).  A workgroup is 4 waves on 128 consecutive positions of one sequence and one head, a wave two 16-query
-// tiles.  The waves share the K and V blocks: a ring of ATT_NS stages (32 keys, K and V, one contiguous piece of a page)
+// sequence).  A workgroup is NW waves on 32 NW consecutive positions of one sequence and one head, a wave two 16-query
+// tiles.  The waves share the K and V blocks: a ring of NS stages (32 keys, K and V, one contiguous piece of a page)
 // is filled by LDS-direct loads ahead of their use, one bare barrier per stage; each wave loading its own fragments
 // asked four times as much of the CU's memory path (64 bytes per clock).
+// Four waves, and a ring of three stages; where no sequence has more than 32 or 64 positions one or two, and a stage for
+// each of their blocks.  As workgroups of four with waves that have nothing to do, 128 prompts of 16 tokens (32 heads of
+// 128) took 24.5 us instead of 17.4, of 48 tokens (32 heads of 64) 24.0 instead of 20.9.
 // Positions of a wave start at a multiple of 32, so exactly one block, its last, needs the causal mask.
 // The softmax works in units of log2 and against a reference m that is raised only when a score exceeds it by more than
 // 8 (weights up to 2^8: bf16 and fp32 keep their relative precision), so that most blocks need no cross-lane maximum
 // and no rescaling of the 64 accumulators; the denominator comes from the matrix cores (a row of ones), summed over the
 // rounded weights as the numerator is.
-constexpr int ATT_NS = 3;
+constexpr int att_stages(int NW) { return NW == 4 ? 3 : NW; }
 
-template <int DH>
-__global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, 3) void k_attention_rows(AttnRowsArgs a) {
   constexpr int QC = DH / 32, VM = DH / 16, NT = 2;
-  constexpr int FR = 2 * QC + VM, LPW = FR / 4;  // fragments per stage, loads per wave and stage
-  extern __shared__ bf16x8 ring[];               // [ATT_NS][FR][64 lanes]
+  constexpr int NS = att_stages(NW), AHEAD = NW == 4 ? NS - 1 : NS;  // stages requested before the first is used
+  constexpr int FR = 2 * QC + VM, LPW = FR / NW;  // fragments per stage, loads per wave and stage
+  extern __shared__ bf16x8 ring[];                // [NS][FR][64 lanes]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int grp = lane >> 4, col = lane & 15;
   const int h = blockIdx.x, b = blockIdx.y % a.B;
-  const int g0 = (int)(gridDim.y / a.B - 1 - blockIdx.y / a.B) * 128;  // longest key ranges are dispatched first
-  const int len = a.rm.P - a.rm.start[b];                               // real positions of this sequence
+  const int g0 = (int)(gridDim.y / a.B - 1 - blockIdx.y / a.B) * (32 * NW);  // longest key ranges are dispatched first
+  const int len = a.rm.P - a.rm.start[b];                                    // real positions of this sequence
   if (g0 >= len) return;
   const int d = a.kv.H * DH;
-  const int nblk = (min(g0 + 127, len - 1) >> 5) + 1;  // blocks the workgroup walks
+  const int nblk = (min(g0 + 32 * NW - 1, len - 1) >> 5) + 1;  // blocks the workgroup walks (NW < 4: at most NW, g0 is 0)
   const int p0 = g0 + 32 * wave;                       // first position of this wave
   const int mine = p0 < len ? p0 >> 5 : -1;            // this wave's last block
   const long row0 = (long)a.rm.first_row[b] + p0;
@@ -1779,37 +1783,49 @@ __global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
 
+  bf16x8 qf[NT][QC];
+  auto load_q = [&]() {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int k = 0; k < QC; ++k) {
+        qf[t][k] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+        if (p0 + 16 * t < len)  // the tile exists
+          qf[t][k] = ((const bf16x8 *)a.q)[(((row0 >> 4) + t) * (d >> 5) + ((h * DH) >> 5) + k) * 64 + act_lane(lane)];
+      }
+  };
+  if constexpr (NW < 4) load_q();  // (four waves: behind the ring, 5 % faster for one sequence of 1024 positions)
+
   // blocks are issued in order: block ib of page ip comes next.  Lane l holds page 64 w + l of the row for the window w
   // of 64 pages that ip is in; a window is waited for where it is loaded (waited for at its use, in the loop, the
   // compiler would wait for the ring's loads as well).
+  // With one or two blocks the pages are scalar loads.
   int ip = 0, ib = 0, pages = 0;
+  const int page0 = NW < 4 ? bt_row[0] : 0, page1 = NW < 4 ? bt_row[min(1, a.kv.max_pages - 1)] : 0;
   auto issue = [&](int blk) {
-    if (ib == 0 && (ip & 63) == 0) {
-      pages = ip + lane < a.kv.max_pages ? bt_row[ip + lane] : 0;
-      asm volatile("" : "+v"(pages));
+    int page = ip ? page1 : page0;
+    if constexpr (NW == 4) {
+      if (ib == 0 && (ip & 63) == 0) {
+        pages = ip + lane < a.kv.max_pages ? bt_row[ip + lane] : 0;
+        asm volatile("" : "+v"(pages));
+      }
+      page = __builtin_amdgcn_readlane(pages, ip & 63);
     }
-    const int page = __builtin_amdgcn_readlane(pages, ip & 63);
     const bf16x8 *src = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * (a.kv.page_tokens * DH * 2) +
                                          (long)ib * (64 * DH)) + wave * LPW * 64;
-    bf16x8 *dst = ring + ((blk % ATT_NS) * FR + wave * LPW) * 64;
+    bf16x8 *dst = ring + ((blk % NS) * FR + wave * LPW) * 64;
 #pragma unroll
-    for (int i = 0; i < LPW; ++i)
+    for (int i = 0; i < LPW; ++i) {
+      if (NW == 1 && i >= QC && i < 2 * QC && len <= 16) continue;  // keys 16 .. 31: the mask covers them whatever LDS holds
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)&(src + i * 64)[lane],
                                        (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
+    }
     if (++ib == bpp) { ib = 0; ++ip; }
   };
 #pragma unroll
-  for (int i = 0; i < ATT_NS - 1; ++i)
+  for (int i = 0; i < AHEAD; ++i)
     if (i < nblk) issue(i);
-  bf16x8 qf[NT][QC];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int k = 0; k < QC; ++k) {
-      qf[t][k] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      if (p0 + 16 * t < len)  // the tile exists
-        qf[t][k] = ((const bf16x8 *)a.q)[(((row0 >> 4) + t) * (d >> 5) + ((h * DH) >> 5) + k) * 64 + act_lane(lane)];
-    }
+  if constexpr (NW == 4) load_q();
   // the queries arrive before the loop: waited for inside it, they would make the compiler wait for every load in flight
   wait_vmcnt<0>();
 #pragma unroll
@@ -1817,7 +1833,7 @@ __global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
 #pragma unroll
     for (int k = 0; k < QC; ++k) asm volatile("" : "+v"(qf[t][k]));
   auto use = [&](int blk, bool diagonal) {
-    const bf16x8 *kv = ring + (blk % ATT_NS) * (FR * 64) + lane;
+    const bf16x8 *kv = ring + (blk % NS) * (FR * 64) + lane;
     floatx4 S[NT][2];
 #pragma unroll
     for (int tl = 0; tl < 2; ++tl) {
@@ -1873,13 +1889,14 @@ __global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
   };
   auto open = [&](int blk) {
     // this wave's loads of stage blk have landed once only those of the later stages in flight are outstanding
-    if (blk + 1 < nblk) wait_vmcnt<(ATT_NS - 2) * LPW>();
+    if (blk + 1 < nblk) wait_vmcnt<LPW>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of stage blk - 1
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (blk + ATT_NS - 1 < nblk) issue(blk + ATT_NS - 1);  // into the slot of stage blk - 1
+    if constexpr (NW == 4)
+      if (blk + AHEAD < nblk) issue(blk + AHEAD);  // into the slot of stage blk - 1
   };
   int blk = 0;
   for (; blk <= mine; ++blk) {
@@ -1900,11 +1917,17 @@ __global__ __launch_bounds__(256, 3) void k_attention_rows(AttnRowsArgs a) {
   }
 }
 
+template <int DH, int NW>
+static void launch_attention_rows(hipStream_t s, const AttnRowsArgs &a) {
+  const dim3 grid(a.kv.H, a.B * ((a.max_len + 32 * NW - 1) / (32 * NW)));
+  const size_t lds = (size_t)att_stages(NW) * 32 * DH * 2 * sizeof(bf16_t);  // 8 or 16 KiB a stage
+  SKD_LAUNCH((k_attention_rows<DH, NW>), grid, dim3(64 * NW), lds, s, a);
+}
 void bf16_attention_rows(hipStream_t s, const AttnRowsArgs &a) {
-  const dim3 grid(a.kv.H, a.B * ((a.max_len + 127) / 128));
-  const size_t lds = (size_t)ATT_NS * 32 * a.kv.dh * 2 * sizeof(bf16_t);  // 32 or 64 KiB
-  if (a.kv.dh == 64) SKD_LAUNCH(k_attention_rows<64>, grid, dim3(256), lds, s, a);
-  else SKD_LAUNCH(k_attention_rows<128>, grid, dim3(256), lds, s, a);
+#define SKD_ATT(DH) (a.max_len <= 32 ? launch_attention_rows<DH, 1>(s, a) : a.max_len <= 64 ? launch_attention_rows<DH, 2>(s, a) : launch_attention_rows<DH, 4>(s, a))
+  if (a.kv.dh == 64) SKD_ATT(64);
+  else SKD_ATT(128);
+#undef SKD_ATT
 }
 
 // ------------------------------------------------------------------ row kernels of the batched prompt

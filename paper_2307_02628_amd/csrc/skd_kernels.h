@@ -203,7 +203,7 @@ struct AttnArgs {
   float *part;              // splits > 1: [splits][B*H][dh + 2]
 };
 void bf16_attention(hipStream_t s, const AttnArgs &a);
-// Causal attention of a whole prompt: query rows (b, pos), 128 positions per workgroup, keys of columns start[b] .. pos.
+// Causal attention of a whole prompt: query rows (b, pos), up to 128 positions per workgroup, keys of columns start[b] .. pos.
 struct AttnRowsArgs {
   const bf16_t *q;          // activation tiles [rows][d]
   const bf16_t *pool;
