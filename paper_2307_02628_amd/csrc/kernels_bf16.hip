@@ -17,7 +17,22 @@
 //     the QK^T accumulator already in B-operand position.
 #include "skd_kernels.h"
 
+#include <initializer_list>
+
+#include "once_per_device.h"
+
 namespace skd {
+
+// Lets the kernels use `bytes` of dynamic LDS on the current device; `done` belongs to these kernels.
+static bool allow_lds(std::atomic<uint64_t> &done, std::initializer_list<const void *> kernels, size_t bytes) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return false;
+  return once_per_device(done, device, [&]() {
+    for (const void *k : kernels)
+      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
+    return true;
+  });
+}
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
@@ -526,15 +541,12 @@ template <int R, int EPI>
 static int launch_gemm_ln(hipStream_t s, const GemmArgs &a, dim3 grid) {
   const int NB = a.B <= 1 ? 1 : a.B <= 2 ? 2 : 4;
   const size_t lds = (size_t)8 * R * 64 * sizeof(floatx4) + (size_t)NB * ln_row_stride(a.K) * sizeof(bf16_t);
-  static bool configured = false;
-  if (!configured) {
-    const int most = 8 * R * 64 * (int)sizeof(floatx4) + 4 * ln_row_stride(2048) * (int)sizeof(bf16_t);  // more than 2 rows of 4096
-    if (hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm<1, R, EPI, 1, 8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess)
-      return -1;
-    configured = true;
-  }
+  const int most = 8 * R * 64 * (int)sizeof(floatx4) + 4 * ln_row_stride(2048) * (int)sizeof(bf16_t);  // more than 2 rows of 4096
+  static std::atomic<uint64_t> done{0};
+  if (!allow_lds(done, {(const void *)k_gemm<1, R, EPI, 1, 8, 1>,
+                        (const void *)k_gemm<1, R, EPI, 1, 8, 2>,
+                        (const void *)k_gemm<1, R, EPI, 1, 8, 4>}, most))
+    return -1;
   if (NB == 1) SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 1>), grid, dim3(512), lds, s, a);
   else if (NB == 2) SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 2>), grid, dim3(512), lds, s, a);
   else SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 4>), grid, dim3(512), lds, s, a);
@@ -822,15 +834,12 @@ static int launch_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, dim3 grid) 
   constexpr size_t ring = (size_t)WS_NS * WS_CW * MB * 64 * sizeof(bf16x8);
   constexpr size_t redb = (size_t)WS_CW * R * MB * 64 * sizeof(floatx4);
   constexpr size_t lds = ring > redb ? ring : redb;
-  static bool configured = false;
-  if (!configured) {
-    if (hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_QKV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_ws<MB, R, EPI_LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return -1;
-    configured = true;
-  }
+  static std::atomic<uint64_t> done{0};
+  if (!allow_lds(done, {(const void *)k_gemm_ws<MB, R, EPI_PARTIAL>,
+                        (const void *)k_gemm_ws<MB, R, EPI_QKV>,
+                        (const void *)k_gemm_ws<MB, R, EPI_RELU>,
+                        (const void *)k_gemm_ws<MB, R, EPI_LOGITS>}, lds))
+    return -1;
   const dim3 blk(512);
   switch (epi) {
     case EPI_PARTIAL: SKD_LAUNCH((k_gemm_ws<MB, R, EPI_PARTIAL>), grid, blk, lds, s, a); break;
@@ -1155,15 +1164,12 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
   if (a.split != 1 && epi != EPI_PARTIAL) return -1;
   const dim3 grid((a.N / 256) * ((a.rows + 255) / 256) * a.split), blk(512);
   const size_t lds = (size_t)TILE_NS * TILE_FR * 64 * sizeof(bf16x8);  // 128 KiB of the CU's 160
-  static bool configured = false;
-  if (!configured) {
-    if (hipFuncSetAttribute((const void *)k_gemm_tile<EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_tile<EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_tile<EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_tile<EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return -1;
-    configured = true;
-  }
+  static std::atomic<uint64_t> done{0};
+  if (!allow_lds(done, {(const void *)k_gemm_tile<EPI_QKV_ROWS>,
+                        (const void *)k_gemm_tile<EPI_RESID>,
+                        (const void *)k_gemm_tile<EPI_PARTIAL>,
+                        (const void *)k_gemm_tile<EPI_RELU>}, lds))
+    return -1;
   switch (epi) {
     case EPI_QKV_ROWS: SKD_LAUNCH(k_gemm_tile<EPI_QKV_ROWS>, grid, blk, lds, s, a); break;
     case EPI_RESID: SKD_LAUNCH(k_gemm_tile<EPI_RESID>, grid, blk, lds, s, a); break;
@@ -1319,15 +1325,12 @@ static int launch_gemm_mid(hipStream_t s, const GemmArgs &a, int epi) {
   constexpr int BN = 16 * RT * WN, BM = 16 * MT * WM;
   constexpr size_t lds = (size_t)NS * (BN + BM) * 4 * sizeof(bf16x8);
   if (a.N % BN) return -1;
-  static bool configured = false;
-  if (!configured) {
-    if (hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_QKV_ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RESID>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_PARTIAL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RELU>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return -1;
-    configured = true;
-  }
+  static std::atomic<uint64_t> done{0};
+  if (!allow_lds(done, {(const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_QKV_ROWS>,
+                        (const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RESID>,
+                        (const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_PARTIAL>,
+                        (const void *)k_gemm_mid<RT, MT, WN, WM, NS, EPI_RELU>}, lds))
+    return -1;
   const dim3 grid((a.N / BN) * ((a.rows + BM - 1) / BM) * a.split), blk(WN * WM * 64);
   switch (epi) {
     case EPI_QKV_ROWS: SKD_LAUNCH((k_gemm_mid<RT, MT, WN, WM, NS, EPI_QKV_ROWS>), grid, blk, lds, s, a); break;
