@@ -552,11 +552,15 @@ static int launch_gemm_ln(hipStream_t s, const GemmArgs &a, dim3 grid) {
   else SKD_LAUNCH((k_gemm<1, R, EPI, 1, 8, 4>), grid, dim3(512), lds, s, a);
   return 0;
 }
-int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epi, int R) {
+int bf16_gemm_ln_check(const GemmArgs &a, int epi, int R) {
   if (a.B < 1 || a.B > 4 || a.B_pad != 16 || a.K % 32 || a.K < 32 || a.K > 2048 * ln_chunks(a.B) || a.split != 1 || a.rows != 0)
     return -1;
   if (R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.N < 1 || a.ln_split < 1 || (epi != EPI_QKV && epi != EPI_RELU)) return -1;
-  const int groups = bf16_gemm_groups(a.N, R);
+  return bf16_gemm_groups(a.N, R);
+}
+int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epi, int R) {
+  const int groups = bf16_gemm_ln_check(a, epi, R);
+  if (groups < 0) return -1;
   const dim3 grid(groups);
   int rc;
 #define SKD_LN(R) (epi == EPI_QKV ? launch_gemm_ln<R, EPI_QKV>(s, a, grid) : launch_gemm_ln<R, EPI_RELU>(s, a, grid))

@@ -442,8 +442,13 @@ bool decode_shapes_ok(const skd_state *st) {
     ga.N = N; ga.K = K; ga.G = p.R; ga.split = p.split;
     return check_gemm(ga, epi, p) > 0;
   };
+  auto ok_ln = [&](int N, const GemmPlan &p, const GemmPlan &before, int epi) {  // behind the partial sums of `before`
+    ga.N = N; ga.K = d; ga.G = p.R; ga.split = p.split; ga.ln_split = before.split;
+    return bf16_gemm_ln_check(ga, epi, p.R) > 0;
+  };
   return ok(3 * d, d, st->p_qkv, EPI_QKV) && ok(d, d, st->p_out, EPI_PARTIAL) && ok(f, d, st->p_ffn1, EPI_RELU) &&
-         ok(d, f, st->p_ffn2, EPI_PARTIAL) && ok(c.vocab, d, st->p_head, EPI_LOGITS);
+         ok(d, f, st->p_ffn2, EPI_PARTIAL) && ok(c.vocab, d, st->p_head, EPI_LOGITS) &&
+         (!st->fuse_ln || (ok_ln(3 * d, st->p_qkv, st->p_ffn2, EPI_QKV) && ok_ln(f, st->p_ffn1, st->p_out, EPI_RELU)));
 }
 
 // Waves per workgroup and workgroups per (row, head) of decode attention at position t: no more waves than there are

@@ -161,8 +161,10 @@ struct GemmArgs {
 // waves in {4,8}: waves per workgroup.  K/32 must be a multiple of a.split.
 // Returns the number of row groups launched (grid.x), or -1 for an unsupported shape.
 int bf16_gemm(hipStream_t s, const GemmArgs &a, int epilogue, int R, int U, int waves);
-// At most 4 rows, K <= 4096, EPI_QKV or EPI_RELU: with the row reducer in the prologue (ln_*; a.A is not read).
+// At most 4 rows, K <= 4096 (2048 for 3 and 4), EPI_QKV or EPI_RELU: with the row reducer in the prologue (ln_*; a.A is
+// not read).  The check launches nothing (N, K, B, B_pad, G, split, rows and ln_split of `a` are read): groups or -1.
 int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epilogue, int R);
+int bf16_gemm_ln_check(const GemmArgs &a, int epilogue, int R);
 // The same shape checks without a launch (only N, K, B_pad, G, split and rows of `a` are read): groups or -1.
 int bf16_gemm_check(const GemmArgs &a, int epilogue, int R, int U, int waves);
 int bf16_gemm_groups(int N, int R);

@@ -2,6 +2,8 @@
 and the oracle on the same seeded inputs and compare per-step logits."""
 from __future__ import annotations
 
+import subprocess
+
 import numpy as np
 
 from oracle import oracle as O
@@ -66,3 +68,11 @@ def compare(shape, w, prompts, P, N, n_min, n_max, tol, warmup=0, mask=None, dty
     assert err.max() <= tol, f"per-step max|dlogit|/range = {err}"
     check_argmax(got["logits"], ref["logits"], tol, min_decided)
     return got, ref, err
+
+
+def internal(name):
+    """A function of the library's C++ side (namespace skd)."""
+    out = subprocess.run(["nm", "-D", "--defined-only", skd.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    sym = [l.split()[-1] for l in out.splitlines() if l.split()[-1].startswith(f"_ZN3skd{len(name)}{name}E")]
+    assert len(sym) == 1, (name, sym)
+    return getattr(skd.lib(), sym[0])

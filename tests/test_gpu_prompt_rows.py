@@ -2,28 +2,17 @@
 wave keeps a row of (multiples of 256 up to 4096, each compiled by itself) and the row counts at which the rows of a
 workgroup change, and their cost where one wave per row once lost time."""
 import ctypes as C
-import subprocess
 
 import numpy as np
 import pytest
 
-from paper_2307_02628_amd import skd
+from tests.helpers import internal
 
 pytestmark = pytest.mark.gpu
 
 
 class RowMap(C.Structure):
     _fields_ = [("seq", C.c_void_p), ("first_row", C.c_void_p), ("start", C.c_void_p), ("P", C.c_int)]
-
-
-def internal(name):
-    """A function of the library's C++ side (namespace skd)."""
-    out = subprocess.run(["nm", "-D", "--defined-only", skd.LIB_PATH], capture_output=True, text=True, check=True).stdout
-    sym = [l.split()[-1] for l in out.splitlines() if l.split()[-1].startswith(f"_ZN3skd{len(name)}{name}E")]
-    assert len(sym) == 1, sym
-    f = getattr(skd.lib(), sym[0])
-    f.restype = None
-    return f
 
 
 class Rows:

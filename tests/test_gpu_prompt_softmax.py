@@ -11,8 +11,8 @@ import ctypes as C
 import numpy as np
 import pytest
 
-from paper_2307_02628_amd import skd
-from tests.test_gpu_prompt_rows import RowMap, internal
+from tests.helpers import internal
+from tests.test_gpu_prompt_rows import RowMap
 
 pytestmark = pytest.mark.gpu
 
