@@ -83,6 +83,16 @@ def step_bytes(shape, n_layers, sum_len):
     return n_layers * (per_layer_w + per_layer_kv) + 2 * V * d
 
 
+def prompt_projection_flops(shape, lens):
+    """Projections of a prompt pass: 2 flops per weight and real prompt token, all L layers; from 512 rows on (whole 16-row
+    tiles of each sequence) only k and v of the top one, whose rest then runs for the last positions alone (not counted,
+    nor is attention)."""
+    layer = 4 * shape.d * shape.d + 2 * shape.d * shape.f
+    rows = sum(-(-int(n) // 16) * 16 for n in lens)
+    top = 2 * shape.d * shape.d if rows >= 512 else layer
+    return 2.0 * float(sum(int(n) for n in lens)) * ((shape.L - 1) * layer + top)
+
+
 def class_bytes(shape, cls, sum_len):
     d, f, V = shape.d, shape.f, shape.V
     return {"gemm_qkv": 2 * 3 * d * d, "gemm_out": 2 * d * d, "gemm_ffn1": 2 * d * f, "gemm_ffn2": 2 * d * f,
@@ -177,10 +187,7 @@ def run_generation(skd, torch, shape, w, B, P, T, n_min, n_max, mask, steps, war
             t = {k: a.elapsed_time(b) for k, a, b in pairs}
             rep_ms.append(sum(t[k] for k in ks))
             first_ms.append(t[0])
-    # projections of the prompt pass: 2 flops per weight and real prompt token, all L layers, of the top one only k and v
-    # (the rest of it runs for the last positions; attention not counted)
-    prefill_flop = 2.0 * float(P * B - start.sum()) * ((shape.L - 1) * (4 * shape.d * shape.d + 2 * shape.d * shape.f) +
-                                                       2 * shape.d * shape.d)
+    prefill_flop = prompt_projection_flops(shape, P - start)
     out = {"rep_ms": rep_ms, "first_step_ms": first_ms, "prefill_s": prefill_s, "ks": ks,
            "prefill_projection_pflops": prefill_flop / prefill_s / 1e15,
            "layers": [layers[k] for k in ks], "sum_len": [sum_len[k] for k in ks],

@@ -78,3 +78,12 @@ def test_timed_sample_has_the_schedules_mean_depth(name, steps):
     mean_all, mean_sample = np.mean(n_all), np.mean([n_all[k] for k in ks])
     assert abs(mean_sample - mean_all) <= 0.02 * mean_all + 0.5 / steps * (n_max - n_min)
     assert bench.sample_positions(T, T) == list(range(T)) == bench.sample_positions(T, T + 7)
+
+
+def test_prompt_projection_flops():
+    # 1.3B: 4 d^2 + 2 d f = 50 331 648 weights a layer, k and v 8 388 608
+    s = S.OPT_1_3B
+    assert bench.prompt_projection_flops(s, [256] * 16) == 2.0 * 4096 * (23 * 50_331_648 + 8_388_608)
+    assert bench.prompt_projection_flops(s, [31] * 16) == 2.0 * 496 * (23 * 50_331_648 + 8_388_608)     # 512 padded rows
+    assert bench.prompt_projection_flops(s, [496]) == 2.0 * 496 * 24 * 50_331_648       # below: the top layer in full
+    assert bench.prompt_projection_flops(s, [16, 15]) == 2.0 * 31 * 24 * 50_331_648
