@@ -55,3 +55,10 @@ def test_forced_tiles(shape, tile):
     (WIDE, 13, 97, 20), (NARROW, 40, 31, 1)])                                      # ragged, more than 512 rows: top layer as a column
 def test_planned_shapes(shape, B, P, shortest):
     check(shape, B, P, shortest, {}, 50)
+
+
+# more than 512 rows, no multiple of 256: the top layer computes only k and v, from the weight tile behind q's
+@pytest.mark.parametrize("shape", [WIDE, NARROW])
+@pytest.mark.parametrize("tile", ["256x256x1", "256x128x2", "128x256x1", "128x128x1", "64x128x1", "128x64x1", "64x64x2"])
+def test_forced_tiles_behind_q(shape, tile):
+    check(shape, 9, 83, 50, {"SKD_PREFILL_TILE": tile}, 60)
