@@ -193,9 +193,10 @@ int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logits_out);
  * logits_out [B][vocab] (either may be NULL) are device memory and the call
  * only enqueues work on the state's stream.  Limit:
  * ceil(vocab / (16 R)) * B_pad <= 262144 partials, R = LM-head tile rows per
- * workgroup (2 below batch 32, else 4; SKD_R_HEAD), B_pad = batch padded to
- * 16/32/64/128, i.e. vocabularies up to 131072 at batch 128 and larger ones
- * at smaller batches; beyond the limit SKD_ERR_RANGE and nothing is launched.  All calls on one GPU, from whatever
+ * workgroup (1 to 4; for large vocabularies 2 up to batch 16, else 4;
+ * SKD_R_HEAD), B_pad = batch padded to 16/32/48/64/96/128, i.e. vocabularies
+ * up to 131072 at batch 128 and larger ones at smaller batches; beyond the
+ * limit SKD_ERR_RANGE and nothing is launched.  All calls on one GPU, from whatever
  * state, share that GPU's array: calls that may overlap there (different
  * streams, different threads) race; calls on one stream are safe.  The array
  * keeps the previous call's contents; nothing in it needs clearing, since the
@@ -279,14 +280,15 @@ int skd_debug_kv_read(skd_state *st, int32_t layer, int32_t b, float *k_out, flo
  * SKD_ERR_RANGE (mode), SKD_ERR_HIP. */
 typedef enum {
   SKD_PROF_EMBED_LN = 0, /* embedding gather + first LayerNorm */
-  SKD_PROF_GEMM_QKV = 1, /* q,k,v projection + KV page write  */
+  SKD_PROF_GEMM_QKV = 1, /* q,k,v projection                   */
   SKD_PROF_ATTENTION = 2,/* decode attention over the paged KV (incl. split merge) */
   SKD_PROF_GEMM_OUT = 3, /* attention output projection        */
-  SKD_PROF_REDUCE_LN = 4,/* split-K reduce + bias + residual + LayerNorm */
+  SKD_PROF_REDUCE_LN = 4,/* split-K reduce + bias + residual + LayerNorm (with few rows
+                            mostly inside GEMM_QKV and GEMM_FFN1) */
   SKD_PROF_GEMM_FFN1 = 5,
   SKD_PROF_GEMM_FFN2 = 6,
   SKD_PROF_LM_HEAD = 7,  /* LM head projection with per-workgroup argmax */
-  SKD_PROF_ARGMAX = 8,   /* final argmax reduction             */
+  SKD_PROF_ARGMAX = 8,   /* final argmax reduction, or the sampling head's passes */
   SKD_PROF_OTHER = 9,    /* fp32 debug path kernels            */
   SKD_PROF_CLASSES = 10
 } skd_prof_class;

@@ -204,7 +204,7 @@ __device__ inline void gemm_epilogue<EPI_RESID>(const GemmArgs &a, int row, int 
 // LDS, from the residual rows and the partial sums of the projection before: x + bias + sums, then LayerNorm.  Every
 // workgroup repeats that, workgroup 0 also stores the new residual rows (to another buffer: the others still read the
 // old ones).  The first weights are requested before it, so they arrive under it.  For few rows this costs less than
-// the reducer's launch (one row of 4096: about 64 KiB from L2 per workgroup).
+// the reducer's launch (one row of 4096 with two partial sums: 96 KiB from L2 per workgroup, half of it bias, gain and offset).
 constexpr int ln_chunks(int NB) { return NB > 2 ? 1 : 2; }  // float4 chunks per thread: rows of 2048 NC at most
 constexpr int ln_row_stride(int K) { return K + 32; }  // bf16 units: rows start 16 banks apart
 template <int NB, typename F>
@@ -1189,9 +1189,11 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
 // N = d projections, on 256 CUs).  The same ring and fragment order with WN x WM waves of RT x MT MFMA tiles each: the
 // workgroup owns 16 RT WN weight rows x 16 MT WM activation rows, the ring has NS stages, and the K range can be split
 // over `a.split` workgroups whose fp32 partial sums the row reducer adds.  With 4 waves two workgroups share a CU, so
-// one multiplies while the other waits at its barrier.  What bounds it is how many bytes a CU takes in per MFMA: the
-// memory path delivers about 60 GB/s to a CU at the latency of these loads whatever the ring depth (64 x 128 tiles: 5
-// and 6 stages alike, 64 x 64: 5 and 9), so the largest tile that still fills the chip wins.
+// one multiplies while the other waits at its barrier.  What bounds it is how many bytes a CU takes in per MFMA: at 912
+// rows of the 1.3B shape the 128 x 256 tiles read 10.4 TB/s through L2 (41 GB/s to each CU) with the matrix cores 34 %
+// busy, whatever the ring depth (64 x 128 tiles: 5 and 6 stages alike, 64 x 64: 5 and 9), so the largest tile that
+// still fills the chip wins.  The q | k | v launches take in less (7.6 and 9.0 TB/s): their epilogue begins its page
+// lookups behind the loop, and with one round of workgroups nothing runs under them.
 // us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
 // FFN1 80 -> 44, FFN2 296 -> 46 (split 4), all 128 x 128; 1024 rows of the 1.3B shape QKV 44 -> 32 and FFN1 45 -> 35
 // (128 x 256; 128 x 128: 37 and 41), output 51 -> 15 (128 x 128, split 2), FFN2 153 -> 37 (128 x 256, split 4).

@@ -276,9 +276,10 @@ GemmPlan plan_direct(int N, int B_pad) {  // whole K inside the workgroup
 GemmPlan plan_split(int N, int K, int B_pad) {  // partial sums, reduced by the LayerNorm kernel
   GemmPlan p;
   p.waves = plan_waves(B_pad);
-  // A wave of these short K ranges has 2 to 16 k-steps: two per buffer with one batch tile (1.3B model, 16 rows, 8 steps:
-  // 7172 -> 7029 us; 6.7B widths, 8 rows: 921 -> 918); four put too much in flight (7118), and wider batches have no
-  // registers to gain from it
+  // A wave of these K ranges has 1 (K = 256) to 32 k-steps (16384, split by 2): two per buffer with one batch tile (1.3B
+  // model, 16 rows, 8 steps: 7172 -> 7029 us; 6.7B widths, 8 rows: 921 -> 918); four put too much in flight (7118), and
+  // wider batches have no registers to gain from it.  At K = 256 and 384 two leave waves without a buffer of their own;
+  // the launch takes 4.2 to 4.5 us either way
   if (B_pad <= 16) p.U = 2;
   const int Kf = K / 32;
   // tile rows per workgroup: enough that the activation re-reads (B_pad / (16 R) of the weight bytes) stay at
@@ -620,8 +621,9 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
 
   if (st->bf16) {
     st->max_split = std::max(st->p_out.split, st->p_ffn2.split);
-    // The prologue reads x and the partial sums of every row in every workgroup: up to 128 KiB (two rows of 4096 with a
-    // split of 2, three of 2048 with 4) that takes less than the reducer's launch.  It is paid per workgroup, and the
+    // The prologue reads x and the partial sums of every row in every workgroup, and bias, gain and offset once: up to
+    // 128 KiB of the former (two rows of 4096 with a split of 2: 96, three of 2048 with 4: 120) that takes less than the
+    // reducer's launch.  It is paid per workgroup, and the
     // activations come from LDS, so the projections behind it take the row groups of a wider batch: one workgroup per CU
     // instead of two for FFN1 at 4096 x 16384.  One row of 4096, 4 steps of 2 to 4 layers at 2000 keys: 1355 us with
     // separate reducers, 1300 with two workgroups per CU, 1287 with one; two rows of 256: 1910 -> 1740 us for 16 steps.
@@ -822,6 +824,8 @@ constexpr long kRowsPartialMax = 32L << 20;  // fp32 partial sums of one project
 // workgroups) to 0.75 (all CUs: the clock drops); 256 x 128 and 128 x 256 0.45 to 0.51; 128 x 128 0.32 alone on a CU,
 // 0.52 for two; 64 x 128 0.255 / 0.44; 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
 // at 1024 rows of the 6.7B shape FFN1 takes 100 us on 256 x 256 and 138 on 128 x 128, at 256 rows 80 and 44.
+// The epilogue is not in the estimate, and the traffic of the partial sums counts the reducer's reads: at 912 rows of the
+// 1.3B shape estimate and launch are 34 / 40 us (QKV), 23.5 / 31 (k | v alone), 35 / 38 (FFN1) and 45 / 39 (FFN2, split 4).
 RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   RowsGemm best;
   const int Kf = K / 32;
@@ -936,9 +940,10 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
   // What leaves the prompt pass is the cache of every layer and the hidden state of each sequence's last position, so
   // of the top layer's rows only the last positions are needed beyond their keys and values: its q | k | v projection
   // computes k | v for all rows, and the last positions go through that layer as a decode column at position P - 1.
-  // From 512 rows on (below, a layer of all rows costs little more than streaming its weights, which the column streams
-  // too: 256 rows of the 6.7B shape, 165 us against 130; at 912 rows of the 1.3B shape 165 against 70, at 16384 of
-  // the 6.7B shape 5200 against 950).
+  // From 512 rows on: at 912 rows of the 1.3B shape 165 us against 70, at 16384 of the 6.7B shape 5200 against 950.  Below,
+  // a layer of all rows costs little more than streaming its weights, which the column streams too; at 256 rows of the
+  // 6.7B shape the column was estimated at 130 us against 165, so the line lies on the safe side of where the two cross,
+  // which has not been measured.
   const RowsGemm r_kv = plan(2 * d, d, false);
   const bool last_as_column = rows >= 512 && (r_kv.kind == RowsGemm::TILE || r_kv.kind == RowsGemm::MID);
   for (int l = 0; l < L; ++l) {
