@@ -877,8 +877,14 @@ int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, int R) {
 // land at the wave's LDS base + 16 * lane: fragments arrive ready-made and no
 // register holds data in flight), three stages ahead of the one being
 // multiplied.  Each wave accumulates a 64 x 128 sub-tile (4 x 8 MFMA tiles, 128
-// accumulator registers), reading 12 fragments from LDS per 32 MFMAs, one
-// k-step ahead of the MFMAs that use them.
+// accumulator registers), reading 12 fragments from LDS per 32 MFMAs.
+// A k-step takes 1024 cycles of a CU's matrix cores and 1024 of its LDS (96 KiB read, 32 KiB written, 128 bytes a clock),
+// so the two waves of a SIMD take turns: while one multiplies the other one reads.  With all 8 waves in phase, each
+// reading the next k-step among its MFMAs, a k-step took 0.55 us on an otherwise idle chip, now 0.465 (1116 cycles at
+// 2.4 GHz).  With every CU busy it takes 0.72: the power limit lowers the clock (16384 rows x 4096 x 16384, TFLOP/s: 1436
+// -> 1541 with normal operands, 1817 -> 1832 with zeros).  Stand-alone, us: 16384 x 4096 x 16384 1553 -> 1470, x 16384 x
+// 4096 1531 -> 1427, x 4096 x 12288 1197 -> 1114.  Slower: v_mfma 32x32x16 (1270 TFLOP/s; alone it reaches 1840 against
+// 2100 of 16x16x32), four waves of 128 x 128 (1371).
 constexpr int TILE_NS = 4;   // ring stages
 constexpr int TILE_FR = 32;  // fragments per stage: 16 weight tiles, then 16 activation-row tiles
 
@@ -1076,88 +1082,57 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)&(src[i] + (long)st * sstride)[vlane],
                                        (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
   };
-  auto read = [&](int buf, bf16x8(&wf)[4], bf16x8(&xf)[8]) {  // 12 fragments of a stage into registers
-    const bf16x8 *base = tile_lds + buf * (TILE_FR * 64) + lane;
+  auto bar = [&]() {  // bare: __syncthreads() would also wait for the loads of the later stages
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // One k-step of a wave: a slot for memory (12 LDS reads of stage st, the requests of stage st + 3), a barrier, a slot
+  // for the matrix cores, a barrier.  Waves 4 .. 7 run one barrier behind waves 0 .. 3, so of the two waves on a SIMD one
+  // multiplies while the other one reads.
+  // Ring: stage st + 3 goes into the slot of stage st - 1, which every wave has read by then (the late group read it
+  // in its memory slot before last, with lgkmcnt 0 before the barrier).  Stage st + 1 has landed for every wave that
+  // reads it: each wave waits for its own loads of it (all but the `later` stages behind it) in its memory slot st, and
+  // at least one barrier lies between the last of these waits and the first read.
+  auto k_step = [&](int st, bool more, int later) {
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 wf[4], xf[8];
+    const bf16x8 *base = tile_lds + (st % TILE_NS) * (TILE_FR * 64) + lane;
 #pragma unroll
     for (int r = 0; r < 4; ++r) wf[r] = base[(wr * 4 + r) * 64];
 #pragma unroll
     for (int m = 0; m < 8; ++m) xf[m] = base[(16 + wc * 8 + m) * 64];
-  };
-  auto mma = [&](const bf16x8(&wf)[4], const bf16x8(&xf)[8]) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < 8; ++m) acc[r][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[r], xf[m], acc[r][m], 0, 0, 0);
-  };
-  // Stage st becomes readable.  This wave's loads of it have landed once at most the loads of the (up to two)
-  // later stages in flight are outstanding, and its own LDS reads (of stage st - 1) have completed; the barrier
-  // then says both of every wave, so stage st may be read and the ring slot of stage st - 1 refilled.  It is a
-  // bare s_barrier between compiler fences: __syncthreads() would also wait for the loads of the later stages.
-  auto open_stage = [&](int st) {
-    const int later = min(Kf - 1 - st, TILE_NS - 2);
+    if (more) issue(st + TILE_NS - 1);
+    __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt_le(4 * later);
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (st + TILE_NS - 1 < Kf) issue(st + TILE_NS - 1);
+    bar();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    // neighbours share an operand (activation tile outer, weight tiles back and forth): the registers that feed the
+    // matrix cores change less, which at this load is clock (1464 -> 1496 TFLOP/s)
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = (m & 1) ? 3 - i : i;
+        acc[r][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[r], xf[m], acc[r][m], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    __builtin_amdgcn_s_setprio(0);
+    bar();
   };
 
 #pragma unroll
   for (int i = 0; i < TILE_NS - 1; ++i)
     if (i < Kf) issue(i);
-  // Two register sets of fragments: while the matrix cores work on stage st out of one, the LDS reads of stage
-  // st + 1 fill the other.  With one set, every k-step began with all 8 waves waiting for 96 KiB of LDS reads
-  // (the barrier puts them in phase) while the matrix cores sat idle.
-  bf16x8 wfA[4], xfA[8], wfB[4], xfB[8];
-  open_stage(0);
-  read(0, wfA, xfA);
-  // Steady state (three later stages still to be requested): one straight-line block per k-step, in which the
-  // scheduler is told to deal the 12 LDS reads of the next stage out among the 32 MFMAs of the current one, so
-  // that a wave does not sit on a full LDS queue with MFMAs ready behind it (instructions issue in order).
-  auto steady = [&](int nx, bf16x8(&wn)[4], bf16x8(&xn)[8], const bf16x8(&wc_)[4], const bf16x8(&xc)[8]) {
-    wait_vmcnt_le(8);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    issue(nx + TILE_NS - 1);
-    read(nx % TILE_NS, wn, xn);
-    mma(wc_, xc);
-    __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // the 4 LDS-direct loads first
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {  // the reads early: (MFMA, read) x 4, (MFMA x 2, read) x 8, then 12 MFMAs, so that
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // no read is still in flight when the wave reaches the
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // next barrier
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
-  };
+  wait_vmcnt_le(4 * min(Kf - 1, TILE_NS - 2));
+  bar();  // stage 0 is here
+  if (wave >= 4) bar();
   int st = 0;
-  for (; st + 5 < Kf; st += 2) {
-    steady(st + 1, wfB, xfB, wfA, xfA);
-    steady(st + 2, wfA, xfA, wfB, xfB);
-  }
-  for (; st < Kf; st += 2) {  // the last stages, where waits and requests depend on what is left
-    if (st + 1 < Kf) {
-      open_stage(st + 1);
-      read((st + 1) % TILE_NS, wfB, xfB);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    mma(wfA, xfA);
-    if (st + 1 < Kf) {
-      if (st + 2 < Kf) {
-        open_stage(st + 2);
-        read((st + 2) % TILE_NS, wfA, xfA);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      mma(wfB, xfB);
-    }
-  }
+  for (; st + TILE_NS - 1 < Kf; ++st) k_step(st, true, TILE_NS - 2);
+  for (; st < Kf; ++st) k_step(st, false, max(Kf - 2 - st, 0));
+  if (wave < 4) bar();
 
   tile_epilogue<EPI, 4, 8>(a, acc, a.t0 + tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
 }
