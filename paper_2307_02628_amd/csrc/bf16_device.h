@@ -1,0 +1,66 @@
+// Device helpers shared by the bf16 kernels: fragment types, conversions, activation and page addressing.
+#pragma once
+#include <initializer_list>
+
+#include "once_per_device.h"
+#include "skd_kernels.h"
+
+namespace skd {
+
+// Lets the kernels use `bytes` of dynamic LDS on the current device; `done` belongs to these kernels.
+inline bool allow_lds(std::atomic<uint64_t> &done, std::initializer_list<const void *> kernels, size_t bytes) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return false;
+  return once_per_device(done, device, [&]() {
+    for (const void *k : kernels)
+      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
+    return true;
+  });
+}
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t uint32x4;
+
+// fp32 -> bf16, round to nearest even: the conversion instruction of gfx950 (v_cvt_pk_bf16_f32), which the compiler
+// emits for these casts; the same rounding in integer arithmetic takes five instructions per value.
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float floatx2;
+__device__ inline uint32_t f2bf(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ inline float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
+__device__ inline uint32_t pack2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
+}
+
+template <int N>
+__device__ inline void wait_vmcnt() {  // at most N vector-memory operations of this wave outstanding (vmcnt: bits 15:14, 3:0)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// Activations [rows][K]: 16-row x 32-column tiles in the order [row / 16][col / 32], each tile 16 rows of 64
+// contiguous bytes.  A producer that owns one row writes 64-byte runs (whole 32-byte sectors); a consumer reads a
+// tile as one MFMA B-operand fragment, lane l taking the 16 bytes at row l % 16, columns 8 * (l / 16) .. + 7,
+// i.e. 16-byte slot act_lane(l) of the 1 KiB tile.
+__device__ inline long d_act_index(long row, long col, long K) {
+  return ((row >> 4) * (K >> 5) + (col >> 5)) * 512 + (row & 15) * 32 + (col & 31);
+}
+__device__ inline int act_lane(int lane) { return (lane & 15) * 4 + (lane >> 4); }
+
+// ------------------------------------------------------------------ KV page addressing
+// Page (one batch row, one layer): [head][32-key block][K block | V block],
+// K block = [tile 0..1][chunk 0..dh/32-1][lane][8], V block = [dh/16][lane][8].
+__device__ inline long kv_block_base(int h, int tt, const KvGeom &g) {
+  return (long)h * (g.page_tokens * g.dh * 2) + (long)(tt >> 5) * (64 * g.dh);
+}
+__device__ inline long kv_k_off(int h, int tt, int e, const KvGeom &g) {
+  const int kk = tt & 31;
+  return kv_block_base(h, tt, g) +
+         ((long)((kk >> 4) * (g.dh >> 5) + (e >> 5)) * 64 + (kk & 15) + 16 * ((e & 31) >> 3)) * 8 + (e & 7);
+}
+__device__ inline long kv_v_off(int h, int tt, int e, const KvGeom &g) {
+  const int kk = tt & 31;
+  return kv_block_base(h, tt, g) + 32 * g.dh +
+         ((long)(e >> 4) * 64 + 16 * ((kk & 15) >> 2) + (e & 15)) * 8 + 4 * (kk >> 4) + (kk & 3);
+}
+
+}  // namespace skd

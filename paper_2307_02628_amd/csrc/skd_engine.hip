@@ -139,6 +139,9 @@ struct skd_state {
   int max_split = 1, attn_splits = 1, attn_waves = 4;
   bool attn_fixed = false;         // by override: the same shape at every position
   int start_min = 0;               // first real column of the longest row
+  // whole columns in one launch (narrow models)
+  bool team = false;
+  TeamArgs team_args{};            // what is the same for every column
   // batched prompt workspace (allocated by the first batched skd_prefill)
   float *pf_x = nullptr;
   float *pf_partial = nullptr;     // K parts of the prompt projections
@@ -520,6 +523,14 @@ int run_layer(skd_state *st, int l, int t, const LayerW *prev, const LayerW *nex
   return SKD_OK;
 }
 
+// Whether the list is what a schedule gives: warm-up layers, then the top of the stack.
+bool scheduled_set(const skd_state *st, const int32_t *layers, int n) {
+  const skd_config &c = st->cfg;
+  for (int i = 0; i < n; ++i)
+    if (layers[i] != (i < c.warmup ? i : c.L - n + i)) return false;
+  return n >= c.warmup;
+}
+
 // One column (all B rows at position t) through the given ascending layer list.  Everything that can refuse
 // the column (layer list, cache lengths, launch shapes) is checked before the first launch, so an error leaves
 // the caches as they were.
@@ -549,6 +560,15 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
       { ProfScope ps_(st, SKD_PROF_OTHER); f32_linear(s, (const float *)w.w2, w.b2, u, st->x, B, f, d, 0, 1); }
       st->kv_len[layers[i]] = t + 1;
     }
+  } else if (st->team && !st->profiling && scheduled_set(st, layers, n)) {  // per-kernel timing times separate kernels
+    TeamArgs ta = st->team_args;
+    ta.n = n;
+    ta.t = t;
+    ta.longest = t - st->start_min;
+    ta.tokens = tokens_dev;
+    ta.order = st->ragged ? st->order_dev : nullptr;
+    if (!bf16_team_column(s, ta)) return SKD_ERR_SHAPE;
+    for (int i = 0; i < n; ++i) st->kv_len[layers[i]] = t + 1;
   } else {
     const LayerW &w0 = st->lw[layers[0]];
     { ProfScope ps_(st, SKD_PROF_EMBED_LN); bf16_embed_ln(s, tokens_dev, st->start_dev, t, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, w0.ln1_g, w0.ln1_b, st->x, (bf16_t *)st->a, B, d, c.vocab); }
@@ -564,6 +584,62 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
 }
 
 }  // namespace
+
+// Whether a launch shape of the separate decode kernels is forced: then they are what is to run.
+static bool launch_overrides() {
+  for (const char *p : {"SKD_R_", "SKD_S_", "SKD_U_", "SKD_W_"})
+    for (const char *m : {"QKV", "OUT", "FFN1", "FFN2", "HEAD"}) {
+      char name[16];
+      snprintf(name, sizeof(name), "%s%s", p, m);
+      if (getenv(name)) return true;
+    }
+  for (const char *name : {"SKD_ATTN_WAVES", "SKD_ATTN_SPLITS", "SKD_FUSE_LN", "SKD_GEMM_WS", "SKD_WS_ROT"})
+    if (getenv(name)) return true;
+  return false;
+}
+
+// Buffers and layer table of bf16_team_column.
+static int prepare_team(skd_state *st) {
+  const skd_config &c = st->cfg;
+  const int L = c.L, d = c.d_model, f = c.ffn;
+  TeamArgs &ta = st->team_args;
+  int cus = 0;
+  HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, st->device));
+  std::vector<TeamLayer> host(L);
+  for (int l = 0; l < L; ++l) {
+    const LayerW &w = st->lw[l];
+    host[l] = TeamLayer{(const bf16_t *)w.wqkv, (const bf16_t *)w.wo, (const bf16_t *)w.w1, (const bf16_t *)w.w2, w.ln1_g, w.ln1_b,
+                        w.bqkv, w.bo, w.ln2_g, w.ln2_b, w.b1, w.b2, bt_layer(st, l)};
+  }
+  TeamLayer *layers = nullptr;
+  SKDCHECK(dev_alloc(st, &layers, L));
+  HIPCHECK(hipMemcpyAsync(layers, host.data(), L * sizeof(TeamLayer), hipMemcpyHostToDevice, st->stream));
+  SKDCHECK(dev_alloc(st, &ta.ctl, 1));
+  HIPCHECK(hipMemsetAsync(ta.ctl, 0, sizeof(TeamCtl), st->stream));
+  const size_t rows = bf16_team_rows();
+  SKDCHECK(dev_alloc(st, &ta.work.q, rows * d));
+  SKDCHECK(dev_alloc(st, &ta.work.kv, rows * 2 * d));
+  SKDCHECK(dev_alloc(st, &ta.work.o, rows * d));
+  SKDCHECK(dev_alloc(st, &ta.work.u, rows * f));
+  SKDCHECK(dev_alloc(st, &ta.work.y, rows * d));
+  SKDCHECK(dev_alloc(st, &ta.work.part, bf16_team_part()));
+  HIPCHECK(hipStreamSynchronize(st->stream));  // `host` ends here
+  ta.layers = layers;
+  ta.warmup = c.warmup; ta.L = L;
+  ta.G_qkv = st->p_qkv.R; ta.G_out = st->p_out.R; ta.G_ffn1 = st->p_ffn1.R; ta.G_ffn2 = st->p_ffn2.R;
+  ta.d = d; ta.f = f; ta.B = c.batch; ta.V = c.vocab;
+  ta.groups = bf16_team_groups(c.batch);
+  ta.workgroups = std::max(cus, 1);
+  ta.members = bf16_team_members(cus, d);
+  if (const int m = env_int("SKD_TEAM_WGS", 0); m >= 1 && m <= ta.members) ta.members = m;
+  ta.start = st->start_dev;
+  ta.tok_emb = (const bf16_t *)st->tok_emb; ta.pos_emb = (const bf16_t *)st->pos_emb;
+  ta.lnf_g = st->lnf_g; ta.lnf_b = st->lnf_b;
+  ta.pool = (bf16_t *)st->pool; ta.kv = st->geom;
+  ta.x_out = st->x; ta.a_out = (bf16_t *)st->a;
+  st->team = true;
+  return SKD_OK;
+}
 
 static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_stream, const int32_t *n_table,
                        skd_state **out) {
@@ -753,6 +829,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     A(&st->attn_part, (size_t)B * c.n_heads * c.sequence_length);
     A(&st->logits_dev, (size_t)B * V);
   }
+  if (rc == SKD_OK && st->bf16 && bf16_team_ok(d, f, B) && env_int("SKD_TEAM", 1) != 0 && !launch_overrides()) rc = prepare_team(st);
   if (rc != SKD_OK) return fail(rc);
   if (st->bf16 && !c.io_on_device) {
     const hipError_t e = hipHostMalloc((void **)&st->pin, sizeof(Pinned), hipHostMallocDefault);

@@ -229,6 +229,53 @@ void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const floa
 void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens,
                        int32_t *tokens2, int B);
 
+// A whole decode column of a narrow model in one launch (team_column.hip).
+struct TeamLayer {
+  const bf16_t *wqkv, *wo, *w1, *w2;  // fragment-major
+  const float *ln1_g, *ln1_b, *bqkv, *bo, *ln2_g, *ln2_b, *b1, *b2;
+  const int32_t *bt;                  // [B][max_pages]
+};
+constexpr int TEAM_SLOTS = 16;        // XCDs at most
+struct TeamSlot {                     // a line each: one XCD
+  uint32_t registered, team, next, pad0[29];
+  uint32_t arrived, pad1[31];
+};
+struct TeamCtl {                      // zero before the first launch; every launch leaves it zero
+  TeamSlot slot[TEAM_SLOTS];
+  uint32_t next_group, pad0[31];
+  uint32_t left, pad1[31];
+};
+struct TeamWork {                     // for 8 groups of 16 rows each
+  bf16_t *q, *kv, *o, *u;             // [16][d] | [16][k | v][d] | activation tiles [16][d] | activation tiles [16][f]
+  float *y;                           // [16][d]
+  float *part;                        // [32][132]: numerators, maximum and denominator of a share of a pair's keys
+};
+struct TeamArgs {
+  const TeamLayer *layers;            // device, all L
+  int n, warmup, L;                   // active: 0 .. warmup - 1 and L - n + warmup .. L - 1
+  int G_qkv, G_out, G_ffn1, G_ffn2;   // tile-group sizes of the layouts
+  int d, f, B, V, t;
+  int groups;                         // bf16_team_groups(B)
+  int longest;                        // cached positions of the longest row
+  int workgroups;                     // of the launch: one per CU
+  int members;                        // of a team, at most
+  const int32_t *tokens, *start, *order;  // [B]; order: rows by descending length, or null
+  const bf16_t *tok_emb, *pos_emb;
+  const float *lnf_g, *lnf_b;
+  bf16_t *pool;
+  KvGeom kv;
+  TeamWork work;
+  TeamCtl *ctl;
+  float *x_out;                       // [B][d] residual rows behind the last layer
+  bf16_t *a_out;                      // activation tiles [B_pad][d]: their final LayerNorm
+};
+bool bf16_team_ok(int d, int f, int B);
+int bf16_team_groups(int B);
+int bf16_team_members(int cus, int d);
+size_t bf16_team_rows();              // rows of each work buffer
+size_t bf16_team_part();              // floats of work.part
+bool bf16_team_column(hipStream_t s, const TeamArgs &a);
+
 // weight preparation (source fp32 or bf16 row-major, on device)
 void prep_matrix_frag(hipStream_t s, const void *src, int src_is_bf16, bf16_t *dst, long N, long K, long N_pad,
                       int G);
