@@ -241,8 +241,12 @@ __device__ inline void ln_prologue(const GemmArgs &a, bf16_t *act, float *sh, in
   bar();
 }
 
-template <int MB, int R, int EPI, int U, int WAVES, int NB = 0>
-__global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
+template <int R>
+struct RowTiles { static constexpr int value = R; };
+
+// tile0: first of the R weight tiles; group: place of this workgroup's (max, argmax) partials (LM head)
+template <int MB, int R, int EPI, int U, int WAVES, int NB>
+__device__ __forceinline__ void gemm_body(const GemmArgs &a, int tile0, int group) {
   constexpr int RM = R * MB;
   extern __shared__ floatx4 red[];  // [WAVES][RM][64 lanes]
   // The wave index is the same in all lanes.  Saying so makes the loop conditions that depend on it scalar: as
@@ -261,7 +265,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
   long woff[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int T = blockIdx.x * R + r;
+    const int T = tile0 + r;
     woff[r] = (((long)(T / a.G) * Kf + kw0) * a.G + T % a.G) * 64;
   }
   const int row0 = blockIdx.z * (MB * 16);  // chunk of activation rows (0 when decoding)
@@ -317,7 +321,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
       const int p = wave + i * WAVES;
       const int r = r0 + p / MB, m = p % MB;
       if (p < RS * MB && r < R)
-        pre[i] = epi_prefetch<EPI>(a, row0 + m * 16 + (lane & 15), (blockIdx.x * R + r) * 16 + 4 * (lane >> 4));
+        pre[i] = epi_prefetch<EPI>(a, row0 + m * 16 + (lane & 15), (tile0 + r) * 16 + 4 * (lane >> 4));
     }
   };
   if constexpr (EARLY) fetch_pre(0);
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
       if (p < RS * MB && r < R) {
         floatx4 v = red[p * 64 + lane];
         for (int w = 1; w < WAVES; ++w) v += red[(w * (RS * MB) + p) * 64 + lane];
-        const int n0 = (blockIdx.x * R + r) * 16 + 4 * (lane >> 4);
+        const int n0 = (tile0 + r) * 16 + 4 * (lane >> 4);
         if constexpr (EPI != EPI_LOGITS) {
           gemm_epilogue<EPI>(a, row0 + m * 16 + (lane & 15), n0, v, pre[i]);
         } else {
@@ -422,13 +426,59 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
         const int oi = ci[(r * MB + m) * 16 + c];
         if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
       }
-      a.pmax[(long)blockIdx.x * a.B_pad + m * 16 + c] = best;
-      a.pidx[(long)blockIdx.x * a.B_pad + m * 16 + c] = bi;
+      a.pmax[(long)group * a.B_pad + m * 16 + c] = best;
+      a.pidx[(long)group * a.B_pad + m * 16 + c] = bi;
     }
   }
 }
 
+// The LM head is several rounds of workgroups, and 16 R rows of a vocabulary of 50272 are 3.07 workgroups per CU: with equal
+// ones the last round keeps a few CUs busy for as long as a full one.  So whole rounds get R tiles, what is left of a round
+// one size of fewer, and the remainder single tiles (head_tiles; a logit is the same sum whatever group its tile is in).
+// us with the argmax, 50272 x 4096, equal groups -> this, 16, 32, 48, 64, 96 and 128 rows: 75 -> 71, 83 -> 77, 92 -> 84,
+// 106 -> 97, 130 -> 122, 146 -> 137; 50272 x 2048: 41 -> 40, 47 -> 45, 53 -> 50, 64 -> 59, 78 -> 71, 90 -> 83; 32000 rows are
+// 1.95 rounds either way.
+template <int R, typename F>
+__device__ __forceinline__ void head_dispatch(const GemmArgs &a, F body) {
+  const int id = blockIdx.x, mid = id - a.head_full, rest = mid - a.head_mid;
+  if (mid < 0) { body(RowTiles<R>{}, id * R); return; }
+  const int mid0 = a.head_full * R;
+  if (rest >= 0) { body(RowTiles<1>{}, mid0 + a.head_mid * a.head_mid_r + rest); return; }
+  if constexpr (R > 3) if (a.head_mid_r == 3) { body(RowTiles<3>{}, mid0 + mid * 3); return; }
+  if constexpr (R > 2) body(RowTiles<2>{}, mid0 + mid * 2);
+}
+
+template <int MB, int R, int EPI, int U, int WAVES, int NB = 0>
+__global__ __launch_bounds__(WAVES * 64) void k_gemm(GemmArgs a) {
+  if constexpr (EPI == EPI_LOGITS)
+    head_dispatch<R>(a, [&](auto r, int tile0) { gemm_body<MB, decltype(r)::value, EPI, U, WAVES, NB>(a, tile0, blockIdx.x); });
+  else
+    gemm_body<MB, R, EPI, U, WAVES, NB>(a, blockIdx.x * R, blockIdx.x);
+}
+
 int bf16_gemm_groups(int N, int R) { return (N + 16 * R - 1) / (16 * R); }
+// Workgroups of the LM head: a.head_full of R tiles, a.head_mid of a.head_mid_r, the rest of one.  slots: workgroups that run
+// at once; 0: equal groups.
+int bf16_head_tiles(GemmArgs &a, int R, int slots) {
+  const int tiles = (a.N + 15) / 16;
+  a.head_full = bf16_gemm_groups(a.N, R);
+  a.head_mid = a.head_mid_r = 0;
+  if (slots <= 0 || tiles <= R * slots) return a.head_full;
+  a.head_full = tiles / (R * slots) * slots;
+  int rest = tiles - a.head_full * R;
+  int r = rest / slots;
+  const bool whole = rest - r * slots <= slots / 2;  // a round of r and a few single tiles, or a round of r + 1 that is not full
+  if (!whole) ++r;
+  if (r >= R) {
+    a.head_full += rest / R;
+    rest %= R;
+  } else if (r > 1) {  // (one tile each: the last sort)
+    a.head_mid_r = r;
+    a.head_mid = whole ? slots : rest / r;
+    rest -= r * a.head_mid;
+  }
+  return a.head_full + a.head_mid + rest;
+}
 
 template <int MB, int R, int U, int WAVES>
 static void launch_gemm_epi(hipStream_t s, const GemmArgs &a, int epi, dim3 grid) {
@@ -511,6 +561,19 @@ int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epi, int R) {
   return rc < 0 ? -1 : groups;
 }
 
+// Every tile of the vocabulary in exactly one group of a size that is compiled; the last group of R may run over the end.
+static int bf16_head_groups(const GemmArgs &a) {
+  const int tiles = (a.N + 15) / 16, R = a.G;
+  const int left = tiles - a.head_full * R - a.head_mid * a.head_mid_r;
+  return a.head_full + a.head_mid + (left > 0 ? left : 0);
+}
+static bool head_shape(const GemmArgs &a, int R) {
+  if (a.G != R || a.head_full < 0 || a.head_mid < 0) return false;
+  if (a.head_mid && (a.head_mid_r < 2 || a.head_mid_r >= R)) return false;
+  const long covered = (long)a.head_full * R + (long)a.head_mid * a.head_mid_r, tiles = (a.N + 15) / 16;
+  return covered < tiles + R && (covered <= tiles || a.head_mid == 0);
+}
+
 // Batch tiles of 16 rows are compiled for B_pad in {16, 32, 48, 64, 96, 128}.
 // Launch shape of a skinny GEMM, or false if the kernel cannot run it: nothing is launched here.
 static bool gemm_shape(const GemmArgs &a, int epi, int R, int &U, int waves, dim3 &grid, int &groups) {
@@ -523,7 +586,8 @@ static bool gemm_shape(const GemmArgs &a, int epi, int R, int &U, int waves, dim
   if (split < 1 || Kf % split) return false;  // equal K ranges per workgroup
   while (U > 1 && (Kf / split) % U) U >>= 1;  // whole buffers only
   if (U < 1) return false;
-  groups = bf16_gemm_groups(a.N, R);
+  groups = epi == EPI_LOGITS ? bf16_head_groups(a) : bf16_gemm_groups(a.N, R);
+  if (epi == EPI_LOGITS && !head_shape(a, R)) return false;
   const bool by_rows = epi == EPI_QKV_ROWS || epi == EPI_RESID || (epi == EPI_RELU && a.rows > 0);
   if (epi == EPI_RESID && MB != 8) return false;
   if ((epi == EPI_QKV_ROWS || epi == EPI_RESID) && a.rows <= 0) return false;
@@ -572,7 +636,7 @@ constexpr int WS_CW = 4;  // MFMA waves = loader waves = k-steps per stage
 // MB: batch tiles, 6 or 8
 
 template <int MB, int R, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
+__device__ __forceinline__ void gemm_ws_body(const GemmArgs &a, int tile0, int group) {
   constexpr int NS = WS_NS;
   constexpr int STAGE = WS_CW * MB * 64;     // bf16x8 units per stage (24 or 32 KiB)
   extern __shared__ bf16x8 ws_lds[];         // ring [NS][WS_CW][MB][64 lanes]; later the reduction buffer
@@ -629,7 +693,7 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
     long wbase[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int T = blockIdx.x * R + r;
+      const int T = tile0 + r;
       wbase[r] = (((long)(T / a.G) * Kf + kw0 + wave) * a.G + T % a.G) * 64;
     }
     const long cstride = (long)a.G * 64 * WS_CW;  // one stage further along K
@@ -691,7 +755,7 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     const int p = wave + i * NW;
-    if (p < R * MB) pre[i] = epi_prefetch<EPI>(a, (p % MB) * 16 + (lane & 15), (blockIdx.x * R + p / MB) * 16 + 4 * (lane >> 4));
+    if (p < R * MB) pre[i] = epi_prefetch<EPI>(a, (p % MB) * 16 + (lane & 15), (tile0 + p / MB) * 16 + 4 * (lane >> 4));
   }
   __syncthreads();
   float cand_v[NP];
@@ -703,7 +767,7 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
     if (p < R * MB) {
       floatx4 v = red[p * 64 + lane];
       for (int w = 1; w < WS_CW; ++w) v += red[(w * (R * MB) + p) * 64 + lane];
-      const int n0 = (blockIdx.x * R + r) * 16 + 4 * (lane >> 4);
+      const int n0 = (tile0 + r) * 16 + 4 * (lane >> 4);
       if constexpr (EPI != EPI_LOGITS) {
         gemm_epilogue<EPI>(a, m * 16 + (lane & 15), n0, v, pre[i]);
       } else {
@@ -748,10 +812,18 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
         const int oi = ci[(r * MB + m) * 16 + c];
         if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
       }
-      a.pmax[(long)blockIdx.x * a.B_pad + m * 16 + c] = best;
-      a.pidx[(long)blockIdx.x * a.B_pad + m * 16 + c] = bi;
+      a.pmax[(long)group * a.B_pad + m * 16 + c] = best;
+      a.pidx[(long)group * a.B_pad + m * 16 + c] = bi;
     }
   }
+}
+
+template <int MB, int R, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
+  if constexpr (EPI == EPI_LOGITS)
+    head_dispatch<R>(a, [&](auto r, int tile0) { gemm_ws_body<MB, decltype(r)::value, EPI>(a, tile0, blockIdx.x); });
+  else
+    gemm_ws_body<MB, R, EPI>(a, blockIdx.x * R, blockIdx.x);
 }
 
 // Decode projections at 96 or 128 (padded) batch rows on the wave-specialised kernel.  Returns the number of row groups,
@@ -762,7 +834,8 @@ static bool gemm_ws_shape(const GemmArgs &a, int epi, int R, dim3 &grid, int &gr
   const int split = epi == EPI_LOGITS ? 1 : a.split;
   const int Kf = a.K / 32;
   if (split < 1 || Kf % split || (Kf / split) % WS_CW || Kf / split < WS_CW) return false;
-  groups = bf16_gemm_groups(a.N, R);
+  groups = epi == EPI_LOGITS ? bf16_head_groups(a) : bf16_gemm_groups(a.N, R);
+  if (epi == EPI_LOGITS && !head_shape(a, R)) return false;
   grid = dim3(groups, split, 1);
   return true;
 }

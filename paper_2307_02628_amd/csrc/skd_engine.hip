@@ -66,6 +66,7 @@ struct GemmPlan {
   int R = 1, split = 1, U = 1, waves = 8;
   bool ws = false;  // 96 and 128 batch rows: the wave-specialised kernel (weight-streaming waves + activation-loading waves)
   int ws_rot = 0;   // workgroups start their K range at different stages
+  int slots = 0;    // LM head: workgroups that run at once (bf16_head_tiles)
 };
 
 }  // namespace
@@ -276,6 +277,16 @@ GemmPlan plan_direct(int N, int B_pad) {  // whole K inside the workgroup
   }
   return p;
 }
+// The LM head of a large vocabulary: whole rounds of 256 workgroups of 4 tiles, smaller ones for what is left (head_dispatch
+// in kernels_bf16.hip).  Four tiles at 16 rows too: 50272 x 4096, us with the argmax, 2 tiles 75, 4 tiles 71.
+GemmPlan plan_head(int V, int B_pad) {
+  GemmPlan p = plan_direct(V, B_pad);
+  if (bf16_gemm_groups(V, 4) >= 256) {
+    p.R = 4;
+    p.slots = 256;
+  }
+  return p;
+}
 GemmPlan plan_split(int N, int K, int B_pad) {  // partial sums, reduced by the LayerNorm kernel
   GemmPlan p;
   p.waves = plan_waves(B_pad);
@@ -444,6 +455,7 @@ bool decode_shapes_ok(const skd_state *st) {
   ga.B = c.batch; ga.B_pad = st->B_pad;
   auto ok = [&](int N, int K, const GemmPlan &p, int epi) {
     ga.N = N; ga.K = K; ga.G = p.R; ga.split = p.split;
+    if (epi == EPI_LOGITS) bf16_head_tiles(ga, p.R, p.slots);
     return check_gemm(ga, epi, p) > 0;
   };
   auto ok_ln = [&](int N, const GemmPlan &p, const GemmPlan &before, int epi) {  // behind the partial sums of `before`
@@ -683,7 +695,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     const int Bp = st->B_pad;
     st->p_qkv = plan_direct(3 * d, Bp);
     st->p_ffn1 = plan_direct(f, Bp);
-    st->p_head = plan_direct(V, Bp);
+    st->p_head = plan_head(V, Bp);
     st->p_out = plan_split(d, d, Bp);
     st->p_ffn2 = plan_split(d, f, Bp);
     ov("SKD_R_QKV", st->p_qkv.R, 1, 4); ov("SKD_R_FFN1", st->p_ffn1.R, 1, 4); ov("SKD_R_HEAD", st->p_head.R, 1, 4);
@@ -719,6 +731,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     ga.B = B; ga.B_pad = st->B_pad;
     auto pick = [&](int N, int K, GemmPlan &p, int epi) {
       ga.N = N; ga.K = K; ga.G = p.R; ga.split = p.split;
+      if (epi == EPI_LOGITS) bf16_head_tiles(ga, p.R, 0);
       p.ws = bf16_gemm_ws_check(ga, epi, p.R) > 0;
       // rotated K start: pays while the XCD's L2 (4 MiB) holds the activation matrix beside the weight stream
       // (measured at 128 x 4096: FFN1 35.5 -> 33.7 us; at 128 x 16384, 4 MiB, FFN2 36.3 -> 38.8 us)
@@ -817,7 +830,9 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     A(&st->kv_new, (size_t)B * 2 * d);
     A(&st->partial, (size_t)st->max_split * Bp * d);
     A(&st->attn_part, (size_t)st->attn_splits * B * c.n_heads * (st->dh + 2));
-    const int groups = bf16_gemm_groups(V, st->p_head.R);
+    GemmArgs ga{};
+    ga.N = V;
+    const int groups = std::max(bf16_head_tiles(ga, st->p_head.R, st->p_head.slots), bf16_gemm_groups(V, st->p_head.R));
     A(&st->pmax, (size_t)groups * Bp); A(&st->pidx, (size_t)groups * Bp);
     A(&st->logits_dev, (size_t)B * V);
   } else {
@@ -1172,7 +1187,7 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
     GemmArgs ga{};
     ga.B = B; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;  // a = final LayerNorm output
     ga.N = V; ga.K = d; ga.split = 1; ga.logits = logits_target; ga.pmax = st->pmax; ga.pidx = st->pidx;
-    int groups = 0;
+    int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);
     { ProfScope ps_(st, SKD_PROF_LM_HEAD); groups = launch_gemm(s, ga, EPI_LOGITS, st->p_head); }
     if (groups < 0) return SKD_ERR_SHAPE;
     if (want_argmax) { ProfScope ps_(st, SKD_PROF_ARGMAX); bf16_argmax_final(s, st->pmax, st->pidx, groups, st->B_pad, st->argmax_dev, tokens_target, B); }
@@ -1223,16 +1238,18 @@ extern "C" int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, flo
   if (!st->have_hidden) return SKD_ERR_ORDER;
   const skd_config &c = st->cfg;
   if (!st->bf16 || !c.io_on_device) return SKD_ERR_SHAPE;
-  const int groups = bf16_gemm_groups(c.vocab, st->p_head.R);
+  GemmArgs ga{};
+  ga.N = c.vocab;
+  int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);
+  if ((int64_t)groups * st->B_pad > SKD_NOALLOC_MAX_PARTIALS) groups = bf16_head_tiles(ga, st->p_head.R, 0);  // fewer, equal ones
   if ((int64_t)groups * st->B_pad > SKD_NOALLOC_MAX_PARTIALS) return SKD_ERR_RANGE;  // beyond the static scratch
   void *base = (st->device >= 0 && st->device < kMaxDevices) ? g_scratch_ptr[st->device] : nullptr;
   if (!base) return SKD_ERR_ORDER;  // resolved by skd_create on the state's device
   float *pmax = (float *)base;
   int32_t *pidx = (int32_t *)((unsigned char *)base + 4 * (size_t)SKD_NOALLOC_MAX_PARTIALS);
   hipStream_t s = st->stream;
-  GemmArgs ga{};
   ga.B = c.batch; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;
-  ga.N = c.vocab; ga.K = c.d_model; ga.split = 1; ga.logits = logits_out; ga.pmax = pmax; ga.pidx = pidx;
+  ga.K = c.d_model; ga.split = 1; ga.logits = logits_out; ga.pmax = pmax; ga.pidx = pidx;
   if (check_gemm(ga, EPI_LOGITS, st->p_head) != groups) return SKD_ERR_SHAPE;
   // every partial the final reduction reads is written by the projection of this same call: nothing to clear
   (void)launch_gemm(s, ga, EPI_LOGITS, st->p_head);

@@ -154,6 +154,7 @@ struct GemmArgs {
   float *ln_x_out;
   int ln_split;
   float *logits;       // EPI_LOGITS (nullable)
+  int head_full, head_mid, head_mid_r;  // EPI_LOGITS: workgroups of R = G tiles, of head_mid_r; then single tiles (bf16_head_tiles)
   float *pmax;         // EPI_LOGITS: [groups][B_pad]
   int32_t *pidx;       // EPI_LOGITS
 };
@@ -168,6 +169,8 @@ int bf16_gemm_ln_check(const GemmArgs &a, int epilogue, int R);
 // The same shape checks without a launch (only N, K, B_pad, G, split and rows of `a` are read): groups or -1.
 int bf16_gemm_check(const GemmArgs &a, int epilogue, int R, int U, int waves);
 int bf16_gemm_groups(int N, int R);
+// Sets head_* of `a` for workgroups of R tiles of which `slots` run at once (0: equal groups) and returns their number.
+int bf16_head_tiles(GemmArgs &a, int R, int slots);
 // Decode projections with B_pad = 96 or 128 on the wave-specialised kernel (weight-streaming waves + activation-loading
 // waves); (K / 32 / split) must be a multiple of 4.  Returns the row groups launched, or -1 (nothing launched) for
 // shapes it does not handle; bf16_gemm_ws_check answers the same without launching.
