@@ -153,37 +153,111 @@ constexpr int SAMPLE_C = 64;
 constexpr int SAMPLE_CAND = 4096;  // candidates that four waves finish, 16 per lane
 constexpr int SAMPLE_MID = 1024;   // tokens between the bounds of the threshold that one wave searches, 16 per lane
 
+// Sums over each row of 16 lanes, the same value in every lane of the row (the pairs that are added are the same seen
+// from each lane, so the float result is too).
+__device__ inline int row_sum_i(int v) {
+#define SKD_ROR(n) v += __builtin_amdgcn_mov_dpp(v, 0x120 + n, 0xF, 0xF, true)
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  return v;
+}
+__device__ inline int wave_sum_i(int v) {  // the same value in every lane, as wave_sum_f
+  v = row_sum_i(v);
+  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) + (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+__device__ inline float row_sum_f(float v) {
+#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  return v;
+}
+
 struct SampleExchange {  // LDS of the finishing waves
-  float sums[2][4];      // one set per round in turn
+  float sums[2][4];
   int pick[4], tail[4];
+  float mass[2][16];  // sample_search: one set per round in turn
+  int count[2][16];
 };
-// The rest of a row on its C <= 64 PER NW candidates (ascending index), by the first NW (1 or 4) waves of the workgroup:
-// threshold bit by bit, then the draw.
+// The threshold among C <= 64 PER candidates, by all 16 waves: every wave holds all of them and sums the masses at or above
+// a trial value of its own, so a round divides the interval [lo, hi) by 17; it ends where one candidate is left in it
+// (ties: where its bits are known).  One wave alone, two bits a round, took 8.6 us for 260 to 820 candidates.
+template <int PER>
+__device__ inline unsigned sample_search(const float *cand_p, int C, unsigned lo, unsigned hi, float target, SampleExchange &ex) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float v[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = 64 * j + lane < C ? cand_p[64 * j + lane] : 0.f;
+  int c_lo = C, c_hi = -1;  // candidates at or above lo, hi (-1: not counted)
+  for (int set = 0; hi - lo > 1 && (c_hi < 0 || c_lo - c_hi > 1); set ^= 1) {
+    // ascending with the wave; the largest lies above lo and none reaches hi, so the interval shrinks
+    const unsigned q = (hi - lo) / 17, r = (hi - lo) % 17;
+    auto trial = [&](int k) { return lo + q * (k + 1) + r * (k + 1) / 17; };
+    const unsigned t = trial(w);
+    float m = 0.f;
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const bool in = __float_as_uint(v[j]) >= t;
+      m += in ? v[j] : 0.f;
+      c += in ? 1 : 0;
+    }
+    m = wave_sum_f(m);
+    c = wave_sum_i(c);
+    if (lane == 0) {
+      ex.mass[set][w] = m;
+      ex.count[set][w] = c;
+    }
+    __syncthreads();  // (a set is written again two rounds later)
+    const float mk = ex.mass[set][lane & 15];
+    const int ck = ex.count[set][lane & 15];
+    // descending with the wave: sums of the same terms in the same order, fewer of them
+    const int K = __popcll(__ballot(mk >= target) & 0xffffull);
+    if (K < 16) {
+      hi = trial(K);
+      c_hi = __builtin_amdgcn_readlane(ck, K);
+    }
+    if (K > 0) {
+      const unsigned at = trial(K - 1);
+      c_lo = __builtin_amdgcn_readlane(ck, K - 1);
+      lo = at;
+    }
+  }
+  return lo;
+}
+// The rest of a row on its C <= 64 PER NW candidates (ascending index), by the first NW (1 or 4) waves of the workgroup: the
+// draw among those at or above the threshold, which one wave is given (T) and four find bit by bit (16 candidates a lane keep
+// the SIMDs busy; dividing by 17 would take more work than it saves rounds: 9000 tokens of a flat row 42 -> 45 us).
 template <int PER, int NW>
 __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int C, unsigned lower, unsigned upper,
-                                     float target, float u, int32_t *token, int32_t *token2, SampleExchange &ex) {
+                                     float target, unsigned T, float u, int32_t *token, int32_t *token2, SampleExchange &ex) {
   const int lane = threadIdx.x & 63, w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c0 = (w * 64 + lane) * PER;  // this lane's candidates c0 .. c0 + PER - 1 (index order)
   float v[PER];
 #pragma unroll
   for (int j = 0; j < PER; ++j) v[j] = c0 + j < C ? cand_p[c0 + j] : 0.f;
   int set = 0;
-  unsigned T = 0;
-  for (int bit = 29; bit >= 0; --bit) {
-    const unsigned cand = T | (1u << bit);
-    if (cand >= upper) continue;
-    if (cand <= lower) { T = cand; continue; }
-    float m = 0;
+  if constexpr (NW > 1) {
+    T = 0;
+    for (int bit = 29; bit >= 0; --bit) {
+      const unsigned cand = T | (1u << bit);
+      if (cand >= upper) continue;
+      if (cand <= lower) { T = cand; continue; }
+      float m = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) m += (__float_as_uint(v[j]) >= cand) ? v[j] : 0.f;
-    m = wave_sum_f(m);
-    if constexpr (NW > 1) {
+      for (int j = 0; j < PER; ++j) m += (__float_as_uint(v[j]) >= cand) ? v[j] : 0.f;
+      m = wave_sum_f(m);
       set ^= 1;
       if (lane == 0) ex.sums[set][w] = m;
       __syncthreads();  // the set is written again two rounds later, after the next round's barrier
       m = (ex.sums[set][0] + ex.sums[set][1]) + (ex.sums[set][2] + ex.sums[set][3]);
+      if (m >= target) T = cand;
     }
-    if (m >= target) T = cand;
   }
   float lm = 0;
   int last = -1;
@@ -247,15 +321,46 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
   }
 }
 
+// The same for at most 64 candidates, one per lane: a candidate is in the nucleus if those more likely than it have less
+// than the target mass.
+__device__ inline void sample_finish_few(const float *cand_p, const int *cand_i, int C, float target, float u, int32_t *token, int32_t *token2) {
+  const int lane = threadIdx.x & 63;
+  float v = lane < C ? cand_p[lane] : 0.f;
+  const int tok = lane < C ? cand_i[lane] : 0;
+  float above = 0.f;
+  for (int k = 0; k < C; ++k) {
+    const float o = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
+    above += o > v ? o : 0.f;
+  }
+  if (!(above < target)) v = 0.f;
+  float run = v;  // inclusive prefix in index order
+  for (int off = 1; off < 64; off <<= 1) {
+    const float t = __shfl_up(run, off);
+    if (lane >= off) run += t;
+  }
+  const float goal = u * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, run), 63));
+  const unsigned long long in = __ballot(v > 0.f), over = __ballot(v > 0.f && run > goal);
+  // (rounding at the very end: the last member; no member where the masses are not numbers: token 0)
+  const int k = over ? (int)__builtin_ctzll(over) : in ? 63 - (int)__builtin_clzll(in) : -1;
+  if (lane == max(k, 0)) {
+    *token = k >= 0 ? tok : 0;
+    if (token2) *token2 = k >= 0 ? tok : 0;
+  }
+}
+
 __device__ __forceinline__ void sample_rest(const float *cand_p, const int *cand_i, int C, unsigned lower, unsigned upper, float target,
                                    const float *u, int b, int32_t *tokens, int32_t *tokens2, SampleExchange &ex) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (C <= 256) {
-    if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+  if (C <= 64) {
+    if (w == 0) sample_finish_few(cand_p, cand_i, C, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr);
+  } else if (C <= 256) {
+    const unsigned T = sample_search<4>(cand_p, C, lower, upper, target, ex);
+    if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, T, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
   } else if (C <= 1024) {
-    if (w == 0) sample_finish<16, 1>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+    const unsigned T = sample_search<16>(cand_p, C, lower, upper, target, ex);
+    if (w == 0) sample_finish<16, 1>(cand_p, cand_i, C, lower, upper, target, T, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
   } else if (w < 4) {  // the barriers in there are those of the waves that remain
-    sample_finish<16, 4>(cand_p, cand_i, C, lower, upper, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
+    sample_finish<16, 4>(cand_p, cand_i, C, lower, upper, target, 0u, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
   }
 }
 
@@ -264,36 +369,11 @@ __device__ __forceinline__ void sample_rest(const float *cand_p, const int *cand
 // above the lowest of four bounds that no more than sc.cap of them reach (with one bound for all, 2^-10, any chunk with
 // more than 512 tokens above it sent its row back to a single workgroup).  A factor of 0.99 covers the rounding of expf.
 // One workgroup per row read and exponentiated 200 KB on one of 256 CUs: 50272 tokens, 32 rows, 46 us for everything;
-// 18 us for both kernels.
+// 18 us for both kernels (8 and 10).
 constexpr int SAMPLE_CHUNK = 4096;
 constexpr int SAMPLE_BOUNDS = 4;
 // 2^-first, 2^-(first + 3), .. of the chunk's maximum; first = 4 or, for nuclei that reach deep (top_p above 0.97), 10
 __device__ inline float sample_bound(int first, int j) { return __uint_as_float((127u - (first + 3u * j)) << 23); }
-// Sums over each row of 16 lanes, the same value in every lane of the row (the pairs that are added are the same seen
-// from each lane, so the float result is too).
-__device__ inline int row_sum_i(int v) {
-#define SKD_ROR(n) v += __builtin_amdgcn_mov_dpp(v, 0x120 + n, 0xF, 0xF, true)
-  SKD_ROR(8);
-  SKD_ROR(4);
-  SKD_ROR(2);
-  SKD_ROR(1);
-#undef SKD_ROR
-  return v;
-}
-__device__ inline int wave_sum_i(int v) {  // the same value in every lane, as wave_sum_f
-  v = row_sum_i(v);
-  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) + (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
-}
-__device__ inline float row_sum_f(float v) {
-#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
-  SKD_ROR(8);
-  SKD_ROR(4);
-  SKD_ROR(2);
-  SKD_ROR(1);
-#undef SKD_ROR
-  return v;
-}
-
 template <int NW>  // waves
 __global__ __launch_bounds__(NW * 64) void k_sample_chunk(const float *logits, int V, float inv_temp, SampleScratch sc) {
   constexpr int NR = SAMPLE_CHUNK / (64 * NW);  // tokens per lane
@@ -411,7 +491,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   bool known = false;  // (uniform) mx, target and s from the first pass
   if constexpr (RC <= 52) if (sc.chunks) {  // the first pass's candidates, if they hold the target mass
     constexpr int NK = (SAMPLE_CHUNK_CAND + 1023) / 1024;
-    __shared__ int kw[NK][16];
+    __shared__ int kw[16];
     // lane 16 r + c of every wave holds chunk c: no barrier
     const int c16 = lane & 15;
     const bool have = c16 < sc.chunks;
@@ -434,11 +514,12 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
       // every token of the row at or above beta (and 1 % for rounding) is among the candidates
       beta = fmaxf(1.01f * beta, 0x1p-40f);
       const float bound[3] = {fmaxf(0x1p-5f, beta), fmaxf(0x1p-10f, beta), beta};
+      // four consecutive candidates per thread: index order is thread order
       float pc[NK], q[3] = {};
       int ic[NK];
 #pragma unroll
       for (int k = 0; k < NK; ++k) {
-        const int i = tid + 1024 * k;
+        const int i = NK * tid + k;
         pc[k] = 0;
         ic[k] = 0;
         if (i < N) {
@@ -460,44 +541,43 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
         q[j] = wave_sum_f(q[j]);
         if (lane == 0) mass_at[j][wave] = q[j];
       }
+      {  // how many candidates reach each bound, 10 bits each (a wave has 256)
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) c += __popcll(__ballot(pc[k] >= bound[j])) << (10 * j);
+        if (lane == 0) kw[wave] = c;
+      }
       __syncthreads();
       // the highest bound whose upper set has the target mass, and the next one above it, which has not
-      bool enough = false;
+      int at_bound = -1;
       s.upper = 1u << 30;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const float sum = row_sum_f(mass_at[j][lane & 15]);
-        if (enough) continue;
+        if (at_bound >= 0) continue;
         if (sum >= target) {
-          enough = true;
+          at_bound = j;
           s.lower = __float_as_uint(bound[j]);
         } else {
           s.upper = __float_as_uint(bound[j]);
           s.above = sum;
         }
       }
-      if (__builtin_amdgcn_readfirstlane(enough)) {  // uniform: every thread has the same sums
-        unsigned long long in[NK];
+      at_bound = __builtin_amdgcn_readfirstlane(at_bound);  // uniform: every thread has the same sums
+      if (at_bound >= 0) {
+        const int c = (kw[lane & 15] >> (10 * at_bound)) & 1023;
+        const int C = __builtin_amdgcn_readfirstlane(row_sum_i(c));
+        int at = row_sum_i((lane & 15) < wave ? c : 0);
 #pragma unroll
-        for (int k = 0; k < NK; ++k) {
-          in[k] = __ballot(__float_as_uint(pc[k]) >= s.lower);
-          if (lane == 0) kw[k][wave] = __popcll(in[k]);
-        }
-        __syncthreads();
-        int C = 0, at[NK];
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-          const int c = kw[k][lane & 15];
-          at[k] = C + row_sum_i((lane & 15) < wave ? c : 0);
-          C += row_sum_i(c);
-        }
-        C = __builtin_amdgcn_readfirstlane(C);
+        for (int k = 0; k < NK; ++k) at += __popcll(__ballot(__float_as_uint(pc[k]) >= s.lower) & ((1ull << lane) - 1ull));
 #pragma unroll
         for (int k = 0; k < NK; ++k)
           if (__float_as_uint(pc[k]) >= s.lower) {
-            const int j = at[k] + __popcll(in[k] & ((1ull << lane) - 1ull));
-            cand_p[j] = pc[k];
-            cand_i[j] = ic[k];
+            cand_p[at] = pc[k];
+            cand_i[at] = ic[k];
+            ++at;
           }
         __syncthreads();
         sample_rest(cand_p, cand_i, C, __builtin_amdgcn_readfirstlane(s.lower), __builtin_amdgcn_readfirstlane(s.upper), target, u, b, tokens, tokens2, ex);
