@@ -83,7 +83,7 @@ struct StateTimer final : LaunchTimer {
 };
 
 // Pinned host memory of a bf16 state with host buffers: the kernels read tokens and uniform numbers from it and write
-// tokens to it, and small logits are copied into it, so that a call needs one wait instead of one per copy.  Every call
+// tokens to it, and small logits are written or copied into it, so that a call needs one wait instead of one per copy.  Every call
 // waits for its work before it returns, so the next one finds the buffers free.
 constexpr size_t kPinnedLogits = 1 << 20;  // bytes; larger logits are copied to the caller's memory directly
 struct Pinned {
@@ -143,6 +143,7 @@ struct skd_state {
   // whole columns in one launch (narrow models)
   bool team = false;
   TeamArgs team_args{};            // what is the same for every column
+  std::vector<unsigned char> team_table;  // source of the copy at the head of its buffers
   // batched prompt workspace (allocated by the first batched skd_prefill)
   float *pf_x = nullptr;
   float *pf_partial = nullptr;     // K parts of the prompt projections
@@ -617,26 +618,26 @@ static int prepare_team(skd_state *st) {
   TeamArgs &ta = st->team_args;
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, st->device));
-  std::vector<TeamLayer> host(L);
+  // one allocation and one copy: control words (zero) and layer table, then the work buffers
+  const size_t rows = bf16_team_rows(), head = sizeof(TeamCtl) + (L * sizeof(TeamLayer) + 255) / 256 * 256;
+  const size_t n16[] = {rows * d, rows * 2 * d, rows * d, rows * f}, n32[] = {rows * d, bf16_team_part()};  // multiples of 128 each
+  unsigned char *base = nullptr;
+  SKDCHECK(dev_alloc(st, &base, head + 2 * (n16[0] + n16[1] + n16[2] + n16[3]) + 4 * (n32[0] + n32[1])));
+  st->team_table.assign(head, 0);
+  TeamLayer *host = (TeamLayer *)(st->team_table.data() + sizeof(TeamCtl));
   for (int l = 0; l < L; ++l) {
     const LayerW &w = st->lw[l];
     host[l] = TeamLayer{(const bf16_t *)w.wqkv, (const bf16_t *)w.wo, (const bf16_t *)w.w1, (const bf16_t *)w.w2, w.ln1_g, w.ln1_b,
                         w.bqkv, w.bo, w.ln2_g, w.ln2_b, w.b1, w.b2, bt_layer(st, l)};
   }
-  TeamLayer *layers = nullptr;
-  SKDCHECK(dev_alloc(st, &layers, L));
-  HIPCHECK(hipMemcpyAsync(layers, host.data(), L * sizeof(TeamLayer), hipMemcpyHostToDevice, st->stream));
-  SKDCHECK(dev_alloc(st, &ta.ctl, 1));
-  HIPCHECK(hipMemsetAsync(ta.ctl, 0, sizeof(TeamCtl), st->stream));
-  const size_t rows = bf16_team_rows();
-  SKDCHECK(dev_alloc(st, &ta.work.q, rows * d));
-  SKDCHECK(dev_alloc(st, &ta.work.kv, rows * 2 * d));
-  SKDCHECK(dev_alloc(st, &ta.work.o, rows * d));
-  SKDCHECK(dev_alloc(st, &ta.work.u, rows * f));
-  SKDCHECK(dev_alloc(st, &ta.work.y, rows * d));
-  SKDCHECK(dev_alloc(st, &ta.work.part, bf16_team_part()));
-  HIPCHECK(hipStreamSynchronize(st->stream));  // `host` ends here
-  ta.layers = layers;
+  HIPCHECK(hipMemcpyAsync(base, st->team_table.data(), head, hipMemcpyHostToDevice, st->stream));  // create waits for it
+  ta.ctl = (TeamCtl *)base;
+  ta.layers = (const TeamLayer *)(base + sizeof(TeamCtl));
+  base += head;
+  bf16_t **p16[] = {&ta.work.q, &ta.work.kv, &ta.work.o, &ta.work.u};
+  for (int i = 0; i < 4; base += 2 * n16[i++]) *p16[i] = (bf16_t *)base;
+  ta.work.y = (float *)base;
+  ta.work.part = (float *)(base + 4 * n32[0]);
   ta.warmup = c.warmup; ta.L = L;
   ta.G_qkv = st->p_qkv.R; ta.G_out = st->p_out.R; ta.G_ffn1 = st->p_ffn1.R; ta.G_ffn2 = st->p_ffn2.R;
   ta.d = d; ta.f = f; ta.B = c.batch; ta.V = c.vocab;
@@ -1196,19 +1197,26 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
   return SKD_OK;
 }
 
-// Host buffers: waits for the head and hands its results over.
-static int head_results(skd_state *st, int32_t *tokens_out, float *logits_out) {
+// Whether logits go through the pinned buffer.  The argmax head's kernels write them there themselves (nothing on the device
+// reads them again): the copy behind them took 2 us of a step of 61 with 1 or 2 rows of 1000, 7 to 10 of 70 to 100 with 8
+// to 128.  Larger ones, and those that the sampler reads, are written to device memory and copied.
+static bool pin_logits(const skd_state *st) {
+  return st->pin && (size_t)st->cfg.batch * st->cfg.vocab * sizeof(float) <= kPinnedLogits;
+}
+
+// Host buffers: waits for the head and hands its results over.  direct: the logits are in the pinned buffer already.
+static int head_results(skd_state *st, int32_t *tokens_out, float *logits_out, bool direct) {
   const skd_config &c = st->cfg;
   const size_t n = (size_t)c.batch * c.vocab;
   hipStream_t s = st->stream;
-  const bool pin_logits = st->pin && n * sizeof(float) <= kPinnedLogits;
+  const bool pinned = pin_logits(st);
   if (tokens_out && !st->pin)
     HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, c.batch * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  if (logits_out)
-    HIPCHECK(hipMemcpyAsync(pin_logits ? st->pin->logits : logits_out, st->logits_dev, n * sizeof(float), hipMemcpyDeviceToHost, s));
+  if (logits_out && !direct)
+    HIPCHECK(hipMemcpyAsync(pinned ? st->pin->logits : logits_out, st->logits_dev, n * sizeof(float), hipMemcpyDeviceToHost, s));
   HIPCHECK(hipStreamSynchronize(s));
   if (tokens_out && st->pin) std::copy(st->pin->tok_out, st->pin->tok_out + c.batch, tokens_out);
-  if (logits_out && pin_logits) std::copy(st->pin->logits, st->pin->logits + n, logits_out);
+  if (logits_out && pinned) std::copy(st->pin->logits, st->pin->logits + n, logits_out);
   return SKD_OK;
 }
 
@@ -1219,7 +1227,8 @@ extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logi
   const int B = c.batch;
   hipStream_t s = st->stream;
   float *logits_target = nullptr;  // where the kernels write logits, if anywhere
-  if (logits_out) logits_target = c.io_on_device ? logits_out : st->logits_dev;
+  const bool direct = logits_out && pin_logits(st);  // the LM head writes them where the host reads them
+  if (logits_out) logits_target = c.io_on_device ? logits_out : direct ? st->pin->logits : st->logits_dev;
   SKDCHECK(head_logits(st, logits_target, true, c.io_on_device ? tokens_out : st->pin ? st->pin->tok_out : nullptr));
   st->have_argmax = true;
   if (c.io_on_device) {
@@ -1227,7 +1236,7 @@ extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logi
       HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, B * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     return SKD_OK;
   }
-  return head_results(st, tokens_out, logits_out);
+  return head_results(st, tokens_out, logits_out, direct);
 }
 
 // skd_logits_argmax for callers that cannot allocate: same kernels, with the LM head's per-workgroup partials in
@@ -1287,7 +1296,7 @@ extern "C" int skd_logits_sample(skd_state *st, const float *u, float temperatur
   HIPCHECK(hipGetLastError());
   st->have_argmax = true;  // skd_decode_step(.., NULL) continues from the sampled tokens
   if (c.io_on_device) return SKD_OK;  // the sampler has written tokens_out
-  return head_results(st, tokens_out, logits_out);
+  return head_results(st, tokens_out, logits_out, false);
 }
 
 extern "C" int skd_rewind(skd_state *st, int32_t t) {
