@@ -241,6 +241,59 @@ __device__ inline void ln_prologue(const GemmArgs &a, bf16_t *act, float *sh, in
   bar();
 }
 
+// With NB > 0 and EPI_PARTIAL (the output projection of one or two rows) the activations are the shares of the keys that the
+// attention left behind: the workgroup merges the rows of its own K range into LDS, a float4 chunk per thread and row, while
+// its first weights are in flight.  The merge's own launch took 4.8 us of a layer.  us per step, separate -> merged here, 4
+// layers of 2048 at 2000 keys: 1 row 179 -> 166, 2 rows 192 -> 185; 2 layers of 4096: 199 -> 191, 208 -> 206; three rows of
+// 2048 (64 KiB more in every workgroup) were slower, 223 -> 230, and keep the launch.
+constexpr int MERGE_SPLITS = 8;
+template <int NB, typename F>
+__device__ inline void merge_prologue(const GemmArgs &a, bf16_t *act, int kw0, int kw1, F request_weights) {
+  const int c0 = 32 * kw0, n4 = 8 * (kw1 - kw0), dh = a.kv.dh, H = a.K / dh, pairs = a.B * H;
+  bool first = true;
+  for (int i = threadIdx.x; i < n4 || first; i += 512) {
+    floatx4 num[NB][MERGE_SPLITS];
+    floatx2 ml[NB][MERGE_SPLITS];
+    const int c = c0 + 4 * i, h = c / dh, e = c - h * dh;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int k = 0; k < MERGE_SPLITS; ++k)
+        if (i < n4) {
+          const float *p = a.attn_part + ((long)(k < a.attn_splits ? k : 0) * pairs + b * H + h) * (dh + 4);
+          num[b][k] = *(const floatx4 *)(p + e);
+          ml[b][k] = *(const floatx2 *)(p + dh);
+        }
+    if (first) {
+      __builtin_amdgcn_sched_barrier(0);
+      request_weights();
+      __builtin_amdgcn_sched_barrier(0);
+      first = false;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (i < n4) {
+        float M = ml[b][0][0], den = 0.f;
+#pragma unroll
+        for (int k = 1; k < MERGE_SPLITS; ++k) M = fmaxf(M, ml[b][k][0]);
+        floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < MERGE_SPLITS; ++k) {
+          const float g = k < a.attn_splits ? __expf(ml[b][k][0] - M) : 0.f;
+          v += num[b][k] * g;
+          den += ml[b][k][1] * g;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = den > 0.f ? v[k] / den : 0.f;
+        *(uint2 *)&act[b * ln_row_stride(a.K) + c] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+      }
+  }
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // bare barrier: the weights in flight are not waited for
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int R>
 struct RowTiles { static constexpr int value = R; };
 
@@ -331,7 +384,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs &a, int tile0, int grou
   // makes the compiler keep two copies of the accumulators and move all of them between the copies every iteration.
   const bool idle = wave >= nbuf;
   int j = idle ? 0 : wave;
-  if constexpr (NB > 0) ln_prologue<NB>(a, act, (float *)red, wave, lane, [&]() { load(j, w0, x0); });
+  if constexpr (NB > 0 && EPI == EPI_PARTIAL) merge_prologue<NB>(a, act, kw0, kw1, [&]() { load(j, w0, x0); });
+  else if constexpr (NB > 0) ln_prologue<NB>(a, act, (float *)red, wave, lane, [&]() { load(j, w0, x0); });
   else load(j, w0, x0);
   if (idle) {
 #pragma unroll
@@ -572,6 +626,29 @@ static bool head_shape(const GemmArgs &a, int R) {
   if (a.head_mid && (a.head_mid_r < 2 || a.head_mid_r >= R)) return false;
   const long covered = (long)a.head_full * R + (long)a.head_mid * a.head_mid_r, tiles = (a.N + 15) / 16;
   return covered < tiles + R && (covered <= tiles || a.head_mid == 0);
+}
+
+// The output projection of one or two rows with the merge of the attention's shares in its prologue (a.attn_*).
+template <int R, int U>
+static void launch_gemm_merge(hipStream_t s, const GemmArgs &a, dim3 grid) {
+  const size_t lds = (size_t)8 * R * 64 * sizeof(floatx4) + (size_t)a.B * ln_row_stride(a.K) * sizeof(bf16_t);  // 32 KiB at most
+  if (a.B == 1) SKD_LAUNCH((k_gemm<1, R, EPI_PARTIAL, U, 8, 1>), grid, dim3(512), lds, s, a);
+  else SKD_LAUNCH((k_gemm<1, R, EPI_PARTIAL, U, 8, 2>), grid, dim3(512), lds, s, a);
+}
+int bf16_gemm_merge_check(const GemmArgs &a, int R, int waves) {
+  if (a.B < 1 || a.B > 2 || a.B_pad != 16 || a.K % 32 || a.K < 32 || a.K > 4096 || a.rows != 0 || waves != 8) return -1;
+  if (R < 1 || R > 2 || a.G < 1 || a.G > 4 || a.N < 1 || a.split < 1 || (a.K / 32) % a.split) return -1;
+  if ((a.kv.dh != 64 && a.kv.dh != 128) || a.K % a.kv.dh || a.attn_splits < 2 || a.attn_splits > MERGE_SPLITS) return -1;
+  return bf16_gemm_groups(a.N, R);
+}
+int bf16_gemm_merge(hipStream_t s, const GemmArgs &a, int R, int U, int waves) {
+  const int groups = bf16_gemm_merge_check(a, R, waves);
+  if (groups < 0) return -1;
+  const dim3 grid(groups, a.split);
+  if ((a.K / 32 / a.split) % 2) U = 1;  // whole buffers
+  if (R == 1) U >= 2 ? launch_gemm_merge<1, 2>(s, a, grid) : launch_gemm_merge<1, 1>(s, a, grid);
+  else U >= 2 ? launch_gemm_merge<2, 2>(s, a, grid) : launch_gemm_merge<2, 1>(s, a, grid);
+  return groups;
 }
 
 // Batch tiles of 16 rows are compiled for B_pad in {16, 32, 48, 64, 96, 128}.
@@ -1668,7 +1745,7 @@ __global__ __launch_bounds__(NW * 64, 4) void k_attention(AttnArgs a) {  // 4 wa
       const float r = den > 0.f ? num / den : 0.f;
       a.o[d_act_index(b, h * DH + e, d)] = (bf16_t)f2bf(r);
     } else {
-      float *pp = a.part + ((long)blockIdx.y * gridDim.x + (long)b * H + h) * (DH + 2);
+      float *pp = a.part + ((long)blockIdx.y * gridDim.x + (long)b * H + h) * (DH + 4);
       pp[e] = num;
       if (e == 0) { pp[DH] = M; pp[DH + 1] = den; }
     }
@@ -1689,7 +1766,7 @@ __global__ __launch_bounds__(DH) void k_attn_merge(AttnArgs a) {
 #pragma unroll
   for (int s = 0; s < 16; ++s)
     if (s < a.splits) {
-      const float *pp = a.part + ((long)s * gridDim.x + blockIdx.x) * (DH + 2);
+      const float *pp = a.part + ((long)s * gridDim.x + blockIdx.x) * (DH + 4);
       m[s] = pp[DH];
       l[s] = pp[DH + 1];
       n[s] = pp[e];
@@ -1718,14 +1795,14 @@ void bf16_attention(hipStream_t s, const AttnArgs &a) {
     else if (nw == 8) SKD_LAUNCH((k_attention<64, 8>), grid, dim3(512), 0, s, a);
     else if (nw == 2) SKD_LAUNCH((k_attention<64, 2>), grid, dim3(128), 0, s, a);
     else SKD_LAUNCH((k_attention<64, 4>), grid, dim3(256), 0, s, a);
-    if (a.splits > 1) SKD_LAUNCH(k_attn_merge<64>, dim3(a.B * a.kv.H), dim3(64), 0, s, a);
+    if (a.splits > 1 && a.merge) SKD_LAUNCH(k_attn_merge<64>, dim3(a.B * a.kv.H), dim3(64), 0, s, a);
   } else {
     if (nw == 1) SKD_LAUNCH((k_attention<128, 1>), grid, dim3(64), 0, s, a);
     else if (nw == 16) SKD_LAUNCH((k_attention<128, 16>), grid, dim3(1024), 0, s, a);
     else if (nw == 8) SKD_LAUNCH((k_attention<128, 8>), grid, dim3(512), 0, s, a);
     else if (nw == 2) SKD_LAUNCH((k_attention<128, 2>), grid, dim3(128), 0, s, a);
     else SKD_LAUNCH((k_attention<128, 4>), grid, dim3(256), 0, s, a);
-    if (a.splits > 1) SKD_LAUNCH(k_attn_merge<128>, dim3(a.B * a.kv.H), dim3(128), 0, s, a);
+    if (a.splits > 1 && a.merge) SKD_LAUNCH(k_attn_merge<128>, dim3(a.B * a.kv.H), dim3(128), 0, s, a);
   }
 }
 

@@ -512,10 +512,16 @@ int run_layer(skd_state *st, int l, int t, const LayerW *prev, const LayerW *nex
   AttnArgs aa{};
   aa.q = q; aa.kv_new = st->kv_new; aa.pool = (bf16_t *)st->pool; aa.bt_layer = bt_layer(st, l); aa.start = st->start_dev; aa.order = st->ragged ? st->order_dev : nullptr;
   aa.t = t; aa.B = B; attn_shape(st, t, aa.waves, aa.splits); aa.kv = st->geom; aa.o = o; aa.part = st->attn_part;
-  { ProfScope ps_(st, SKD_PROF_ATTENTION); bf16_attention(s, aa); }
   // output projection -> partials; bias + residual + LayerNorm 2 in the reducer
   ga.W = (const bf16_t *)w.wo; ga.G = st->p_out.R; ga.A = o; ga.N = d; ga.K = d; ga.split = st->p_out.split; ga.partial = st->partial;
-  { ProfScope ps_(st, SKD_PROF_GEMM_OUT); grc = launch_gemm(s, ga, EPI_PARTIAL, st->p_out); }
+  ga.attn_part = st->attn_part; ga.attn_splits = aa.splits;
+  // one or two rows: the projection merges the attention's splits
+  aa.merge = !(st->fuse_ln && bf16_gemm_merge_check(ga, st->p_out.R, st->p_out.waves) > 0);
+  { ProfScope ps_(st, SKD_PROF_ATTENTION); bf16_attention(s, aa); }
+  {
+    ProfScope ps_(st, SKD_PROF_GEMM_OUT);
+    grc = aa.splits > 1 && !aa.merge ? bf16_gemm_merge(s, ga, st->p_out.R, st->p_out.U, st->p_out.waves) : launch_gemm(s, ga, EPI_PARTIAL, st->p_out);
+  }
   if (grc < 0) return SKD_ERR_SHAPE;
   if (!st->fuse_ln) { ProfScope ps_(st, SKD_PROF_REDUCE_LN); bf16_reduce_ln(s, st->partial, st->p_out.split, st->B_pad, w.bo, st->x, st->x, w.ln2_g, w.ln2_b, a, B, d); }
   ga.W = (const bf16_t *)w.w1; ga.G = st->p_ffn1.R; ga.A = a; ga.bias = w.b1; ga.N = f; ga.K = d; ga.split = 1; ga.act_out = u;
@@ -830,7 +836,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     A(&t16, (size_t)Bp * f); st->u = t16;
     A(&st->kv_new, (size_t)B * 2 * d);
     A(&st->partial, (size_t)st->max_split * Bp * d);
-    A(&st->attn_part, (size_t)st->attn_splits * B * c.n_heads * (st->dh + 2));
+    A(&st->attn_part, (size_t)st->attn_splits * B * c.n_heads * (st->dh + 4));
     GemmArgs ga{};
     ga.N = V;
     const int groups = std::max(bf16_head_tiles(ga, st->p_head.R, st->p_head.slots), bf16_gemm_groups(V, st->p_head.R));

@@ -154,6 +154,8 @@ struct GemmArgs {
   float *ln_x_out;
   int ln_split;
   float *logits;       // EPI_LOGITS (nullable)
+  const float *attn_part;  // bf16_gemm_merge: the attention's shares (AttnArgs::part), attn_splits of them
+  int attn_splits;
   int head_full, head_mid, head_mid_r;  // EPI_LOGITS: workgroups of R = G tiles, of head_mid_r; then single tiles (bf16_head_tiles)
   float *pmax;         // EPI_LOGITS: [groups][B_pad]
   int32_t *pidx;       // EPI_LOGITS
@@ -166,6 +168,10 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epilogue, int R, int U, int 
 // not read).  The check launches nothing (N, K, B, B_pad, G, split, rows and ln_split of `a` are read): groups or -1.
 int bf16_gemm_ln(hipStream_t s, const GemmArgs &a, int epilogue, int R);
 int bf16_gemm_ln_check(const GemmArgs &a, int epilogue, int R);
+// The output projection (EPI_PARTIAL) of one or two rows, K <= 4096, behind an attention of 2 to 8 splits that were not merged:
+// merges them itself (attn_*, kv.dh; a.A is not read).  R is 1 or 2.  Groups or -1.
+int bf16_gemm_merge(hipStream_t s, const GemmArgs &a, int R, int U, int waves);
+int bf16_gemm_merge_check(const GemmArgs &a, int R, int waves);
 // The same shape checks without a launch (only N, K, B_pad, G, split and rows of `a` are read): groups or -1.
 int bf16_gemm_check(const GemmArgs &a, int epilogue, int R, int U, int waves);
 int bf16_gemm_groups(int N, int R);
@@ -205,7 +211,8 @@ struct AttnArgs {
   int waves;                // waves per workgroup: 2, 4, 8 or 16
   KvGeom kv;
   bf16_t *o;                // activation tiles [B_pad][d]
-  float *part;              // splits > 1: [splits][B*H][dh + 2]
+  bool merge;               // splits > 1: whether their merge is launched too (else bf16_gemm_merge reads `part`)
+  float *part;              // splits > 1: [splits][B*H][dh + 4], numerators, maximum and denominator
 };
 void bf16_attention(hipStream_t s, const AttnArgs &a);
 // Causal attention of a whole prompt: query rows (b, pos), up to 128 positions per workgroup, keys of columns start[b] .. pos.
