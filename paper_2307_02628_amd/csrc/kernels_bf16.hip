@@ -1253,11 +1253,11 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
 // N = d projections, on 256 CUs).  The same ring and fragment order with WN x WM waves of RT x MT MFMA tiles each: the
 // workgroup owns 16 RT WN weight rows x 16 MT WM activation rows, the ring has NS stages, and the K range can be split
 // over `a.split` workgroups whose fp32 partial sums the row reducer adds.  With 4 waves two workgroups share a CU, so
-// one multiplies while the other waits at its barrier.  What bounds it is how many bytes a CU takes in per MFMA: at 912
-// rows of the 1.3B shape the 128 x 256 tiles read 10.4 TB/s through L2 (41 GB/s to each CU) with the matrix cores 34 %
-// busy, whatever the ring depth (64 x 128 tiles: 5 and 6 stages alike, 64 x 64: 5 and 9), so the largest tile that
-// still fills the chip wins.  The q | k | v launches take in less (7.6 and 9.0 TB/s): their epilogue begins its page
-// lookups behind the loop, and with one round of workgroups nothing runs under them.
+// one multiplies while the other waits at its barrier; with 8 waves the two of a SIMD take turns.  What bounds it is how
+// many bytes a CU takes in per MFMA: at 912 rows of the 1.3B shape FFN1's 128 x 256 tiles read 11.2 TB/s through L2
+// (44 GB/s to each CU) with the matrix cores 37 % busy, whatever the ring depth (64 x 128 tiles: 5 and 6 stages alike,
+// 64 x 64: 5 and 9), so the largest tile that still fills the chip wins.  The q | k | v launches take in less (7.9 TB/s):
+// their epilogue begins its page lookups behind the loop, and with one round of workgroups nothing runs under them.
 // us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
 // FFN1 80 -> 44, FFN2 296 -> 46 (split 4), all 128 x 128; 1024 rows of the 1.3B shape QKV 44 -> 32 and FFN1 45 -> 35
 // (128 x 256; 128 x 128: 37 and 41), output 51 -> 15 (128 x 128, split 2), FFN2 153 -> 37 (128 x 256, split 4).
@@ -1334,57 +1334,108 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  // stage st becomes readable, the slot of stage st - 1 is refilled (see k_gemm_tile)
-  auto open_stage = [&](int st) {
-    const int later = min(n - 1 - st, NS - 2);
-    if (later == 0) wait_vmcnt<0>();
-    else if (later == 1) wait_vmcnt<LPW>();
-    else if (later == 2) wait_vmcnt<2 * LPW>();
-    else if (later == 3) wait_vmcnt<3 * LPW>();
-    else wait_vmcnt<(NS - 2) * LPW>();
-    bar();
-    if (st + NS - 1 < n) issue(st + NS - 1);
-  };
+  if constexpr (WN * WM == 8) {
+    // The two waves of a SIMD take turns at LDS and matrix cores as in k_gemm_tile, two k-steps (a pair of stages) to a
+    // turn: waves 4 .. 7 run one barrier behind waves 0 .. 3.  Ring: pair p + 2 goes into the slots of pair p - 1, which
+    // the late group has read in its memory turn before last; pair p + 1 has landed for every reader: each wave waits for
+    // its own loads of it in its memory turn p, and at least one barrier lies between the last such wait and the first read.
+    // With all waves in phase, LDS reads dealt out among the MFMAs, a k-step took 0.45 us alone and 0.51 with every CU busy;
+    // in turns 0.325 with 64 workgroups, 0.38 with 128, 0.44 with 256 (24 KiB to each CU: 14 TB/s).  912 rows of the 1.3B
+    // shape, us: QKV 40.4 -> 38.7, FFN1 38.1 -> 35.8, FFN2 39.2 -> 37.2; about 9 us of each lie outside the loop.
+    static_assert(NS == 6, "three pairs of stages");
+    auto turn = [&](int st, bool two, bool more, int later) {  // later: stages of the pair after next
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 wf[2][RT], xf[2][MT];
+      read(st, wf[0], xf[0]);
+      if (two) read(st + 1, wf[1], xf[1]);
+      if (more || st + 4 < n) issue(st + 4);
+      if (more || st + 5 < n) issue(st + 5);
+      __builtin_amdgcn_sched_barrier(0);
+      if (later == 2) wait_vmcnt<2 * LPW>();
+      else if (later == 1) wait_vmcnt<LPW>();
+      else wait_vmcnt<0>();
+      bar();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i)
-    if (i < n) issue(i);
-  bf16x8 wfA[RT], xfA[MT], wfB[RT], xfB[MT];
-  open_stage(0);
-  read(0, wfA, xfA);
-  // steady state: the LDS reads of the next stage are dealt out among the MFMAs of the current one
-  auto steady = [&](int nx, bf16x8(&wn)[RT], bf16x8(&xn)[MT], const bf16x8(&wc_)[RT], const bf16x8(&xc)[MT]) {
-    wait_vmcnt<(NS - 2) * LPW>();
-    bar();
-    issue(nx + NS - 1);
-    read(nx, wn, xn);
-    mma(wc_, xc);
-    __builtin_amdgcn_sched_group_barrier(0x020, LPW, 0);
+      for (int h = 0; h < 2; ++h)
+        if (h == 0 || two)
 #pragma unroll
-    for (int i = 0; i < RT + MT; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {  // neighbours share an operand
+              const int r = (m & 1) ? RT - 1 - i : i;
+              acc[r][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][r], xf[h][m], acc[r][m], 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+      __builtin_amdgcn_s_setprio(0);
+      bar();
+    };
+#pragma unroll
+    for (int i = 0; i < NS - 2; ++i)
+      if (i < n) issue(i);
+    if (n >= 4) wait_vmcnt<2 * LPW>();
+    else if (n == 3) wait_vmcnt<LPW>();
+    else wait_vmcnt<0>();
+    bar();  // pair 0 is here
+    if (wave >= 4) bar();
+    int st = 0;
+    for (; st + NS <= n; st += 2) turn(st, true, true, 2);
+    for (; st < n; st += 2) turn(st, st + 1 < n, false, min(max(n - 4 - st, 0), 2));
+    if (wave < 4) bar();
+  } else {
+    // stage st becomes readable, the slot of stage st - 1 is refilled (see k_gemm_tile)
+    auto open_stage = [&](int st) {
+      const int later = min(n - 1 - st, NS - 2);
+      if (later == 0) wait_vmcnt<0>();
+      else if (later == 1) wait_vmcnt<LPW>();
+      else if (later == 2) wait_vmcnt<2 * LPW>();
+      else if (later == 3) wait_vmcnt<3 * LPW>();
+      else wait_vmcnt<(NS - 2) * LPW>();
+      bar();
+      if (st + NS - 1 < n) issue(st + NS - 1);
+    };
+#pragma unroll
+    for (int i = 0; i < NS - 1; ++i)
+      if (i < n) issue(i);
+    bf16x8 wfA[RT], xfA[MT], wfB[RT], xfB[MT];
+    open_stage(0);
+    read(0, wfA, xfA);
+    // steady state: the LDS reads of the next stage are dealt out among the MFMAs of the current one
+    auto steady = [&](int nx, bf16x8(&wn)[RT], bf16x8(&xn)[MT], const bf16x8(&wc_)[RT], const bf16x8(&xc)[MT]) {
+      wait_vmcnt<(NS - 2) * LPW>();
+      bar();
+      issue(nx + NS - 1);
+      read(nx, wn, xn);
+      mma(wc_, xc);
+      __builtin_amdgcn_sched_group_barrier(0x020, LPW, 0);
+#pragma unroll
+      for (int i = 0; i < RT + MT; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, RT * MT - (RT + MT), 0);
+    };
+    int st = 0;
+    for (; st + NS + 1 < n; st += 2) {
+      steady(st + 1, wfB, xfB, wfA, xfA);
+      steady(st + 2, wfA, xfA, wfB, xfB);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, RT * MT - (RT + MT), 0);
-  };
-  int st = 0;
-  for (; st + NS + 1 < n; st += 2) {
-    steady(st + 1, wfB, xfB, wfA, xfA);
-    steady(st + 2, wfA, xfA, wfB, xfB);
-  }
-  for (; st < n; st += 2) {  // the last stages
-    if (st + 1 < n) {
-      open_stage(st + 1);
-      read(st + 1, wfB, xfB);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    mma(wfA, xfA);
-    if (st + 1 < n) {
-      if (st + 2 < n) {
-        open_stage(st + 2);
-        read(st + 2, wfA, xfA);
+    for (; st < n; st += 2) {  // the last stages
+      if (st + 1 < n) {
+        open_stage(st + 1);
+        read(st + 1, wfB, xfB);
       }
       __builtin_amdgcn_sched_barrier(0);
-      mma(wfB, xfB);
+      mma(wfA, xfA);
+      if (st + 1 < n) {
+        if (st + 2 < n) {
+          open_stage(st + 2);
+          read(st + 2, wfA, xfA);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mma(wfB, xfB);
+      }
     }
   }
   tile_epilogue<EPI, RT, MT>(a, acc, a.t0 + tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);

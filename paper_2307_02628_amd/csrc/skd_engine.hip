@@ -924,7 +924,10 @@ constexpr long kRowsPartialMax = 32L << 20;  // fp32 partial sums of one project
 // 0.52 for two; 64 x 128 0.255 / 0.44; 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
 // at 1024 rows of the 6.7B shape FFN1 takes 100 us on 256 x 256 and 138 on 128 x 128, at 256 rows 80 and 44.
 // The epilogue is not in the estimate, and the traffic of the partial sums counts the reducer's reads: at 912 rows of the
-// 1.3B shape estimate and launch are 34 / 40 us (QKV), 23.5 / 31 (k | v alone), 35 / 38 (FFN1) and 45 / 39 (FFN2, split 4).
+// 1.3B shape estimate and launch are 34 / 39 us (QKV), 23.5 / 30 (k | v alone), 35 / 36 (FFN1) and 45 / 37 (FFN2, split 4).
+// For that reason 256 x 128 and 128 x 256 keep the step times above although a step alone now takes 0.325 (64 workgroups)
+// to 0.44 (256): with those, prompts of 1200 to 2000 rows of the 6.7B shape were 1 to 3 % faster, but 360 and from 800
+// rows on of the 1.3B shape 2 to 5 % slower.
 RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   RowsGemm best;
   const int Kf = K / 32;

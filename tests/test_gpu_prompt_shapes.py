@@ -64,8 +64,9 @@ def test_forced_tiles_behind_q(shape, tile):
     check(shape, 9, 83, 50, {"SKD_PREFILL_TILE": tile}, 60)
 
 
-# K parts of 1 to 9 k-steps (512 and 1536 columns over 16, 12, 8 and 5 parts): fewer than, as many as and more than the
-# stages of the 256 x 256 kernel's ring
+# K parts of 1 to 9 k-steps (512 and 1536 columns over 16, 12, 8 and 5 parts), even and odd: fewer than, as many as and
+# more than the stages of the rings of the kernels of eight waves
+@pytest.mark.parametrize("tile", ["256x256", "256x128", "128x256"])
 @pytest.mark.parametrize("split", [16, 12, 8, 5])
-def test_short_k_parts(split):
-    check(WIDE, 7, 83, 9, {"SKD_PREFILL_TILE": f"256x256x{split}"}, 70)
+def test_short_k_parts(split, tile):
+    check(WIDE, 7, 83, 9, {"SKD_PREFILL_TILE": f"{tile}x{split}"}, 70)
