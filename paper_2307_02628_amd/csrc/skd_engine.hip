@@ -584,6 +584,7 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
     ta.n = n;
     ta.t = t;
     ta.longest = t - st->start_min;
+    attn_shape(st, t, ta.attn_waves, ta.attn_splits);
     ta.tokens = tokens_dev;
     ta.order = st->ragged ? st->order_dev : nullptr;
     if (!bf16_team_column(s, ta)) return SKD_ERR_SHAPE;
@@ -622,10 +623,19 @@ static int prepare_team(skd_state *st) {
   const skd_config &c = st->cfg;
   const int L = c.L, d = c.d_model, f = c.ffn;
   TeamArgs &ta = st->team_args;
+  ta.d = d; ta.f = f; ta.B = c.batch; ta.V = c.vocab;
+  ta.kv = st->geom;
+  ta.groups = bf16_team_groups(c.batch);
+  auto sums = [](const GemmPlan &p) { return TeamSums{p.R, p.ws ? 4 : p.waves, p.ws ? 1 : p.U, p.split, p.ws && p.ws_rot}; };
+  auto take_sums = [&](TeamStep *out, TeamStep *ffn2) {
+    return bf16_team_sums(ta, st->B_pad, sums(st->p_qkv), sums(st->p_out), sums(st->p_ffn1), sums(st->p_ffn2), out, ffn2);
+  };
+  if (!take_sums(nullptr, nullptr) || !bf16_team_states(ta, st->attn_waves, st->attn_splits)) return SKD_OK;  // separate kernels
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, st->device));
-  // one allocation and one copy: control words (zero) and layer table, then the work buffers
-  const size_t rows = bf16_team_rows(), head = sizeof(TeamCtl) + (L * sizeof(TeamLayer) + 255) / 256 * 256;
+  // one allocation and one copy: control words (zero), layer table and step tables, then the work buffers
+  const size_t rows = bf16_team_rows(), steps = bf16_team_steps(d);
+  const size_t head = (sizeof(TeamCtl) + L * sizeof(TeamLayer) + 2 * steps * sizeof(TeamStep) + 255) / 256 * 256;
   const size_t n16[] = {rows * d, rows * 2 * d, rows * d, rows * f}, n32[] = {rows * d, bf16_team_part()};  // multiples of 128 each
   unsigned char *base = nullptr;
   SKDCHECK(dev_alloc(st, &base, head + 2 * (n16[0] + n16[1] + n16[2] + n16[3]) + 4 * (n32[0] + n32[1])));
@@ -636,25 +646,27 @@ static int prepare_team(skd_state *st) {
     host[l] = TeamLayer{(const bf16_t *)w.wqkv, (const bf16_t *)w.wo, (const bf16_t *)w.w1, (const bf16_t *)w.w2, w.ln1_g, w.ln1_b,
                         w.bqkv, w.bo, w.ln2_g, w.ln2_b, w.b1, w.b2, bt_layer(st, l)};
   }
+  const size_t at_steps = sizeof(TeamCtl) + L * sizeof(TeamLayer);
+  TeamStep *host_steps = (TeamStep *)(st->team_table.data() + at_steps);
+  if (!take_sums(host_steps, host_steps + steps)) return SKD_ERR_SHAPE;
   HIPCHECK(hipMemcpyAsync(base, st->team_table.data(), head, hipMemcpyHostToDevice, st->stream));  // create waits for it
   ta.ctl = (TeamCtl *)base;
   ta.layers = (const TeamLayer *)(base + sizeof(TeamCtl));
+  ta.out_steps = (const TeamStep *)(base + at_steps);
+  ta.ffn2_steps = ta.out_steps + steps;
   base += head;
   bf16_t **p16[] = {&ta.work.q, &ta.work.kv, &ta.work.o, &ta.work.u};
   for (int i = 0; i < 4; base += 2 * n16[i++]) *p16[i] = (bf16_t *)base;
   ta.work.y = (float *)base;
   ta.work.part = (float *)(base + 4 * n32[0]);
   ta.warmup = c.warmup; ta.L = L;
-  ta.G_qkv = st->p_qkv.R; ta.G_out = st->p_out.R; ta.G_ffn1 = st->p_ffn1.R; ta.G_ffn2 = st->p_ffn2.R;
-  ta.d = d; ta.f = f; ta.B = c.batch; ta.V = c.vocab;
-  ta.groups = bf16_team_groups(c.batch);
   ta.workgroups = std::max(cus, 1);
   ta.members = bf16_team_members(cus, d);
   if (const int m = env_int("SKD_TEAM_WGS", 0); m >= 1 && m <= ta.members) ta.members = m;
   ta.start = st->start_dev;
   ta.tok_emb = (const bf16_t *)st->tok_emb; ta.pos_emb = (const bf16_t *)st->pos_emb;
   ta.lnf_g = st->lnf_g; ta.lnf_b = st->lnf_b;
-  ta.pool = (bf16_t *)st->pool; ta.kv = st->geom;
+  ta.pool = (bf16_t *)st->pool;
   ta.x_out = st->x; ta.a_out = (bf16_t *)st->a;
   st->team = true;
   return SKD_OK;

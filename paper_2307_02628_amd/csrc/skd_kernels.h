@@ -258,15 +258,26 @@ struct TeamCtl {                      // zero before the first launch; every lau
 struct TeamWork {                     // for 8 groups of 16 rows each
   bf16_t *q, *kv, *o, *u;             // [16][d] | [16][k | v][d] | activation tiles [16][d] | activation tiles [16][f]
   float *y;                           // [16][d]
-  float *part;                        // [32][132]: numerators, maximum and denominator of a share of a pair's keys
+  float *part;                        // [128][132]: numerators, maximum and denominator of a share of a pair's keys
+};
+struct TeamStep {                     // k-steps of a wave and a tile, in order (team_steps)
+  uint16_t e[8];
+};
+struct TeamSums {                     // of the separate kernel
+  int tiles, waves, unit, split;      // tiles of a workgroup and of a group of the layout, waves, k-steps of a buffer, K parts
+  bool rotate;
 };
 struct TeamArgs {
   const TeamLayer *layers;            // device, all L
   int n, warmup, L;                   // active: 0 .. warmup - 1 and L - n + warmup .. L - 1
-  int G_qkv, G_out, G_ffn1, G_ffn2;   // tile-group sizes of the layouts
   int d, f, B, V, t;
   int groups;                         // bf16_team_groups(B)
   int longest;                        // cached positions of the longest row
+  int attn_waves, attn_splits;        // waves and splits of the separate attention
+  const TeamStep *out_steps, *ffn2_steps;  // [d / 16][8 waves]
+  int out_parts, ffn2_parts;          // K parts
+  int rot_qkv, rot_ffn1;              // waves begin rotated
+  bool wide;                          // 96 or 128 padded rows
   int workgroups;                     // of the launch: one per CU
   int members;                        // of a team, at most
   const int32_t *tokens, *start, *order;  // [B]; order: rows by descending length, or null
@@ -284,6 +295,12 @@ int bf16_team_groups(int B);
 int bf16_team_members(int cus, int d);
 size_t bf16_team_rows();              // rows of each work buffer
 size_t bf16_team_part();              // floats of work.part
+// Sets what `a` says about sums (d, f given) and the two tables of bf16_team_steps(d) entries, or only checks (null);
+// false: not among those that the column can take.
+bool bf16_team_sums(TeamArgs &a, int B_pad, const TeamSums &qkv, const TeamSums &out, const TeamSums &ffn1, const TeamSums &ffn2,
+                    TeamStep *out_steps, TeamStep *ffn2_steps);
+size_t bf16_team_steps(int d);
+bool bf16_team_states(const TeamArgs &a, int states, int splits);
 bool bf16_team_column(hipStream_t s, const TeamArgs &a);
 
 // weight preparation (source fp32 or bf16 row-major, on device)

@@ -16,13 +16,18 @@
 // Per layer, with a barrier behind each: q | k | v, attention, output projection, FFN1, FFN2.  Every member keeps the
 // residual rows (fp32) of its group in LDS and adds the projection's output and applies LayerNorm itself, so the row
 // reducers need no phase of their own.  A phase's first weights, and a wave's first K and V block, are requested between
-// arrival at the barrier before it and its end.  What a phase takes (256 wide, 2 rows at 16 keys, us): q | k | v 0.6,
-// attention 1.7, output projection 0.7, LayerNorm and FFN1 1.2, FFN2 1.3, LayerNorm 0.6, and 0.8 to 1.4 for each barrier
-// with the stores before it; 5 to 7 for a launch's start, embeddings and end.
+// arrival at the barrier before it and its end.
+//
+// A column gives the same bits as the separate kernels, whatever the size of the teams that form: every sum is taken in the
+// order in which those take it (NV, TeamStep, attn_waves and attn_splits below), and a team only shares out the work.  So a
+// state may change between the two, and nothing depends on what else is on the GPU.  For the order of the attention's sums a
+// wave carries up to four softmax states; at 2000 keys that is 5 to 12 % of a step.
 // Tried: workgroups beside the team that pull the coming weights into the L2 (slower by 3 to 10 %), a ninth wave that only
 // polls (registers), K and V two barriers ahead (the loads behind them wait for them: slower).
 // Ordering: a wave's stores have been acknowledged by the L2 (vmcnt 0) before its workgroup arrives; what other members
 // have written is read with agent-scope loads, which do not look into the L1.
+#include <algorithm>
+
 #include "bf16_device.h"
 
 namespace skd {
@@ -32,7 +37,12 @@ constexpr int TEAM_THREADS = 64 * TEAM_WAVES;
 constexpr int TEAM_ROWS = 16;    // rows of a group: one batch tile
 constexpr int TEAM_MAX_D = 512;  // 16 k-steps: the weight tile of a wave, and the K and V of a 32-key block, fit 16 fragments
 constexpr int TEAM_MAX_F = 2048; // 8 waves x 8 k-steps
-constexpr int TEAM_SPLITS = 4, TEAM_PARTS = 32;  // shares of one pair's keys, of all pairs (one per workgroup of the team)
+constexpr int TEAM_SPLITS = 8, TEAM_PARTS = 128;  // shares of one pair's keys, of all pairs of a group
+constexpr int TEAM_SUMS = 32;    // partial sums of a tile along K, and softmax states of the pairs that a workgroup has at a time
+constexpr int TEAM_OUT_STEPS = 2, TEAM_OUT_STEPS_WIDE = 4, TEAM_FFN2_STEPS = 8;  // k-steps of a wave
+// an entry of TeamStep: k-step in bits 0 .. 5, whether there is one, whether the sum ends here, which sum (and not zero)
+constexpr uint32_t TEAM_STEP_K = 1 << 6, TEAM_STEP_LAST = 1 << 7, TEAM_STEP_USED = 1 << 8;
+constexpr int TEAM_STEP_SUM = 9;
 constexpr int TEAM_REG_POLLS = 400;       // about 100 us: how long a leader waits for workgroups that have not started
 constexpr int TEAM_MAX_POLLS = 1 << 22;   // over a second; never reached: members run until they arrive
 
@@ -42,6 +52,10 @@ __device__ inline bf16x8 load_shared16(const void *p, int byte_offset) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7fffffff, 0x00027000);
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, 0, 16));
 }
+__device__ inline floatx2 load_shared8(const void *p, int byte_offset) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7fffffff, 0x00027000);
+  return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(r, byte_offset, 0, 16));
+}
 __device__ inline uint32_t ctl_load(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void ctl_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline uint32_t ctl_add(uint32_t *p, uint32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -49,20 +63,48 @@ __device__ inline uint32_t ctl_add(uint32_t *p, uint32_t v) { return __hip_atomi
 typedef const TeamArgs __attribute__((address_space(4))) *ArgsPtr;
 typedef const TeamLayer __attribute__((address_space(4))) *LayerPtr;
 
+typedef const uint32_t __attribute__((address_space(4))) *WordPtr;
+
+__device__ inline float row_sum(float v) {  // over 16 lanes, the pairs of a butterfly of 8, 4, 2, 1
+#define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  return v;
+}
+
 template <int N>
-struct Parts { static constexpr int value = N; };  // k-steps of a wave
+struct Parts { static constexpr int value = N; };
+
+// A wave's k-steps of a tile (TeamSteps), at most N of them: f(place, step).
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void walk_steps(const uint32x4 &steps, F f) {
+  if constexpr (I < N) {
+    const uint32_t e = (steps[I >> 1] >> (16 * (I & 1))) & 0xffffu;
+    if (e) {
+      f(I, e);
+      walk_steps<N, I + 1>(steps, f);
+    }
+  }
+}
 
 struct TeamLds {
   float x[TEAM_ROWS][TEAM_MAX_D];             // residual rows
   bf16_t act[TEAM_ROWS][TEAM_MAX_D + 32];     // their LayerNorm (rows 16 banks apart)
-  floatx4 red[2][TEAM_WAVES][64];             // cross-wave sums, two sets in turn
-  float m[TEAM_WAVES], l[TEAM_WAVES], dot[TEAM_WAVES], o[TEAM_WAVES][128];
+  union {
+    floatx4 red[TEAM_SUMS][64];               // of a tile along K
+    float o[TEAM_SUMS][128];                  // numerators of the softmax states
+  };
+  float m[TEAM_SUMS], l[TEAM_SUMS], dot[2 * TEAM_WAVES];
   int row[TEAM_ROWS], start[TEAM_ROWS], tok[TEAM_ROWS];
   int all_tok[128], all_start[128], all_order[128];
   int rank, size, group;
 };
 
-template <int DH, int KD>
+// NV: waves of the separate kernels' projections (8, or 4 from 65 rows on), see the sums below
+template <int DH, int KD, int NV>
 __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value) {
   constexpr int QC = DH / 32, VM = DH / 16, d = 32 * KD, d4 = d / 4, NC = (d4 + 63) / 64, Kd = KD, H = d / DH;
   constexpr int NW = KD > 8 ? KD : 8;  // weight fragments in registers: a tile over all of d, or an eighth of one over f
@@ -153,13 +195,12 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
     auto wk_y = [&]() __attribute__((always_inline)) { return ap->work.y + (long)group * TEAM_ROWS * d; };
 
     constexpr int wg_tiles = d / 16;
+    typedef Parts<NV == 8 ? TEAM_OUT_STEPS : TEAM_OUT_STEPS_WIDE> OutSteps;
     bf16x8 w[NW];  // the phase's first weight tile of this wave, or its first K and V block, requested ahead of the barrier
     bf16x8 kv[2 * QC + VM];  // K and V of 32 keys: fragments 0 .. 2 QC - 1, and those behind them
     floatx4 bias;
-    // fragment (tile, k) of a layout in groups of G is base + 1024 k G bytes + 16 lane: a scalar base and a 32-bit offset
-    auto tile_base = [&](const bf16_t *W, int G, int Kt, int tile, int k) __attribute__((always_inline)) {
-      return (const char *)W + ((long)(tile / G) * Kt * G + (long)k * G + tile % G) * 1024;
-    };
+    // fragment (tile, k) of a layout in groups of one tile is base + 1024 k bytes + 16 lane: a scalar base and a 32-bit offset
+    auto tile_base = [&](const bf16_t *W, int Kt, int tile) __attribute__((always_inline)) { return (const char *)W + (long)tile * Kt * 1024; };
     // what a conditional load leaves as it was is not wanted any more: without this it would stay in registers
     auto forget_w = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -169,22 +210,35 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
 #pragma unroll
       for (int k = 0; k < 2 * QC + VM; ++k) asm volatile("" : "=v"(kv[k]));
     };
+    // Sums along K are taken as the separate kernels take them: one per wave of theirs (NV of them, which have the k-steps
+    // in turn, one or two at a time), added in wave order, then the sums of their K parts in order, then the bias.  With 96
+    // and 128 padded rows a wave begins at a step that depends on the tile and the part (rotated).
+    constexpr bool ROT = NV == 4;
+    constexpr int CH = KD % 4 == 0 ? KD / 4 : 1;  // steps of a wave where they may be rotated
+    int rot = 0;  // of the tile in w
+    auto k_of = [&](int j) __attribute__((always_inline)) {  // k-step of w[j] in load_tile
+      if constexpr (!ROT || KD % 4) return j;
+      const int c = (j >> 2) + rot;
+      return 4 * (c >= CH ? c - CH : c) + (j & 3);
+    };
     // a wave's own tile over all of K (q | k | v, FFN1)
-    auto load_tile = [&](const bf16_t *W, int G, const float *b, int tile) __attribute__((always_inline)) {
-      const char *base = tile_base(W, G, Kd, tile, 0);
-      uint32_t off = 16 * lane;
+    auto load_tile = [&](const bf16_t *W, int rotate, const float *b, int tile) __attribute__((always_inline)) {
+      const char *base = tile_base(W, Kd, tile);
+      if constexpr (ROT) rot = rotate ? (tile >> 3) * 5 % CH : 0;
 #pragma unroll
-      for (int k = 0; k < Kd; ++k) { w[k] = *(const bf16x8 *)(base + off); off += 1024 * G; }
+      for (int j = 0; j < Kd; ++j) w[j] = *(const bf16x8 *)(base + (uint32_t)(16 * lane + 1024 * k_of(j)));
       bias = *(const floatx4 *)&b[tile * 16 + 4 * grp];
     };
     // a workgroup's tile, K shared out among the waves (output projection, FFN2)
-    auto load_part = [&](auto np, const bf16_t *W, int G, int Kt, const float *b, int tile) __attribute__((always_inline)) {
-      constexpr int NP = decltype(np)::value;
-      const char *base = tile_base(W, G, Kt, tile, wave);
-      const uint32_t off = 16 * lane;
+    uint32x4 steps;  // of the tile in w
+    auto load_part = [&](auto np, const bf16_t *W, const TeamStep *table, int Kt, const float *b, int tile) __attribute__((always_inline)) {
+      const char *base = tile_base(W, Kt, tile);
+      const WordPtr at = (WordPtr)table + (tile * TEAM_WAVES + wave) * (sizeof(TeamStep) / 4);
 #pragma unroll
-      for (int i = 0; i < NP; ++i)
-        if (wave + TEAM_WAVES * i < Kt) w[i] = *(const bf16x8 *)(base + (off + 1024 * TEAM_WAVES * i * G));
+      for (int i = 0; i < 4; ++i) steps[i] = at[i];
+      walk_steps<decltype(np)::value>(steps, [&](int i, uint32_t e) __attribute__((always_inline)) {
+        if (e & TEAM_STEP_K) w[i] = *(const bf16x8 *)(base + (uint32_t)(16 * lane + 1024 * (e & 63)));
+      });
       if (wave == 0) bias = *(const floatx4 *)&b[tile * 16 + 4 * grp];
     };
     int tile0 = wave * T + rank;  // spread over the workgroups first
@@ -199,19 +253,24 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       }
     };
     auto row_ln = [&](floatx4(&v)[NC], floatx4(&y)[NC]) __attribute__((always_inline)) {  // LayerNorm of the row in v
-      float sum = 0.f;
+      float sum = 0.f, sq = 0.f;  // 256 columns at a time, as the row kernels' waves
 #pragma unroll
-      for (int i = 0; i < NC; ++i)
-        if (lane + 64 * i < d4) sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-      const float mean = wave_sum_f(sum) / d;
-      float q = 0.f;
+      for (int i = 0; i < NC; ++i) {
+        float s = 0.f;
+        if (lane + 64 * i < d4) s += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+        sum += wave_sum_f(s);
+      }
+      const float mean = sum / d;
 #pragma unroll
-      for (int i = 0; i < NC; ++i)
+      for (int i = 0; i < NC; ++i) {
+        float q = 0.f;
         if (lane + 64 * i < d4) {
           const floatx4 t = v[i] - mean;
           q += (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]);
         }
-      const float rstd = 1.0f / sqrtf(wave_sum_f(q) / d + 1e-5f);
+        sq += wave_sum_f(q);
+      }
+      const float rstd = 1.0f / sqrtf(sq / d + 1e-5f);
 #pragma unroll
       for (int i = 0; i < NC; ++i)
         if (lane + 64 * i < d4) y[i] = (v[i] - mean) * rstd * gv[i] + bv[i];
@@ -250,25 +309,30 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       }
     };
     auto mul_tile = [&]() __attribute__((always_inline)) {  // w x act: rows 4 grp .. + 3 of the tile, batch row col
-      floatx4 acc[2] = {bias, floatx4{0.f, 0.f, 0.f, 0.f}};
+      constexpr int NA = KD < NV ? KD : NV;
+      floatx4 acc[NA];
 #pragma unroll
-      for (int k = 0; k < Kd; ++k) {
-          const bf16x8 x = *(const bf16x8 *)&s.act[col][32 * k + 8 * grp];  // rows past R: columns that nobody reads
-          acc[k & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[k], x, acc[k & 1], 0, 0, 0);
-          if ((k & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four LDS reads in flight: registers
-        }
-      return acc[0] + acc[1];
+      for (int j = 0; j < Kd; ++j) {
+        const bf16x8 x = *(const bf16x8 *)&s.act[col][32 * k_of(j) + 8 * grp];  // rows past R: columns that nobody reads
+        acc[j % NV] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], x, j < NV ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[j % NV], 0, 0, 0);
+        if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four LDS reads in flight: registers
+      }
+      floatx4 v = acc[0];
+#pragma unroll
+      for (int j = 1; j < NA; ++j) v += acc[j];
+      return v + bias;
     };
-    // the splits of all pairs -> s.act, a float4 chunk per thread (at most TEAM_PARTS / 2 pairs of 128)
+    // the splits of all pairs -> s.act, a float4 chunk per thread at a time
     auto merge_splits = [&](int splits, int pairs) __attribute__((always_inline)) {
-      const int at = 4 * (int)threadIdx.x, j = at / d, c = at - j * d, p = j * H + c / DH, e = c % DH;
-      if (j < R) {
-        floatx4 num[TEAM_SPLITS], ml[TEAM_SPLITS];
+      for (int at = 4 * (int)threadIdx.x; at < R * d; at += 4 * TEAM_THREADS) {
+        const int j = at / d, c = at - j * d, p = j * H + c / DH, e = c % DH;
+        floatx4 num[TEAM_SPLITS];
+        floatx2 ml[TEAM_SPLITS];
 #pragma unroll
         for (int k = 0; k < TEAM_SPLITS; ++k) {
           const int part = ((k < splits ? k : 0) * pairs + p) * (DH + 4);
           num[k] = __builtin_bit_cast(floatx4, load_shared16(wk_part(), (part + e) * 4));
-          ml[k] = __builtin_bit_cast(floatx4, load_shared16(wk_part(), (part + DH) * 4));
+          ml[k] = load_shared8(wk_part(), (part + DH) * 4);
         }
         float M = ml[0][0], den = 0.f;
 #pragma unroll
@@ -286,85 +350,105 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       }
       bar();
     };
-    int set = 0;
     // the d / 16 tiles of in (activation tiles of Kt k-steps) x W + b -> y; the first tile's weights are in w
-    auto project = [&](auto np, const bf16_t *W, int G, int Kt, const float *b, const bf16_t *in, bool from_lds) __attribute__((always_inline)) {
+    auto project = [&](auto np, const bf16_t *W, const TeamStep *table, int parts, int Kt, const float *b, const bf16_t *in, bool from_lds) __attribute__((always_inline)) {
       constexpr int NP = decltype(np)::value;
       anew(rank), anew(T);
-      for (int tile = rank; tile - rank < wg_tiles; tile += T) {
-        if (tile < wg_tiles) {
-          bf16x8 x[NP];
-#pragma unroll
-          for (int i = 0; i < NP; ++i)
-            if (!from_lds && wave + TEAM_WAVES * i < Kt) x[i] = load_shared16(in, (wave + TEAM_WAVES * i) * 1024 + act_lane(lane) * 16);
-          if (from_lds)
-#pragma unroll
-            for (int i = 0; i < NP; ++i)
-              if (wave + TEAM_WAVES * i < Kt) x[i] = *(const bf16x8 *)&s.act[col][32 * (wave + TEAM_WAVES * i) % TEAM_MAX_D + 8 * grp];
-          if (tile != rank) load_part(np, W, G, Kt, b, tile);
-          floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int i = 0; i < NP; ++i)
-            if (wave + TEAM_WAVES * i < Kt) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], x[i], acc, 0, 0, 0);
-          s.red[set][wave][lane] = acc;
+      for (int tile = rank; tile < wg_tiles; tile += T) {
+        if (tile != rank) {
+          load_part(np, W, table, Kt, b, tile);
+          bar();  // the sums of the tile before have been read
         }
+        bf16x8 x[NP];
+        if (from_lds)
+          walk_steps<NP>(steps, [&](int i, uint32_t e) __attribute__((always_inline)) {
+            if (e & TEAM_STEP_K) x[i] = *(const bf16x8 *)&s.act[col][32 * (e & 63) % TEAM_MAX_D + 8 * grp];
+          });
+        else
+          walk_steps<NP>(steps, [&](int i, uint32_t e) __attribute__((always_inline)) {
+            if (e & TEAM_STEP_K) x[i] = load_shared16(in, (e & 63) * 1024 + act_lane(lane) * 16);
+          });
+        floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+        walk_steps<NP>(steps, [&](int i, uint32_t e) __attribute__((always_inline)) {
+          if (e & TEAM_STEP_K) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], x[i], acc, 0, 0, 0);
+          if (e & TEAM_STEP_LAST) {
+            s.red[e >> TEAM_STEP_SUM][lane] = acc;
+            acc = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+        });
         bar();
-        if (wave == 0 && tile < wg_tiles) {
-          floatx4 v = bias;
+        if (wave == 0) {
+          auto part_sum = [&](int part) __attribute__((always_inline)) {
+            floatx4 p = s.red[part * NV][lane];
 #pragma unroll
-          for (int k = 0; k < TEAM_WAVES; ++k) v += s.red[set][k][lane];
+            for (int k = 1; k < NV; ++k) p += s.red[part * NV + k][lane];
+            return p;
+          };
+          floatx4 v;
+          if (parts == 2) {  // (both requested together)
+            const floatx4 v0 = part_sum(0), v1 = part_sum(1);
+            v = v0 + v1;
+          } else {
+            v = part_sum(0);
+            for (int part = 1; part < parts; ++part) v += part_sum(part);
+          }
+          v += bias;
           if (col < R) *(floatx4 *)&wk_y()[(long)col * d + tile * 16 + 4 * grp] = v;
         }
-        set ^= 1;  // (two iterations on, a barrier lies between these reads and the next writes)
       }
     };
 
-    // attention: W waves share a (row, head) pair
-    int pairs = R * H;
-    int wpp = TEAM_WAVES;
-    while (wpp > 1 && (pairs * wpp > T * TEAM_WAVES || wpp / 2 * 32 >= ap->longest)) wpp >>= 1;
-    // long rows of few pairs: workgroups that would have no pair take a share of the keys of one (att_iters is 1 then)
-    int splits = 1;
-    if (wpp == TEAM_WAVES)
-      while (2 * splits * pairs <= T && splits < TEAM_SPLITS && 32 * TEAM_WAVES * splits < ap->longest) splits *= 2;
-    int stride = wpp * splits;  // blocks between two of a wave
-    int sub = wave / wpp, ws0 = wave % wpp;
-    const int teams = TEAM_WAVES / wpp, att_iters = (pairs + T * teams - 1) / (T * teams);
-    int split = splits > 1 ? rank / pairs : 0, pair0 = splits > 1 ? (split < splits ? rank - split * pairs : pairs) : sub * T + rank;
-    int ws = ws0 + wpp * split;  // the wave's first block
-    const int bpp = ap->kv.page_tokens >> 5;
+    // Attention: the keys of a (row, head) pair are shared out over `splits` x `states` softmax states, every states-th
+    // block of a split each, as the separate kernels share them out over workgroups and waves; they say how the sums are taken.
+    // rw waves of a workgroup have the states of one (pair, split) between them: what a team of another size changes.
+    auto splits_of = [&]() __attribute__((always_inline)) { return ap->attn_splits; };
+    int lrw = 3;  // log2 of rw
+    while (lrw > 0 && ((1 << lrw) > ap->attn_waves || (4 << lrw > ap->attn_waves &&  // (at most four states a wave: TEAM_SUMS)
+                                                       ((R * H * ap->attn_splits << lrw) > T * TEAM_WAVES || 16 << lrw >= ap->longest))))
+      --lrw;
+    // page of a block; block / blocks per page, exact below 2^20 blocks: the quotient is half a block from the next integer
+    auto page_at = [&](WordPtr pages, int blk) __attribute__((always_inline)) {
+      return (int)pages[__builtin_amdgcn_readfirstlane((int)(((float)blk + 0.5f) * __builtin_amdgcn_rcpf((float)(ap->kv.page_tokens >> 5))))];
+    };
     const KvGeom kvg{ap->kv.page_tokens, ap->kv.max_pages, H, DH, ap->kv.page_elems};
     int first_page = -1;  // of the wave's first block, looked up before it is needed; -1: it has none
-    auto page_of = [&](const int32_t *bt, int p, int blk) __attribute__((always_inline)) {
-      return bt[(long)__builtin_amdgcn_readfirstlane(s.row[p / H]) * ap->kv.max_pages + blk / bpp];
+    auto split_len = [](int splits, int nblk) __attribute__((always_inline)) { return splits > 1 ? (nblk + splits - 1) / splits : nblk; };  // blocks
+    auto pages_of = [&](const int32_t *bt, int p) __attribute__((always_inline)) {
+      return (WordPtr)bt + (long)__builtin_amdgcn_readfirstlane(s.row[p / H]) * ap->kv.max_pages;
     };
-    auto load_block = [&](int page, int p, int blk) __attribute__((always_inline)) {
+    auto load_block = [&](bf16x8(&kv)[2 * QC + VM], int page, int p, int blk) __attribute__((always_inline)) {
       const bf16x8 *kp = (const bf16x8 *)(ap->pool + (long)page * ap->kv.page_elems + (long)(p % H) * (ap->kv.page_tokens * DH * 2) +
-                                          (long)(blk % bpp) * (64 * DH)) + lane;
+                                          (long)(blk % (ap->kv.page_tokens >> 5)) * (64 * DH)) + lane;
 #pragma unroll
       for (int i = 0; i < 2 * QC + VM; ++i) kv[i] = kp[i * 64];
     };
-    auto find_first = [&](const int32_t *bt, int p) __attribute__((always_inline)) {
-      first_page = -1;
-      if (p < pairs && 32 * ws < ap->t - __builtin_amdgcn_readfirstlane(s.start[p / H])) first_page = page_of(bt, p, ws);
-    };
-    auto first_block = [&](int p) __attribute__((always_inline)) {
-      forget_kv();
-      if (first_page >= 0) load_block(first_page, p, ws);
+    auto first_block = [&](const int32_t *bt, bool load) __attribute__((always_inline)) {
+      const int splits = splits_of(), pairs = R * H, item = (wave >> lrw) * T + rank, sp = splits > 1 ? item / pairs : 0, p = item - sp * pairs;
+      const int nblk = sp < splits && p < pairs ? (ap->t - __builtin_amdgcn_readfirstlane(s.start[p / H]) + 31) >> 5 : 0;
+      const int per = split_len(splits, nblk), blk = sp * per + (wave & ((1 << lrw) - 1));
+      if (load) {
+        forget_kv();
+        if (first_page >= 0) load_block(kv, first_page, p, blk);
+      } else {
+        first_page = blk < min(sp * per + per, nblk) ? page_at(pages_of(bt, p), blk) : -1;
+      }
     };
     const float scale = 1.0f / sqrtf((float)DH);
     auto attend = [&](const int32_t *bt) __attribute__((always_inline)) {
-      anew(ws), anew(ws0), anew(sub), anew(wpp), anew(stride), anew(pair0), anew(split), anew(pairs);
-      for (int it = 0; it < att_iters; ++it) {
-        const int p = pair0 + it * teams * T;
-        const bool live = p < pairs;
-        const int j = live ? p / H : 0, h = live ? p - j * H : 0;
+      anew(lrw), anew(rank), anew(T);
+      const int states = ap->attn_waves, splits = splits_of(), pairs = R * H, rw = 1 << lrw, sub = wave >> lrw, ws0 = wave & (rw - 1);
+      const int at_once = T * (TEAM_WAVES >> lrw), items = pairs * splits, item0 = sub * T + rank;
+      for (int it = 0; it == 0 || it * at_once < items; ++it) {
+        const int item = item0 + it * at_once;
+        const bool live = item < items;
+        const int sp = live && splits > 1 ? item / pairs : 0, p = live ? item - sp * pairs : 0;
+        const int j = p / H, h = p - j * H;
         const int len = ap->t - __builtin_amdgcn_readfirstlane(s.start[j]);  // cached keys (negative: column t is still padding for this row)
-        const int nblk = (len + 31) >> 5;
-        const int te = ws0 * 64 + lane;     // this thread's element of the new position (and te + 64 for a wave alone on 128)
-        constexpr int EPT = DH / 64;
+        const int nblk = (len + 31) >> 5, per = split_len(splits, nblk), lo = sp * per, hi = min(lo + per, nblk);
+        constexpr int EPT = DH / 64;        // this thread's elements of the new position: te + 64 rw i, below DH
+        const int te = ws0 * 64 + lane;
         bf16_t q_bits[EPT], k_bits[EPT], v_bits[EPT];
-        const bool with_new = live && len >= 0 && split == 0;
+        const bool with_new = live && len >= 0 && sp + 1 == splits;
         int page_t = 0;
         if (live) {
           bf16x8 qf[QC];
@@ -372,7 +456,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
           for (int c = 0; c < QC; ++c) qf[c] = load_shared16(wk_q(), (j * d + h * DH + 32 * c + 8 * grp) * 2);
 #pragma unroll
           for (int i = 0; i < EPT; ++i) {
-            const int e = te + i * wpp * 64;
+            const int e = te + i * rw * 64;
             q_bits[i] = k_bits[i] = v_bits[i] = 0;
             if (with_new && e < DH) {
               const bf16_t *kr = wk_kv() + (long)j * 2 * d + h * DH + e;
@@ -381,12 +465,27 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
               q_bits[i] = __hip_atomic_load(wk_q() + (long)j * d + h * DH + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
           }
-          if (with_new) page_t = bt[(long)__builtin_amdgcn_readfirstlane(s.row[j]) * ap->kv.max_pages + len / ap->kv.page_tokens];
+          const WordPtr pages = pages_of(bt, p);
+          if (with_new) page_t = (int)pages[len / ap->kv.page_tokens];
           floatx4 O[VM];
+          float m_run, l_run;
+          auto fresh = [&]() __attribute__((always_inline)) {
 #pragma unroll
-          for (int m = 0; m < VM; ++m) O[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-          float m_run = -1.0e30f, l_run = 0.f;
-          auto use_block = [&](int blk) __attribute__((always_inline)) {
+            for (int m = 0; m < VM; ++m) O[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+            m_run = -1.0e30f;
+            l_run = 0.f;
+          };
+          auto leave = [&](int st) __attribute__((always_inline)) {  // the state to LDS
+            const int at = sub * states + st;
+            if (lane == 0) { s.m[at] = m_run; s.l[at] = l_run; }
+            if (col == 0) {
+#pragma unroll
+              for (int m = 0; m < VM; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s.o[at][16 * m + 4 * grp + i] = O[m][i];
+            }
+          };
+          auto use_block = [&](bf16x8(&kv)[2 * QC + VM], int blk) __attribute__((always_inline)) {
             floatx4 S[2];
 #pragma unroll
             for (int tl = 0; tl < 2; ++tl) {
@@ -421,58 +520,103 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
               O[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv[2 * QC + m], pv, O[m], 0, 0, 0);
             }
           };
-          if (ws < nblk) {
-            if (it) load_block(page_of(bt, p, ws), p, ws);
-            use_block(ws);
+          const int filled = min(hi - lo, states);  // states with a block; the others are left as they begin
+          fresh();
+          for (int st = ws0; st < states; st += rw)
+            if (st >= filled) leave(st);
+          int st = ws0, blk = lo + ws0, st1 = st, blk1 = blk, page1 = 0;
+          auto advance = [&]() __attribute__((always_inline)) {  // to the wave's next block
+            blk1 += states;
+            if (blk1 >= hi) {
+              st1 += rw;
+              blk1 = lo + st1;
+            }
+            if (st1 < filled) page1 = page_at(pages, blk1);
+          };
+          // one block, and the request for the next one (64-wide heads: ahead of it)
+          auto step = [&](bf16x8(&kv)[2 * QC + VM], bf16x8(&next)[2 * QC + VM]) __attribute__((always_inline)) {
+            const bool more = st1 < filled;
+            const int st_next = st1, blk_next = blk1, page_next = page1;
+            if constexpr (DH == 64) if (more) load_block(next, page_next, p, blk_next);
+            advance();
+            use_block(kv, blk);
+            if (st_next != st) {
+              __builtin_amdgcn_sched_barrier(0);
+              l_run += __shfl_xor(l_run, 16);
+              l_run += __shfl_xor(l_run, 32);
+              leave(st);
+              fresh();
+            }
+            if constexpr (DH != 64) if (more) load_block(next, page_next, p, blk_next);
+            st = st_next;
+            blk = blk_next;
+            return more;
+          };
+          if (st < filled) {
+            if (it) load_block(kv, page_at(pages, blk), p, blk);
+            advance();
+            if constexpr (DH == 64) {
+              bf16x8 kv1[2 * QC + VM];
+              while (step(kv, kv1) && step(kv1, kv)) {}
+            } else {
+              while (step(kv, kv)) {}
+            }
           }
-          for (int blk = ws + stride; blk < nblk; blk += stride) {
-            load_block(page_of(bt, p, blk), p, blk);
-            use_block(blk);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          l_run += __shfl_xor(l_run, 16);
-          l_run += __shfl_xor(l_run, 32);
-          float dot = 0.f;
 #pragma unroll
-          for (int i = 0; i < EPT; ++i) dot += bf2f(q_bits[i]) * bf2f(k_bits[i]);
-          dot = wave_sum_f(dot);
-          if (lane == 0) { s.m[wave] = m_run; s.l[wave] = l_run; s.dot[wave] = dot; }
-          if (col == 0) {
-#pragma unroll
-            for (int m = 0; m < VM; ++m)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) s.o[wave][16 * m + 4 * grp + i] = O[m][i];
+          for (int i = 0; i < EPT; ++i) {  // q . k of the new position, 64 elements at a time
+            float dot = bf2f(q_bits[i]) * bf2f(k_bits[i]);
+            dot += __shfl_xor(dot, 32);
+            dot += __shfl_xor(dot, 16);
+            dot = row_sum(dot);
+            if (lane == 0 && ws0 + i * rw < EPT) s.dot[sub * 2 + ws0 + i * rw] = dot;
           }
         }
-        if (wpp > 1) bar();
+        if (rw > 1) bar();
         else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (live) {
-          const int w0 = sub * wpp;
-          float pm[TEAM_WAVES], pl[TEAM_WAVES], M = -1.0e30f, s_t = 0.f;  // all partial results requested together
+        auto merge = [&](auto chunk) __attribute__((always_inline)) {  // states requested together
+          constexpr int N = decltype(chunk)::value;
+          const int w0 = sub * states;
+          float pm[N], pl[N], M = -1.0e30f, s_t = 0.f;
+          auto request = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-          for (int k = 0; k < TEAM_WAVES; ++k) {
-            const int at = w0 + (k < wpp ? k : 0);
-            pm[k] = s.m[at];
-            pl[k] = s.l[at];
+            for (int k = 0; k < N; ++k) {
+              const int at = w0 + (k0 + k < states ? k0 + k : 0);
+              pm[k] = s.m[at];
+              pl[k] = s.l[at];
+            }
+          };
+          request(0);
+          float dots[EPT];
+#pragma unroll
+          for (int k = 0; k < EPT; ++k) dots[k] = s.dot[sub * 2 + k];
+          for (int k0 = 0;;) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) M = fmaxf(M, pm[k]);
+            if ((k0 += N) >= states) break;
+            request(k0);
           }
-#pragma unroll
-          for (int k = 0; k < TEAM_WAVES; ++k) M = fmaxf(M, pm[k]);
           if (with_new) {
-            for (int k = 0; k < wpp && k < EPT; ++k) s_t += s.dot[w0 + k];
+#pragma unroll
+            for (int k = 0; k < EPT; ++k) s_t += dots[k];
             s_t *= scale;
             M = fmaxf(M, s_t);
           }
 #pragma unroll
-          for (int k = 0; k < TEAM_WAVES; ++k) pm[k] = k < wpp ? __expf(pm[k] - M) : 0.f;
-#pragma unroll
           for (int i = 0; i < EPT; ++i) {
-            const int e = te + i * wpp * 64;
+            const int e = te + i * rw * 64;
             if (e >= DH) continue;
             float num = 0.f, den = 0.f;
+            for (int k0 = 0; k0 < states; k0 += N) {
+              float po[N];
+              if (states > N) request(k0);
 #pragma unroll
-            for (int k = 0; k < TEAM_WAVES; ++k) {
-              num += pm[k] * s.o[w0 + (k < wpp ? k : 0)][e];
-              den += pm[k] * pl[k];
+              for (int k = 0; k < N; ++k) po[k] = s.o[w0 + (k0 + k < states ? k0 + k : 0)][e];
+#pragma unroll
+              for (int k = 0; k < N; ++k) {
+                const float g = k0 + k < states ? __expf(pm[k] - M) : 0.f;
+                num += g * po[k];
+                den += g * pl[k];
+              }
             }
             if (with_new) {
               const float g = __expf(s_t - M);
@@ -482,7 +626,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
             if (splits == 1) {
               wk_o()[d_act_index(j, h * DH + e, d)] = (bf16_t)f2bf(den > 0.f ? num / den : 0.f);
             } else {
-              float *part = wk_part() + (long)(split * pairs + p) * (DH + 4);
+              float *part = wk_part() + (long)item * (DH + 4);
               part[e] = num;
               if (e < 2) part[DH + e] = e ? den : M;
             }
@@ -493,8 +637,12 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
               pg[kv_v_off(h, tt, e, kvg)] = v_bits[i];
             }
           }
+        };
+        if (live) {
+          if (states <= 2) merge(Parts<2>{});
+          else merge(Parts<DH == 64 ? 8 : 4>{});
         }
-        if (wpp > 1 && it + 1 < att_iters) bar();  // the partial results have been read
+        if (rw > 1 && (it + 1) * at_once < items) bar();  // the partial results have been read
       }
     };
     auto layer_of = [&](int i) __attribute__((always_inline)) -> LayerPtr { return (LayerPtr)ap->layers + (i < ap->warmup ? i : ap->L - ap->n + i); };
@@ -519,7 +667,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       }
       load_ln(L0->ln1_g, L0->ln1_b);
       forget_w();
-          if (tile0 < 3 * wg_tiles) load_tile(L0->wqkv, ap->G_qkv, L0->bqkv, tile0);
+      if (tile0 < 3 * wg_tiles) load_tile(L0->wqkv, ap->rot_qkv, L0->bqkv, tile0);
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int j = wave + 8 * jj;
@@ -540,11 +688,11 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       phase();
       anew(R), anew(group);
       anew(tile0);
-      find_first(L->bt, pair0);
+      first_block(L->bt, false);
       bar();  // act
       {
         for (int tile = tile0; tile < 3 * wg_tiles; tile += TEAM_WAVES * T) {
-          if (tile != tile0) load_tile(L->wqkv, ap->G_qkv, L->bqkv, tile);
+          if (tile != tile0) load_tile(L->wqkv, ap->rot_qkv, L->bqkv, tile);
           const floatx4 v = mul_tile();
           const int n0 = tile * 16 + 4 * grp, which = n0 / d, within = n0 - which * d;
           const uint2 pk = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
@@ -554,24 +702,24 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
           }
         }
       }
-      team_bar([&]() __attribute__((always_inline)) { forget_w(); first_block(pair0); });
+      team_bar([&]() __attribute__((always_inline)) { forget_w(); first_block(L->bt, true); });
       // ---- attention
       phase();
       anew(R), anew(group);
       attend(L->bt);
       team_bar([&]() __attribute__((always_inline)) {
         forget_w();
-        if (rank < wg_tiles) load_part(Parts<(Kd + TEAM_WAVES - 1) / TEAM_WAVES>{}, L->wo, ap->G_out, Kd, L->bo, rank);
+        if (rank < wg_tiles) load_part(OutSteps{}, L->wo, ap->out_steps, Kd, L->bo, rank);
       });
       // ---- output projection
       phase();
       anew(R), anew(group);
-      if (splits > 1) merge_splits(splits, pairs);
-      project(Parts<(Kd + TEAM_WAVES - 1) / TEAM_WAVES>{}, L->wo, ap->G_out, Kd, L->bo, wk_o(), splits > 1);
+      if (splits_of() > 1) merge_splits(splits_of(), R * H);
+      project(OutSteps{}, L->wo, ap->out_steps, ap->out_parts, Kd, L->bo, wk_o(), splits_of() > 1);
       team_bar([&]() __attribute__((always_inline)) {
         load_ln(L->ln2_g, L->ln2_b);
         forget_w();
-        if (tile0 < Kf * 2) load_tile(L->w1, ap->G_ffn1, L->b1, tile0);
+        if (tile0 < Kf * 2) load_tile(L->w1, ap->rot_ffn1, L->b1, tile0);
       });
       // ---- FFN1
       phase();
@@ -581,7 +729,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       bar();
       {
         for (int tile = tile0; tile < Kf * 2; tile += TEAM_WAVES * T) {
-          if (tile != tile0) load_tile(L->w1, ap->G_ffn1, L->b1, tile);
+          if (tile != tile0) load_tile(L->w1, ap->rot_ffn1, L->b1, tile);
           floatx4 v = mul_tile();
           for (int k = 0; k < 4; ++k) v[k] = fmaxf(v[k], 0.f);
           if (col < R) *(uint2 *)&wk_u()[d_act_index(col, tile * 16 + 4 * grp, f)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
@@ -589,12 +737,12 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       }
       team_bar([&]() __attribute__((always_inline)) {
         forget_w();
-        if (rank < wg_tiles) load_part(Parts<(TEAM_MAX_F / 32 + TEAM_WAVES - 1) / TEAM_WAVES>{}, L->w2, ap->G_ffn2, Kf, L->b2, rank);
+        if (rank < wg_tiles) load_part(Parts<TEAM_FFN2_STEPS>{}, L->w2, ap->ffn2_steps, Kf, L->b2, rank);
       });
       // ---- FFN2
       phase();
       anew(R), anew(group);
-      project(Parts<(TEAM_MAX_F / 32 + TEAM_WAVES - 1) / TEAM_WAVES>{}, L->w2, ap->G_ffn2, Kf, L->b2, wk_u(), false);
+      project(Parts<TEAM_FFN2_STEPS>{}, L->w2, ap->ffn2_steps, ap->ffn2_parts, Kf, L->b2, wk_u(), false);
       if (i + 1 == ap->n && rank == 0 && threadIdx.x == 64 * (TEAM_WAVES - 1))  // another group that no team has taken
         ctl_store(&slot->next, ctl_add(&ap->ctl->next_group, 1u));
       team_bar([&]() __attribute__((always_inline)) {
@@ -602,7 +750,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
           LayerPtr N = layer_of(i + 1);
           load_ln(N->ln1_g, N->ln1_b);
           forget_w();
-          if (tile0 < 3 * wg_tiles) load_tile(N->wqkv, ap->G_qkv, N->bqkv, tile0);
+          if (tile0 < 3 * wg_tiles) load_tile(N->wqkv, ap->rot_qkv, N->bqkv, tile0);
         } else {
           load_ln(ap->lnf_g, ap->lnf_b);
         }
@@ -651,8 +799,8 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
 
 // Every XCD reads all the weights: at the widest model taken here 6 to 8 MiB a layer at about 1.0 TB/s for each of eight
 // XCDs, 6 to 8 us, and the rest of a layer takes 9 to 12.  us per step of 4 layers, separate kernels -> this: (256, ffn 1024)
-// 1 row at 16 keys 69 -> 52, 16 rows at 200 keys 90 -> 57, at 2000 keys 116 -> 75, 128 rows at 200 keys 125 -> 80;
-// (384, 1024) 77 -> 61, 96 -> 67, 140 -> 90, 147 -> 96; (512, 1536) 82 -> 68, 102 -> 80, 145 -> 112, 159 -> 115.
+// 1 row at 16 keys 90 -> 48, 16 rows at 200 keys 117 -> 57, at 2000 keys 147 -> 82, 128 rows at 200 keys 148 -> 82;
+// (384, 1024) 90 -> 56, 125 -> 67, 161 -> 97, 165 -> 99; (512, 2048) 95 -> 74, 127 -> 89, 161 -> 125, 172 -> 124.
 bool bf16_team_ok(int d, int f, int B) {
   return d <= TEAM_MAX_D && f <= TEAM_MAX_F && d % 64 == 0 && f % 32 == 0 && B >= 1 && B <= 128;
 }
@@ -662,18 +810,68 @@ int bf16_team_members(int cus, int d) { return cus < d / 16 ? (cus > 1 ? cus : 1
 int bf16_team_groups(int B) { return B < 8 ? B : 8; }
 size_t bf16_team_rows() { return 8 * TEAM_ROWS; }
 size_t bf16_team_part() { return 8 * TEAM_PARTS * (128 + 4); }
+// The k-steps of every tile and wave of a projection whose separate kernel has p.waves waves, p.unit k-steps a buffer, p.split
+// K parts and maybe a rotated start (table: null, or [N / 16][TEAM_WAVES]); false if they are not among what the column can
+// take, at most `most` steps of a wave.
+static bool team_steps(TeamStep *table, int N, int K, const TeamSums &p, int most) {
+  const int Kf = K / 32;
+  if ((p.waves != 8 && p.waves != 4) || p.unit < 1 || p.split < 1 || Kf % p.split || p.split * p.waves > TEAM_SUMS) return false;
+  const int n = Kf / p.split;
+  int unit = p.unit;
+  while (unit > 1 && n % unit) unit >>= 1;  // whole buffers, as the launch takes them
+  if (p.rotate && (n % 4 || p.waves != 4 || unit != 1)) return false;
+  for (int tile = 0; tile < N / 16; ++tile)
+    for (int wave = 0; wave < TEAM_WAVES; ++wave) {
+      TeamStep list{};
+      int at = 0;
+      for (int part = wave / p.waves; part < p.split; part += TEAM_WAVES / p.waves) {  // (wave % p.waves) of the separate kernel
+        const int turns = std::max(1, (n / unit - wave % p.waves + p.waves - 1) / p.waves), rot = p.rotate ? ((tile >> 3) * 5 + part * 3) % (n / 4) : 0;
+        for (int i = 0; i < turns * unit; ++i) {
+          if (at >= most) return false;
+          int k = (wave % p.waves + p.waves * (i / unit)) * unit + i % unit;
+          uint32_t e = TEAM_STEP_USED;
+          if (k < n) e |= TEAM_STEP_K | (part * n + (k + 4 * rot) % n);
+          if (i + 1 == turns * unit) e |= TEAM_STEP_LAST;
+          list.e[at++] = (uint16_t)(e | (part * p.waves + wave % p.waves) << TEAM_STEP_SUM);
+        }
+      }
+      if (table) table[tile * TEAM_WAVES + wave] = list;
+    }
+  return true;
+}
+size_t bf16_team_steps(int d) { return (size_t)(d / 16) * TEAM_WAVES; }
+bool bf16_team_sums(TeamArgs &a, int B_pad, const TeamSums &qkv, const TeamSums &out, const TeamSums &ffn1, const TeamSums &ffn2,
+                    TeamStep *out_steps, TeamStep *ffn2_steps) {
+  a.wide = B_pad >= 96;
+  for (const TeamSums *p : {&qkv, &out, &ffn1, &ffn2})
+    if (p->tiles != 1 || p->waves != (a.wide ? 4 : 8)) return false;
+  for (const TeamSums *p : {&qkv, &ffn1})
+    if (p->unit != 1 || p->split != 1 || (p->rotate && (!a.wide || a.d % 128))) return false;
+  a.rot_qkv = qkv.rotate;
+  a.rot_ffn1 = ffn1.rotate;
+  a.out_parts = out.split;
+  a.ffn2_parts = ffn2.split;
+  return team_steps(out_steps, a.d, a.d, out, a.wide ? TEAM_OUT_STEPS_WIDE : TEAM_OUT_STEPS) &&
+         team_steps(ffn2_steps, a.d, a.f, ffn2, TEAM_FFN2_STEPS);
+}
+// Keys shared out over `states` softmax states in each of `splits` parts.
+bool bf16_team_states(const TeamArgs &a, int states, int splits) {
+  const int rows = (a.B + a.groups - 1) / a.groups, pairs = rows * (a.d / a.kv.dh);
+  return states >= 1 && states <= 16 && !(states & (states - 1)) && splits >= 1 && splits <= TEAM_SPLITS && (splits == 1 || pairs * splits <= TEAM_PARTS);
+}
 
 bool bf16_team_column(hipStream_t s, const TeamArgs &a) {
   static_assert(sizeof(TeamLds) <= 96 * 1024, "LDS of a workgroup");
-  if (!bf16_team_ok(a.d, a.f, a.B) || a.n < 1 || a.workgroups < 1 || a.members < 1 || a.members > TEAM_PARTS) return false;
+  if (!bf16_team_ok(a.d, a.f, a.B) || a.n < 1 || a.workgroups < 1 || a.members < 1 || !bf16_team_states(a, a.attn_waves, a.attn_splits)) return false;
   const dim3 grid(a.workgroups), blk(TEAM_THREADS);
-#define SKD_TEAM(DH, KD)                                                                                \
+#define SKD_TEAM_NV(DH, KD, NV)                                                                         \
   {                                                                                                     \
     static std::atomic<uint64_t> done{0};                                                               \
-    if (!allow_lds(done, {(const void *)k_team_column<DH, KD>}, sizeof(TeamLds))) return false;         \
-    SKD_LAUNCH((k_team_column<DH, KD>), grid, blk, sizeof(TeamLds), s, a);                              \
+    if (!allow_lds(done, {(const void *)k_team_column<DH, KD, NV>}, sizeof(TeamLds))) return false;     \
+    SKD_LAUNCH((k_team_column<DH, KD, NV>), grid, blk, sizeof(TeamLds), s, a);                          \
     break;                                                                                              \
   }
+#define SKD_TEAM(DH, KD) if (a.wide) SKD_TEAM_NV(DH, KD, 4) else SKD_TEAM_NV(DH, KD, 8)
   if (a.kv.dh == 64) switch (a.d / 64) {
     case 1: SKD_TEAM(64, 2) case 2: SKD_TEAM(64, 4) case 3: SKD_TEAM(64, 6) case 4: SKD_TEAM(64, 8)
     case 5: SKD_TEAM(64, 10) case 6: SKD_TEAM(64, 12) case 7: SKD_TEAM(64, 14) case 8: SKD_TEAM(64, 16)
@@ -681,6 +879,7 @@ bool bf16_team_column(hipStream_t s, const TeamArgs &a) {
     case 1: SKD_TEAM(128, 4) case 2: SKD_TEAM(128, 8) case 3: SKD_TEAM(128, 12) case 4: SKD_TEAM(128, 16)
   }
 #undef SKD_TEAM
+#undef SKD_TEAM_NV
   return true;
 }
 
