@@ -142,6 +142,7 @@ struct skd_state {
   int start_min = 0;               // first real column of the longest row
   // whole columns in one launch (narrow models)
   bool team = false;
+  bool team_always = false;        // by override: at every number of cached keys
   TeamArgs team_args{};            // what is the same for every column
   std::vector<unsigned char> team_table;  // source of the copy at the head of its buffers
   // batched prompt workspace (allocated by the first batched skd_prefill)
@@ -542,6 +543,13 @@ int run_layer(skd_state *st, int l, int t, const LayerW *prev, const LayerW *nex
   return SKD_OK;
 }
 
+// Whether the column at position t is one that the one-launch kernel does faster (bf16_team_keys).
+bool team_keys(const skd_state *st, int t) {
+  int64_t total = 0;
+  for (int b = 0; b < st->cfg.batch; ++b) total += std::max(0, t - (st->start_host.empty() ? 0 : st->start_host[b]));
+  return st->team_always || bf16_team_keys(st->cfg.d_model, st->cfg.batch, t - st->start_min, total);
+}
+
 // Whether the list is what a schedule gives: warm-up layers, then the top of the stack.
 bool scheduled_set(const skd_state *st, const int32_t *layers, int n) {
   const skd_config &c = st->cfg;
@@ -579,7 +587,7 @@ int run_column(skd_state *st, int t, const int32_t *tokens_dev, const int32_t *l
       { ProfScope ps_(st, SKD_PROF_OTHER); f32_linear(s, (const float *)w.w2, w.b2, u, st->x, B, f, d, 0, 1); }
       st->kv_len[layers[i]] = t + 1;
     }
-  } else if (st->team && !st->profiling && scheduled_set(st, layers, n)) {  // per-kernel timing times separate kernels
+  } else if (st->team && !st->profiling && scheduled_set(st, layers, n) && team_keys(st, t)) {  // per-kernel timing times separate kernels
     TeamArgs ta = st->team_args;
     ta.n = n;
     ta.t = t;
@@ -669,6 +677,7 @@ static int prepare_team(skd_state *st) {
   ta.pool = (bf16_t *)st->pool;
   ta.x_out = st->x; ta.a_out = (bf16_t *)st->a;
   st->team = true;
+  st->team_always = env_int("SKD_TEAM", 1) == 2;
   return SKD_OK;
 }
 

@@ -291,6 +291,8 @@ struct TeamArgs {
   bf16_t *a_out;                      // activation tiles [B_pad][d]: their final LayerNorm
 };
 bool bf16_team_ok(int d, int f, int B);
+// Whether a column of B rows whose longest has `longest` cached keys, and all of them `total`, is faster this way.
+bool bf16_team_keys(int d, int B, long longest, long total);
 int bf16_team_groups(int B);
 int bf16_team_members(int cus, int d);
 size_t bf16_team_rows();              // rows of each work buffer

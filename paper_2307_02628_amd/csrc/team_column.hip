@@ -804,6 +804,19 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
 bool bf16_team_ok(int d, int f, int B) {
   return d <= TEAM_MAX_D && f <= TEAM_MAX_F && d % 64 == 0 && f % 32 == 0 && B >= 1 && B <= 128;
 }
+// d / 2 workgroups share out the keys, the separate kernels spread them over 256 CUs: the time they take grows with rows x
+// keys here and with rows x keys x d there.  us per step of 4 layers, separate -> this, by total of cached keys:
+//   (64, ffn 256)  32 rows  96 000: 150 -> 139, 128 000: 154 -> 159;  (64, 2048) 64 rows 96 000: 154 -> 155
+//   (128, 512)     64 rows  96 000: 132 -> 123, 128 000: 141 -> 141, 192 000: 160 -> 200
+//   (192, 768)    128 rows 128 000: 177 -> 180, 64 rows: 175 -> 172
+//   (256, 1024)    96 rows 144 000: 212 -> 202, 288 000: 299 -> 310
+//   (320, 1024)    96 rows 192 000: 259 -> 256;  (384, 1024) 128 rows 256 000: 353 -> 336
+//   (512, 2048)    32 rows 192 000: 326 -> 320, 256 000: 401 -> 400
+// Fewer rows than XCDs leave some idle: (512, 2048) one row of 4000 keys 112 -> 106, of 6000 114 -> 118, four of 8000 148 ->
+// 141; (384, 1024) one of 8000 119 -> 103, (256, 1024) 96 -> 90, (64, 256) 98 -> 81; more than 8192 keys were not measured.
+bool bf16_team_keys(int d, int B, long longest, long total) {
+  return total <= (d >= 384 ? 256000 : 320L * (d + 176)) && (B >= 8 || longest <= (d > 384 && B <= 2 ? 4096 : 8192));
+}
 // As many as the output projection and FFN2 have tiles (at most TEAM_PARTS): a larger team only makes the barriers longer
 // (256 wide, 16 rows at 16 keys: 53, 59, 65 us per step of 4 layers with 16, 24, 32), a smaller one has two rounds.
 int bf16_team_members(int cus, int d) { return cus < d / 16 ? (cus > 1 ? cus : 1) : d / 16; }

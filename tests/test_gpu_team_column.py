@@ -65,6 +65,18 @@ def test_contexts(d, H, B, P):
 
 
 @pytest.mark.gpu
+def test_route_changes_within_a_generation():
+    """128 rows of 64 columns take separate kernels from 600 cached keys on: the state goes on with the same bits."""
+    compare(3, 64, 1, 256, 128, 598, 5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,H,B,P", [(64, 1, 128, 1100), (128, 2, 97, 1500), (512, 8, 1, 4500)])
+def test_more_keys_than_pay(d, H, B, P):
+    compare(2, d, H, 256, B, P, 2, env={"SKD_TEAM": "2"})
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("page_tokens", [32, 96, 416])  # 1, 3 and 13 blocks to a page
 def test_pages(page_tokens):
     compare(2, 256, 4, 256, 3, 900, 3, shortest=50, page_tokens=page_tokens)
