@@ -238,7 +238,11 @@ int skd_kv_len(const skd_state *st, int32_t layer);
 int64_t skd_kv_pages_reserved(const skd_state *st);
 int64_t skd_kv_pages_dense(const skd_state *st);
 
-/* Wait until everything enqueued by this state has finished. */
+/* Wait until everything enqueued by this state has finished.  SKD_ERR_HIP with
+ * skd_last_hip_error() = hipErrorLaunchTimeOut, here and from every other call
+ * that computes or hands over results: a kernel of this state had to go on
+ * without a workgroup that it had waited for over a second.  What the state
+ * holds is then not to be used, and it stays so until skd_destroy. */
 int skd_synchronize(skd_state *st);
 
 /* Test / measurement hooks ------------------------------------------------ */

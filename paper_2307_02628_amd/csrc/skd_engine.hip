@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/skd.h"
+#include "gave_up.h"
 #include "skd_kernels.h"
 
 using namespace skd;
@@ -144,6 +145,7 @@ struct skd_state {
   bool team = false;
   bool team_always = false;        // by override: at every number of cached keys
   TeamArgs team_args{};            // what is the same for every column
+  GaveUp team_gave_up;             // pinned host memory
   std::vector<unsigned char> team_table;  // source of the copy at the head of its buffers
   // batched prompt workspace (allocated by the first batched skd_prefill)
   float *pf_x = nullptr;
@@ -639,6 +641,11 @@ static int prepare_team(skd_state *st) {
     return bf16_team_sums(ta, st->B_pad, sums(st->p_qkv), sums(st->p_out), sums(st->p_ffn1), sums(st->p_ffn2), out, ffn2);
   };
   if (!take_sums(nullptr, nullptr) || !bf16_team_states(ta, st->attn_waves, st->attn_splits)) return SKD_OK;  // separate kernels
+  void *word = nullptr;
+  HIPCHECK(hipHostMalloc(&word, sizeof(uint32_t), hipHostMallocDefault));
+  st->team_gave_up.word = (volatile uint32_t *)word;
+  *st->team_gave_up.word = 0;
+  ta.gave_up = (uint32_t *)word;
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, st->device));
   // one allocation and one copy: control words (zero), layer table and step tables, then the work buffers
@@ -905,7 +912,24 @@ extern "C" void skd_destroy(skd_state *st) {
   for (hipEvent_t e : st->prof_free) (void)hipEventDestroy(e);
   for (void *p : st->allocs) (void)hipFree(p);
   if (st->pin) (void)hipHostFree(st->pin);
+  if (st->team_gave_up.word) (void)hipHostFree((void *)st->team_gave_up.word);
   delete st;
+}
+
+// where a state's one-launch columns report a wait that ran out (null: it has none)
+namespace skd {
+volatile uint32_t *team_gave_up(const skd_state *st) { return st->team_gave_up.word; }
+}
+// SKD_ERR_HIP once a column's kernel had to go on without a workgroup that it waited for: caches, hidden rows and tokens
+// behind it are not to be used.
+static int intact(const skd_state *st) {
+  if (!GaveUp{team_gave_up(st)}.seen()) return SKD_OK;
+  g_last_hip = (int)hipErrorLaunchTimeOut;
+  return SKD_ERR_HIP;
+}
+static int wait_stream(skd_state *st) {
+  HIPCHECK(hipStreamSynchronize(st->stream));
+  return intact(st);
 }
 
 // per-row padding offsets and the dispatch order of the attention workgroups (longest rows first)
@@ -1120,6 +1144,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
 
 extern "C" int skd_prefill(skd_state *st, const int32_t *tokens, const uint8_t *attn_mask) {
   if (!st || !tokens) return SKD_ERR_NULL;
+  SKDCHECK(intact(st));
   const skd_config &c = st->cfg;
   const int B = c.batch, P = c.prompt_size;
   std::vector<int32_t> start(B, 0);
@@ -1166,8 +1191,7 @@ extern "C" int skd_prefill(skd_state *st, const int32_t *tokens, const uint8_t *
     }
   }
   st->prefilled = true;
-  if (!c.io_on_device) HIPCHECK(hipStreamSynchronize(st->stream));
-  return SKD_OK;
+  return c.io_on_device ? SKD_OK : wait_stream(st);
 }
 
 extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_in) {
@@ -1176,6 +1200,7 @@ extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_i
   if (!st->prefilled) return SKD_ERR_ORDER;
   if (t < 0 || t >= c.sequence_length) return SKD_ERR_RANGE;
   if (t != c.prompt_size + st->steps_done) return SKD_ERR_ORDER;
+  SKDCHECK(intact(st));
   const int32_t *tok = nullptr;
   if (!tokens_in) {
     if (!st->have_argmax) return SKD_ERR_ORDER;
@@ -1198,8 +1223,7 @@ extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_i
   if (n < 0) return n;
   SKDCHECK(run_column(st, t, tok, st->layers_tmp.data(), n));
   st->steps_done += 1;
-  if (!c.io_on_device) HIPCHECK(hipStreamSynchronize(st->stream));
-  return SKD_OK;
+  return c.io_on_device ? SKD_OK : wait_stream(st);
 }
 
 // Final LayerNorm + LM head (+ greedy argmax into argmax_dev).  logits_target: device buffer [B][V] or null.
@@ -1244,7 +1268,7 @@ static int head_results(skd_state *st, int32_t *tokens_out, float *logits_out, b
     HIPCHECK(hipMemcpyAsync(tokens_out, st->argmax_dev, c.batch * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   if (logits_out && !direct)
     HIPCHECK(hipMemcpyAsync(pinned ? st->pin->logits : logits_out, st->logits_dev, n * sizeof(float), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
+  SKDCHECK(wait_stream(st));
   if (tokens_out && st->pin) std::copy(st->pin->tok_out, st->pin->tok_out + c.batch, tokens_out);
   if (logits_out && pinned) std::copy(st->pin->logits, st->pin->logits + n, logits_out);
   return SKD_OK;
@@ -1253,6 +1277,7 @@ static int head_results(skd_state *st, int32_t *tokens_out, float *logits_out, b
 extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logits_out) {
   if (!st) return SKD_ERR_NULL;
   if (!st->have_hidden) return SKD_ERR_ORDER;
+  SKDCHECK(intact(st));
   const skd_config &c = st->cfg;
   const int B = c.batch;
   hipStream_t s = st->stream;
@@ -1277,6 +1302,7 @@ extern "C" int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, flo
   if (!st->have_hidden) return SKD_ERR_ORDER;
   const skd_config &c = st->cfg;
   if (!st->bf16 || !c.io_on_device) return SKD_ERR_SHAPE;
+  SKDCHECK(intact(st));
   GemmArgs ga{};
   ga.N = c.vocab;
   int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);
@@ -1306,6 +1332,7 @@ extern "C" int skd_logits_sample(skd_state *st, const float *u, float temperatur
   const skd_config &c = st->cfg;
   const int B = c.batch, V = c.vocab;
   if (V > 65536) return SKD_ERR_SHAPE;
+  SKDCHECK(intact(st));
   hipStream_t s = st->stream;
   const float *u_dev = u;
   if (!c.io_on_device) {
@@ -1371,8 +1398,7 @@ extern "C" int64_t skd_kv_pages_dense(const skd_state *st) { return st ? st->pag
 
 extern "C" int skd_synchronize(skd_state *st) {
   if (!st) return SKD_ERR_NULL;
-  HIPCHECK(hipStreamSynchronize(st->stream));
-  return SKD_OK;
+  return wait_stream(st);
 }
 
 extern "C" int skd_debug_read_hidden(skd_state *st, float *x_out) {
@@ -1380,8 +1406,7 @@ extern "C" int skd_debug_read_hidden(skd_state *st, float *x_out) {
   if (!st->have_hidden) return SKD_ERR_ORDER;
   HIPCHECK(hipMemcpyAsync(x_out, st->x, (size_t)st->cfg.batch * st->cfg.d_model * sizeof(float), hipMemcpyDeviceToHost,
                           st->stream));
-  HIPCHECK(hipStreamSynchronize(st->stream));
-  return SKD_OK;
+  return wait_stream(st);
 }
 
 extern "C" int skd_debug_kv_load(skd_state *st, int32_t cols, const float *const *Kin, const float *const *Vin,
@@ -1452,5 +1477,5 @@ extern "C" int skd_debug_kv_read(skd_state *st, int32_t layer, int32_t b, float 
     rc = SKD_ERR_HIP;
   (void)hipFree(kd);
   (void)hipFree(vd);
-  return rc;
+  return rc != SKD_OK ? rc : intact(st);
 }

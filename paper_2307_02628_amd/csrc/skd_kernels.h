@@ -287,6 +287,7 @@ struct TeamArgs {
   KvGeom kv;
   TeamWork work;
   TeamCtl *ctl;
+  uint32_t *gave_up;                  // host memory: written if a wait runs out (GaveUp)
   float *x_out;                       // [B][d] residual rows behind the last layer
   bf16_t *a_out;                      // activation tiles [B_pad][d]: their final LayerNorm
 };

@@ -44,7 +44,7 @@ constexpr int TEAM_OUT_STEPS = 2, TEAM_OUT_STEPS_WIDE = 4, TEAM_FFN2_STEPS = 8; 
 constexpr uint32_t TEAM_STEP_K = 1 << 6, TEAM_STEP_LAST = 1 << 7, TEAM_STEP_USED = 1 << 8;
 constexpr int TEAM_STEP_SUM = 9;
 constexpr int TEAM_REG_POLLS = 400;       // about 100 us: how long a leader waits for workgroups that have not started
-constexpr int TEAM_MAX_POLLS = 1 << 22;   // over a second; never reached: members run until they arrive
+constexpr int TEAM_MAX_POLLS = 1 << 22;   // over a second; members run until they arrive, so a wait that long is an error (GaveUp)
 
 // 16 bytes that another CU of this XCD may have written in this launch: a buffer load with sc1 (agent scope), which the L1
 // does not answer.  (As two 8-byte atomic loads: 1.8 instead of 1.3 us for FFN2's phase at d = 256, f = 1024.)
@@ -58,6 +58,7 @@ __device__ inline floatx2 load_shared8(const void *p, int byte_offset) {
 }
 __device__ inline uint32_t ctl_load(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void ctl_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void give_up(uint32_t *word) { __hip_atomic_store(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 __device__ inline uint32_t ctl_add(uint32_t *p, uint32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 typedef const TeamArgs __attribute__((address_space(4))) *ArgsPtr;
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       ctl_store(&slot->team, t);
     } else {
       for (int i = 0; i < TEAM_MAX_POLLS && !(t = ctl_load(&slot->team)); ++i) {}
+      if (!t) give_up(ap->gave_up);
     }
     s.rank = rank;
     s.size = (int)(t & 0xffffu);
@@ -163,16 +165,22 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
     asm volatile("" ::: "memory");
   };
   uint32_t arrived = 0;  // by the team, once this workgroup may go on
+  int patience = TEAM_MAX_POLLS;  // of the wave that polls; none left once it had to go on without the others
   // of the team; what the waves do meanwhile: requests for the next phase
   auto team_bar = [&](auto meanwhile) __attribute__((always_inline)) {
     wait_vmcnt<0>();  // stores
     bar();
     arrived += (uint32_t)T;
-    const bool polls = wave == TEAM_WAVES - 1 && lane == 0;  // the wave with the least to request
-    if (polls) (void)ctl_add(&slot->arrived, 1u);
+    const bool polls = wave == TEAM_WAVES - 1;  // the wave with the least to request
+    if (polls && lane == 0) (void)ctl_add(&slot->arrived, 1u);
     meanwhile();
     if (polls)
-      for (int i = 0; i < TEAM_MAX_POLLS && (int)(ctl_load(&slot->arrived) - arrived) < 0; ++i) {}
+      for (int i = 0; __builtin_amdgcn_readfirstlane((int)(ctl_load(&slot->arrived) - arrived)) < 0; ++i)
+        if (i >= patience) {
+          give_up(ap->gave_up);
+          patience = 0;
+          break;
+        }
     bar();
   };
 
@@ -758,7 +766,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       if (i + 1 < ap->n) make_act(true);
     }
     // ---- final LayerNorm: a row per wave of the team
-    if (threadIdx.x == 0) s.group = (int)ctl_load(&slot->next);
+    if (threadIdx.x == 64 * (TEAM_WAVES - 1)) s.group = patience > 0 ? (int)ctl_load(&slot->next) : ap->groups;
     {
       for (int j = tile0; j < R; j += TEAM_WAVES * T) {
         floatx4 v[NC], y[NC];
