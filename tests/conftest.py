@@ -12,6 +12,13 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
 
 
+@pytest.fixture(params=["separate", "default"])
+def narrow_columns(request, monkeypatch):
+    """Models of up to 512 columns decode in one launch per column unless told otherwise: both ways."""
+    if request.param == "separate":
+        monkeypatch.setenv("SKD_TEAM", "0")
+
+
 def pytest_collection_modifyitems(config, items):
     """GPU tests are skipped (not failed) where no GPU is visible."""
     try:

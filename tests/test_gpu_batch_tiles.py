@@ -1,11 +1,12 @@
-"""Batches around the limits of the padded batch sizes (32, 48, 64, 96, 128 rows) against the oracle."""
+"""Batches around the limits of the padded batch sizes (32, 48, 64, 96, 128 rows) against the oracle, on the separate decode
+kernels and on the one-launch columns."""
 import pytest
 
 import synth_inputs as S
 from paper_2307_02628_amd import skd
 from tests.helpers import compare
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("narrow_columns")]
 
 BF16_TOL = 2e-2     # of the logit range: the bar of the bf16 path
 WIDE = S.ModelShape(L=2, d=512, H=4, f=1536, V=1000, max_pos=64)      # 96 and 128 rows on the wave-specialised kernel

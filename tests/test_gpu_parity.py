@@ -33,6 +33,7 @@ def test_config1_fp32():
     print("fp32 config-1 per-step error:", err.max())
 
 
+@pytest.mark.usefixtures("narrow_columns")
 def test_config1_bf16():
     w = bf16_weights(S.TINY, 0)
     pr = S.make_prompts(2, 16, S.TINY.V, 1)
@@ -52,6 +53,7 @@ MID = S.ModelShape(L=3, d=512, H=4, f=1536, V=1000, max_pos=128)      # head_dim
 MID64 = S.ModelShape(L=5, d=384, H=6, f=1024, V=777, max_pos=160)     # head_dim 64
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("dtype,tol", [(skd.FP32, FP32_TOL), (skd.BF16, BF16_TOL)])
 def test_mid_ragged_left_padded(dtype, tol):
     # several KV pages and 32-key blocks, ragged batch (5 rows), left padding, page size 32
@@ -67,6 +69,7 @@ def test_mid_ragged_left_padded(dtype, tol):
     compare(MID, w, pr, P, N, 1, 3, tol, mask=mask, dtype=dtype, page_tokens=32)
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("B", [1, 16, 17, 33, 64, 100])     # activation tiles 1, 1, 2, 4, 4, 8 (batch padded to 16/32/64/128)
 def test_batch_tiles_bf16(B):
     w = bf16_weights(MID64, 5)
@@ -101,6 +104,7 @@ def test_batch_128_projection_kernels(B, ws, small):
             os.environ["SKD_GEMM_WS"] = old
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("dtype,tol", [(skd.FP32, FP32_TOL), (skd.BF16, BF16_TOL)])
 def test_warmup_layer(dtype, tol):
     # one warm-up layer at the bottom + top window (the setting of every Table 2 row)
@@ -203,6 +207,7 @@ def test_device_io_mode_matches_host_io():
         np.testing.assert_array_equal(toks.cpu().numpy(), host["logits"].argmax(-1))
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("dtype,tol", [(skd.FP32, FP32_TOL), (skd.BF16, BF16_TOL)])
 @pytest.mark.parametrize("warm", [0, 1])
 def test_custom_monotone_schedule_table(dtype, tol, warm):
@@ -371,6 +376,7 @@ def test_sampling_head_full_vocab_both_paths():
                     assert pz[tok[b]] >= srt[min(k, srt.size - 1)] * (1 - 1e-4), (temperature, top_p, b)
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("dtype,tol", [(skd.FP32, FP32_TOL), (skd.BF16, BF16_TOL)])
 def test_minimal_sizes(dtype, tol):
     # one row, one prompt token, two decode steps; and a prompt that ends exactly on a page boundary
@@ -404,6 +410,7 @@ def test_rewind_regenerates_identically():
         assert [dec.kv_len(l) for l in range(4)] == lens
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("shape,batched", [(MID, "1"), (MID, "0"), (MID64, "0")])
 def test_kv_page_contents_match_oracle(shape, batched):
     # every key and value the cache holds after prefill + decode against the oracle's cache, element by element:
@@ -669,6 +676,7 @@ def test_wide_model_bf16(d):
     compare(shape, w, pr, 3, 6, 1, 1, BF16_TOL, dtype=skd.BF16, min_decided=0.0)
 
 
+@pytest.mark.usefixtures("narrow_columns")
 @pytest.mark.parametrize("seed", range(8))
 def test_random_small_configurations(seed):
     # seeded draw over the knobs that change code paths: head size, batch tile count, prompt length against the
