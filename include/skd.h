@@ -193,8 +193,8 @@ int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logits_out);
  * logits_out [B][vocab] (either may be NULL) are device memory and the call
  * only enqueues work on the state's stream.  Limit:
  * ceil(vocab / (16 R)) * B_pad <= 262144 partials, R = LM-head tile rows per
- * workgroup (1 to 4; for large vocabularies 2 up to batch 16, else 4;
- * SKD_R_HEAD), B_pad = batch padded to 16/32/48/64/96/128, i.e. vocabularies
+ * workgroup (4 for vocabularies above 16320, 1 to 4 below; SKD_R_HEAD),
+ * B_pad = batch padded to 16/32/48/64/96/128, i.e. vocabularies
  * up to 131072 at batch 128 and larger ones at smaller batches; beyond the
  * limit SKD_ERR_RANGE and nothing is launched.  All calls on one GPU, from whatever
  * state, share that GPU's array: calls that may overlap there (different
@@ -276,7 +276,9 @@ int skd_debug_kv_read(skd_state *st, int32_t layer, int32_t b, float *k_out, flo
  * instead records one event before and one after the launches of each class
  * on the state's stream, which adds the cost of the two markers to every
  * measurement; 0 switches timing off.  Neither mode serialises anything, but
- * both cost host time per launch, so time whole runs with timing off.
+ * both cost host time per launch, so time whole runs with timing off.  A
+ * column that would otherwise run as one launch (narrow bf16 models) runs as
+ * separate kernels while timing is on: the same results, other times.
  * skd_profile_read waits for the stream and adds the elapsed milliseconds and
  * launch counts per kernel class into ms[SKD_PROF_CLASSES] and
  * launches[SKD_PROF_CLASSES] (either may be NULL), then clears the internal

@@ -68,6 +68,25 @@ def test_noalloc_argmax_matches_allocating_entry_point():
             dec.close()
 
 
+# the workgroups that the state's own head takes (some of fewer tiles) have more partials than the array holds, equal ones
+# fit: 2112 against 2000 at 128000; 2048 workgroups, as many as fit
+@pytest.mark.parametrize("V,B", [(128000, 97), (128000, 128), (131072, 128)])
+def test_noalloc_argmax_at_the_limit(V, B):
+    import torch
+    shape = S.ModelShape(L=1, d=64, H=1, f=64, V=V, max_pos=8)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        dec, pr, _ = _state(torch, shape, B, 2, 4, 60, stream)
+        out = [(torch.full((B,), -7, dtype=torch.int32, device="cuda"), torch.full((B, V), float("nan"), device="cuda")) for _ in range(2)]
+        dec.prefill(pr)
+        assert dec.logits_argmax_noalloc_rc(*out[0]) == skd.OK
+        dec.logits_argmax_device(*out[1])
+        dec.synchronize()
+        assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0], out[1][0])
+        assert torch.equal(out[0][0].long(), out[0][1].argmax(-1))
+        dec.close()
+
+
 def test_noalloc_argmax_refusals():
     import torch
     shape = S.ModelShape(L=1, d=128, H=2, f=64, V=140000, max_pos=8)      # 2188 workgroups x 128 rows > 262144 partials
