@@ -631,7 +631,7 @@ static bool head_shape(const GemmArgs &a, int R) {
 // The output projection of one or two rows with the merge of the attention's shares in its prologue (a.attn_*).
 template <int R, int U>
 static void launch_gemm_merge(hipStream_t s, const GemmArgs &a, dim3 grid) {
-  const size_t lds = (size_t)8 * R * 64 * sizeof(floatx4) + (size_t)a.B * ln_row_stride(a.K) * sizeof(bf16_t);  // 32 KiB at most
+  const size_t lds = (size_t)8 * R * 64 * sizeof(floatx4) + (size_t)a.B * ln_row_stride(a.K) * sizeof(bf16_t);  // 32896 bytes at most: two rows of 4096, two tiles
   if (a.B == 1) SKD_LAUNCH((k_gemm<1, R, EPI_PARTIAL, U, 8, 1>), grid, dim3(512), lds, s, a);
   else SKD_LAUNCH((k_gemm<1, R, EPI_PARTIAL, U, 8, 2>), grid, dim3(512), lds, s, a);
 }
