@@ -183,8 +183,34 @@ struct SampleExchange {  // LDS of the finishing waves
   int pick[4], tail[4];
   float mass[2][16];  // sample_search: one set per round in turn
   int count[2][16];
+  float at[64];       // sample_search_few
 };
-// The threshold among C <= 64 PER candidates, by all 16 waves: every wave holds all of them and sums the masses at or above
+// The searches below find the largest value of [lower, upper) whose upper set has the target mass (or `lower`).  All of them
+// add up the masses as sample_finish does, PER consecutive candidates to a lane, so that which one runs does not show where
+// rounding decides.
+
+// At most 64 candidates: the masses from every candidate on, four to a wave; one round.
+__device__ inline unsigned sample_search_few(const float *cand_p, int C, unsigned lower, unsigned upper, float target, SampleExchange &ex) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = 4 * lane + j < C ? cand_p[4 * lane + j] : 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // candidates 4 w + i
+    const float t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[i]), w));
+    float m = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m += __float_as_uint(v[j]) >= __float_as_uint(t) ? v[j] : 0.f;
+    m = wave_sum_f(m);
+    if (lane == 0) ex.at[4 * w + i] = m;
+  }
+  __syncthreads();
+  // (candidates at or above `upper`: what they have together counts from upper - 1 on)
+  unsigned T = lane < C && ex.at[lane] >= target ? min(__float_as_uint(cand_p[lane]), upper - 1u) : lower;
+  for (int o = 32; o > 0; o >>= 1) T = max(T, (unsigned)__shfl_xor((int)T, o));
+  return T;
+}
+// C <= 64 PER candidates, by all 16 waves: every wave holds all of them and sums the masses at or above
 // a trial value of its own, so a round divides the interval [lo, hi) by 17; it ends where one candidate is left in it
 // (ties: where its bits are known).  One wave alone, two bits a round, took 8.6 us for 260 to 820 candidates.
 template <int PER>
@@ -192,7 +218,7 @@ __device__ inline unsigned sample_search(const float *cand_p, int C, unsigned lo
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float v[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) v[j] = 64 * j + lane < C ? cand_p[64 * j + lane] : 0.f;
+  for (int j = 0; j < PER; ++j) v[j] = PER * lane + j < C ? cand_p[PER * lane + j] : 0.f;
   int c_lo = C, c_hi = -1;  // candidates at or above lo, hi (-1: not counted)
   for (int set = 0; hi - lo > 1 && (c_hi < 0 || c_lo - c_hi > 1); set ^= 1) {
     // ascending with the wave; the largest lies above lo and none reaches hi, so the interval shrinks
@@ -321,38 +347,12 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
   }
 }
 
-// The same for at most 64 candidates, one per lane: a candidate is in the nucleus if those more likely than it have less
-// than the target mass.
-__device__ inline void sample_finish_few(const float *cand_p, const int *cand_i, int C, float target, float u, int32_t *token, int32_t *token2) {
-  const int lane = threadIdx.x & 63;
-  float v = lane < C ? cand_p[lane] : 0.f;
-  const int tok = lane < C ? cand_i[lane] : 0;
-  float above = 0.f;
-  for (int k = 0; k < C; ++k) {
-    const float o = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
-    above += o > v ? o : 0.f;
-  }
-  if (!(above < target)) v = 0.f;
-  float run = v;  // inclusive prefix in index order
-  for (int off = 1; off < 64; off <<= 1) {
-    const float t = __shfl_up(run, off);
-    if (lane >= off) run += t;
-  }
-  const float goal = u * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, run), 63));
-  const unsigned long long in = __ballot(v > 0.f), over = __ballot(v > 0.f && run > goal);
-  // (rounding at the very end: the last member; no member where the masses are not numbers: token 0)
-  const int k = over ? (int)__builtin_ctzll(over) : in ? 63 - (int)__builtin_clzll(in) : -1;
-  if (lane == max(k, 0)) {
-    *token = k >= 0 ? tok : 0;
-    if (token2) *token2 = k >= 0 ? tok : 0;
-  }
-}
-
 __device__ __forceinline__ void sample_rest(const float *cand_p, const int *cand_i, int C, unsigned lower, unsigned upper, float target,
                                    const float *u, int b, int32_t *tokens, int32_t *tokens2, SampleExchange &ex) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (C <= 64) {
-    if (w == 0) sample_finish_few(cand_p, cand_i, C, target, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr);
+    const unsigned T = sample_search_few(cand_p, C, lower, upper, target, ex);
+    if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, T, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
   } else if (C <= 256) {
     const unsigned T = sample_search<4>(cand_p, C, lower, upper, target, ex);
     if (w == 0) sample_finish<4, 1>(cand_p, cand_i, C, lower, upper, target, T, u[b], &tokens[b], tokens2 ? &tokens2[b] : nullptr, ex);
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
   bool known = false;  // (uniform) mx, target and s from the first pass
   if constexpr (RC <= 52) if (sc.chunks) {  // the first pass's candidates, if they hold the target mass
     constexpr int NK = (SAMPLE_CHUNK_CAND + 1023) / 1024;
-    __shared__ int kw[16];
+    __shared__ int kw[NK][16];
     // lane 16 r + c of every wave holds chunk c: no barrier
     const int c16 = lane & 15;
     const bool have = c16 < sc.chunks;
@@ -514,12 +514,11 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
       // every token of the row at or above beta (and 1 % for rounding) is among the candidates
       beta = fmaxf(1.01f * beta, 0x1p-40f);
       const float bound[3] = {fmaxf(0x1p-5f, beta), fmaxf(0x1p-10f, beta), beta};
-      // four consecutive candidates per thread: index order is thread order
       float pc[NK], q[3] = {};
       int ic[NK];
 #pragma unroll
       for (int k = 0; k < NK; ++k) {
-        const int i = NK * tid + k;
+        const int i = tid + 1024 * k;
         pc[k] = 0;
         ic[k] = 0;
         if (i < N) {
@@ -541,13 +540,12 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
         q[j] = wave_sum_f(q[j]);
         if (lane == 0) mass_at[j][wave] = q[j];
       }
-      {  // how many candidates reach each bound, 10 bits each (a wave has 256)
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {  // how many candidates of each wave reach each bound, 10 bits each (64 at most)
         int c = 0;
 #pragma unroll
-        for (int k = 0; k < NK; ++k)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) c += __popcll(__ballot(pc[k] >= bound[j])) << (10 * j);
-        if (lane == 0) kw[wave] = c;
+        for (int j = 0; j < 3; ++j) c += __popcll(__ballot(pc[k] >= bound[j])) << (10 * j);
+        if (lane == 0) kw[k][wave] = c;
       }
       __syncthreads();
       // the highest bound whose upper set has the target mass, and the next one above it, which has not
@@ -567,18 +565,20 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
       }
       at_bound = __builtin_amdgcn_readfirstlane(at_bound);  // uniform: every thread has the same sums
       if (at_bound >= 0) {
-        const int c = (kw[lane & 15] >> (10 * at_bound)) & 1023;
-        const int C = __builtin_amdgcn_readfirstlane(row_sum_i(c));
-        int at = row_sum_i((lane & 15) < wave ? c : 0);
+        int C = 0;
 #pragma unroll
-        for (int k = 0; k < NK; ++k) at += __popcll(__ballot(__float_as_uint(pc[k]) >= s.lower) & ((1ull << lane) - 1ull));
-#pragma unroll
-        for (int k = 0; k < NK; ++k)
-          if (__float_as_uint(pc[k]) >= s.lower) {
+        for (int k = 0; k < NK; ++k) {
+          const int c = (kw[k][lane & 15] >> (10 * at_bound)) & 1023;
+          int at = C + row_sum_i((lane & 15) < wave ? c : 0);
+          C += row_sum_i(c);
+          const bool in = __float_as_uint(pc[k]) >= s.lower;
+          at += __popcll(__ballot(in) & ((1ull << lane) - 1ull));
+          if (in) {
             cand_p[at] = pc[k];
             cand_i[at] = ic[k];
-            ++at;
           }
+        }
+        C = __builtin_amdgcn_readfirstlane(C);
         __syncthreads();
         sample_rest(cand_p, cand_i, C, __builtin_amdgcn_readfirstlane(s.lower), __builtin_amdgcn_readfirstlane(s.upper), target, u, b, tokens, tokens2, ex);
         return;

@@ -1,4 +1,4 @@
-"""The threshold search of the sampling head on few candidates (one per lane: up to 64) and on up to 1024 (interval divided
+"""The threshold search of the sampling head on few candidates (up to 64: all their masses in one round) and on up to 1024 (interval divided
 by 17), with many equal logits: identical vocabulary rows give identical logits, and a nucleus takes all tokens tied with
 its last one.  Tokens equal the oracle's wherever its decision margins exceed fp32 rounding (1e-5 of the mass, the bar of
 the other sampling tests)."""
