@@ -168,6 +168,16 @@ __device__ inline int wave_sum_i(int v) {  // the same value in every lane, as w
   v = row_sum_i(v);
   return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) + (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
 }
+__device__ inline unsigned wave_max_u(unsigned v) {
+#define SKD_ROR(n) v = max(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x120 + n, 0xF, 0xF, true))
+  SKD_ROR(8);
+  SKD_ROR(4);
+  SKD_ROR(2);
+  SKD_ROR(1);
+#undef SKD_ROR
+  auto row = [&](int l) { return (unsigned)__builtin_amdgcn_readlane((int)v, l); };
+  return max(max(row(0), row(16)), max(row(32), row(48)));
+}
 __device__ inline float row_sum_f(float v) {
 #define SKD_ROR(n) v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + n, 0xF, 0xF, true))
   SKD_ROR(8);
@@ -177,6 +187,10 @@ __device__ inline float row_sum_f(float v) {
 #undef SKD_ROR
   return v;
 }
+
+// Place of candidate k in LDS: a lane reads 16 (or 4) in a row, and without the gap 16 waves that do so have 16 lanes on a
+// bank at a time (2 us of the sampling kernel).
+__device__ inline int cand_at(int k) { return k + (k >> 4); }
 
 struct SampleExchange {  // LDS of the finishing waves
   float sums[2][4];
@@ -194,7 +208,7 @@ __device__ inline unsigned sample_search_few(const float *cand_p, int C, unsigne
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float v[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] = 4 * lane + j < C ? cand_p[4 * lane + j] : 0.f;
+  for (int j = 0; j < 4; ++j) v[j] = 4 * lane + j < C ? cand_p[cand_at(4 * lane + j)] : 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {  // candidates 4 w + i
     const float t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[i]), w));
@@ -206,9 +220,8 @@ __device__ inline unsigned sample_search_few(const float *cand_p, int C, unsigne
   }
   __syncthreads();
   // (candidates at or above `upper`: what they have together counts from upper - 1 on)
-  unsigned T = lane < C && ex.at[lane] >= target ? min(__float_as_uint(cand_p[lane]), upper - 1u) : lower;
-  for (int o = 32; o > 0; o >>= 1) T = max(T, (unsigned)__shfl_xor((int)T, o));
-  return T;
+  unsigned T = lane < C && ex.at[lane] >= target ? min(__float_as_uint(cand_p[cand_at(lane)]), upper - 1u) : lower;
+  return wave_max_u(T);
 }
 // C <= 64 PER candidates, by all 16 waves: every wave holds all of them and sums the masses at or above
 // a trial value of its own, so a round divides the interval [lo, hi) by 17; it ends where one candidate is left in it
@@ -218,7 +231,7 @@ __device__ inline unsigned sample_search(const float *cand_p, int C, unsigned lo
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float v[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) v[j] = PER * lane + j < C ? cand_p[PER * lane + j] : 0.f;
+  for (int j = 0; j < PER; ++j) v[j] = PER * lane + j < C ? cand_p[cand_at(PER * lane + j)] : 0.f;
   int c_lo = C, c_hi = -1;  // candidates at or above lo, hi (-1: not counted)
   for (int set = 0; hi - lo > 1 && (c_hi < 0 || c_lo - c_hi > 1); set ^= 1) {
     // ascending with the wave; the largest lies above lo and none reaches hi, so the interval shrinks
@@ -266,7 +279,7 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
   const int c0 = (w * 64 + lane) * PER;  // this lane's candidates c0 .. c0 + PER - 1 (index order)
   float v[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) v[j] = c0 + j < C ? cand_p[c0 + j] : 0.f;
+  for (int j = 0; j < PER; ++j) v[j] = c0 + j < C ? cand_p[cand_at(c0 + j)] : 0.f;
   int set = 0;
   if constexpr (NW > 1) {
     T = 0;
@@ -298,7 +311,7 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
     const float t = __shfl_up(inc, off);
     if (lane >= off) inc += t;
   }
-  float before = 0, mass = __shfl(inc, 63);
+  float before = 0, mass = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, inc), 63));
   if constexpr (NW > 1) {
     if (lane == 0) ex.sums[set ^ 1][w] = mass;  // last read before the barrier of the last round
     __syncthreads();
@@ -324,9 +337,10 @@ __device__ inline void sample_finish(const float *cand_p, const int *cand_i, int
       }
       if (k < 0) k = last;  // rounding between the lane's two summation orders: its last member
     }
-    k = __shfl(k, L);
+    k = __builtin_amdgcn_readlane(k, L);
   }
-  for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o));
+  const unsigned long long members = __ballot(last >= 0);  // ascending with the lane
+  last = members ? __builtin_amdgcn_readlane(last, 63 - (int)__builtin_clzll(members)) : -1;
   if constexpr (NW > 1) {  // the first wave that found it
     if (lane == 0) {
       ex.pick[w] = k;
@@ -474,7 +488,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
                                                        const float *u, int32_t *tokens, int32_t *tokens2, SampleScratch sc) {
   __shared__ float sh[16], wmass[16], mass_at[3][16], sums[2][16];
   __shared__ int wcount[2][16];
-  __shared__ float cand_p[SAMPLE_CAND];  // candidates of the short cut, ascending token index
+  __shared__ float cand_p[SAMPLE_CAND + SAMPLE_CAND / 16];  // candidates of the short cut, ascending token index (cand_at)
   __shared__ int cand_i[SAMPLE_CAND];
   __shared__ SampleExchange ex;
   __shared__ float rows[RC * 64];  // the rows of the one wave that walks its range
@@ -574,7 +588,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
           const bool in = __float_as_uint(pc[k]) >= s.lower;
           at += __popcll(__ballot(in) & ((1ull << lane) - 1ull));
           if (in) {
-            cand_p[at] = pc[k];
+            cand_p[cand_at(at)] = pc[k];
             cand_i[at] = ic[k];
           }
         }
@@ -688,7 +702,7 @@ __global__ __launch_bounds__(1024) void k_sample_top_p(const float *logits, int 
         if (m) {  // most rows have none
           if (c) {
             const int k = pos + __popcll(m & ((1ull << lane) - 1ull));
-            cand_p[k] = p[i];
+            cand_p[cand_at(k)] = p[i];
             cand_i[k] = first + 64 * i;
           }
           pos += __popcll(m);
