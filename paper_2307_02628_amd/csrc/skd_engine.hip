@@ -282,7 +282,9 @@ GemmPlan plan_direct(int N, int B_pad) {  // whole K inside the workgroup
   return p;
 }
 // The LM head of a large vocabulary: whole rounds of 256 workgroups of 4 tiles, smaller ones for what is left (head_dispatch
-// in kernels_bf16.hip).  Four tiles at 16 rows too: 50272 x 4096, us with the argmax, 2 tiles 75, 4 tiles 71.
+// in kernels_bf16.hip; 256: the CUs of the part that this is written for).  Four tiles at 16 rows too, us with the argmax, 2
+// tiles -> 4: 16 rows, 20000 x 4096 33.2 -> 32.2, 32000 x 4096 48.0 -> 44.5, 50272 x 4096 72.8 -> 70.9, 65000 x 4096 95.8 ->
+// 88.7; one row 32.5 -> 31.5, 47.3 -> 44.3, 71.1 -> 69.5, 88.4 -> 85.3; 32000 x 2048 28.1 -> 25.2, 20000 x 256 8.9 -> 8.3.
 GemmPlan plan_head(int V, int B_pad) {
   GemmPlan p = plan_direct(V, B_pad);
   if (bf16_gemm_groups(V, 4) >= 256) {
@@ -1253,7 +1255,9 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
 
 // Whether logits go through the pinned buffer.  The argmax head's kernels write them there themselves (nothing on the device
 // reads them again): the copy behind them took 2 us of a step of 61 with 1 or 2 rows of 1000, 7 to 10 of 70 to 100 with 8
-// to 128.  Larger ones, and those that the sampler reads, are written to device memory and copied.
+// to 128.  us a call of the head, copied -> written there: one row of 50272 x 4096 100 -> 86, five (981 KiB) 133 -> 119, 128
+// rows of 2000 x 256 (1000 KiB) 70 -> 65.  Larger ones, and those that the sampler reads, are written to device memory and
+// copied.
 static bool pin_logits(const skd_state *st) {
   return st->pin && (size_t)st->cfg.batch * st->cfg.vocab * sizeof(float) <= kPinnedLogits;
 }
