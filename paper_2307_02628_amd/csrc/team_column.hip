@@ -39,7 +39,9 @@ constexpr int TEAM_MAX_D = 512;  // 16 k-steps: the weight tile of a wave, and t
 constexpr int TEAM_MAX_F = 2048; // 8 waves x 8 k-steps
 constexpr int TEAM_SPLITS = 8, TEAM_PARTS = 128;  // shares of one pair's keys, of all pairs of a group
 constexpr int TEAM_SUMS = 32;    // partial sums of a tile along K, and softmax states of the pairs that a workgroup has at a time
-constexpr int TEAM_OUT_STEPS = 2, TEAM_OUT_STEPS_WIDE = 4, TEAM_FFN2_STEPS = 8;  // k-steps of a wave
+// k-steps of a wave; with more than 64 rows, an odd number of k-steps above 32 (FFN2 without a split, by four waves) takes more
+// and keeps the separate kernels
+constexpr int TEAM_OUT_STEPS = 2, TEAM_OUT_STEPS_WIDE = 4, TEAM_FFN2_STEPS = 8;
 // an entry of TeamStep: k-step in bits 0 .. 5, whether there is one, whether the sum ends here, which sum (and not zero)
 constexpr uint32_t TEAM_STEP_K = 1 << 6, TEAM_STEP_LAST = 1 << 7, TEAM_STEP_USED = 1 << 8;
 constexpr int TEAM_STEP_SUM = 9;
@@ -825,7 +827,7 @@ bool bf16_team_ok(int d, int f, int B) {
 bool bf16_team_keys(int d, int B, long longest, long total) {
   return total <= (d >= 384 ? 256000 : 320L * (d + 176)) && (B >= 8 || longest <= (d > 384 && B <= 2 ? 4096 : 8192));
 }
-// As many as the output projection and FFN2 have tiles (at most TEAM_PARTS): a larger team only makes the barriers longer
+// As many as the output projection and FFN2 have tiles: a larger team only makes the barriers longer
 // (256 wide, 16 rows at 16 keys: 53, 59, 65 us per step of 4 layers with 16, 24, 32), a smaller one has two rounds.
 int bf16_team_members(int cus, int d) { return cus < d / 16 ? (cus > 1 ? cus : 1) : d / 16; }
 int bf16_team_groups(int B) { return B < 8 ? B : 8; }
