@@ -966,15 +966,18 @@ constexpr long kRowsPartialMax = 32L << 20;  // fp32 partial sums of one project
 // the decode kernel: QKV 80 / 23, output 87 / 9.9, FFN1 80 / 26, FFN2 292 / 27.
 // Beyond, the tile and the K split with the least estimated time.  The estimate is (k-steps of a workgroup) x (time of
 // a k-step with the number of workgroups a CU then holds), summed over the rounds of workgroups, plus the traffic of
-// the partial sums.  Step times measured at the 6.7B and 1.3B shapes, 64 to 4096 rows (us): 256 x 256 0.47 (few
-// workgroups) to 0.72 (all CUs: the clock drops); 256 x 128 and 128 x 256 0.45 to 0.51; 128 x 128 0.32 alone on a CU,
+// the partial sums.  Step times measured at the 6.7B and 1.3B shapes, 64 to 4096 rows (us): 256 x 256 0.57 (few
+// workgroups) to 0.75 (all CUs: the clock drops); 256 x 128 and 128 x 256 0.45 to 0.51; 128 x 128 0.32 alone on a CU,
 // 0.52 for two; 64 x 128 0.255 / 0.44; 64 x 64 0.19 / 0.33 / 0.44 / 0.55 for one to four.  So the small tiles win only while the chip is not full:
 // at 1024 rows of the 6.7B shape FFN1 takes 100 us on 256 x 256 and 138 on 128 x 128, at 256 rows 80 and 44.
 // The epilogue is not in the estimate, and the traffic of the partial sums counts the reducer's reads: at 912 rows of the
 // 1.3B shape estimate and launch are 34 / 39 us (QKV), 23.5 / 30 (k | v alone), 35 / 36 (FFN1) and 45 / 37 (FFN2, split 4).
-// For that reason 256 x 128 and 128 x 256 keep the step times above although a step alone now takes 0.325 (64 workgroups)
-// to 0.44 (256): with those, prompts of 1200 to 2000 rows of the 6.7B shape were 1 to 3 % faster, but 360 and from 800
-// rows on of the 1.3B shape 2 to 5 % slower.
+// For that reason the 8-wave tiles keep these step times although their two waves of a SIMD take turns now.  256 x 128 and
+// 128 x 256: a step takes 0.325 (64 workgroups) to 0.44 (256); with those times prompts of 1200 to 2000 rows of the 6.7B
+// shape were 1 to 3 % faster, but 360 and from 800 rows on of the 1.3B shape 2 to 5 % slower.  256 x 256: 0.47 to 0.72;
+// with those, us (these -> those): 1.3B, four layers, 672 rows 526 -> 531, 4320 rows (FFN2 without its split of 3) 1667 ->
+// 1702, 4800 and 5120 rows alike; (512, ffn 1536), 8640 rows 438 -> 460; 6.7B, two layers, 144 rows 377 -> 383, 672 rows 509
+// -> 507.  And another split is another order of the sums.
 RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   RowsGemm best;
   const int Kf = K / 32;
@@ -989,7 +992,7 @@ RowsGemm plan_rows(int N, int K, int rows, bool split_ok) {
   }
   // tile, workgroups a CU holds, step time by workgroups on the CU, what a full chip adds
   static const struct { int wr, ar, cap; double step[4], full; } cfg[] = {
-      {256, 256, 1, {0.47}, 0.25}, {256, 128, 1, {0.455}, 0.06}, {128, 256, 1, {0.45}, 0.05}, {128, 128, 2, {0.32, 0.52}, 0.0},
+      {256, 256, 1, {0.57}, 0.18}, {256, 128, 1, {0.455}, 0.06}, {128, 256, 1, {0.45}, 0.05}, {128, 128, 2, {0.32, 0.52}, 0.0},
       {64, 128, 2, {0.255, 0.44}, 0.0}, {128, 64, 2, {0.255, 0.44}, 0.0}, {64, 64, 4, {0.19, 0.33, 0.44, 0.55}, 0.0}};
   static const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16};
   double best_t = 1e30;
