@@ -2290,6 +2290,58 @@ void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, in
   SKD_LAUNCH(k_argmax_final, dim3(B), dim3(256), 0, s, pmax, pidx, groups, B_pad, tokens, tokens2);
 }
 
+// Logits from partial sums along K ([split][B_pad][N], N = whole 16-row tiles; added in order) and the greedy token, one
+// workgroup per row: the end of an LM head whose tiles would leave most CUs without a workgroup.  Logits and tokens are
+// optional, as in k_argmax_final; `whole`: rows of logits can be written 16 bytes at a time.
+__global__ __launch_bounds__(256) void k_logits_sum(const float *partial, int split, int B_pad, int N, int V, float *logits,
+                                                    bool whole, int32_t *tokens, int32_t *tokens2) {
+  __shared__ float sv[4];
+  __shared__ int si[4];
+  const int b = blockIdx.x, n4 = N >> 2;
+  const long part = (long)B_pad * n4;
+  const floatx4 *p4 = (const floatx4 *)partial + (long)b * n4;
+  float best = -3.0e38f;
+  int bi = 0x7fffffff;
+  auto take = [&](float v, int i) {  // larger value, lower index on ties
+    if (v > best || (v == best && i < bi)) { best = v; bi = i; }
+  };
+  for (int c = threadIdx.x; c < n4; c += 256) {
+    floatx4 p[LOGITS_SPLIT];
+#pragma unroll
+    for (int k = 0; k < LOGITS_SPLIT; ++k)
+      if (k < split) p[k] = p4[k * part + c];
+    floatx4 v = p[0];
+#pragma unroll
+    for (int k = 1; k < LOGITS_SPLIT; ++k)
+      if (k < split) v += p[k];
+    float *to = logits ? logits + (long)b * V + 4 * c : nullptr;
+    if (to && whole && 4 * c < V) *(floatx4 *)to = v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (4 * c + k < V) {
+        if (to && !whole) to[k] = v[k];
+        take(v[k], 4 * c + k);
+      }
+  }
+  if (!tokens) return;
+  for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(best, o), __shfl_xor(bi, o));
+  if ((threadIdx.x & 63) == 0) {
+    sv[threadIdx.x >> 6] = best;
+    si[threadIdx.x >> 6] = bi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) take(sv[w], si[w]);
+    tokens[b] = bi;
+    if (tokens2) tokens2[b] = bi;
+  }
+}
+void bf16_logits_sum(hipStream_t s, const float *partial, int split, int B_pad, int N, int V, float *logits, int32_t *tokens,
+                     int32_t *tokens2, int B) {
+  const bool whole = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+  SKD_LAUNCH(k_logits_sum, dim3(B), dim3(256), 0, s, partial, split, B_pad, N, V, logits, whole, tokens, tokens2);
+}
+
 // ------------------------------------------------------------------ weight preparation
 template <typename T>
 __device__ inline float src_to_f(const T *p, long i);

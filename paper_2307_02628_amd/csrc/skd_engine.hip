@@ -138,6 +138,7 @@ struct skd_state {
   int32_t *pidx = nullptr;
   // plans (bf16)
   GemmPlan p_qkv, p_out, p_ffn1, p_ffn2, p_head;
+  bool head_parts = false;         // the LM head's K range is split (p_head.split parts): partial sums, bf16_logits_sum
   int max_split = 1, attn_splits = 1, attn_waves = 4;
   bool attn_fixed = false;         // by override: the same shape at every position
   int start_min = 0;               // first real column of the longest row
@@ -292,6 +293,19 @@ GemmPlan plan_head(int V, int B_pad) {
     p.slots = 256;
   }
   return p;
+}
+// An LM head of few tiles leaves most CUs idle and is a chain of k-steps for the others: its K range in as many parts as
+// fill 256 CUs, of 16 k-steps at least; the kernel that finds the token adds the sums.  0: whole K in the workgroup.  us a call
+// with the argmax, whole -> parts: 1000 x 4096, 4 parts: 1 row 11.1 -> 7.8, 16 9.1 -> 7.8, 47 14.0 -> 9.0, 128 23.2 -> 11.5; 500 x
+// 4096, 8 parts: 10.9 -> 7.4, 8.8 -> 7.6, 13.3 -> 8.0, 22.8 -> 10.4; 2000 x 4096, 2 parts: 11.4 -> 9.6, 11.0 -> 9.6, 14.3 -> 11.7,
+// 24.0 -> 16.5; 1000 x 2048, 4 parts: 8.6 -> 7.4, 7.5 -> 7.3, 10.0 -> 8.3, 15.0 -> 10.0.  Two rounds of workgroups lose (3000 x
+// 4096, 2 parts: 12.0 -> 12.4, 11.8 -> 11.9, 14.4 -> 16.9, 24.6 -> 28.0), and so do parts of 8 k-steps (1000 x 512, 2 parts: 7.3 -> 7.4,
+// 7.2 -> 7.6, 7.3 -> 7.6, 8.6 -> 8.8).
+int plan_head_split(int V, int K) {
+  const int tiles = (V + 15) / 16, Kf = K / 32;
+  int S = 1;
+  while (2 * S <= LOGITS_SPLIT && tiles * 2 * S <= 256 && Kf % (2 * S) == 0 && Kf / (2 * S) >= 16) S *= 2;
+  return S > 1 ? S : 0;
 }
 GemmPlan plan_split(int N, int K, int B_pad) {  // partial sums, reduced by the LayerNorm kernel
   GemmPlan p;
@@ -464,12 +478,13 @@ bool decode_shapes_ok(const skd_state *st) {
     if (epi == EPI_LOGITS) bf16_head_tiles(ga, p.R, p.slots);
     return check_gemm(ga, epi, p) > 0;
   };
+  const int head_n = st->head_parts ? (c.vocab + 15) / 16 * 16 : c.vocab;
   auto ok_ln = [&](int N, const GemmPlan &p, const GemmPlan &before, int epi) {  // behind the partial sums of `before`
     ga.N = N; ga.K = d; ga.G = p.R; ga.split = p.split; ga.ln_split = before.split;
     return bf16_gemm_ln_check(ga, epi, p.R) > 0;
   };
   return ok(3 * d, d, st->p_qkv, EPI_QKV) && ok(d, d, st->p_out, EPI_PARTIAL) && ok(f, d, st->p_ffn1, EPI_RELU) &&
-         ok(d, f, st->p_ffn2, EPI_PARTIAL) && ok(c.vocab, d, st->p_head, EPI_LOGITS) &&
+         ok(d, f, st->p_ffn2, EPI_PARTIAL) && ok(head_n, d, st->p_head, st->head_parts ? EPI_PARTIAL : EPI_LOGITS) &&
          (!st->fuse_ln || (ok_ln(3 * d, st->p_qkv, st->p_ffn2, EPI_QKV) && ok_ln(f, st->p_ffn1, st->p_out, EPI_RELU)));
 }
 
@@ -742,6 +757,16 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     ov("SKD_U_OUT", st->p_out.U, 1, 4); ov("SKD_U_FFN2", st->p_ffn2.U, 1, 4);
     ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8); ov("SKD_W_HEAD", st->p_head.waves, 4, 8);
     ov("SKD_W_OUT", st->p_out.waves, 4, 8); ov("SKD_W_FFN2", st->p_ffn2.waves, 4, 8);
+    int parts = plan_head_split(V, d);
+    for (const char *name : {"SKD_R_HEAD", "SKD_U_HEAD", "SKD_W_HEAD"})
+      if (getenv(name)) parts = 0;
+    ov("SKD_S_HEAD", parts, 1, LOGITS_SPLIT);
+    if (parts > 1) {
+      st->head_parts = true;
+      st->p_head.R = 1;
+      st->p_head.split = parts;
+      st->p_head.U = Bp <= 16 ? 2 : 1;
+    }
   }
 
   if (st->bf16) {
@@ -774,12 +799,13 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
       // (measured at 128 x 4096: FFN1 35.5 -> 33.7 us; at 128 x 16384, 4 MiB, FFN2 36.3 -> 38.8 us)
       // Not for the LM head: there every vocabulary row keeps the same summation order, so that identical rows give
       // identical logits at every batch size (ties are then broken by index, as documented), and it gains nothing.
-      p.ws_rot = epi != EPI_LOGITS && (long)st->B_pad * K * 2 <= (2L << 20);
+      const bool head = &p == &st->p_head;
+      p.ws_rot = !head && (long)st->B_pad * K * 2 <= (2L << 20);
       const int e = env_int("SKD_WS_ROT", -1);
-      if (e == 0 || (e == 1 && epi != EPI_LOGITS)) p.ws_rot = e;
+      if (e == 0 || (e == 1 && !head)) p.ws_rot = e;
     };
     pick(3 * d, d, st->p_qkv, EPI_QKV); pick(d, d, st->p_out, EPI_PARTIAL); pick(f, d, st->p_ffn1, EPI_RELU);
-    pick(d, f, st->p_ffn2, EPI_PARTIAL); pick(V, d, st->p_head, EPI_LOGITS);
+    pick(d, f, st->p_ffn2, EPI_PARTIAL); pick(st->head_parts ? (V + 15) / 16 * 16 : V, d, st->p_head, st->head_parts ? EPI_PARTIAL : EPI_LOGITS);
   }
   if (st->bf16 && !decode_shapes_ok(st)) return fail(SKD_ERR_SHAPE);  // an override the kernels cannot launch
   {  // the device this state lives on, and that device's copy of the static scratch array
@@ -865,7 +891,7 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     A(&t16, (size_t)Bp * d); st->o = t16; if (rc == SKD_OK) rc = hipMemsetAsync(st->o, 0, (size_t)Bp * d * 2, st->stream) == hipSuccess ? SKD_OK : SKD_ERR_HIP;
     A(&t16, (size_t)Bp * f); st->u = t16;
     A(&st->kv_new, (size_t)B * 2 * d);
-    A(&st->partial, (size_t)st->max_split * Bp * d);
+    A(&st->partial, std::max((size_t)st->max_split * Bp * d, st->head_parts ? (size_t)st->p_head.split * Bp * ((V + 15) / 16 * 16) : 0));
     A(&st->attn_part, (size_t)st->attn_splits * B * c.n_heads * (st->dh + 4));
     GemmArgs ga{};
     ga.N = V;
@@ -1247,6 +1273,13 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
     GemmArgs ga{};
     ga.B = B; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;  // a = final LayerNorm output
     ga.N = V; ga.K = d; ga.split = 1; ga.logits = logits_target; ga.pmax = st->pmax; ga.pidx = st->pidx;
+    if (st->head_parts) {
+      ga.N = (V + 15) / 16 * 16; ga.split = st->p_head.split; ga.partial = st->partial;
+      { ProfScope ps_(st, SKD_PROF_LM_HEAD); if (launch_gemm(s, ga, EPI_PARTIAL, st->p_head) < 0) return SKD_ERR_SHAPE; }
+      { ProfScope ps_(st, SKD_PROF_ARGMAX); bf16_logits_sum(s, st->partial, ga.split, st->B_pad, ga.N, V, logits_target, want_argmax ? st->argmax_dev : nullptr, want_argmax ? tokens_target : nullptr, B); }
+      HIPCHECK(hipGetLastError());
+      return SKD_OK;
+    }
     int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);
     { ProfScope ps_(st, SKD_PROF_LM_HEAD); groups = launch_gemm(s, ga, EPI_LOGITS, st->p_head); }
     if (groups < 0) return SKD_ERR_SHAPE;
@@ -1310,6 +1343,11 @@ extern "C" int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, flo
   const skd_config &c = st->cfg;
   if (!st->bf16 || !c.io_on_device) return SKD_ERR_SHAPE;
   SKDCHECK(intact(st));
+  if (st->head_parts) {  // partial sums go to the state's own buffer
+    SKDCHECK(head_logits(st, logits_out, true, tokens_out));
+    st->have_argmax = true;
+    return SKD_OK;
+  }
   GemmArgs ga{};
   ga.N = c.vocab;
   int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);

@@ -239,6 +239,12 @@ void bf16_last_rows_ln(hipStream_t s, const float *x_rows, RowMap rm, const floa
 void bf16_argmax_final(hipStream_t s, const float *pmax, const int32_t *pidx, int groups, int B_pad, int32_t *tokens,
                        int32_t *tokens2, int B);
 
+// logits [B][V] (optional) = partial sums [split][B_pad][N] of an LM head (N = V in whole tiles; EPI_PARTIAL) added up, and the
+// greedy tokens (optional; tokens2: second destination, or null)
+constexpr int LOGITS_SPLIT = 8;       // K parts at most
+void bf16_logits_sum(hipStream_t s, const float *partial, int split, int B_pad, int N, int V, float *logits, int32_t *tokens,
+                     int32_t *tokens2, int B);
+
 // A whole decode column of a narrow model in one launch (team_column.hip).
 struct TeamLayer {
   const bf16_t *wqkv, *wo, *w1, *w2;  // fragment-major
