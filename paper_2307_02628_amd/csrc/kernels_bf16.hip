@@ -986,11 +986,57 @@ __device__ inline void wait_vmcnt_le(int n) {
   }
 }
 
+// EPI_QKV_ROWS: where the keys and values of a wave's MT activation-row tiles go.  The output rows of a wave lie inside one
+// of q | k | v (d is a multiple of 64, a head), and the 16 rows of a tile belong to one sequence, one page and one half of
+// a 32-key block of it, so all this is wave-uniform.  Looked up (three dependent scalar loads) under the first stages of the
+// main loop, which waits 0.5 us longer for it (2 us with vector loads, which return behind the stages).
+template <int MT>
+struct CacheTiles {
+  int which;               // 0 = q, 1 = k, 2 = v
+  int page[MT], slot[MT];  // page (-1: nothing to store), place of the first row in it
+  int valid[MT];           // real positions of the tile; the rest of a sequence's last tile is padding
+};
+template <int MT>
+__device__ inline CacheTiles<MT> row_tiles(const GemmArgs &a, int nt0, int mt0) {
+  CacheTiles<MT> t;
+  t.which = nt0 * 16 / a.d;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) t.page[m] = -1, t.slot[m] = t.valid[m] = 0;
+  if (t.which == 0) return t;
+  // no branches: the loads of all tiles are in flight together (rows past the last sequence are in `seq` too); scalar ones,
+  // which the compiler does not make by itself behind loads to LDS
+  typedef const int32_t __attribute__((address_space(4))) *Words;
+  const Words seq = (Words)a.rm.seq, first_row = (Words)a.rm.first_row, start = (Words)a.rm.start, pages = (Words)a.bt_layer;
+  int b[MT], at[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) b[m] = seq[(mt0 + m) << 4];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int bb = max(b[m], 0), pos = ((mt0 + m) << 4) - first_row[bb];  // = real position of the tile's first row
+    t.valid[m] = b[m] >= 0 ? a.rm.P - start[bb] - pos : 0;
+    const int page = t.valid[m] > 0 ? pos / a.kv.page_tokens : 0;
+    t.slot[m] = pos - page * a.kv.page_tokens;
+    at[m] = bb * a.kv.max_pages + page;
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) t.page[m] = pages[at[m]];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+    if (t.valid[m] <= 0) t.page[m] = -1;
+  return t;
+}
+struct NoCacheTiles {};
+template <int EPI, int MT>
+__device__ inline auto row_tiles_for(const GemmArgs &a, int nt0, int mt0) {
+  if constexpr (EPI == EPI_QKV_ROWS) return row_tiles<MT>(a, nt0, mt0);
+  else return NoCacheTiles{};
+}
+
 // Epilogue of the tiled prompt GEMMs: a wave's RT x MT output tiles, weight tiles nt0 .. nt0 + RT - 1 and activation-row
 // tiles mt0 .. mt0 + MT - 1.  acc[r][m]: lane l holds output rows (weight rows) n0 .. n0 + 3 of activation row
 // row0(m) + (l & 15), n0 = 16 * (weight tile) + 4 * (l >> 4).
-template <int EPI, int RT, int MT>
-__device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT][MT], int nt0, int mt0, int sp, int lane) {
+template <int EPI, int RT, int MT, typename T>
+__device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT][MT], const T &tiles, int nt0, int mt0, int sp, int lane) {
   const int grp = lane >> 4, j = lane & 15;
   auto n0_of = [&](int r) { return ((nt0 + r) << 4) + 4 * grp; };
   auto row0_of = [&](int m) { return (mt0 + m) << 4; };
@@ -1030,52 +1076,42 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
       if (r + 2 < RT) fetch(r + 2, xv[r & 1]);
     }
   } else {  // EPI_QKV_ROWS
-    // The output rows of a wave lie inside one of q | k | v (d is a multiple of 64, a head), and the
-    // 16 activation rows of a tile belong to one sequence and one page: what the stores need to know about a tile
-    // is wave-uniform and is looked up once, with scalar loads, not once per weight tile and lane.
-    const int which = nt0 * 16 / a.d;
-    int t_page[MT], t_slot0[MT], t_len[MT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      t_page[m] = -1;
-      t_slot0[m] = 0;
-      t_len[m] = 0;
-      const int row0 = row0_of(m);
-      if (which != 0 && row0 < a.rows) {
-        const int b = a.rm.seq[row0];
-        if (b >= 0) {
-          t_slot0[m] = row0 - a.rm.first_row[b];  // = real position of the tile's first row
-          t_len[m] = a.rm.P - a.rm.start[b];      // positions of the sequence; the rest of its last tile is padding
-          if (t_slot0[m] < t_len[m]) t_page[m] = a.bt_layer[(long)b * a.kv.max_pages + t_slot0[m] / a.kv.page_tokens];
-        }
-      }
-    }
+    // The offset of a value in a page is a sum of one term for its position (kv_k_off, kv_v_off: uniform per activation
+    // tile, plus a term for the lane) and one for its element, so per store only a base and an offset are added.  With the
+    // lookups, and the divisions of every store, in here an epilogue took 5.8 us of a launch (128 x 256 tiles, 912 rows of
+    // the 1.3B shape) and 7.4 (128 x 128), now 3.5 and 3.3; those that store partial sums or activations take 2 to 2.6.
+    const int dh = a.kv.dh, hs = dh == 64 ? 6 : 7, page_head = a.kv.page_tokens * dh * 2;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-      const int n0 = n0_of(r), within = n0 - which * a.d;
+      const int n0 = n0_of(r), within = n0 - tiles.which * a.d;
       const floatx4 bias = *(const floatx4 *)&a.bias[n0];
-      const int h = within / a.kv.dh, e = within - h * a.kv.dh;
+      if (tiles.which == 0) {
 #pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        floatx4 v = acc[r][m] + bias;
-        if (which == 0) {
+        for (int m = 0; m < MT; ++m) {
+          const floatx4 v = acc[r][m] + bias;
           if (row0_of(m) < a.rows)
             *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, within, a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-          continue;
         }
-        if (t_page[m] < 0) continue;
-        bf16_t *pg = a.kv_pool + (long)t_page[m] * a.kv.page_elems;
-        const int tt = (t_slot0[m] + j) % a.kv.page_tokens;
-        if (which == 1) {
-          if (t_slot0[m] + j < t_len[m])
-            *(uint2 *)&pg[kv_k_off(h, tt, e, a.kv)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        continue;
+      }
+      const int h = within >> hs, e = within & (dh - 1), t = j & 3;
+      // of k: 16 bytes per position; of v: those of element e + t, 8 bytes per four positions
+      const int at_k = h * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + (e & 7) + 8 * j;
+      const int at_v = h * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (tiles.page[m] < 0) continue;
+        floatx4 v = acc[r][m] + bias;
+        bf16_t *pg = a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot[m] >> 5) * (64 * dh);
+        const int half = (tiles.slot[m] >> 4) & 1;
+        if (tiles.which == 1) {
+          if (j < tiles.valid[m]) *(uint2 *)&(pg + half * (dh >> 5) * 512)[at_k] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
           continue;
         }
         // v: a page holds, for one element e, four consecutive positions side by side.  The four lanes of a quad
         // hold positions 4q .. 4q + 3 for elements e .. e + 3 each: transposed inside the quad (two exchanges,
         // with the lane 1 and the lane 2 away), lane t ends up with element e + t of all four positions and
         // stores them as one 8-byte word.
-        const int t = j & 3;
         {
           const float s0 = (t & 1) ? v[0] : v[1], s1 = (t & 1) ? v[2] : v[3];
           const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0xB1, 0xF, 0xF, true));
@@ -1089,15 +1125,14 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
           if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
         }
         // now v[s] = element e + t of position 4 * (j / 4) + s
-        const int pos0 = t_slot0[m] + (j & ~3), nvalid = t_len[m] - pos0;
-        bf16_t *dst = &pg[kv_v_off(h, pos0 % a.kv.page_tokens, e + t, a.kv)];
+        const int nvalid = tiles.valid[m] - (j & ~3);
+        bf16_t *dst = &(pg + 32 * dh + half * 4)[at_v];
         if (nvalid >= 4) {
           *(uint2 *)dst = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
         } else {
           for (int s_ = 0; s_ < 4; ++s_)
             if (s_ < nvalid) dst[s_] = (bf16_t)f2bf(v[s_]);
         }
-        (void)tt;
       }
     }
   }
@@ -1215,6 +1250,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
 #pragma unroll
   for (int i = 0; i < TILE_NS - 1; ++i)
     if (i < Kf) issue(i);
+  const auto tiles = row_tiles_for<EPI, 8>(a, a.t0 + tn * 16 + wr * 4, tm * 16 + wc * 8);
   wait_vmcnt_le(4 * min(Kf - 1, TILE_NS - 2));
   bar();  // stage 0 is here
   if (wave >= 4) bar();
@@ -1223,7 +1259,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   for (; st < Kf; ++st) k_step(st, false, max(Kf - 2 - st, 0));
   if (wave < 4) bar();
 
-  tile_epilogue<EPI, 4, 8>(a, acc, a.t0 + tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
+  tile_epilogue<EPI, 4, 8>(a, acc, tiles, a.t0 + tn * 16 + wr * 4, tm * 16 + wc * 8, sp, lane);
 }
 
 // Batched-prompt projections on 256 x 256 tiles.  Returns 0, or -1 when the shape does not tile.
@@ -1256,8 +1292,7 @@ int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
 // one multiplies while the other waits at its barrier; with 8 waves the two of a SIMD take turns.  What bounds it is how
 // many bytes a CU takes in per MFMA: at 912 rows of the 1.3B shape FFN1's 128 x 256 tiles read 11.2 TB/s through L2
 // (44 GB/s to each CU) with the matrix cores 37 % busy, whatever the ring depth (64 x 128 tiles: 5 and 6 stages alike,
-// 64 x 64: 5 and 9), so the largest tile that still fills the chip wins.  The q | k | v launches take in less (7.9 TB/s):
-// their epilogue begins its page lookups behind the loop, and with one round of workgroups nothing runs under them.
+// 64 x 64: 5 and 9), so the largest tile that still fills the chip wins.
 // us per launch, 256 x 256 -> best tile and split: 256 rows of the 6.7B shape QKV 81 -> 43, output 87 -> 17 (split 4),
 // FFN1 80 -> 44, FFN2 296 -> 46 (split 4), all 128 x 128; 1024 rows of the 1.3B shape QKV 44 -> 32 and FFN1 45 -> 35
 // (128 x 256; 128 x 128: 37 and 41), output 51 -> 15 (128 x 128, split 2), FFN2 153 -> 37 (128 x 256, split 4).
@@ -1334,6 +1369,8 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
+  auto lookups = [&]() { return row_tiles_for<EPI, MT>(a, a.t0 + tn * FW + wr * RT, tm * FA + wc * MT); };
+  decltype(lookups()) tiles;
   if constexpr (WN * WM == 8) {
     // The two waves of a SIMD take turns at LDS and matrix cores as in k_gemm_tile, two k-steps (a pair of stages) to a
     // turn: waves 4 .. 7 run one barrier behind waves 0 .. 3.  Ring: pair p + 2 goes into the slots of pair p - 1, which
@@ -1374,6 +1411,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < NS - 2; ++i)
       if (i < n) issue(i);
+    tiles = lookups();
     if (n >= 4) wait_vmcnt<2 * LPW>();
     else if (n == 3) wait_vmcnt<LPW>();
     else wait_vmcnt<0>();
@@ -1398,6 +1436,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < NS - 1; ++i)
       if (i < n) issue(i);
+    tiles = lookups();
     bf16x8 wfA[RT], xfA[MT], wfB[RT], xfB[MT];
     open_stage(0);
     read(0, wfA, xfA);
@@ -1438,7 +1477,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
       }
     }
   }
-  tile_epilogue<EPI, RT, MT>(a, acc, a.t0 + tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);
+  tile_epilogue<EPI, RT, MT>(a, acc, tiles, a.t0 + tn * FW + wr * RT, tm * FA + wc * MT, sp, lane);
 }
 
 template <int RT, int MT, int WN, int WM, int NS>
