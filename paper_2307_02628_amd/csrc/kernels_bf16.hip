@@ -988,41 +988,33 @@ __device__ inline void wait_vmcnt_le(int n) {
 
 // EPI_QKV_ROWS: where the keys and values of a wave's MT activation-row tiles go.  The output rows of a wave lie inside one
 // of q | k | v (d is a multiple of 64, a head), and the 16 rows of a tile belong to one sequence, one page and one half of
-// a 32-key block of it, so all this is wave-uniform.  Looked up (three dependent scalar loads) under the first stages of the
-// main loop, which waits 0.5 us longer for it (2 us with vector loads, which return behind the stages).
+// a 32-key block of it, so all this is wave-uniform.  The place in the block table and in the page is the same in every
+// layer: k_prompt_map writes it once per prompt, so what is left per output tile are two dependent scalar loads, taken under
+// the main loop (as vector loads they return behind its stages, 2 us later).
 template <int MT>
 struct CacheTiles {
-  int which;               // 0 = q, 1 = k, 2 = v
-  int page[MT], slot[MT];  // page (-1: nothing to store), place of the first row in it
-  int valid[MT];           // real positions of the tile; the rest of a sequence's last tile is padding
+  int which;     // 0 = q, 1 = k, 2 = v
+  int page[MT];  // -1: nothing to store
+  int at[MT];    // CacheTile::at
+  __device__ int slot(int m) const { return at[m] & ((1 << CacheTile::kValidShift) - 1); }
+  __device__ int valid(int m) const { return at[m] >> CacheTile::kValidShift; }
 };
 template <int MT>
 __device__ inline CacheTiles<MT> row_tiles(const GemmArgs &a, int nt0, int mt0) {
   CacheTiles<MT> t;
   t.which = nt0 * 16 / a.d;
 #pragma unroll
-  for (int m = 0; m < MT; ++m) t.page[m] = -1, t.slot[m] = t.valid[m] = 0;
+  for (int m = 0; m < MT; ++m) t.page[m] = -1, t.at[m] = 0;
   if (t.which == 0) return t;
-  // no branches: the loads of all tiles are in flight together (rows past the last sequence are in `seq` too); scalar ones,
-  // which the compiler does not make by itself behind loads to LDS
-  typedef const int32_t __attribute__((address_space(4))) *Words;
-  const Words seq = (Words)a.rm.seq, first_row = (Words)a.rm.first_row, start = (Words)a.rm.start, pages = (Words)a.bt_layer;
-  int b[MT], at[MT];
+  // no branches: the loads of all tiles are in flight together; scalar ones, which the compiler does not make by itself
+  // behind loads to LDS
+  const auto tiles = (const CacheTile __attribute__((address_space(4))) *)a.rm.tiles + mt0;
+  const auto pages = (const int32_t __attribute__((address_space(4))) *)a.bt_layer;
 #pragma unroll
-  for (int m = 0; m < MT; ++m) b[m] = seq[(mt0 + m) << 4];
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const int bb = max(b[m], 0), pos = ((mt0 + m) << 4) - first_row[bb];  // = real position of the tile's first row
-    t.valid[m] = b[m] >= 0 ? a.rm.P - start[bb] - pos : 0;
-    const int page = t.valid[m] > 0 ? pos / a.kv.page_tokens : 0;
-    t.slot[m] = pos - page * a.kv.page_tokens;
-    at[m] = bb * a.kv.max_pages + page;
-  }
-#pragma unroll
-  for (int m = 0; m < MT; ++m) t.page[m] = pages[at[m]];
+  for (int m = 0; m < MT; ++m) t.page[m] = pages[tiles[m].page], t.at[m] = tiles[m].at;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
-    if (t.valid[m] <= 0) t.page[m] = -1;
+    if (t.at[m] == 0) t.page[m] = -1;
   return t;
 }
 struct NoCacheTiles {};
@@ -1079,33 +1071,45 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
     // The offset of a value in a page is a sum of one term for its position (kv_k_off, kv_v_off: uniform per activation
     // tile, plus a term for the lane) and one for its element, so per store only a base and an offset are added.  With the
     // lookups, and the divisions of every store, in here an epilogue took 5.8 us of a launch (128 x 256 tiles, 912 rows of
-    // the 1.3B shape) and 7.4 (128 x 128), now 3.5 and 3.3; those that store partial sums or activations take 2 to 2.6.
-    const int dh = a.kv.dh, hs = dh == 64 ? 6 : 7, page_head = a.kv.page_tokens * dh * 2;
+    // the 1.3B shape) and 7.4 (128 x 128), without them 3.5 and 3.3; those that store partial sums or activations take 2 to
+    // 2.6.  Activation tiles outermost: what is uniform per tile is in scalar registers for one of them at a time.  With the
+    // weight tiles outermost, and the place of every tile worked out in the kernel, a prompt pass took 573 us (912 rows of the
+    // 1.3B shape), 6346 (16384 of the 6.7B shape) and 14683 (128 ragged sequences), now 565, 6267 and 14418.
+    const int dh = a.kv.dh, hs = dh == 64 ? 6 : 7, page_head = a.kv.page_tokens * dh * 2, t = j & 3;
+    int at[RT];  // offset of this lane's first value of weight tile r: of q in its activation tile's row, of k and v in the page
+    floatx4 bias[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-      const int n0 = n0_of(r), within = n0 - tiles.which * a.d;
-      const floatx4 bias = *(const floatx4 *)&a.bias[n0];
-      if (tiles.which == 0) {
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          const floatx4 v = acc[r][m] + bias;
-          if (row0_of(m) < a.rows)
-            *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, within, a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-        }
-        continue;
-      }
-      const int h = within >> hs, e = within & (dh - 1), t = j & 3;
+      const int within = n0_of(r) - tiles.which * a.d, h = within >> hs, e = within & (dh - 1);
+      bias[r] = *(const floatx4 *)&a.bias[n0_of(r)];
       // of k: 16 bytes per position; of v: those of element e + t, 8 bytes per four positions
-      const int at_k = h * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + (e & 7) + 8 * j;
-      const int at_v = h * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
+      at[r] = tiles.which == 0 ? within
+              : tiles.which == 1 ? h * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + (e & 7) + 8 * j
+                                 : h * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
+    }
+    if (tiles.which == 0) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        if (tiles.page[m] < 0) continue;
-        floatx4 v = acc[r][m] + bias;
-        bf16_t *pg = a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot[m] >> 5) * (64 * dh);
-        const int half = (tiles.slot[m] >> 4) & 1;
+        if (row0_of(m) >= a.rows) continue;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          const floatx4 v = acc[r][m] + bias[r];
+          *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, at[r], a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      if (tiles.page[m] < 0) continue;
+      const int valid = tiles.valid(m), half = (tiles.slot(m) >> 4) & 1;
+      bf16_t *pg = a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot(m) >> 5) * (64 * dh);
+      pg += tiles.which == 1 ? half * (dh >> 5) * 512 : 32 * dh + half * 4;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        floatx4 v = acc[r][m] + bias[r];
         if (tiles.which == 1) {
-          if (j < tiles.valid[m]) *(uint2 *)&(pg + half * (dh >> 5) * 512)[at_k] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+          if (j < valid) *(uint2 *)&pg[at[r]] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
           continue;
         }
         // v: a page holds, for one element e, four consecutive positions side by side.  The four lanes of a quad
@@ -1125,8 +1129,8 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
           if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
         }
         // now v[s] = element e + t of position 4 * (j / 4) + s
-        const int nvalid = tiles.valid[m] - (j & ~3);
-        bf16_t *dst = &(pg + 32 * dh + half * 4)[at_v];
+        const int nvalid = valid - (j & ~3);
+        bf16_t *dst = &pg[at[r]];
         if (nvalid >= 4) {
           *(uint2 *)dst = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
         } else {
@@ -2096,8 +2100,9 @@ void bf16_attention_rows(hipStream_t s, const AttnRowsArgs &a) {
 // ------------------------------------------------------------------ row kernels of the batched prompt
 // The row map of a prompt from by-value kernel arguments (at most 128 sequences): workgroup b fills the rows of
 // sequence b, the last one the rows past the last sequence.  Replaces four pageable copies and two host waits.
-__global__ __launch_bounds__(256) void k_prompt_map(PromptMap pm, int B, int rows, int rows_pad, int P, int32_t *start,
-                                                    int32_t *order, int32_t *first, int32_t *seq) {
+__global__ __launch_bounds__(256) void k_prompt_map(PromptMap pm, int B, int rows, int rows_pad, int P, KvGeom kv,
+                                                    int32_t *start, int32_t *order, int32_t *first, int32_t *seq,
+                                                    CacheTile *tiles) {
   const int b = blockIdx.x;
   int lo = rows, n = rows_pad - rows, val = -1;
   if (b < B) {
@@ -2111,10 +2116,16 @@ __global__ __launch_bounds__(256) void k_prompt_map(PromptMap pm, int B, int row
     }
   }
   for (int i = threadIdx.x; i < n; i += 256) seq[lo + i] = val;
+  for (int i = threadIdx.x; i < n >> 4; i += 256) {
+    const int pos = i * 16, page = pos / kv.page_tokens;  // real position of the tile's first row
+    tiles[(lo >> 4) + i] = val < 0 ? CacheTile{0, 0}
+                                   : CacheTile{b * kv.max_pages + page,
+                                               min(16, P - pm.start[b] - pos) << CacheTile::kValidShift | (pos - page * kv.page_tokens)};
+  }
 }
-void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, int32_t *start,
-                     int32_t *order, int32_t *first, int32_t *seq) {
-  SKD_LAUNCH(k_prompt_map, dim3(B + 1), dim3(256), 0, s, pm, B, rows, rows_pad, P, start, order, first, seq);
+void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, const KvGeom &kv, int32_t *start,
+                     int32_t *order, int32_t *first, int32_t *seq, CacheTile *tiles) {
+  SKD_LAUNCH(k_prompt_map, dim3(B + 1), dim3(256), 0, s, pm, B, rows, rows_pad, P, kv, start, order, first, seq, tiles);
 }
 
 __global__ __launch_bounds__(1024) void k_embed_ln_rows_wide(const int32_t *tokens, RowMap rm, const bf16_t *tok_emb,

@@ -152,6 +152,7 @@ struct skd_state {
   float *pf_x = nullptr;
   float *pf_partial = nullptr;     // K parts of the prompt projections
   bf16_t *pf_a = nullptr, *pf_q = nullptr, *pf_o = nullptr, *pf_u = nullptr;
+  CacheTile *pf_tiles = nullptr;  // cache place of each 16-row tile of the prompt pass
   int32_t *pf_seq = nullptr, *pf_first = nullptr;  // row map of the prompt pass (sequence of each row, first row of each sequence)
   int prefill_mode = 1;            // 1 = whole prompt per layer (bf16 path), 0 = column by column
   int prefill_tiles = 1;           // 1 = prompt projections as plan_rows says, 0 = 128-row chunks on the skinny kernel
@@ -1067,6 +1068,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     SKDCHECK(rows_alloc(&st->pf_u, (size_t)cap * f));
     SKDCHECK(dev_alloc(st, &st->pf_partial, (size_t)std::min(kRowsPartialMax, 16 * cap * d)));
     SKDCHECK(dev_alloc(st, &st->pf_seq, (size_t)cap));
+    SKDCHECK(dev_alloc(st, &st->pf_tiles, (size_t)cap / 16));
     SKDCHECK(dev_alloc(st, &st->pf_first, (size_t)B));
     SKDCHECK(rows_alloc(&st->pf_x, (size_t)cap * d));
   }
@@ -1081,8 +1083,8 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
     rows += (P - st->start_host[b] + 15) / 16 * 16;
   }
   const int rows_pad = (rows + 255) / 256 * 256;
-  bf16_prompt_map(s, pm, B, rows, rows_pad, P, st->start_dev, st->order_dev, st->pf_first, st->pf_seq);
-  RowMap rm{st->pf_seq, st->pf_first, st->start_dev, P};
+  bf16_prompt_map(s, pm, B, rows, rows_pad, P, st->geom, st->start_dev, st->order_dev, st->pf_first, st->pf_seq, st->pf_tiles);
+  RowMap rm{st->pf_seq, st->pf_first, st->start_dev, P, st->pf_tiles};
   bf16_embed_ln_rows(s, cols, rm, rows, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, st->lw[0].ln1_g,
                      st->lw[0].ln1_b, st->pf_x, st->pf_a, B, d, c.vocab);
   auto plan = [&](int N, int K, bool split_ok) {

@@ -106,15 +106,22 @@ struct RowMap {
   const int32_t *first_row;  // [B] multiple of 16
   const int32_t *start;      // [B] first real column of each sequence
   int P;                     // prompt columns
+  const struct CacheTile *tiles;  // [rows / 16] where the keys and values of each 16-row tile go
 };
 
+struct CacheTile {
+  int page;  // place of the page's number in a layer's block table
+  int at;    // place of the tile's first position in the page; above it (kValidShift) the real positions of the tile: fewer than
+             // 16 in the last tile of a sequence, none past the last sequence
+  static constexpr int kValidShift = 26;
+};
 struct PromptMap {  // by-value kernel argument
   int32_t start[128], first[128];
   uint8_t order[128];
 };
-// start, order, first [B] and seq [rows_pad] from pm; rows = rows of all sequences (each padded to 16)
-void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, int32_t *start,
-                     int32_t *order, int32_t *first, int32_t *seq);
+// start, order, first [B], seq [rows_pad] and tiles [rows_pad / 16] from pm; rows = rows of all sequences (each padded to 16)
+void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, const KvGeom &kv, int32_t *start,
+                     int32_t *order, int32_t *first, int32_t *seq, CacheTile *tiles);
 
 enum GemmEpilogue {
   EPI_PARTIAL = 0,  // fp32 partial sums [split][B_pad][N], no bias
