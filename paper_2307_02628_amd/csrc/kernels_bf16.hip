@@ -990,6 +990,9 @@ __device__ inline void wait_vmcnt_le(int n) {
     case 0: wait_vmcnt<0>(); break;
     case 4: wait_vmcnt<4>(); break;
     case 8: wait_vmcnt<8>(); break;
+    case 16: wait_vmcnt<16>(); break;
+    case 20: wait_vmcnt<20>(); break;
+    case 24: wait_vmcnt<24>(); break;
     case 32: wait_vmcnt<32>(); break;
     case 36: wait_vmcnt<36>(); break;
     default: wait_vmcnt<40>(); break;
@@ -1034,13 +1037,24 @@ __device__ inline auto row_tiles_for(const GemmArgs &a, int nt0, int mt0) {
   else return NoCacheTiles{};
 }
 
-// Epilogue of the tiled prompt GEMMs: a wave's RT x MT output tiles, weight tiles nt0 .. nt0 + RT - 1 and activation-row
-// tiles mt0 .. mt0 + MT - 1.  acc[r][m]: lane l holds output rows (weight rows) n0 .. n0 + 3 of activation row
+// Two neighbouring weight tiles of one activation-row tile, four outputs of each per lane (those from 4 (l >> 4) on), as
+// bf16: exchanged between 16-lane rows 0 | 1 and 2 | 3, so that a lane gets eight consecutive outputs of one tile, those of
+// tile (l >> 4) & 1 from 8 (l >> 5) on, and a wave stores 1 KiB in 16-byte pieces.
+__device__ inline uint4 pack_tile_pair(floatx4 v0, floatx4 v1) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(pack2(v0[0], v0[1]), pack2(v1[0], v1[1]), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(pack2(v0[2], v0[3]), pack2(v1[2], v1[3]), false, false);
+  return make_uint4(lo[0], hi[0], lo[1], hi[1]);
+}
+
+// Epilogue of the tiled prompt GEMMs: a wave's RT x MT output tiles, weight tiles nt0 .. nt0 + RT - 1 (nt0 even) and
+// activation-row tiles mt0 .. mt0 + MT - 1.  acc[r][m]: lane l holds output rows (weight rows) n0 .. n0 + 3 of activation row
 // row0(m) + (l & 15), n0 = 16 * (weight tile) + 4 * (l >> 4).
 template <int EPI, int RT, int MT, typename T>
 __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT][MT], const T &tiles, int nt0, int mt0, int sp, int lane) {
+  static_assert(RT % 2 == 0, "weight tiles are stored in pairs");
   const int grp = lane >> 4, j = lane & 15;
   auto n0_of = [&](int r) { return ((nt0 + r) << 4) + 4 * grp; };
+  auto pair_n0_of = [&](int r) { return ((nt0 + r + (grp & 1)) << 4) + 8 * (grp >> 1); };  // after pack_tile_pair
   auto row0_of = [&](int m) { return (mt0 + m) << 4; };
   if constexpr (EPI == EPI_PARTIAL) {  // partial sums of K part sp
 #pragma unroll
@@ -1049,14 +1063,17 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
       for (int r = 0; r < RT; ++r)
         *(floatx4 *)&a.partial[((long)sp * a.B_pad + row0_of(m) + j) * a.N + n0_of(r)] = acc[r][m];
   } else if constexpr (EPI == EPI_RELU) {
+    floatx4 bias[RT];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      const int n0 = n0_of(r);
-      EpiPre pre;
-      pre.bias = *(const floatx4 *)&a.bias[n0];
+    for (int r = 0; r < RT; ++r) bias[r] = *(const floatx4 *)&a.bias[n0_of(r)];
 #pragma unroll
-      for (int m = 0; m < MT; ++m) gemm_epilogue<EPI>(a, row0_of(m) + j, n0, acc[r][m], pre);
-    }
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < RT; r += 2) {
+        floatx4 v0 = acc[r][m] + bias[r], v1 = acc[r + 1][m] + bias[r + 1];
+        for (int i = 0; i < 4; ++i) v0[i] = fmaxf(v0[i], 0.f), v1[i] = fmaxf(v1[i], 0.f);
+        *(uint4 *)&a.act_out[d_act_index(row0_of(m) + j, pair_n0_of(r), a.N)] = pack_tile_pair(v0, v1);
+      }
   } else if constexpr (EPI == EPI_RESID) {
     // the residual values of the next weight tile are requested before the current one is stored: one exposed
     // round trip per workgroup instead of four
@@ -1084,62 +1101,91 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
     // the 1.3B shape) and 7.4 (128 x 128), without them 3.5 and 3.3; those that store partial sums or activations take 2 to
     // 2.6.  Activation tiles outermost: what is uniform per tile is in scalar registers for one of them at a time.  With the
     // weight tiles outermost, and the place of every tile worked out in the kernel, a prompt pass took 573 us (912 rows of the
-    // 1.3B shape), 6346 (16384 of the 6.7B shape) and 14683 (128 ragged sequences), now 565, 6267 and 14418.
+    // 1.3B shape), 6346 (16384 of the 6.7B shape) and 14683 (128 ragged sequences), then 565, 6267 and 14418.
     const int dh = a.kv.dh, hs = dh == 64 ? 6 : 7, page_head = a.kv.page_tokens * dh * 2, t = j & 3;
-    int at[RT];  // offset of this lane's first value of weight tile r: of q in its activation tile's row, of k and v in the page
     floatx4 bias[RT];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      const int within = n0_of(r) - tiles.which * a.d, h = within >> hs, e = within & (dh - 1);
-      bias[r] = *(const floatx4 *)&a.bias[n0_of(r)];
-      // of k: 16 bytes per position; of v: those of element e + t, 8 bytes per four positions
-      at[r] = tiles.which == 0 ? within
-              : tiles.which == 1 ? h * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + (e & 7) + 8 * j
-                                 : h * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
-    }
+    for (int r = 0; r < RT; ++r) bias[r] = *(const floatx4 *)&a.bias[n0_of(r)];
     if (tiles.which == 0) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
         if (row0_of(m) >= a.rows) continue;
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-          const floatx4 v = acc[r][m] + bias[r];
-          *(uint2 *)&a.q_out[d_act_index(row0_of(m) + j, at[r], a.d)] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        for (int r = 0; r < RT; r += 2)
+          *(uint4 *)&a.q_out[d_act_index(row0_of(m) + j, pair_n0_of(r), a.d)] =
+              pack_tile_pair(acc[r][m] + bias[r], acc[r + 1][m] + bias[r + 1]);
+      }
+      return;
+    }
+    auto page_of = [&](int m) {  // the 32-key block in the page, of head 0
+      return a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot(m) >> 5) * (64 * dh);
+    };
+    auto half_of = [&](int m) { return (tiles.slot(m) >> 4) & 1; };  // 16 keys of the block
+    if (tiles.which == 1) {  // 16 bytes per position
+      int at[RT / 2];
+#pragma unroll
+      for (int r = 0; r < RT; r += 2) {
+        const int within = pair_n0_of(r) - a.d, e = within & (dh - 1);
+        at[r / 2] = (within >> hs) * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + 8 * j;
+      }
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (tiles.page[m] < 0) continue;
+        bf16_t *pg = page_of(m) + half_of(m) * (dh >> 5) * 512;
+#pragma unroll
+        for (int r = 0; r < RT; r += 2) {
+          const uint4 pk = pack_tile_pair(acc[r][m] + bias[r], acc[r + 1][m] + bias[r + 1]);
+          if (j < tiles.valid(m)) *(uint4 *)&pg[at[r / 2]] = pk;
         }
       }
       return;
     }
+    // v: a page holds, for one element e, four consecutive positions of each half side by side.  The four lanes of a quad
+    // hold positions 4q .. 4q + 3 for elements e .. e + 3 each: transposed inside the quad (two exchanges,
+    // with the lane 1 and the lane 2 away), lane t ends up with element e + t of all four positions, 8 bytes.  Where both
+    // halves of a block are whole and in this wave, they are stored together.
+    auto transposed = [&](floatx4 v) {
+      {
+        const float s0 = (t & 1) ? v[0] : v[1], s1 = (t & 1) ? v[2] : v[3];
+        const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0xB1, 0xF, 0xF, true));
+        const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0xB1, 0xF, 0xF, true));
+        if (t & 1) { v[0] = r0; v[2] = r1; } else { v[1] = r0; v[3] = r1; }
+      }
+      {
+        const float s0 = (t & 2) ? v[0] : v[2], s1 = (t & 2) ? v[1] : v[3];
+        const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0x4E, 0xF, 0xF, true));
+        const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0x4E, 0xF, 0xF, true));
+        if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
+      }
+      return v;  // v[s] = element e + t of position 4 * (j / 4) + s
+    };
+    auto whole_block_at = [&](int m) {
+      return m + 1 < MT && half_of(m) == 0 && tiles.valid(m) == 16 && tiles.page[m + 1] == tiles.page[m] &&
+             tiles.at[m + 1] == tiles.at[m] + 16;
+    };
+    int at[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int within = n0_of(r) - 2 * a.d, e = within & (dh - 1);
+      at[r] = (within >> hs) * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
+    }
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-      if (tiles.page[m] < 0) continue;
-      const int valid = tiles.valid(m), half = (tiles.slot(m) >> 4) & 1;
-      bf16_t *pg = a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot(m) >> 5) * (64 * dh);
-      pg += tiles.which == 1 ? half * (dh >> 5) * 512 : 32 * dh + half * 4;
+      if (tiles.page[m] < 0 || (m > 0 && whole_block_at(m - 1))) continue;
+      bf16_t *pg = page_of(m) + 32 * dh + half_of(m) * 4;
+      if (whole_block_at(m)) {
+        const int m1 = m + 1 < MT ? m + 1 : m;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          const floatx4 v = transposed(acc[r][m] + bias[r]), u = transposed(acc[r][m1] + bias[r]);
+          *(uint4 *)&pg[at[r]] = make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(u[0], u[1]), pack2(u[2], u[3]));
+        }
+        continue;
+      }
+      const int nvalid = tiles.valid(m) - (j & ~3);
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        floatx4 v = acc[r][m] + bias[r];
-        if (tiles.which == 1) {
-          if (j < valid) *(uint2 *)&pg[at[r]] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-          continue;
-        }
-        // v: a page holds, for one element e, four consecutive positions side by side.  The four lanes of a quad
-        // hold positions 4q .. 4q + 3 for elements e .. e + 3 each: transposed inside the quad (two exchanges,
-        // with the lane 1 and the lane 2 away), lane t ends up with element e + t of all four positions and
-        // stores them as one 8-byte word.
-        {
-          const float s0 = (t & 1) ? v[0] : v[1], s1 = (t & 1) ? v[2] : v[3];
-          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0xB1, 0xF, 0xF, true));
-          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0xB1, 0xF, 0xF, true));
-          if (t & 1) { v[0] = r0; v[2] = r1; } else { v[1] = r0; v[3] = r1; }
-        }
-        {
-          const float s0 = (t & 2) ? v[0] : v[2], s1 = (t & 2) ? v[1] : v[3];
-          const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s0), 0x4E, 0xF, 0xF, true));
-          const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s1), 0x4E, 0xF, 0xF, true));
-          if (t & 2) { v[0] = r0; v[1] = r1; } else { v[2] = r0; v[3] = r1; }
-        }
-        // now v[s] = element e + t of position 4 * (j / 4) + s
-        const int nvalid = valid - (j & ~3);
+        const floatx4 v = transposed(acc[r][m] + bias[r]);
         bf16_t *dst = &pg[at[r]];
         if (nvalid >= 4) {
           *(uint2 *)dst = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
@@ -1296,8 +1342,9 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   for (int i = 0; i < TILE_NS - 1; ++i) issue_next();
   wait_vmcnt_le(4 * max(flying - 1, 0));
   bar();  // the first stage is here
-  // what an epilogue issues at least: a store for each of the wave's 32 MFMA tiles, or (q | k | v, which skips padding) none
-  constexpr int EXTRA = EPI == EPI_QKV_ROWS ? 0 : 32;
+  // what an epilogue issues at least: a store for each of the wave's 32 MFMA tiles, for every pair of them (EPI_RELU), or (q | k |
+  // v, which skips padding) none
+  constexpr int EXTRA = EPI == EPI_QKV_ROWS ? 0 : EPI == EPI_RELU ? 16 : 32;
   for (bool again = false;; again = true) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
