@@ -46,6 +46,16 @@ __device__ inline long d_act_index(long row, long col, long K) {
 }
 __device__ inline int act_lane(int lane) { return (lane & 15) * 4 + (lane >> 4); }
 
+// The same tile through LDS: loaded in rows (lane l fetches 16-byte piece staged_piece(l), so four lanes take the 64 bytes of
+// a row, not 64 lanes 64 pieces of 16 rows), and read by the lane that needs row l % 16, piece l / 16 at place staged_lane(l).
+// The pieces of a row are turned by its row / 4, so that 16 lanes that read one piece of 16 rows meet all 64 banks.
+// Loaded in the order of act_lane a fragment costs the CU's vector memory path more, and tiles that are bound by what a CU
+// takes in are slower: 912 rows of the 1.3B shape, us per launch, QKV 34.6 -> 31.3, FFN1 34.4 -> 33.1, FFN2 37.3 -> 34.8
+// (128 x 256), output 16.7 -> 16.2 (128 x 128); 256 x 256 tiles with every CU busy, which the power limit bounds, alike.
+__device__ inline int staged_turn(int row) { return -(row >> 2) & 3; }
+__device__ inline int staged_piece(int lane) { return lane ^ staged_turn(lane >> 2); }
+__device__ inline int staged_lane(int lane) { return (lane & 15) * 4 + ((lane >> 4) ^ staged_turn(lane & 15)); }
+
 // ------------------------------------------------------------------ KV page addressing
 // Page (one batch row, one layer): [head][32-key block][K block | V block],
 // K block = [tile 0..1][chunk 0..dh/32-1][lane][8], V block = [dh/16][lane][8].

@@ -965,8 +965,9 @@ int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, int R) {
 // (16 weight tiles x 16 activation-row tiles).  The operand fragments of one
 // k-step (32 KiB) form a stage; a ring of 4 stages lives in LDS and is filled by
 // LDS-direct global loads (each lane supplies a global address, its 16 bytes
-// land at the wave's LDS base + 16 * lane: fragments arrive ready-made and no
-// register holds data in flight), three stages ahead of the one being
+// land at the wave's LDS base + 16 * lane: no
+// register holds data in flight; weight fragments arrive ready-made, activations
+// in the order of staged_piece), three stages ahead of the one being
 // multiplied.  Each wave accumulates a 64 x 128 sub-tile (4 x 8 MFMA tiles, 128
 // accumulator registers), reading 12 fragments from LDS per 32 MFMAs.
 // A k-step takes 1024 cycles of a CU's matrix cores and 1024 of its LDS (96 KiB read, 32 KiB written, 128 bytes a clock),
@@ -1247,7 +1248,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   const int ld_is_a = wave >> 2, ld_t0 = (wave & 3) * 4;
   const bf16x8 *src[4];  // of the next stage to request
   const long sstride = ld_is_a ? 64 : (long)a.G * 64;
-  const unsigned vlane = ld_is_a ? act_lane(lane) : lane;  // activations in MFMA lane order, so that LDS holds ready-made fragments
+  const unsigned vlane = ld_is_a ? staged_piece(lane) : lane;
   auto sources = [&](const Place &p) {
     const GemmArgs &a = args();
     if (!ld_is_a) {
@@ -1261,7 +1262,7 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
       for (int i = 0; i < 4; ++i) src[i] = (const bf16x8 *)a.A + ((long)(p.tm * 16 + ld_t0 + i) * (a.K >> 5) + p.k0) * 64;
     }
   };
-  const int dfrag = ld_is_a * 16 + ld_t0;
+  const int dfrag = ld_is_a * 16 + ld_t0, xlane = staged_lane(lane);
   int to = 0, from = 0;  // ring slots: of the next stage to request, of the next to multiply
   auto issue = [&]() {  // 4 vector-memory operations per wave and stage
     bf16x8 *dst = tile_lds + (to * TILE_FR + dfrag) * 64;
@@ -1306,11 +1307,11 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   auto k_step = [&](auto steady, int extra) {
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 wf[4], xf[8];
-    const bf16x8 *base = tile_lds + from * (TILE_FR * 64) + lane;
+    const bf16x8 *base = tile_lds + from * (TILE_FR * 64);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) wf[r] = base[(wr * 4 + r) * 64];
+    for (int r = 0; r < 4; ++r) wf[r] = base[(wr * 4 + r) * 64 + lane];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) xf[m] = base[(16 + wc * 8 + m) * 64];
+    for (int m = 0; m < 8; ++m) xf[m] = base[(16 + wc * 8 + m) * 64 + xlane];
     from = (from + 1) % TILE_NS;
     if constexpr (decltype(steady)::value) issue();
     else {
@@ -1440,9 +1441,10 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
     } else {
       src[i] = (const bf16x8 *)a.A + ((long)(tm * FA + fr - FW) * Kf + k0) * 64;
       stride[i] = 64;
-      vl[i] = act_lane(lane);  // fetched in MFMA lane order
+      vl[i] = staged_piece(lane);
     }
   }
+  const int xlane = staged_lane(lane);
   floatx4 acc[RT][MT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
@@ -1457,11 +1459,11 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void k_gemm_mid(GemmArgs a) {
                                        (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
   };
   auto read = [&](int st, bf16x8(&wf)[RT], bf16x8(&xf)[MT]) {
-    const bf16x8 *base = mid_lds + (st % NS) * (FR * 64) + lane;
+    const bf16x8 *base = mid_lds + (st % NS) * (FR * 64);
 #pragma unroll
-    for (int r = 0; r < RT; ++r) wf[r] = base[(wr * RT + r) * 64];
+    for (int r = 0; r < RT; ++r) wf[r] = base[(wr * RT + r) * 64 + lane];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) xf[m] = base[(FW + wc * MT + m) * 64];
+    for (int m = 0; m < MT; ++m) xf[m] = base[(FW + wc * MT + m) * 64 + xlane];
   };
   auto mma = [&](const bf16x8(&wf)[RT], const bf16x8(&xf)[MT]) {
 #pragma unroll
