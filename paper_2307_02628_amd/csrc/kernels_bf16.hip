@@ -1022,7 +1022,7 @@ __device__ inline CacheTiles<MT> row_tiles(const GemmArgs &a, int nt0, int mt0) 
   if (t.which == 0) return t;
   // no branches: the loads of all tiles are in flight together; scalar ones, which the compiler does not make by itself
   // behind loads to LDS
-  const auto tiles = (const CacheTile __attribute__((address_space(4))) *)a.rm.tiles + mt0;
+  const auto tiles = (const CacheTile __attribute__((address_space(4))) *)a.cache_tiles + mt0;
   const auto pages = (const int32_t __attribute__((address_space(4))) *)a.bt_layer;
 #pragma unroll
   for (int m = 0; m < MT; ++m) t.page[m] = pages[tiles[m].page], t.at[m] = tiles[m].at;

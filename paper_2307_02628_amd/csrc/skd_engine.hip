@@ -1084,7 +1084,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
   }
   const int rows_pad = (rows + 255) / 256 * 256;
   bf16_prompt_map(s, pm, B, rows, rows_pad, P, st->geom, st->start_dev, st->order_dev, st->pf_first, st->pf_seq, st->pf_tiles);
-  RowMap rm{st->pf_seq, st->pf_first, st->start_dev, P, st->pf_tiles};
+  RowMap rm{st->pf_seq, st->pf_first, st->start_dev, P};
   bf16_embed_ln_rows(s, cols, rm, rows, (const bf16_t *)st->tok_emb, (const bf16_t *)st->pos_emb, st->lw[0].ln1_g,
                      st->lw[0].ln1_b, st->pf_x, st->pf_a, B, d, c.vocab);
   auto plan = [&](int N, int K, bool split_ok) {
@@ -1129,7 +1129,7 @@ static int prefill_batched(skd_state *st, const int32_t *cols) {
   for (int l = 0; l < L; ++l) {
     const LayerW &w = st->lw[l];
     GemmArgs ga{};
-    ga.B = B; ga.rm = rm; ga.kv = st->geom; ga.d = d; ga.partial = st->pf_partial; ga.x = st->pf_x;
+    ga.B = B; ga.rm = rm; ga.cache_tiles = st->pf_tiles; ga.kv = st->geom; ga.d = d; ga.partial = st->pf_partial; ga.x = st->pf_x;
     ga.W = (const bf16_t *)w.wqkv; ga.G = st->p_qkv.R; ga.A = st->pf_a; ga.bias = w.bqkv; ga.N = 3 * d; ga.K = d;
     ga.q_out = st->pf_q; ga.kv_pool = (bf16_t *)st->pool; ga.bt_layer = bt_layer(st, l);
     if (l == L - 1 && last_as_column) {

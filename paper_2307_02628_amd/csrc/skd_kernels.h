@@ -106,10 +106,9 @@ struct RowMap {
   const int32_t *first_row;  // [B] multiple of 16
   const int32_t *start;      // [B] first real column of each sequence
   int P;                     // prompt columns
-  const struct CacheTile *tiles;  // [rows / 16] where the keys and values of each 16-row tile go
 };
 
-struct CacheTile {
+struct CacheTile {  // where the keys and values of a 16-row tile go
   int page;  // place of the page's number in a layer's block table
   int at;    // place of the tile's first position in the page; above it (kValidShift) the real positions of the tile: fewer than
              // 16 in the last tile of a sequence, none past the last sequence
@@ -149,7 +148,10 @@ struct GemmArgs {
   // outputs (by epilogue)
   float *partial;      // EPI_PARTIAL
   bf16_t *q_out;       // EPI_QKV: [B_pad][d] row-major
-  bf16_t *kv_new;      // EPI_QKV: [B][k | v][d] row-major
+  union {
+    bf16_t *kv_new;                // EPI_QKV: [B][k | v][d] row-major
+    const CacheTile *cache_tiles;  // EPI_QKV_ROWS in bf16_gemm_tile, bf16_gemm_mid: [rows / 16], padded to 256 rows
+  };
   bf16_t *kv_pool;     // EPI_QKV_ROWS
   const int32_t *bt_layer;  // EPI_QKV_ROWS: [B][max_pages]
   int d;               // EPI_QKV, EPI_QKV_ROWS: d_model (N = 3d)
