@@ -703,7 +703,8 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
 // L2 hits adds 7.5 us when separate waves fetch it (12.7 us when the same four waves fetch both in turn, as the
 // general kernel above does).  So the work is split by wave role:
 //   waves 0..3 (one per SIMD) stream the weights into registers, three k-steps deep, and issue the MFMAs;
-//   waves 4..7 fetch the activations with LDS-direct loads (no registers in flight) into a ring of four
+//   waves 4..7 fetch the activations with LDS-direct loads (no registers in flight; in the order of staged_piece:
+//   in that of act_lane a decode step of the 6.7B shape at 128 rows took 3 % longer) into a ring of four
 //   stages; a stage holds the 8 activation fragments of 4 consecutive k-steps; wave 4 + w fetches the k-step
 //   that wave w multiplies.  One bare s_barrier per stage orders the ring (as in the tiled prompt GEMM below).
 // With a.ws_rot the workgroups start their K range at different stages (and wrap), so that at any moment the
@@ -734,7 +735,7 @@ __device__ __forceinline__ void gemm_ws_body(const GemmArgs &a, int tile0, int g
   if (wave >= WS_CW) {
     // ---- loader of k-step kw0 + 4 * chunk + l of every stage
     const int l = wave - WS_CW;
-    const bf16x8 *Ab = (const bf16x8 *)a.A + act_lane(lane);  // fetched in MFMA lane order: LDS holds ready-made fragments
+    const bf16x8 *Ab = (const bf16x8 *)a.A + staged_piece(lane);
     auto issue = [&](int ci) {
       int c = ci + rot;
       if (c >= nchunk) c -= nchunk;
@@ -777,6 +778,7 @@ __device__ __forceinline__ void gemm_ws_body(const GemmArgs &a, int tile0, int g
     }
     const long cstride = (long)a.G * 64 * WS_CW;  // one stage further along K
     const unsigned ulane = (unsigned)lane;
+    const int xlane = staged_lane(lane);
     auto loadw = [&](int ci, bf16x8(&w)[R]) {
       int c = ci + rot;
       if (c >= nchunk) c -= nchunk;
@@ -785,7 +787,7 @@ __device__ __forceinline__ void gemm_ws_body(const GemmArgs &a, int tile0, int g
     };
     auto step = [&](int ci, bf16x8(&w)[R]) {
       bar();
-      const bf16x8 *fs = ws_lds + (ci % NS) * STAGE + wave * (MB * 64) + lane;
+      const bf16x8 *fs = ws_lds + (ci % NS) * STAGE + wave * (MB * 64) + xlane;
       bf16x8 x[MB];
 #pragma unroll
       for (int m = 0; m < MB; ++m) x[m] = fs[m * 64];
