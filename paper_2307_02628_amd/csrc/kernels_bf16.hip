@@ -696,7 +696,7 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
   return groups;
 }
 
-// ------------------------------------------------------------------ skinny GEMM for 48 to 128 batch rows
+// ------------------------------------------------------------------ skinny GEMM for 96 and 128 batch rows
 // With 8 batch tiles a workgroup pulls two bytes of activations out of L2 for every byte of weights it streams
 // from HBM, and on this part a CU's vector memory path serves the two kinds of request largely one after the
 // other: measured per CU with plain streaming waves, 512 KiB of HBM misses take 19.9 us and every further MiB of
@@ -705,7 +705,7 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
 //   waves 0..3 (one per SIMD) stream the weights into registers, three k-steps deep, and issue the MFMAs;
 //   waves 4..7 fetch the activations with LDS-direct loads (no registers in flight; in the order of staged_piece:
 //   in that of act_lane a decode step of the 6.7B shape at 128 rows took 3 % longer) into a ring of four
-//   stages; a stage holds the MB activation fragments of 4 consecutive k-steps; wave 4 + w fetches the k-step
+//   stages; a stage holds the 8 activation fragments of 4 consecutive k-steps; wave 4 + w fetches the k-step
 //   that wave w multiplies.  One bare s_barrier per stage orders the ring (as in the tiled prompt GEMM below).
 // With a.ws_rot the workgroups start their K range at different stages (and wrap), so that at any moment the
 // CUs of an XCD ask its L2 for different lines; the sum over k is then taken in that rotated order: fixed for a
@@ -713,12 +713,12 @@ int bf16_gemm(hipStream_t s, const GemmArgs &a, int epi, int R, int U, int waves
 // it off for the LM head, where identical vocabulary rows are to give identical logits).
 constexpr int WS_NS = 4;  // ring stages
 constexpr int WS_CW = 4;  // MFMA waves = loader waves = k-steps per stage
-// MB: batch tiles, 3, 4, 6 or 8
+// MB: batch tiles, 6 or 8
 
 template <int MB, int R, int EPI>
 __device__ __forceinline__ void gemm_ws_body(const GemmArgs &a, int tile0, int group) {
   constexpr int NS = WS_NS;
-  constexpr int STAGE = WS_CW * MB * 64;     // bf16x8 units per stage (12 to 32 KiB)
+  constexpr int STAGE = WS_CW * MB * 64;     // bf16x8 units per stage (24 or 32 KiB)
   extern __shared__ bf16x8 ws_lds[];         // ring [NS][WS_CW][MB][64 lanes]; later the reduction buffer
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int Kf = a.K >> 5;
@@ -907,11 +907,10 @@ __global__ __launch_bounds__(512) void k_gemm_ws(GemmArgs a) {
     gemm_ws_body<MB, R, EPI>(a, blockIdx.x * R, blockIdx.x);
 }
 
-// Decode projections at 48, 64, 96 or 128 (padded) batch rows on the wave-specialised kernel.  Returns the number of row groups,
+// Decode projections at 96 or 128 (padded) batch rows on the wave-specialised kernel.  Returns the number of row groups,
 // or -1 when the shape is not one it handles (the caller then uses bf16_gemm); nothing is launched in that case.
 static bool gemm_ws_shape(const GemmArgs &a, int epi, int R, dim3 &grid, int &groups) {
-  if (a.B_pad != 48 && a.B_pad != 64 && a.B_pad != 96 && a.B_pad != 128) return false;
-  if (a.rows != 0 || R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.K < 32 || a.K % 32 || a.N < 1) return false;
+  if ((a.B_pad != 96 && a.B_pad != 128) || a.rows != 0 || R < 1 || R > 4 || a.G < 1 || a.G > 4 || a.K < 32 || a.K % 32 || a.N < 1) return false;
   if (epi != EPI_PARTIAL && epi != EPI_QKV && epi != EPI_RELU && epi != EPI_LOGITS) return false;
   const int split = epi == EPI_LOGITS ? 1 : a.split;
   const int Kf = a.K / 32;
@@ -952,8 +951,7 @@ int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, int R) {
   int groups = 0;
   if (!gemm_ws_shape(a, epi, R, grid, groups)) return -1;
   int rc;
-#define SKD_WS(R) (a.B_pad == 48 ? launch_gemm_ws<3, R>(s, a, epi, grid) : a.B_pad == 64 ? launch_gemm_ws<4, R>(s, a, epi, grid) : \
-                   a.B_pad == 96 ? launch_gemm_ws<6, R>(s, a, epi, grid) : launch_gemm_ws<8, R>(s, a, epi, grid))
+#define SKD_WS(R) (a.B_pad == 96 ? launch_gemm_ws<6, R>(s, a, epi, grid) : launch_gemm_ws<8, R>(s, a, epi, grid))
   if (R == 1) rc = SKD_WS(1);
   else if (R == 2) rc = SKD_WS(2);
   else if (R == 3) rc = SKD_WS(3);

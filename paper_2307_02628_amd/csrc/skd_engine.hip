@@ -65,7 +65,7 @@ struct LayerW {
 
 struct GemmPlan {
   int R = 1, split = 1, U = 1, waves = 8;
-  bool ws = false;  // 96 and 128 batch rows, 48 and 64 of wide models: weight-streaming waves + activation-loading waves
+  bool ws = false;  // 96 and 128 batch rows: the wave-specialised kernel (weight-streaming waves + activation-loading waves)
   int ws_rot = 0;   // workgroups start their K range at different stages
   int slots = 0;    // LM head: workgroups that run at once (bf16_head_tiles)
 };
@@ -788,13 +788,8 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
       ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8);
     }
   }
-  if (st->bf16 && (st->B_pad >= 96 || (st->B_pad >= 48 && d >= 2048)) && env_int("SKD_GEMM_WS", 1) != 0) {
-    // Every projection whose K range divides into stages of 4 k-steps per workgroup.  At 33 to 64 rows at most half of what a
-    // CU takes in are activations, and the gain is small: 4 steps of 4 layers and an LM head of 50272, us, general kernel -> this
-    // one: 6.7B shape 33 rows 2308 -> 2300, 47 rows 2102 -> 2092, 50 rows 2515 -> 2475, 64 rows 2367 -> 2313; 1.3B shape 1161 ->
-    // 1143, 1079 -> 1055, 1284 -> 1253, 1219 -> 1186 (the same rows; other cached keys for each number).  At 512 columns the
-    // launches are too short to gain (580 to 600 us, within 3 % either way); at 32 rows the general kernel streams as fast as loads
-    // alone.
+  if (st->bf16 && st->B_pad >= 96 && env_int("SKD_GEMM_WS", 1) != 0) {
+    // 96 and 128 batch rows: every projection whose K range divides into stages of 4 k-steps per workgroup
     GemmArgs ga{};
     ga.B = B; ga.B_pad = st->B_pad;
     auto pick = [&](int N, int K, GemmPlan &p, int epi) {

@@ -87,6 +87,45 @@ def test_noalloc_argmax_at_the_limit(V, B):
         dec.close()
 
 
+# heads of few tiles, whose K range is split: partial sums in the state's own buffer; 2 and 4 parts, rows of logits that are and
+# are not a multiple of 16 bytes, on the wave-specialised kernel too
+@pytest.mark.parametrize("d,V,B", [(1024, 1000, 3), (1024, 777, 17), (2048, 2000, 40), (2048, 1000, 97)])
+def test_noalloc_argmax_split_head(d, V, B):
+    import torch
+    shape = S.ModelShape(L=1, d=d, H=d // 128, f=64, V=V, max_pos=8)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        dec, pr, tape = _state(torch, shape, B, 2, 5, 70, stream)
+        tok = [torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+        flat = [torch.full((B * V + 8,), float("nan"), device="cuda") for _ in range(4)]
+        # logits: 16-byte aligned, and one float behind
+        lg = [f[o:o + B * V].view(B, V) for f, o in zip(flat, (0, 0, 1, 0))]
+        dec.prefill(pr)
+        torch.cuda.synchronize()
+        free0 = torch.cuda.mem_get_info()[0]
+        dec.profile_enable(1)
+        assert dec.logits_argmax_noalloc_rc(tok[0], lg[0]) == skd.OK
+        assert dec.logits_argmax_noalloc_rc(tok[1], None) == skd.OK
+        assert dec.logits_argmax_noalloc_rc(None, lg[1]) == skd.OK
+        assert dec.logits_argmax_noalloc_rc(None, lg[2]) == skd.OK
+        # timed launches take events: the entry point creates none, whatever the mode
+        assert sum(v["launches"] for v in dec.profile_read().values()) == 0
+        dec.profile_enable(0)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free0
+        dec.logits_argmax_device(tok[2], lg[3])
+        dec.synchronize()
+        for t in tok[:2]:
+            assert torch.equal(t, tok[2])
+        for z in lg[:3]:
+            assert torch.equal(z, lg[3])
+        assert torch.isnan(flat[0][B * V:]).all() and torch.isnan(flat[2][:1]).all() and torch.isnan(flat[2][B * V + 1:]).all()
+        assert torch.equal(tok[2].long(), lg[3].argmax(-1))
+        dec.decode_step(2, None)                                             # continues from the tokens kept inside
+        dec.synchronize()
+        dec.close()
+
+
 def test_noalloc_argmax_refusals():
     import torch
     shape = S.ModelShape(L=1, d=128, H=2, f=64, V=140000, max_pos=8)      # 2188 workgroups x 128 rows > 262144 partials
