@@ -201,6 +201,10 @@ int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logits_out);
  * streams, different threads) race; calls on one stream are safe.  The array
  * keeps the previous call's contents; nothing in it needs clearing, since the
  * projection of a call writes every partial its final reduction reads.
+ * Small heads of wide models (vocab <= 2048, d_model >= 1024) are split along
+ * d_model: their partial sums live in a buffer of the state that skd_create has
+ * reserved, they use no part of the static array, and calls of different states
+ * do not race.
  * Errors otherwise as skd_logits_argmax. */
 int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, float *logits_out);
 

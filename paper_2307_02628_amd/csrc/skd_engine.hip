@@ -1259,6 +1259,20 @@ extern "C" int skd_decode_step(skd_state *st, int32_t t, const int32_t *tokens_i
   return c.io_on_device ? SKD_OK : wait_stream(st);
 }
 
+// The two launches of an LM head whose K range is split (plan_head_split): partial sums in the state's own buffer, which the
+// layers use before it and nothing reads behind it; then their sum, to logits (optional) and greedy tokens (optional; tokens2:
+// second destination, or null).  head_parts_gemm < 0: not launched.
+static int head_parts_gemm(skd_state *st) {
+  GemmArgs ga{};
+  ga.B = st->cfg.batch; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;
+  ga.N = (st->cfg.vocab + 15) / 16 * 16; ga.K = st->cfg.d_model; ga.split = st->p_head.split; ga.partial = st->partial;
+  return launch_gemm(st->stream, ga, EPI_PARTIAL, st->p_head);
+}
+static void head_parts_sum(skd_state *st, float *logits, int32_t *tokens, int32_t *tokens2) {
+  bf16_logits_sum(st->stream, st->partial, st->p_head.split, st->B_pad, (st->cfg.vocab + 15) / 16 * 16, st->cfg.vocab, logits, tokens,
+                  tokens2, st->cfg.batch);
+}
+
 // Final LayerNorm + LM head (+ greedy argmax into argmax_dev).  logits_target: device buffer [B][V] or null.
 // final LayerNorm output -> logits (optional) and, unless the caller picks the token itself, the greedy token
 // tokens_target: second destination of the greedy token (device memory), or null
@@ -1272,16 +1286,15 @@ static int head_logits(skd_state *st, float *logits_target, bool want_argmax, in
     { ProfScope ps_(st, SKD_PROF_OTHER); f32_linear(s, (const float *)st->head, nullptr, (const float *)st->a, lg, B, d, V, 0, 0); }
     if (want_argmax) { ProfScope ps_(st, SKD_PROF_OTHER); f32_argmax(s, lg, st->argmax_dev, B, V); }
   } else {
-    GemmArgs ga{};
-    ga.B = B; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;  // a = final LayerNorm output
-    ga.N = V; ga.K = d; ga.split = 1; ga.logits = logits_target; ga.pmax = st->pmax; ga.pidx = st->pidx;
     if (st->head_parts) {
-      ga.N = (V + 15) / 16 * 16; ga.split = st->p_head.split; ga.partial = st->partial;
-      { ProfScope ps_(st, SKD_PROF_LM_HEAD); if (launch_gemm(s, ga, EPI_PARTIAL, st->p_head) < 0) return SKD_ERR_SHAPE; }
-      { ProfScope ps_(st, SKD_PROF_ARGMAX); bf16_logits_sum(s, st->partial, ga.split, st->B_pad, ga.N, V, logits_target, want_argmax ? st->argmax_dev : nullptr, want_argmax ? tokens_target : nullptr, B); }
+      { ProfScope ps_(st, SKD_PROF_LM_HEAD); if (head_parts_gemm(st) < 0) return SKD_ERR_SHAPE; }
+      { ProfScope ps_(st, SKD_PROF_ARGMAX); head_parts_sum(st, logits_target, want_argmax ? st->argmax_dev : nullptr, want_argmax ? tokens_target : nullptr); }
       HIPCHECK(hipGetLastError());
       return SKD_OK;
     }
+    GemmArgs ga{};
+    ga.B = B; ga.B_pad = st->B_pad; ga.W = (const bf16_t *)st->head; ga.G = st->p_head.R; ga.A = (const bf16_t *)st->a;  // a = final LayerNorm output
+    ga.N = V; ga.K = d; ga.split = 1; ga.logits = logits_target; ga.pmax = st->pmax; ga.pidx = st->pidx;
     int groups = bf16_head_tiles(ga, st->p_head.R, st->p_head.slots);
     { ProfScope ps_(st, SKD_PROF_LM_HEAD); groups = launch_gemm(s, ga, EPI_LOGITS, st->p_head); }
     if (groups < 0) return SKD_ERR_SHAPE;
@@ -1337,16 +1350,19 @@ extern "C" int skd_logits_argmax(skd_state *st, int32_t *tokens_out, float *logi
 }
 
 // skd_logits_argmax for callers that cannot allocate: same kernels, with the LM head's per-workgroup partials in
-// the static device array instead of the buffers skd_create reserved.  No hipMalloc / hipFree, no event creation,
-// no host-side staging: outputs are device memory and the call only enqueues work on the state's stream.
+// the static device array instead of the buffers skd_create reserved (a head whose K range is split has none: its partial
+// sums go to the state's own buffer, and it needs no static array).  No hipMalloc / hipFree, no event creation, whatever the
+// profiling mode, no host-side staging: outputs are device memory and the call only enqueues work on the state's stream.
 extern "C" int skd_logits_argmax_noalloc(skd_state *st, int32_t *tokens_out, float *logits_out) {
   if (!st) return SKD_ERR_NULL;
   if (!st->have_hidden) return SKD_ERR_ORDER;
   const skd_config &c = st->cfg;
   if (!st->bf16 || !c.io_on_device) return SKD_ERR_SHAPE;
   SKDCHECK(intact(st));
-  if (st->head_parts) {  // partial sums go to the state's own buffer
-    SKDCHECK(head_logits(st, logits_out, true, tokens_out));
+  if (st->head_parts) {
+    if (head_parts_gemm(st) < 0) return SKD_ERR_SHAPE;
+    head_parts_sum(st, logits_out, st->argmax_dev, tokens_out);
+    HIPCHECK(hipGetLastError());
     st->have_argmax = true;
     return SKD_OK;
   }
