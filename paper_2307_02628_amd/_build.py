@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libskd.so")
 SOURCES = ["skd_schedule.cpp", "skd_engine.hip", "kernels_f32.hip", "kernels_bf16.hip", "team_column.hip"]
-HEADERS = [os.path.join(CSRC, "skd_kernels.h"), os.path.join(CSRC, "bf16_device.h"), os.path.join(CSRC, "once_per_device.h"), os.path.join(CSRC, "gave_up.h"), os.path.join(os.path.dirname(HERE), "include", "skd.h")]
+HEADERS = [os.path.join(CSRC, "skd_kernels.h"), os.path.join(CSRC, "bf16_device.h"), os.path.join(CSRC, "once_per_device.h"), os.path.join(CSRC, "gave_up.h"), os.path.join(CSRC, "kv_pages.h"), os.path.join(os.path.dirname(HERE), "include", "skd.h")]
 
 
 def stale() -> bool:

@@ -56,21 +56,4 @@ __device__ inline int staged_turn(int row) { return -(row >> 2) & 3; }
 __device__ inline int staged_piece(int lane) { return lane ^ staged_turn(lane >> 2); }
 __device__ inline int staged_lane(int lane) { return (lane & 15) * 4 + ((lane >> 4) ^ staged_turn(lane & 15)); }
 
-// ------------------------------------------------------------------ KV page addressing
-// Page (one batch row, one layer): [head][32-key block][K block | V block],
-// K block = [tile 0..1][chunk 0..dh/32-1][lane][8], V block = [dh/16][lane][8].
-__device__ inline long kv_block_base(int h, int tt, const KvGeom &g) {
-  return (long)h * (g.page_tokens * g.dh * 2) + (long)(tt >> 5) * (64 * g.dh);
-}
-__device__ inline long kv_k_off(int h, int tt, int e, const KvGeom &g) {
-  const int kk = tt & 31;
-  return kv_block_base(h, tt, g) +
-         ((long)((kk >> 4) * (g.dh >> 5) + (e >> 5)) * 64 + (kk & 15) + 16 * ((e & 31) >> 3)) * 8 + (e & 7);
-}
-__device__ inline long kv_v_off(int h, int tt, int e, const KvGeom &g) {
-  const int kk = tt & 31;
-  return kv_block_base(h, tt, g) + 32 * g.dh +
-         ((long)(e >> 4) * 64 + 16 * ((kk & 15) >> 2) + (e & 15)) * 8 + 4 * (kk >> 4) + (kk & 3);
-}
-
 }  // namespace skd

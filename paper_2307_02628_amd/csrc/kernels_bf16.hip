@@ -1012,15 +1012,15 @@ struct CacheTiles {
   int which;     // 0 = q, 1 = k, 2 = v
   int page[MT];  // -1: nothing to store
   int at[MT];    // CacheTile::at
-  __device__ int slot(int m) const { return at[m] & ((1 << CacheTile::kValidShift) - 1); }
-  __device__ int valid(int m) const { return at[m] >> CacheTile::kValidShift; }
+  __device__ int slot(int m) const { return CacheTile::slot(at[m]); }
+  __device__ int valid(int m) const { return CacheTile::valid(at[m]); }
 };
 template <int MT>
 __device__ inline CacheTiles<MT> row_tiles(const GemmArgs &a, int nt0, int mt0) {
   CacheTiles<MT> t;
   t.which = nt0 * 16 / a.d;
 #pragma unroll
-  for (int m = 0; m < MT; ++m) t.page[m] = -1, t.at[m] = 0;
+  for (int m = 0; m < MT; ++m) t.page[m] = -1, t.at[m] = -1;
   if (t.which == 0) return t;
   // no branches: the loads of all tiles are in flight together; scalar ones, which the compiler does not make by itself
   // behind loads to LDS
@@ -1030,7 +1030,7 @@ __device__ inline CacheTiles<MT> row_tiles(const GemmArgs &a, int nt0, int mt0) 
   for (int m = 0; m < MT; ++m) t.page[m] = pages[tiles[m].page], t.at[m] = tiles[m].at;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
-    if (t.at[m] == 0) t.page[m] = -1;
+    if (!CacheTile::any(t.at[m])) t.page[m] = -1;
   return t;
 }
 struct NoCacheTiles {};
@@ -1098,14 +1098,15 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
       if (r + 2 < RT) fetch(r + 2, xv[r & 1]);
     }
   } else {  // EPI_QKV_ROWS
-    // The offset of a value in a page is a sum of one term for its position (kv_k_off, kv_v_off: uniform per activation
-    // tile, plus a term for the lane) and one for its element, so per store only a base and an offset are added.  With the
+    // The outputs of a wave lie inside one head, so the place of a value is a 64-bit base per activation tile (page, head,
+    // block, half: uniform) and a 32-bit offset inside the block (lane and element): one addition per store.  With the
     // lookups, and the divisions of every store, in here an epilogue took 5.8 us of a launch (128 x 256 tiles, 912 rows of
     // the 1.3B shape) and 7.4 (128 x 128), without them 3.5 and 3.3; those that store partial sums or activations take 2 to
     // 2.6.  Activation tiles outermost: what is uniform per tile is in scalar registers for one of them at a time.  With the
     // weight tiles outermost, and the place of every tile worked out in the kernel, a prompt pass took 573 us (912 rows of the
     // 1.3B shape), 6346 (16384 of the 6.7B shape) and 14683 (128 ragged sequences), then 565, 6267 and 14418.
-    const int dh = a.kv.dh, hs = dh == 64 ? 6 : 7, page_head = a.kv.page_tokens * dh * 2, t = j & 3;
+    static_assert(16 * RT <= 64, "outputs of a wave in one head");
+    const int dh = a.kv.dh, head = (nt0 * 16 - tiles.which * a.d) >> (dh == 64 ? 6 : 7), t = j & 3;
     floatx4 bias[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) bias[r] = *(const floatx4 *)&a.bias[n0_of(r)];
@@ -1120,21 +1121,18 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
       }
       return;
     }
-    auto page_of = [&](int m) {  // the 32-key block in the page, of head 0
-      return a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + (tiles.slot(m) >> 5) * (64 * dh);
-    };
+    auto block_of = [&](int m) { return a.kv_pool + (long)tiles.page[m] * a.kv.page_elems + kv_block_base(head, tiles.slot(m), a.kv); };
     auto half_of = [&](int m) { return (tiles.slot(m) >> 4) & 1; };  // 16 keys of the block
     if (tiles.which == 1) {  // 16 bytes per position
       int at[RT / 2];
 #pragma unroll
       for (int r = 0; r < RT; r += 2) {
-        const int within = pair_n0_of(r) - a.d, e = within & (dh - 1);
-        at[r / 2] = (within >> hs) * page_head + (e >> 5) * 512 + ((e & 31) >> 3) * 128 + 8 * j;
+        at[r / 2] = kv_k_at(j, (pair_n0_of(r) - a.d) & (dh - 1));
       }
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
         if (tiles.page[m] < 0) continue;
-        bf16_t *pg = page_of(m) + half_of(m) * (dh >> 5) * 512;
+        bf16_t *pg = block_of(m) + kv_k_half(half_of(m), dh);
 #pragma unroll
         for (int r = 0; r < RT; r += 2) {
           const uint4 pk = pack_tile_pair(acc[r][m] + bias[r], acc[r + 1][m] + bias[r + 1]);
@@ -1169,13 +1167,12 @@ __device__ inline void tile_epilogue(const GemmArgs &a, const floatx4 (&acc)[RT]
     int at[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-      const int within = n0_of(r) - 2 * a.d, e = within & (dh - 1);
-      at[r] = (within >> hs) * page_head + (e >> 4) * 512 + ((e & 15) + t) * 8 + (j >> 2) * 128;
+      at[r] = kv_v_at(j, ((n0_of(r) - 2 * a.d) & (dh - 1)) + t);
     }
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       if (tiles.page[m] < 0 || (m > 0 && whole_block_at(m - 1))) continue;
-      bf16_t *pg = page_of(m) + 32 * dh + half_of(m) * 4;
+      bf16_t *pg = block_of(m) + kv_v_half(half_of(m), dh);
       if (whole_block_at(m)) {
         const int m1 = m + 1 < MT ? m + 1 : m;
 #pragma unroll
@@ -1821,7 +1818,7 @@ __global__ __launch_bounds__(NW * 64, 4) void k_attention(AttnArgs a) {  // 4 wa
 
   auto load_blk = [&](int blk, bf16x8(&kf)[2][QC], bf16x8(&vf)[VM]) {
     const int page = bt_row[blk / bpp];
-    const bf16x8 *kp = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * (a.kv.page_tokens * DH * 2) +
+    const bf16x8 *kp = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * a.kv.page_tokens * (DH * 2) +
                                         (long)(blk % bpp) * (64 * DH)) + lane;
 #pragma unroll
     for (int tl = 0; tl < 2; ++tl)
@@ -2084,7 +2081,7 @@ __global__ __launch_bounds__(NW * 64, 3) void k_attention_rows(AttnRowsArgs a) {
       }
       page = __builtin_amdgcn_readlane(pages, ip & 63);
     }
-    const bf16x8 *src = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * (a.kv.page_tokens * DH * 2) +
+    const bf16x8 *src = (const bf16x8 *)(a.pool + (long)page * a.kv.page_elems + (long)h * a.kv.page_tokens * (DH * 2) +
                                          (long)ib * (64 * DH)) + wave * LPW * 64;
     bf16x8 *dst = ring + ((blk % NS) * FR + wave * LPW) * 64;
 #pragma unroll
@@ -2224,9 +2221,8 @@ __global__ __launch_bounds__(256) void k_prompt_map(PromptMap pm, int B, int row
   for (int i = threadIdx.x; i < n; i += 256) seq[lo + i] = val;
   for (int i = threadIdx.x; i < n >> 4; i += 256) {
     const int pos = i * 16, page = pos / kv.page_tokens;  // real position of the tile's first row
-    tiles[(lo >> 4) + i] = val < 0 ? CacheTile{0, 0}
-                                   : CacheTile{b * kv.max_pages + page,
-                                               min(16, P - pm.start[b] - pos) << CacheTile::kValidShift | (pos - page * kv.page_tokens)};
+    tiles[(lo >> 4) + i] = val < 0 ? CacheTile::none()
+                                   : CacheTile::of(b * kv.max_pages + page, pos - page * kv.page_tokens, min(16, P - pm.start[b] - pos));
   }
 }
 void bf16_prompt_map(hipStream_t s, const PromptMap &pm, int B, int rows, int rows_pad, int P, const KvGeom &kv, int32_t *start,

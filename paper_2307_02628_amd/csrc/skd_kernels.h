@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "kv_pages.h"
+
 namespace skd {
 
 typedef uint16_t bf16_t;  // raw bfloat16 bit pattern in host-visible signatures
@@ -45,18 +47,6 @@ __device__ inline float wave_sum_f(float v) {
   auto row = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, l)); };
   return (row(0) + row(16)) + (row(32) + row(48));
 }
-
-// Geometry of the paged KV cache.  A page holds `page_tokens` consecutive
-// positions of ONE batch row in ONE layer, all heads.  On the bf16 path a row's
-// keys are stored by real position (column j of a row that starts at column
-// start[b] sits in slot j - start[b]; padding columns store nothing), so that a
-// left-padded row reads no padding; the fp32 path stores by column.
-struct KvGeom {
-  int page_tokens;
-  int max_pages;      // block-table entries per (layer, row)
-  int H, dh;
-  long page_elems;    // elements (fp32 or bf16) per page = 2 * page_tokens * H * dh
-};
 
 // ---------------------------------------------------------------- fp32 debug path
 // Everything row-major fp32.  KV page layout: [K|V][page_tokens][H*dh].
@@ -108,12 +98,6 @@ struct RowMap {
   int P;                     // prompt columns
 };
 
-struct CacheTile {  // where the keys and values of a 16-row tile go
-  int page;  // place of the page's number in a layer's block table
-  int at;    // place of the tile's first position in the page; above it (kValidShift) the real positions of the tile: fewer than
-             // 16 in the last tile of a sequence, none past the last sequence
-  static constexpr int kValidShift = 26;
-};
 struct PromptMap {  // by-value kernel argument
   int32_t start[128], first[128];
   uint8_t order[128];

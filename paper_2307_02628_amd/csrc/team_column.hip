@@ -427,7 +427,7 @@ __global__ __launch_bounds__(TEAM_THREADS) void k_team_column(TeamArgs by_value)
       return (WordPtr)bt + (long)__builtin_amdgcn_readfirstlane(s.row[p / H]) * ap->kv.max_pages;
     };
     auto load_block = [&](bf16x8(&kv)[2 * QC + VM], int page, int p, int blk) __attribute__((always_inline)) {
-      const bf16x8 *kp = (const bf16x8 *)(ap->pool + (long)page * ap->kv.page_elems + (long)(p % H) * (ap->kv.page_tokens * DH * 2) +
+      const bf16x8 *kp = (const bf16x8 *)(ap->pool + (long)page * ap->kv.page_elems + (long)(p % H) * ap->kv.page_tokens * (DH * 2) +
                                           (long)(blk % (ap->kv.page_tokens >> 5)) * (64 * DH)) + lane;
 #pragma unroll
       for (int i = 0; i < 2 * QC + VM; ++i) kv[i] = kp[i * 64];
