@@ -15,8 +15,6 @@
 //     V per 32-key block as A-operand fragments of V^T (head_dim x keys) with
 //     the key order inside a block chosen so that the softmax weights leave
 //     the QK^T accumulator already in B-operand position.
-#include <algorithm>
-
 #include "bf16_device.h"
 
 namespace skd {
@@ -979,26 +977,22 @@ int bf16_gemm_ws(hipStream_t s, const GemmArgs &a, int epi, int R) {
 // -> 1541 with normal operands, 1817 -> 1832 with zeros).  Stand-alone, us: 16384 x 4096 x 16384 1553 -> 1470, x 16384 x
 // 4096 1531 -> 1427, x 4096 x 12288 1197 -> 1114.  Slower: v_mfma 32x32x16 (1270 TFLOP/s; alone it reaches 1840 against
 // 2100 of 16x16x32), four waves of 128 x 128 (1371).
-// A launch has one workgroup per CU (its LDS holds no second one), and the output tiles beyond that are further turns of the
-// same workgroups, so that the first stages of a tile arrive under the epilogue of the one before.  With a workgroup per tile
-// every tile began with an empty ring and ended with stores that nothing overlapped: prompts of the 6.7B shape, 8 x 2048
-// (3 to 16 tiles per CU) 6267 -> 6040 us, 128 ragged sequences 14418 -> 13890.
+// Sources and ring places advance with the stages; with an address worked out per stage (64-bit products) prompts took, us, 16384
+// rows of the 6.7B shape 6217 instead of 6029, 128 ragged sequences 14278 instead of 13674, 32 x 500 of the 1.3B shape 4628
+// instead of 4530.
+// A workgroup computes one output tile and gives its CU back.  256 workgroups that take several tiles each, the ring running
+// on through them, are no faster (the same three: 6036, 13770, 4549), need 212 registers instead of 190, and hold every CU for
+// the whole launch: a step of 4 layers of 256 beside prompts of 8192 rows of 4096 took 380 us instead of 170, on the separate
+// kernels 690 instead of 450.
 constexpr int TILE_NS = 4;   // ring stages
 constexpr int TILE_FR = 32;  // fragments per stage: 16 weight tiles, then 16 activation-row tiles
-constexpr int TILE_WGS = 256;  // workgroups at most: one per CU
 
-// wait until at most n of this wave's vector-memory operations are outstanding (they complete in order)
+// wait until at most n of this wave's vector-memory operations are outstanding (they complete in order); n: 0, 4 or 8
 __device__ inline void wait_vmcnt_le(int n) {
   switch (n) {
     case 0: wait_vmcnt<0>(); break;
     case 4: wait_vmcnt<4>(); break;
-    case 8: wait_vmcnt<8>(); break;
-    case 16: wait_vmcnt<16>(); break;
-    case 20: wait_vmcnt<20>(); break;
-    case 24: wait_vmcnt<24>(); break;
-    case 32: wait_vmcnt<32>(); break;
-    case 36: wait_vmcnt<36>(); break;
-    default: wait_vmcnt<40>(); break;
+    default: wait_vmcnt<8>(); break;
   }
 }
 
@@ -1203,64 +1197,45 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   extern __shared__ bf16x8 tile_lds[];  // [TILE_NS stages][TILE_FR][64 lanes]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wr = wave >> 1, wc = wave & 1;  // sub-tile: weight tiles 4wr .. 4wr+3, activation tiles 8wc .. 8wc+7
-  // Output tiles of this workgroup.  Workgroups are dealt to the 8 XCDs round-robin; the ones that share an XCD (and
+  // workgroup -> output tile.  Workgroups are dealt to the 8 XCDs round-robin; the ones that share an XCD (and
   // its L2) at any moment should share operands, so each XCD walks its own contiguous range of tiles in bands
   // of 4 activation tiles x all weight tiles, weight tile fastest in groups of 4 rows (the last band has the
-  // gy % 4 activation tiles that are left; XCD x owns the workgroups with id % 8 == x, one tile more than the others
-  // when x < total % 8).  With more tiles than CUs a workgroup takes every (workgroups of an XCD)-th of them, and the k-steps
-  // of all its tiles are one stream: the first stages of a tile are requested during the last k-steps of the one before, and
-  // arrive under its epilogue.
-  const int total = (a.N >> 8) * ((a.rows + 255) >> 8) * a.split, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
-  const int first = xcd * per + min(xcd, rem), end = first + per + (xcd < rem), stride = ((int)gridDim.x + 7) >> 3;
-  // q | k | v: what the loop does not use is loaded anew from the kernel's arguments: there are too many for the scalar registers
-  auto args = [&]() -> const GemmArgs & {
-    if constexpr (EPI != EPI_QKV_ROWS) return a;
-    auto p = (const GemmArgs __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const GemmArgs *)p;
-  };
-  struct Place { int tn, tm, sp, k0, n; };
-  auto place = [&](int logical) {
-    Place p;
-    const GemmArgs &a = args();
-    const int gx = a.N >> 8, gy = (a.rows + 255) >> 8, tiles_all = gx * gy;
-    p.sp = logical / tiles_all;  // K part
-    logical -= p.sp * tiles_all;
+  // gy % 4 activation tiles that are left; XCD x owns the workgroups with id % 8 == x, one more than the others
+  // when x < total % 8).
+  int tn, tm, sp;
+  {
+    const int gx = a.N >> 8, gy = (a.rows + 255) >> 8, tiles = gx * gy, total = tiles * a.split;
+    const int id = blockIdx.x;
+    const int xcd = id & 7, per = total >> 3, rem = total & 7;
+    int logical = xcd * per + min(xcd, rem) + (id >> 3);
+    sp = logical / tiles;  // K part
+    logical -= sp * tiles;
     const int full = gy >> 2, tail0 = full * 4 * gx;
     if (logical < tail0) {
       const int band = logical / (4 * gx), within = logical - band * 4 * gx;
-      p.tn = within >> 2;
-      p.tm = band * 4 + (within & 3);
+      tn = within >> 2;
+      tm = band * 4 + (within & 3);
     } else {
       const int hb = gy & 3, within = logical - tail0;  // hb > 0 here
-      p.tn = within / hb;
-      p.tm = full * 4 + within % hb;
+      tn = within / hb;
+      tm = full * 4 + within % hb;
     }
-    p.k0 = (int)((long)(a.K >> 5) * p.sp / a.split);
-    p.n = (int)((long)(a.K >> 5) * (p.sp + 1) / a.split) - p.k0;
-    return p;
-  };
+  }
+  const int k0 = (int)((long)(a.K >> 5) * sp / a.split), Kf = (int)((long)(a.K >> 5) * (sp + 1) / a.split) - k0;
 
   // this wave's share of a stage: 4 fragments; waves 0..3 fetch the weight tiles, waves 4..7 the activation tiles.
   // Fragment bases are wave-uniform (scalar registers); the only per-lane part of an address is the lane's place
   // in the fragment, one 32-bit register.
   const int ld_is_a = wave >> 2, ld_t0 = (wave & 3) * 4;
   const bf16x8 *src[4];  // of the next stage to request
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int T = a.t0 + tn * 16 + ld_t0 + i;
+    src[i] = ld_is_a ? (const bf16x8 *)a.A + ((long)(tm * 16 + ld_t0 + i) * (a.K >> 5) + k0) * 64
+                     : (const bf16x8 *)a.W + (((long)(T / a.G) * (a.K >> 5) + k0) * a.G + T % a.G) * 64;
+  }
   const long sstride = ld_is_a ? 64 : (long)a.G * 64;
   const unsigned vlane = ld_is_a ? staged_piece(lane) : lane;
-  auto sources = [&](const Place &p) {
-    const GemmArgs &a = args();
-    if (!ld_is_a) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int T = a.t0 + p.tn * 16 + ld_t0 + i;
-        src[i] = (const bf16x8 *)a.W + (((long)(T / a.G) * (a.K >> 5) + p.k0) * a.G + T % a.G) * 64;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) src[i] = (const bf16x8 *)a.A + ((long)(p.tm * 16 + ld_t0 + i) * (a.K >> 5) + p.k0) * 64;
-    }
-  };
   const int dfrag = ld_is_a * 16 + ld_t0, xlane = staged_lane(lane);
   int to = 0, from = 0;  // ring slots: of the next stage to request, of the next to multiply
   auto issue = [&]() {  // 4 vector-memory operations per wave and stage
@@ -1273,37 +1248,24 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
     }
     to = (to + 1) % TILE_NS;
   };
-  int at = first + ((int)blockIdx.x >> 3), ahead = at + stride;  // this tile, the next one to take stages from
-  Place cur = place(at), nxt = cur;
-  sources(cur);
-  int left = cur.n, flying = 0;  // stages of the source tile not requested yet; requested and not multiplied
-  auto issue_next = [&]() {
-    if (left == 0) {
-      if (ahead >= end) return;
-      nxt = place(ahead);
-      ahead += stride;
-      sources(nxt);
-      left = nxt.n;
-    }
-    issue();
-    --left;
-    ++flying;
-  };
   auto bar = [&]() {  // bare: __syncthreads() would also wait for the loads of the later stages
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
   floatx4 acc[4][8];
-  // One k-step of a wave: a slot for memory (12 LDS reads of a stage, the requests of the stage three further on), a barrier, a
-  // slot for the matrix cores, a barrier.  Waves 4 .. 7 run one barrier behind waves 0 .. 3, so of the two waves on a SIMD one
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) acc[r][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // One k-step of a wave: a slot for memory (12 LDS reads of stage st, the requests of stage st + 3), a barrier, a slot
+  // for the matrix cores, a barrier.  Waves 4 .. 7 run one barrier behind waves 0 .. 3, so of the two waves on a SIMD one
   // multiplies while the other one reads.
   // Ring: stage st + 3 goes into the slot of stage st - 1, which every wave has read by then (the late group read it
   // in its memory slot before last, with lgkmcnt 0 before the barrier).  Stage st + 1 has landed for every wave that
-  // reads it: each wave waits for its own loads of it (all but those of the stages behind it, and what an epilogue between
-  // them has issued: at least `extra` operations) in its memory slot st, and
+  // reads it: each wave waits for its own loads of it (all but the `later` stages behind it) in its memory slot st, and
   // at least one barrier lies between the last of these waits and the first read.
-  auto k_step = [&](auto steady, int extra) {
+  auto k_step = [&](bool more, int later) {
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 wf[4], xf[8];
     const bf16x8 *base = tile_lds + from * (TILE_FR * 64);
@@ -1312,14 +1274,9 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
 #pragma unroll
     for (int m = 0; m < 8; ++m) xf[m] = base[(16 + wc * 8 + m) * 64 + xlane];
     from = (from + 1) % TILE_NS;
-    if constexpr (decltype(steady)::value) issue();
-    else {
-      --flying;
-      issue_next();
-    }
+    if (more) issue();
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (decltype(steady)::value) wait_vmcnt<4 * (TILE_NS - 2)>();
-    else wait_vmcnt_le(4 * max(flying - 1, 0) + extra);
+    wait_vmcnt_le(4 * later);
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     bar();
     __builtin_amdgcn_sched_barrier(0);
@@ -1339,40 +1296,25 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   };
 
 #pragma unroll
-  for (int i = 0; i < TILE_NS - 1; ++i) issue_next();
-  wait_vmcnt_le(4 * max(flying - 1, 0));
-  bar();  // the first stage is here
-  // what an epilogue issues at least: a store for each of the wave's 32 MFMA tiles, for every pair of them (EPI_RELU), or (q | k |
-  // v, which skips padding) none
-  constexpr int EXTRA = EPI == EPI_QKV_ROWS ? 0 : EPI == EPI_RELU ? 16 : 32;
-  for (bool again = false;; again = true) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < 8; ++m) acc[r][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (wave >= 4) bar();
-    int st = 0;
-    for (; st < min(2, cur.n); ++st) k_step(RowTiles<0>{}, again ? EXTRA : 0);
-    const int steady = cur.n - st - (TILE_NS - 1);
-    if (steady > 0) {
-      for (; st + TILE_NS - 1 < cur.n; ++st) k_step(RowTiles<1>{}, 0);
-      left -= steady;
-    }
-    const auto tiles = row_tiles_for<EPI, 8>(args(), args().t0 + cur.tn * 16 + wr * 4, cur.tm * 16 + wc * 8);
-    for (; st < cur.n; ++st) k_step(RowTiles<0>{}, 0);
-    if (wave < 4) bar();
-    tile_epilogue<EPI, 4, 8>(args(), acc, tiles, args().t0 + cur.tn * 16 + wr * 4, cur.tm * 16 + wc * 8, cur.sp, lane);
-    at += stride;
-    if (at >= end) break;
-    cur = place(at);
-  }
+  for (int i = 0; i < TILE_NS - 1; ++i)
+    if (i < Kf) issue();
+  wait_vmcnt_le(4 * min(Kf - 1, TILE_NS - 2));
+  bar();  // stage 0 is here
+  if (wave >= 4) bar();
+  int st = 0;
+  for (; st + TILE_NS - 1 < Kf; ++st) k_step(true, TILE_NS - 2);
+  const int nt0 = a.t0 + tn * 16 + wr * 4, mt0 = tm * 16 + wc * 8;
+  const auto tiles = row_tiles_for<EPI, 8>(a, nt0, mt0);  // arrive under the last k-steps
+  for (; st < Kf; ++st) k_step(false, max(Kf - 2 - st, 0));
+  if (wave < 4) bar();
+  tile_epilogue<EPI, 4, 8>(a, acc, tiles, nt0, mt0, sp, lane);
 }
 
 // Batched-prompt projections on 256 x 256 tiles.  Returns 0, or -1 when the shape does not tile.
 int bf16_gemm_tile(hipStream_t s, const GemmArgs &a, int epi) {
   if (a.rows <= 0 || a.N % 256 || a.K % 32 || a.G < 1 || a.G > 4 || a.split < 1 || a.split > a.K / 32) return -1;
   if (a.split != 1 && epi != EPI_PARTIAL) return -1;
-  const dim3 grid(std::min((a.N / 256) * ((a.rows + 255) / 256) * a.split, TILE_WGS)), blk(512);
+  const dim3 grid((a.N / 256) * ((a.rows + 255) / 256) * a.split), blk(512);
   const size_t lds = (size_t)TILE_NS * TILE_FR * 64 * sizeof(bf16x8);  // 128 KiB of the CU's 160
   static std::atomic<uint64_t> done{0};
   if (!allow_lds(done, {(const void *)k_gemm_tile<EPI_QKV_ROWS>,

@@ -72,8 +72,8 @@ def test_short_k_parts(split, tile):
     check(WIDE, 7, 83, 9, {"SKD_PREFILL_TILE": f"{tile}x{split}"}, 70)
 
 
-# 256 x 256 tiles, a workgroup each or several: 12 tiles (no multiple of 8: some XCDs have one more), 270 of 1 to 4 k-steps
-# (more than CUs, stages of three tiles in flight), and 294 to 882 of 16 and 48 k-steps with every epilogue
+# 256 x 256 tiles: 12 workgroups (no multiple of 8: some XCDs have one more), 270 of 1 to 4 k-steps (more than CUs), and 294 to
+# 882 of 16 and 48 k-steps with every epilogue
 @pytest.mark.parametrize("split,B,P,shortest", [(1, 13, 97, 0), (15, 24, 96, 80), (1, 128, 300, 270)])
 def test_several_tiles_per_workgroup(split, B, P, shortest):
     check(WIDE, B, P, shortest, {"SKD_PREFILL_TILE": f"256x256x{split}"}, 80)
