@@ -743,7 +743,12 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
   st->layers_tmp.resize(L);
 
   // ---- launch shapes (the weight layout below depends on them)
-  auto ov = [&](const char *name, int &v, int lo, int hi) { const int e = env_int(name, 0); if (e >= lo && e <= hi) v = e; };
+  auto ov = [&](const char *name, int &v, int lo, int hi) {  // whether there is an override, in range
+    const int e = env_int(name, 0);
+    if (e < lo || e > hi) return false;
+    v = e;
+    return true;
+  };
   if (st->bf16) {
     const int Bp = st->B_pad;
     st->p_qkv = plan_direct(3 * d, Bp);
@@ -751,16 +756,16 @@ static int create_impl(const skd_config *cfg, const skd_weights *w, void *hip_st
     st->p_head = plan_head(V, Bp);
     st->p_out = plan_split(d, d, Bp);
     st->p_ffn2 = plan_split(d, f, Bp);
-    ov("SKD_R_QKV", st->p_qkv.R, 1, 4); ov("SKD_R_FFN1", st->p_ffn1.R, 1, 4); ov("SKD_R_HEAD", st->p_head.R, 1, 4);
+    ov("SKD_R_QKV", st->p_qkv.R, 1, 4); ov("SKD_R_FFN1", st->p_ffn1.R, 1, 4);
     ov("SKD_R_OUT", st->p_out.R, 1, 4); ov("SKD_R_FFN2", st->p_ffn2.R, 1, 4);
     ov("SKD_S_OUT", st->p_out.split, 1, 32); ov("SKD_S_FFN2", st->p_ffn2.split, 1, 32);
-    ov("SKD_U_QKV", st->p_qkv.U, 1, 4); ov("SKD_U_FFN1", st->p_ffn1.U, 1, 4); ov("SKD_U_HEAD", st->p_head.U, 1, 4);
+    ov("SKD_U_QKV", st->p_qkv.U, 1, 4); ov("SKD_U_FFN1", st->p_ffn1.U, 1, 4);
     ov("SKD_U_OUT", st->p_out.U, 1, 4); ov("SKD_U_FFN2", st->p_ffn2.U, 1, 4);
-    ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8); ov("SKD_W_HEAD", st->p_head.waves, 4, 8);
+    ov("SKD_W_QKV", st->p_qkv.waves, 4, 8); ov("SKD_W_FFN1", st->p_ffn1.waves, 4, 8);
     ov("SKD_W_OUT", st->p_out.waves, 4, 8); ov("SKD_W_FFN2", st->p_ffn2.waves, 4, 8);
-    int parts = plan_head_split(V, d);
-    for (const char *name : {"SKD_R_HEAD", "SKD_U_HEAD", "SKD_W_HEAD"})
-      if (getenv(name)) parts = 0;
+    const bool head_r = ov("SKD_R_HEAD", st->p_head.R, 1, 4), head_u = ov("SKD_U_HEAD", st->p_head.U, 1, 4),
+               head_w = ov("SKD_W_HEAD", st->p_head.waves, 4, 8);
+    int parts = head_r || head_u || head_w ? 0 : plan_head_split(V, d);  // these are shapes of the whole K range
     ov("SKD_S_HEAD", parts, 1, LOGITS_SPLIT);
     if (parts > 1) {
       st->head_parts = true;

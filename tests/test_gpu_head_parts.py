@@ -54,3 +54,23 @@ def test_identical_rows_give_identical_logits():
     for i in (517, 990):
         np.testing.assert_array_equal(lg[:, i], lg[:, 18])
     np.testing.assert_array_equal(tok, lg.argmax(-1))
+
+
+def test_overrides_out_of_range_are_ignored(monkeypatch):
+    shape = S.ModelShape(L=1, d=1024, H=8, f=64, V=1000, max_pos=8)
+    w = S.weights_to_bf16_values(S.make_weights(shape, 9))
+    tokens = S.make_prompts(5, 3, 1000, 10)
+
+    def logits(name=None, value=None):
+        with monkeypatch.context() as m:
+            if name:
+                m.setenv(name, value)
+            with skd.Decoder(skd.make_config(shape, 5, 3, 6, 1, 1), w) as dec:
+                dec.prefill(tokens)
+                return dec.logits_argmax()[1].copy()
+    parts, whole = logits(), logits("SKD_S_HEAD", "1")
+    assert (parts != whole).any()  # another order of the sums
+    for name, value in (("SKD_R_HEAD", "9"), ("SKD_R_HEAD", ""), ("SKD_U_HEAD", "0"), ("SKD_W_HEAD", "16"), ("SKD_S_HEAD", "9")):
+        np.testing.assert_array_equal(logits(name, value), parts)
+    for name, value in (("SKD_R_HEAD", "2"), ("SKD_U_HEAD", "1"), ("SKD_W_HEAD", "8")):
+        np.testing.assert_array_equal(logits(name, value), whole)
